@@ -172,9 +172,10 @@ int fsr_verify_attention_static(const void* q, const void* k_cache, const void* 
 /*
  * Which kernel fsr_verify_attention runs for shapes *p (host query, no GPU work): FSR_PATH_STREAM,
  * the HBM-bandwidth kernel (bf16, D = 128, P = 16, H_q / H_kv <= 16, B <= 4096), or
- * FSR_PATH_GENERIC, one wavefront per (row, head) for every other supported shape (fp32 inputs,
- * D = 64, other page sizes, wider groups, larger batches): correct, but it re-reads K/V per query
- * head and row and is many times slower on large batches.  Negative on invalid shapes.
+ * FSR_PATH_GENERIC, one workgroup per (request, KV head) for every other supported shape (fp32
+ * inputs, D = 64, other page sizes, wider groups, larger batches): it needs no workspace and takes no
+ * plan; keys are read once per KV head, but a batch of few or very uneven requests leaves compute
+ * units idle.  Negative on invalid shapes.
  */
 #define FSR_PATH_GENERIC 0
 #define FSR_PATH_STREAM 1

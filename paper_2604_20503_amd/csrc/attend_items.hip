@@ -1,0 +1,555 @@
+// Verification attention (Sec. 2.1 / 3.1) for the shapes the stream kernel of verify_attention.hip is not built for:
+// fp32 inputs, heads of 64, page sizes other than 16, more than 16 query heads per KV head, very large batches.
+// Nothing is handed from one workgroup to another, so the call needs no workspace.
+//
+// What bounds it is reading K and V (bf16) or the fp32 matrix instructions (fp32), so the work is laid out to read a
+// request's keys once per KV head: one workgroup per (request, KV head, group of up to 16 * MT query rows), its waves
+// take the keys' tiles in turn and are merged through LDS at the end.  Longer suffixes than a group holds are further
+// workgroups (grid.z), or further rounds of the same one where the caller has not said how long they are.  A ragged
+// batch loads the compute units unevenly, but a compute unit draws about twice its even share of the HBM bandwidth
+// when others are idle, which covers a longest context of twice the mean.
+//   bf16: 32-key tiles.  Whole key rows are loaded (1 KB of consecutive bytes per load, each lane 16) and put through
+//     wave-private swizzled LDS tiles, from which K is read as matrix operand and V transposed; while a tile is worked
+//     on, the next one is in flight in registers, and the places of the keys of the one after it.  Probabilities go to
+//     the matrix cores as bf16 terms: two (17 bits) for a bf16 result, three (the fp32 value exactly) for an fp32 one.
+//     A wave spends about as many cycles on its vector instructions as on waiting, so two waves per SIMD matter more
+//     than a second tile in flight: at 32 requests of 256 to 4096 tokens, 8 KV heads, D = 64, bf16, 36 us as built, 45 us
+//     with two tiles in flight (the registers spill), 59 us with four waves of 512 registers.
+//   fp32: 16-key tiles on v_mfma_f32_16x16x4_f32, operands straight from memory in the operand layout.
+// All global accesses are declared with the element's alignment only (the hardware takes unaligned vectors).
+//
+// Measured, us a call, against one wave per (row, query head) with vector FMAs, which re-reads the keys for each of them:
+//   bf16 D = 64, 32/8 heads, 32 requests of 256-4096 tokens, 1-8 drafts      716 -> 39
+//   bf16 D = 64, 32/8 heads, 1 request of 8192 tokens, no drafts             317 -> 51 (eight workgroups in all)
+//   bf16 D = 64, 32/32 heads, 64 requests of 256-4096 tokens, 0-7 drafts     1324 -> 225
+//   bf16 D = 128, 64/2 heads, 16 requests of 1024-2048 tokens, 1-8 drafts    761 -> 56
+//   fp32 D = 128, 32/8 heads, 32 requests of 1024-2048 tokens, 1-8 drafts    1588 -> 145
+//   fp32 D = 64, 8/2 heads, 4 requests of 64-256 tokens, 0-4 drafts          20 -> 9 (kernel)
+#include "attend_items.hpp"
+
+#include <algorithm>
+#include <cstdint>
+#include <type_traits>
+
+#include "device_utils.hpp"
+
+namespace fsr {
+namespace {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+// 16 bytes of global memory aligned to the element type only
+typedef __attribute__((__vector_size__(16), __aligned__(2))) uint32_t gu32x4;
+typedef __attribute__((__vector_size__(16), __aligned__(4))) float gf32x4;
+
+constexpr double kLog2e = 1.4426950408889634074;
+constexpr float kLn2 = 0.6931471805599453f;
+
+struct ItemArgs {
+    const void* q;
+    const void* k;
+    const void* v;
+    const int32_t* bt;
+    const int32_t* ctx;
+    const int32_t* cu_q;
+    void* out;
+    float* lse;
+    int B, N_cap, H_q, H_kv, G, P, p_shift, max_pages, n_pages;  // p_shift: log2(P), or -1 if P is no power of two
+    int out_bf16;
+    long long page_stride, slot_stride, head_stride;  // of the caches, in bytes
+    float scale_log2, scale_rest;  // softmax scale times log2(e), and (times ln 2) what rounding took off it
+};
+
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ uint16_t to_bf16(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
+__device__ __forceinline__ void lds_fence() {  // orders a wave's own LDS accesses (it issues them in order)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+template <bool BF16, int D, int MT>
+struct Map {
+    // waves of a workgroup: eight at 256 registers each, or four at 512 where a tile in flight and the accumulators
+    // need more than that (measured by the compiler's spill counts)
+    static constexpr int kW = D == 128 || MT == 4 ? 4 : 8;
+    static constexpr int kThreads = kW * 64;
+    static constexpr int kElem = BF16 ? 2 : 4;
+    static constexpr int kTile = BF16 ? 32 : 16;             // keys of a wave tile
+    static constexpr int kKt = kTile / 16;
+    static constexpr int kRow = D * kElem;                   // bytes of a key row
+    static constexpr int kQPieces = kRow / 64;               // 1 KB operand pieces of a query tile (64 B of each of 16 rows)
+    static constexpr int kStage = BF16 ? kW * 2 * kTile * kRow : 0;  // K and V tiles of the waves
+    static constexpr int kRedStride = D + 4;                 // floats
+    static constexpr int kRed = kW * 16 * kRedStride * 4;    // one query tile's accumulators of all waves
+    static constexpr int kShared = kStage > kRed ? kStage : kRed;
+    static constexpr int kMl = kShared;                      // references and sums of all waves
+    static constexpr int kQ = kMl + 2 * kW * 16 * MT * 4;
+    static constexpr int kSmem = kQ + MT * kQPieces * 1024;
+};
+
+// LDS places of 16-byte chunk ch of key row `row`, such that the accesses of 16 lanes cover all banks: K is written and
+// read row by row and chunk by chunk, V read transposed in pieces of two neighbouring chunks.
+template <int D>
+__device__ __forceinline__ int k_off(int row, int ch) {
+    return D == 64 ? row * 128 + ((ch ^ ((row >> 1) & 7)) << 4) : row * 256 + ((ch ^ (row & 15)) << 4);
+}
+template <int D>
+__device__ __forceinline__ int v_off(int row, int ch) {
+    return D == 64 ? row * 128 + ((ch ^ (((row >> 1) & 3) << 1)) << 4) : row * 256 + ((ch ^ ((row & 7) << 1)) << 4);
+}
+
+template <bool NT>
+__device__ __forceinline__ u32x4 load16(const char* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(p));
+    else return *reinterpret_cast<const gu32x4*>(p);
+}
+
+// Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see, merge the waves,
+// write the rows.  TERMS: bf16 terms a probability is split into (bf16 only).  MTMAX: what the LDS is laid out for.
+template <bool BF16, int D, int MTMAX, int MT, bool NT, int TERMS>
+__device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0) {
+    typedef Map<BF16, D, MTMAX> L;
+    constexpr int kTile = L::kTile, kKt = L::kKt, kDB = D / 16, kW = L::kW;
+    const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6), lg = lane >> 4, li = lane & 15;
+    const int kv_cap = (int)min((long long)a.max_pages * a.P, 1LL << 30);
+    const int32_t* bt = a.bt + (size_t)i * a.max_pages;
+    const char* kc = reinterpret_cast<const char*>(a.k) + (size_t)g * a.head_stride;
+    const char* vc = reinterpret_cast<const char*>(a.v) + (size_t)g * a.head_stride;
+    char* qbuf = smem + L::kQ;
+    float* red_m = reinterpret_cast<float*>(smem + L::kMl);  // [kW][16 * MT]
+    float* red_l = red_m + kW * 16 * MT;
+    char* kbuf = smem + w * 2 * kTile * L::kRow;  // the wave's tiles (bf16)
+    char* vbuf = kbuf + kTile * L::kRow;
+
+    const int rows = min(16 * MT, M - m0);
+    const int first_lim = c + m0 / a.G;                           // last key the group's first row sees
+    const int kend = min(c + (m0 + rows - 1) / a.G + 1, kv_cap);  // keys any row of the group sees
+    const int kb0 = w * kTile, step = kW * kTile;
+    const int nw = kb0 < kend ? (kend - kb0 + step - 1) / step : 0;
+    // the wave's first n_plain tiles lie wholly below every row's causal limit
+    const int below = min(first_lim + 1, kend) - kTile - kb0;
+    const int n_plain = below < 0 ? 0 : below / step + 1;
+
+    // ---- query operands to LDS: piece (mt, s) holds for lane (li, lg) 16 bytes of row mt * 16 + li
+    for (int pr = w; pr < MT * L::kQPieces; pr += kW) {
+        const int m = m0 + (pr / L::kQPieces) * 16 + li;
+        const bool ok = m < M;
+        const int j = (ok ? m : m0) / a.G, gq = (ok ? m : m0) % a.G;
+        const char* src = reinterpret_cast<const char*>(a.q) + ((size_t)(q0 + j) * a.H_q + g * a.G + gq) * L::kRow +
+                          64 * (pr % L::kQPieces) + 16 * lg;
+        u32x4 x = *reinterpret_cast<const gu32x4*>(src);
+        if (!ok) x = u32x4{0u, 0u, 0u, 0u};
+        *reinterpret_cast<u32x4*>(qbuf + (pr * 64 + lane) * 16) = x;
+    }
+    int lim[MT];  // last key that query row mt * 16 + li sees
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = mt * 16 + li;
+        lim[mt] = m < rows ? min(c + (m0 + m) / a.G, kv_cap - 1) : -1;
+    }
+
+    // ---- key rows: lane l looks up the place of key kb + l % kTile of a tile (keys past the end: the last one)
+    uint32_t at_lo = 0, at_hi = 0;
+    auto look_up = [&](int t) {
+        const int key = max(min(kb0 + t * step + (lane & (kTile - 1)), kend - 1), 0);
+        const int pg = a.p_shift >= 0 ? key >> a.p_shift : key / a.P;
+        const int page = min(max(bt[pg], 0), a.n_pages - 1);
+        const long long at = page * a.page_stride + (key - pg * a.P) * a.slot_stride;
+        at_lo = (uint32_t)at;
+        at_hi = (uint32_t)((unsigned long long)at >> 32);
+    };
+    auto row_at = [&](int r) {  // byte offset of key row r of the tile looked up last
+        return (long long)(((unsigned long long)(uint32_t)__shfl((int)at_hi, r, 64) << 32) | (uint32_t)__shfl((int)at_lo, r, 64));
+    };
+    // registers of a tile in flight.  bf16: load n covers rows n * kRpl + lane / kCh, 16-byte chunk lane % kCh.
+    // fp32: K is the matrix operand itself (row li, floats 16 s + 4 lg ..), V[e][db] = V[key 4 lg + e][16 db + li].
+    constexpr int kCh = D * 2 / 16, kRpl = 64 / kCh, kLoads = BF16 ? kTile / kRpl : 1;
+    u32x4 kr[BF16 ? kLoads : 1], vr[BF16 ? kLoads : 1];
+    f32x4 kf[BF16 ? 1 : D / 16];
+    float vf[BF16 ? 1 : 4][BF16 ? 1 : kDB];
+    auto issue = [&]() {
+        if constexpr (BF16) {
+            long long at[kLoads];
+#pragma unroll
+            for (int n = 0; n < kLoads; ++n) at[n] = row_at(n * kRpl + lane / kCh) + (lane % kCh) * 16;
+#pragma unroll
+            for (int n = 0; n < kLoads; ++n) kr[n] = load16<NT>(kc + at[n]);
+#pragma unroll
+            for (int n = 0; n < kLoads; ++n) vr[n] = load16<NT>(vc + at[n]);
+        } else {
+            const char* kp = kc + row_at(li) + 16 * lg;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) kf[s] = *reinterpret_cast<const gf32x4*>(kp + 64 * s);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const char* vp = vc + row_at(4 * lg + e) + 4 * li;
+#pragma unroll
+                for (int db = 0; db < kDB; ++db) vf[e][db] = *reinterpret_cast<const float*>(vp + 64 * db);
+            }
+        }
+    };
+
+    float m_run[MT], l_run[MT];
+    f32x4 acc[MT][kDB];
+    auto start = [&]() {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            m_run[mt] = -INFINITY;
+            l_run[mt] = 0.0f;
+#pragma unroll
+            for (int db = 0; db < kDB; ++db) acc[mt][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (nw > 0) {
+            look_up(0);
+            issue();
+            look_up(min(1, nw - 1));
+        }
+    };
+    // One tile.  masked: some row does not see all of its keys.  careful: V may hold Inf or NaN, which must reach
+    // exactly the rows that see their key, and an infinite value must meet the whole probability and not its zero
+    // parts: the sum is formed without the matrix cores.
+    auto tile = [&](int t, auto masked_, auto careful_) {
+        constexpr bool masked = decltype(masked_)::value, careful = decltype(careful_)::value;
+        const int kb = kb0 + t * step;
+        // ---- scores: s[mt][kt][e] = key kb + 16 kt + 4 lg + e, query row mt * 16 + li
+        f32x4 s[MT][kKt];
+        float vt[BF16 ? 1 : 4][BF16 ? 1 : kDB];
+        if constexpr (BF16) {
+#pragma unroll
+            for (int n = 0; n < kLoads; ++n) {
+                const int row = n * kRpl + lane / kCh, ch = lane % kCh;
+                *reinterpret_cast<u32x4*>(kbuf + k_off<D>(row, ch)) = kr[n];
+                *reinterpret_cast<u32x4*>(vbuf + v_off<D>(row, ch)) = vr[n];
+            }
+        } else {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                f32x4 chain[4];  // four shorter sums: less rounding, and the matrix instructions need not wait for each other
+#pragma unroll
+                for (int e = 0; e < 4; ++e) chain[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ss = 0; ss < D / 16; ++ss) {
+                    const f32x4 qop = *reinterpret_cast<const f32x4*>(qbuf + ((mt * L::kQPieces + ss) * 64 + lane) * 16);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        chain[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[ss][e], qop[e], chain[e], 0, 0, 0);
+                }
+                s[mt][0] = (chain[0] + chain[1]) + (chain[2] + chain[3]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int db = 0; db < kDB; ++db) vt[e][db] = vf[e][db];
+        }
+        if (t + 1 < nw) {  // the registers are free: send for the next tile, look up the keys of the one after it
+            issue();
+            look_up(min(t + 2, nw - 1));
+        }
+        if constexpr (BF16) {
+            lds_fence();
+            bf16x8 kop[2][D / 32];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int kk = 0; kk < D / 32; ++kk)
+                    kop[h][kk] = *reinterpret_cast<const bf16x8*>(kbuf + k_off<D>(16 * h + li, 4 * kk + lg));
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                s[mt][0] = s[mt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < D / 32; ++kk) {
+                    const bf16x8 qop = *reinterpret_cast<const bf16x8*>(qbuf + ((mt * L::kQPieces + kk) * 64 + lane) * 16);
+                    s[mt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[0][kk], qop, s[mt][0], 0, 0, 0);
+                    s[mt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[1][kk], qop, s[mt][1], 0, 0, 0);
+                }
+            }
+        }
+        // ---- masking, exponent references (raised, with a rescale, only when a score exceeds one by 2^8)
+        float x[MT][4 * kKt], top[MT];
+        bool raise = false;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            top[mt] = -INFINITY;
+#pragma unroll
+            for (int kt = 0; kt < kKt; ++kt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float z = s[mt][kt][e];
+                    if (masked && kb + 16 * kt + 4 * lg + e > lim[mt]) z = -INFINITY;
+                    x[mt][kt * 4 + e] = z;
+                    top[mt] = fmaxf(top[mt], z);
+                }
+            top[mt] *= a.scale_log2;
+            raise |= top[mt] > m_run[mt] + 8.0f;
+        }
+        if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                float up = fmaxf(top[mt], __shfl_xor(top[mt], 16, 64));
+                up = fmaxf(up, __shfl_xor(up, 32, 64));
+                const float m_new = fmaxf(m_run[mt], up);
+                const float alpha = m_new == -INFINITY ? 1.0f : exp2_fast(m_run[mt] - m_new);
+                m_run[mt] = m_new;
+                l_run[mt] *= alpha;
+#pragma unroll
+                for (int db = 0; db < kDB; ++db) acc[mt][db] *= alpha;
+            }
+        }
+        // ---- probabilities in place of the scores; what rounding took off the scale comes back as a factor near 1
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const float neg_m = m_run[mt] == -INFINITY ? 0.0f : -m_run[mt];
+            float sum = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4 * kKt; ++e) {
+                float p = exp2_fast(fmaf(x[mt][e], a.scale_log2, neg_m));
+                if constexpr (TERMS == 3) p = fmaf(p, fmaxf(x[mt][e], -1e30f) * a.scale_rest, p);
+                x[mt][e] = p;
+                sum += p;
+            }
+            l_run[mt] += sum;
+        }
+        // ---- O^T += V^T P^T
+        if constexpr (careful) {
+#pragma unroll 1
+            for (int quad = 0; quad < 4; ++quad)
+#pragma unroll
+                for (int kt = 0; kt < kKt; ++kt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = 16 * kt + 4 * quad + e;  // key row of the tile
+#pragma unroll
+                        for (int db = 0; db < kDB; ++db) {
+                            float v4[4];
+                            if constexpr (BF16) {
+                                const uint2 t2 = *reinterpret_cast<const uint2*>(vbuf + v_off<D>(r, 2 * db + (lg >> 1)) + (lg & 1) * 8);
+                                v4[0] = __builtin_bit_cast(float, t2.x << 16);
+                                v4[1] = __builtin_bit_cast(float, t2.x & 0xffff0000u);
+                                v4[2] = __builtin_bit_cast(float, t2.y << 16);
+                                v4[3] = __builtin_bit_cast(float, t2.y & 0xffff0000u);
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) v4[u] = __shfl(vt[e][db], quad * 16 + 4 * lg + u, 64);
+                            }
+#pragma unroll
+                            for (int mt = 0; mt < MT; ++mt) {
+                                const float p = __shfl(x[mt][kt * 4 + e], quad * 16 + li, 64);
+                                if (kb + r <= lim[mt]) {
+#pragma unroll
+                                    for (int u = 0; u < 4; ++u) acc[mt][db][u] = fmaf(p, v4[u], acc[mt][db][u]);
+                                }
+                            }
+                        }
+                    }
+        } else if constexpr (BF16) {
+            bf16x8 vop[kDB];  // element e < 4: key 4 lg + e, e >= 4: key 16 + 4 lg + (e - 4), at d = 16 db + li
+#pragma unroll
+            for (int db = 0; db < kDB; ++db) {
+                const int off = v_off<D>(4 * lg + (li >> 2), 2 * db + ((li & 3) >> 1)) + (li & 1) * 8;
+                const s16x4 t0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vbuf + off));
+                const s16x4 t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vbuf + off + 16 * L::kRow));
+                vop[db] = __builtin_bit_cast(bf16x8, s16x8{t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]});
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                // x = hi + lo (+ rest): hi, and with three terms lo too, by truncation; the last term by rounding or,
+                // as the third, exactly
+                uint32_t hi[4], lo[4], rest[4];
+                bf16x8 lo2;
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    uint32_t b0 = __builtin_bit_cast(uint32_t, x[mt][e]), b1 = __builtin_bit_cast(uint32_t, x[mt][e + 1]);
+                    hi[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                    const float r0 = x[mt][e] - __builtin_bit_cast(float, b0 & 0xffff0000u);
+                    const float r1 = x[mt][e + 1] - __builtin_bit_cast(float, b1 & 0xffff0000u);
+                    if constexpr (TERMS == 3) {
+                        b0 = __builtin_bit_cast(uint32_t, r0);
+                        b1 = __builtin_bit_cast(uint32_t, r1);
+                        lo[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                        b0 = __builtin_bit_cast(uint32_t, r0 - __builtin_bit_cast(float, b0 & 0xffff0000u));
+                        b1 = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b1 & 0xffff0000u));
+                        rest[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                    } else {
+                        lo2[e] = (__bf16)r0;
+                        lo2[e + 1] = (__bf16)r1;
+                    }
+                }
+                const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{hi[0], hi[1], hi[2], hi[3]});
+                if constexpr (TERMS == 3) lo2 = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], lo[2], lo[3]});
+#pragma unroll
+                for (int db = 0; db < kDB; ++db) {
+                    if constexpr (TERMS == 3) {
+                        const bf16x8 pr = __builtin_bit_cast(bf16x8, u32x4{rest[0], rest[1], rest[2], rest[3]});
+                        acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], pr, acc[mt][db], 0, 0, 0);
+                    }
+                    acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], lo2, acc[mt][db], 0, 0, 0);
+                    acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], ph, acc[mt][db], 0, 0, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int db = 0; db < kDB; ++db)
+                        acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vt[e][db], x[mt][e], acc[mt][db], 0, 0, 0);
+        }
+        if constexpr (BF16) lds_fence();  // the next tile's stores must not overtake this tile's reads
+    };
+    start();
+    __syncthreads();  // the query operands are staged
+    int t = 0;
+#pragma unroll 1
+    for (; t < n_plain; ++t) tile(t, std::false_type{}, std::false_type{});
+#pragma unroll 1
+    for (; t < nw; ++t) tile(t, std::true_type{}, std::false_type{});
+    // an accumulator that is not finite: once more from the start, with care (0 * x is NaN for exactly those)
+    float zero = 0.0f;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) zero = fmaf(acc[mt][db][u], 0.0f, zero);
+    if (__builtin_amdgcn_ballot_w64(!(zero == 0.0f)) != 0) {
+        start();
+#pragma unroll 1
+        for (t = 0; t < nw; ++t) tile(t, std::true_type{}, std::true_type{});
+    }
+
+    // ---- merge the waves, one query tile at a time
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        l_run[mt] += __shfl_xor(l_run[mt], 16, 64);
+        l_run[mt] += __shfl_xor(l_run[mt], 32, 64);
+        if (lg == 0) {
+            red_m[w * 16 * MT + mt * 16 + li] = m_run[mt];
+            red_l[w * 16 * MT + mt * 16 + li] = l_run[mt];
+        }
+    }
+    float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        __syncthreads();  // every wave is done with what lies here: its K/V tiles, the previous query tile's sums
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+            *reinterpret_cast<f32x4*>(red + (w * 16 + li) * L::kRedStride + db * 16 + 4 * lg) = acc[mt][db];
+        __syncthreads();
+        constexpr int kPer = 16 * D / L::kThreads;  // a thread sums kPer consecutive values of one row
+        const int row = threadIdx.x / (D / kPer), d0 = (threadIdx.x % (D / kPer)) * kPer, m = mt * 16 + row;
+        float top = -INFINITY;
+#pragma unroll
+        for (int ww = 0; ww < kW; ++ww) top = fmaxf(top, red_m[ww * 16 * MT + m]);
+        const float ref = top == -INFINITY ? 0.0f : top;
+        float sum = 0.0f, o[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) o[u] = 0.0f;
+#pragma unroll
+        for (int ww = 0; ww < kW; ++ww) {
+            const float e = exp2_fast(red_m[ww * 16 * MT + m] - ref);  // 0 for a wave that saw no key of the row
+            sum = fmaf(red_l[ww * 16 * MT + m], e, sum);
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const float part = red[(ww * 16 + row) * L::kRedStride + d0 + u];
+                o[u] = fmaf(part, e, o[u]);
+            }
+        }
+        if (m < rows) {
+            const int j = (m0 + m) / a.G, h = g * a.G + (m0 + m) % a.G;
+            const size_t at = ((size_t)(q0 + j) * a.H_q + h) * D + d0;
+            const float inv = 1.0f / sum;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                if (a.out_bf16) reinterpret_cast<uint16_t*>(a.out)[at + u] = to_bf16(o[u] * inv);
+                else reinterpret_cast<float*>(a.out)[at + u] = o[u] * inv;
+            }
+            if (a.lse && d0 == 0) a.lse[(size_t)(q0 + j) * a.H_q + h] = top * kLn2 + logf(sum);
+        }
+    }
+}
+
+template <bool BF16, int D, int MTMAX, bool NT, int TERMS>
+__global__ __launch_bounds__((Map<BF16, D, MTMAX>::kThreads)) void attend_items_kernel(ItemArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int g = blockIdx.x, i = blockIdx.y;
+    const int q0 = a.cu_q[i], q_len = min(a.cu_q[i + 1], a.N_cap) - q0, c = a.ctx[i];
+    const int M = q_len * a.G;
+    if (q_len <= 0) return;
+    for (int m0 = blockIdx.z * 16 * MTMAX; m0 < M; m0 += gridDim.z * 16 * MTMAX) {
+        const int mt = (min(M - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
+        if constexpr (MTMAX >= 4)
+            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+        if constexpr (MTMAX >= 3)
+            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+        if constexpr (MTMAX >= 2)
+            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+        __syncthreads();  // before the next group's query operands and tiles
+    }
+}
+
+template <bool BF16, int D, int MT>
+int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
+    const dim3 grid((unsigned)a.H_kv, (unsigned)a.B, groups), block(Map<BF16, D, MT>::kThreads);
+    const size_t smem = Map<BF16, D, MT>::kSmem;
+    // keys that one workgroup reads once bypass the caches' replacement (non-temporal); further groups of a request
+    // find them in the caches
+    if constexpr (BF16) {
+        if (a.out_bf16 && groups == 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true, 2>), grid, block, smem, s, a);
+        else if (a.out_bf16) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false, 2>), grid, block, smem, s, a);
+        else hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false, 3>), grid, block, smem, s, a);
+    } else {
+        hipLaunchKernelGGL((attend_items_kernel<false, D, MT, false, 3>), grid, block, smem, s, a);
+    }
+    return check_launch("attend_items_kernel");
+}
+
+template <bool BF16, int D>
+int launch_mt(const ItemArgs& a, long long rows, bool bounded, hipStream_t s) {
+    constexpr int kMost = D == 64 ? 4 : 3;  // query tiles a wave holds without spilling
+    const int mt = (int)std::min<long long>(kMost, (rows + 15) / 16);
+    // an item gets as many workgroups as its rows need groups; with a bound too small, or none given, a workgroup may
+    // have to take several
+    const unsigned groups = (unsigned)std::min<long long>(bounded ? 64 : 4, (rows + 16 * mt - 1) / (16 * mt));
+    switch (mt) {
+        case 1: return launch<BF16, D, 1>(a, groups, s);
+        case 2: return launch<BF16, D, 2>(a, groups, s);
+        case 3: return launch<BF16, D, 3>(a, groups, s);
+        default: return launch<BF16, D, kMost>(a, groups, s);
+    }
+}
+
+}  // namespace
+
+int attend_items_launch(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_tables,
+                        const int32_t* ctx_lens, const int32_t* cu_q, void* out, float* lse, const fsr_attn_params* p,
+                        hipStream_t s, const char* who) {
+    if (p->N_cap > 65535) return fail(FSR_EUNSUP, "%s: the scratch-free path is limited to N_cap <= 65535 rows", who);
+    ItemArgs a;
+    const long long e = p->dtype == FSR_BF16 ? 2 : 4, row = p->D * e;
+    a.q = q; a.k = k_cache; a.v = v_cache; a.bt = block_tables; a.ctx = ctx_lens; a.cu_q = cu_q; a.out = out; a.lse = lse;
+    a.B = p->B; a.N_cap = p->N_cap; a.H_q = p->H_q; a.H_kv = p->H_kv; a.G = p->H_q / p->H_kv; a.P = p->P;
+    a.max_pages = p->max_pages; a.n_pages = p->n_pages;
+    a.p_shift = (p->P & (p->P - 1)) == 0 ? __builtin_ctz((unsigned)p->P) : -1;
+    a.out_bf16 = p->out_dtype == FSR_BF16;
+    a.page_stride = (long long)p->P * p->H_kv * row;
+    const bool token_major = p->kv_layout == FSR_KV_TOKEN_MAJOR;
+    a.slot_stride = token_major ? p->H_kv * row : row;
+    a.head_stride = token_major ? row : p->P * row;
+    a.scale_log2 = p->scale * (float)kLog2e;
+    a.scale_rest = (float)(p->scale - a.scale_log2 / kLog2e);
+    // query rows a KV head of one request can have: the caller's bound on its rows, or all rows of the call
+    const bool bounded = p->max_q_len > 0;
+    const long long rows = (long long)a.G * (bounded ? std::min(p->max_q_len, p->N_cap) : p->N_cap);
+    if (p->dtype == FSR_BF16) return p->D == 64 ? launch_mt<true, 64>(a, rows, bounded, s) : launch_mt<true, 128>(a, rows, bounded, s);
+    return p->D == 64 ? launch_mt<false, 64>(a, rows, bounded, s) : launch_mt<false, 128>(a, rows, bounded, s);
+}
+
+}  // namespace fsr

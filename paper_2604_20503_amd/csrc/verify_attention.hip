@@ -27,14 +27,15 @@
 //   * an item that lies inside one share is normalised and written directly; an item cut by
 //     a share boundary leaves (reference, sum, accumulator) partials -- at most two per workgroup
 //     -- and the workgroup whose piece arrives last combines them, in the same launch.
-// Generic path (fp32 or bf16, D in {64,128}, any page size): one wave per (row, head), plain
-// fp32 FMAs -- a correctness path for small or unusual shapes, not a bandwidth kernel.
+// Every other shape (fp32 inputs, D = 64, other page sizes, G > 16, B > 4096) is taken by
+// attend_items.hip, which needs no scratch memory.
 #include <algorithm>
 #include <atomic>
 #include <map>
 #include <mutex>
 #include <type_traits>
 
+#include "attend_items.hpp"
 #include "common.hpp"
 #include "device_utils.hpp"
 
@@ -1377,98 +1378,9 @@ __global__ __launch_bounds__(kThreads) void attn_planned_kernel(FastArgs a) {
     }
 }
 
-__device__ __forceinline__ int find_request(const int32_t* __restrict__ cu_q, int B, int row) {
-    int lo = 0, hi = B;  // largest i with cu_q[i] <= row, skipping empty requests to the right
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (cu_q[mid] <= row) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// ---------------------------------------------------------------------------------------
-// Generic path: one wave per (row, head); lanes stride over the keys.
-// ---------------------------------------------------------------------------------------
-struct GenericArgs {
-    const void* q;
-    const void* k;
-    const void* v;
-    const int32_t* bt;
-    const int32_t* ctx;
-    const int32_t* cu_q;
-    void* out;
-    float* lse;
-    int B, H_q, H_kv, P, max_pages, n_pages;
-    int token_major;  // 1: caches are [page][P][H_kv][D], 0: [page][H_kv][P][D]
-    float scale;
-};
-
-template <typename T>
-__device__ __forceinline__ float to_f32(T x);
-template <>
-__device__ __forceinline__ float to_f32<float>(float x) { return x; }
-template <>
-__device__ __forceinline__ float to_f32<uint16_t>(uint16_t x) { return __builtin_bit_cast(float, (uint32_t)x << 16); }
-
-template <typename T, typename OutT, int D>
-__global__ __launch_bounds__(64) void attn_generic_kernel(GenericArgs a) {
-    __shared__ float qs[D];
-    const int h = blockIdx.x, row = blockIdx.y, lane = threadIdx.x;
-    if (row >= a.cu_q[a.B]) return;
-    const int i = find_request(a.cu_q, a.B, row);
-    const int j = row - a.cu_q[i];
-    const int L = min(a.ctx[i] + j + 1, a.max_pages * a.P);
-    const int g = h / (a.H_q / a.H_kv);
-    const T* q = reinterpret_cast<const T*>(a.q) + ((size_t)row * a.H_q + h) * D;
-    for (int d = lane; d < D; d += 64) qs[d] = to_f32<T>(q[d]);
-    __syncthreads();
-    float m = -INFINITY, l = 0.0f;
-    float o[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) o[d] = 0.0f;
-    // the block table is read-only input: reading it through the constant address space lets the
-    // compiler use scalar loads for the (wave-uniform) page look-ups
-    const const_i32* bt = (const const_i32*)(a.bt + (size_t)i * a.max_pages);
-    const T* kc = reinterpret_cast<const T*>(a.k);
-    const T* vc = reinterpret_cast<const T*>(a.v);
-    for (int t = lane; t < L; t += 64) {
-        const int pg = min(max(bt[t / a.P], 0), a.n_pages - 1);
-        const size_t base = a.token_major ? (((size_t)pg * a.P + t % a.P) * a.H_kv + g) * D
-                                          : (((size_t)pg * a.H_kv + g) * a.P + t % a.P) * D;
-        float s = 0.0f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) s = fmaf(qs[d], to_f32<T>(kc[base + d]), s);
-        s *= a.scale;
-        const float m_new = fmaxf(m, s);
-        const float alpha = expf(m - m_new), p = expf(s - m_new);
-        l = l * alpha + p;
-#pragma unroll
-        for (int d = 0; d < D; ++d) o[d] = fmaf(p, to_f32<T>(vc[base + d]), o[d] * alpha);
-        m = m_new;
-    }
-    const float m_star = wave_max(m);  // L >= 1: lane 0 always has a key
-    const float f = m == -INFINITY ? 0.0f : expf(m - m_star);
-    float ls = l * f;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) ls += __shfl_xor(ls, off, 64);
-    const float inv = 1.0f / ls;
-    OutT* out = reinterpret_cast<OutT*>(a.out) + ((size_t)row * a.H_q + h) * D;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        float x = o[d] * f;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        if (lane == (d & 63)) {
-            if constexpr (sizeof(OutT) == 4) out[d] = x * inv;
-            else out[d] = f32_to_bf16_rne(x * inv);
-        }
-    }
-    if (a.lse && lane == 0) a.lse[(size_t)row * a.H_q + h] = m_star + logf(ls);
-}
-
 // How a call is run.
 struct Setup {
-    bool fast;   // the stream kernel (bf16, D = 128, P = 16, G <= 16, B <= kMaxB); else one wave per (row, head)
+    bool fast;   // the stream kernel (bf16, D = 128, P = 16, G <= 16, B <= kMaxB); else attend_items.hip
     int mt_max;  // 16-row query tiles a team of waves takes (template argument of the kernel)
     bool wide;   // row groups of two teams (requests with more than kMaxMT query tiles of rows per KV head)
     int m_cap;   // rows a partial slot holds
@@ -1690,24 +1602,7 @@ int attention_call(const void* q, const void* k_cache, const void* v_cache, cons
 #undef FSR_LAUNCH_K
         return check_launch(plan ? "attn_planned_kernel" : "attn_stream_kernel");
     }
-    GenericArgs g;
-    g.q = q; g.k = k_cache; g.v = v_cache; g.bt = block_tables; g.ctx = ctx_lens; g.cu_q = cu_q; g.out = out; g.lse = lse;
-    g.B = p->B; g.H_q = p->H_q; g.H_kv = p->H_kv; g.P = p->P; g.max_pages = p->max_pages; g.n_pages = p->n_pages;
-    g.scale = p->scale;
-    g.token_major = p->kv_layout == FSR_KV_TOKEN_MAJOR;
-    const dim3 grid(p->H_q, p->N_cap), block(64);
-    if (p->N_cap > 65535) return fail(FSR_EUNSUP, "%s: the one-wave-per-row path is limited to N_cap <= 65535 rows", who);
-    const bool bf_in = p->dtype == FSR_BF16, bf_out = p->out_dtype == FSR_BF16;
-    if (p->D == 64) {
-        if (!bf_in) hipLaunchKernelGGL((attn_generic_kernel<float, float, 64>), grid, block, 0, s, g);
-        else if (bf_out) hipLaunchKernelGGL((attn_generic_kernel<uint16_t, uint16_t, 64>), grid, block, 0, s, g);
-        else hipLaunchKernelGGL((attn_generic_kernel<uint16_t, float, 64>), grid, block, 0, s, g);
-    } else {
-        if (!bf_in) hipLaunchKernelGGL((attn_generic_kernel<float, float, 128>), grid, block, 0, s, g);
-        else if (bf_out) hipLaunchKernelGGL((attn_generic_kernel<uint16_t, uint16_t, 128>), grid, block, 0, s, g);
-        else hipLaunchKernelGGL((attn_generic_kernel<uint16_t, float, 128>), grid, block, 0, s, g);
-    }
-    return check_launch("attn_generic_kernel");
+    return attend_items_launch(q, k_cache, v_cache, block_tables, ctx_lens, cu_q, out, lse, p, s, who);
 }
 }  // namespace
 
@@ -1822,7 +1717,7 @@ extern "C" int fsr_verify_attention_static(const void* q, const void* k_cache, c
     int rc = validate(p, "fsr_verify_attention_static");
     if (rc != FSR_OK) return rc;
     const Setup su = make_setup(*p, kStaticShares);
-    if (!su.fast)  // the one-wave-per-row kernel uses no scratch buffer at all
+    if (!su.fast)  // the other kernel uses no scratch buffer at all
         return attention_call(q, k_cache, v_cache, nullptr, nullptr, false, block_tables, ctx_lens, cu_q, out, lse, p, nullptr, nullptr, 0,
                               kStaticShares, stream, "fsr_verify_attention_static");
     if (su.ws_bytes() > kStaticScratchBytes)

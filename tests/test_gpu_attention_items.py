@@ -1,0 +1,108 @@
+"""GPU parity of the attention shapes outside the stream kernel (fp32, heads of 64, other page sizes, wide query groups)
+against the oracle: edges of key tiles and of query-row groups, both layouts, any alignment, Inf and NaN values."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from gpu_utils import announce, check_attention, dev
+
+pytestmark = pytest.mark.gpu
+
+# contexts around the 16- and 32-key tiles, their stride over four and eight waves, and page ends
+CTX = [0, 1, 14, 15, 16, 31, 32, 63, 64, 127, 128, 240, 255, 256, 257, 300, 511, 513, 700]
+SPEC = [2, 0, 1, 0, 3, 7, 1, 4, 0, 8, 2, 15, 0, 5, 1, 9, 0, 3, 6]
+
+
+@pytest.fixture(scope="module")
+def fsr():
+    import paper_2604_20503_amd as f
+    f.load_library()
+    return f
+
+
+def make(rng, dtype, H_q, H_kv, D, P, ctx, spec):
+    ctx, spec = np.asarray(ctx, np.int32), np.asarray(spec, np.int32)
+    tok = ctx + spec + 1
+    npg = (tok + P - 1) // P
+    n_pages = int(npg.sum()) + 2
+    perm = rng.permutation(n_pages).astype(np.int32)
+    bt = np.full((len(ctx), int(npg.max()) + 1), -1, np.int32)
+    at = 0
+    for i, n in enumerate(npg):
+        bt[i, :n] = perm[at:at + n]
+        at += n
+    cu = workloads.exclusive_offsets(spec + 1)
+    st = lambda s: workloads._normal_store(rng, s, dtype)  # noqa: E731
+    return dict(ctx=ctx, cu=cu, bt=bt, q=st((int(cu[-1]), H_q, D)), k=st((n_pages, H_kv, P, D)), v=st((n_pages, H_kv, P, D)))
+
+
+def run(fsr, oracle, x, dtype, H_q, H_kv, D, P, *, token_major=False, out_dtype=torch.float32, hint=0, shift=0):
+    bf = dtype == "bf16"
+    swap = (lambda t: np.ascontiguousarray(np.swapaxes(t, 1, 2))) if token_major else (lambda t: t)
+
+    def place(t):  # the tensor at an address `shift` elements past an aligned one
+        flat = dev(t, bf).reshape(-1)
+        room = torch.empty(flat.numel() + shift, dtype=flat.dtype, device="cuda")
+        room[shift:] = flat
+        return room[shift:].view(t.shape)
+
+    q, k, v = place(x["q"]), place(swap(x["k"])), place(swap(x["v"]))
+    out = torch.empty(q.numel() + shift, dtype=out_dtype, device="cuda")[shift:].view(q.shape)
+    lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+    scale = 1.0 / np.sqrt(D)
+    fsr.verify_attention(q, k, v, dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=scale, out=out, lse=lse,
+                         max_q_len=hint, kv_layout=1 if token_major else 0)
+    torch.cuda.synchronize()
+    ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=H_q, H_kv=H_kv, D=D, P=P,
+                                           dtype=dtype, scale=float(np.float32(scale)))
+    return out, lse, ref, lse_ref
+
+
+@pytest.mark.parametrize("dtype,H_q,H_kv,D,P,token_major", [
+    ("f32", 8, 2, 64, 16, False), ("f32", 6, 6, 128, 16, True), ("f32", 14, 2, 64, 24, False), ("f32", 40, 2, 128, 8, False),
+    ("bf16", 8, 2, 64, 16, False), ("bf16", 6, 6, 64, 16, True), ("bf16", 14, 2, 64, 24, True), ("bf16", 20, 1, 64, 1, False),
+    ("bf16", 8, 2, 128, 32, False), ("bf16", 34, 2, 128, 16, True), ("bf16", 80, 1, 128, 16, False)])
+def test_shapes_outside_the_stream_kernel(fsr, oracle, dtype, H_q, H_kv, D, P, token_major):
+    rng = np.random.Generator(np.random.PCG64(31 * H_q + D + P))
+    x = make(rng, dtype, H_q, H_kv, D, P, CTX, SPEC)
+    # the bound on a request's rows given, given too small, not given (different query tiles and groups)
+    for hint in (max(SPEC) + 1, 2, 0):
+        announce(f"items {dtype} heads={H_q}/{H_kv} D={D} P={P} token_major={token_major} hint={hint}")
+        out, lse, ref, lse_ref = run(fsr, oracle, x, dtype, H_q, H_kv, D, P, token_major=token_major, hint=hint)
+        err = check_attention(out, ref, "f32", len(ref))  # fp32 accuracy for bf16 inputs too: nothing is rounded to 16 bits
+        np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+        print(f"max rel err {err:.2e}")
+
+
+@pytest.mark.parametrize("dtype,D,shift,out_dtype", [("f32", 64, 1, torch.float32), ("bf16", 64, 1, torch.bfloat16),
+                                                     ("bf16", 64, 3, torch.float32)])
+def test_inputs_aligned_to_their_elements_only(fsr, oracle, dtype, D, shift, out_dtype):
+    announce(f"items {dtype} shift={shift} out={out_dtype}")
+    rng = np.random.Generator(np.random.PCG64(5))
+    x = make(rng, dtype, 8, 2, D, 16, CTX[:8], SPEC[:8])
+    out, _, ref, _ = run(fsr, oracle, x, dtype, 8, 2, D, 16, out_dtype=out_dtype, hint=9, shift=shift)
+    check_attention(out, ref, "f32" if out_dtype == torch.float32 else "bf16", len(ref))
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_values_that_are_not_finite_reach_their_rows_only(fsr, oracle, dtype, D, bad):
+    """One element of V at the second drafted token's position: rows before it are untouched, rows from it on carry the
+    value in that element (and only there); keys of another request never matter."""
+    announce(f"items {dtype} D={D} V={bad}")
+    rng = np.random.Generator(np.random.PCG64(9))
+    P = 16 if D == 64 else 32
+    ctx, spec = [40, 33], [4, 3]
+    x = make(rng, dtype, 4, 1, D, P, ctx, spec)
+    ref, _ = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=4, H_kv=1, D=D, P=P, dtype=dtype,
+                                     scale=float(np.float32(1.0 / np.sqrt(D))))
+    t, d = ctx[0] + 2, 5
+    code = np.float32(bad) if dtype == "f32" else np.uint16(np.float32(bad).view(np.uint32) >> 16)
+    x["v"][x["bt"][0, t // P], 0, t % P, d] = code
+    out, _, _, _ = run(fsr, oracle, x, dtype, 4, 1, D, P, hint=5)
+    o = out.cpu().numpy()
+    hit = np.zeros(ref.shape, bool)
+    hit[2:5, :, d] = True
+    assert np.array_equal(o[hit], np.full(hit.sum(), bad, np.float32), equal_nan=True)
+    np.testing.assert_allclose(o[~hit], ref[~hit], rtol=0, atol=1e-5 * np.abs(ref).max())
