@@ -1,0 +1,48 @@
+"""Plans whose shares hold many segments: the planned call is bit-identical to the one that schedules itself (the oracle
+covers the latter)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from gpu_utils import announce, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fsr():
+    import paper_2604_20503_amd as f
+    f.load_library()
+    return f
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,spec_hi,max_workgroups,hint", [
+    (300, 8, 8, 3, 3, 4),      # 2400 items on three shares: a wave takes more than 64 segments; two rounds of the prefix
+    (65, 32, 8, 20, 7, 0),     # no bound on the rows: several row groups per request (two-team kernel)
+    (65, 32, 8, 20, 0, 2),     # a bound that is too small: several one-tile groups per request
+    (1, 16, 1, 0, 0, 1),       # one item, cut into as many pieces as it has tiles or workgroups
+])
+def test_many_segments_per_share(fsr, B, H_q, H_kv, spec_hi, max_workgroups, hint):
+    announce(f"plan segments B={B} heads={H_q}/{H_kv} workgroups={max_workgroups} hint={hint}")
+    rng = np.random.Generator(np.random.PCG64(B + H_q))
+    ctx = rng.integers(0, 200, size=B) if B > 1 else np.array([3000])
+    spec = rng.integers(0, spec_hi + 1, size=B)
+    b = workloads.make_batch(2, with_probs=False, H_q=H_q, H_kv=H_kv, ctx_lens=ctx, spec_lens=spec)
+    cu = b.cu_q.copy()
+    if B > 1:  # every fifth request has no rows: its rows go to the next one's neighbour
+        lens = np.diff(cu)
+        lens[::5] = 0
+        cu = workloads.exclusive_offsets(lens)
+    q, k, v = dev(b.q, True), dev(b.k_cache, True), dev(b.v_cache, True)
+    bt, ctx_d, cu_d = dev(b.block_tables), dev(b.ctx_lens), dev(cu)
+    kw = dict(scale=b.scale, max_q_len=hint, max_workgroups=max_workgroups)
+    outs = []
+    for plan in (None, fsr.attn_plan(q, k, bt, ctx_d, cu_d, **kw)):
+        out = torch.zeros(q.shape, dtype=torch.float32, device="cuda")
+        lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+        fsr.verify_attention(q, k, v, bt, ctx_d, None, cu_d, out=out, lse=lse, plan=plan, **kw)
+        torch.cuda.synchronize()
+        assert torch.isfinite(out).all()
+        outs.append((out, lse))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
