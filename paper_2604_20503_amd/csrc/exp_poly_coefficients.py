@@ -4,7 +4,10 @@
 The polynomial takes the values of exp at the 11 Chebyshev nodes of [-a, a], a = ln2 / 2 widened by 0.05 %; the
 linear system is solved by Gaussian elimination in x87 extended precision (numpy.longdouble) and the result rounded
 to fp64.  Prints the coefficients (constant term first) and the largest relative error of the fp64 Horner
-evaluation over the interval.  Run it to check or regenerate the constants in the kernel source."""
+evaluation over the interval.  Run it to check or regenerate the constants in the kernel source; with the argument
+--table it prints exp_table.inc instead, the 256 values 2^(j/256) that exp_table looks up."""
+import sys
+
 import numpy as np
 
 LD = np.longdouble
@@ -39,7 +42,29 @@ def max_relative_error(c, samples=200001):
     return float(np.max(np.abs(p.astype(LD) / np.exp(x.astype(LD)) - 1)))
 
 
+def table():
+    """2^(j/256), j = 0 .. 255: products of the square roots 2^(1/2), 2^(1/4), ... in extended precision."""
+    roots = []
+    r = LD(2)
+    for _ in range(8):
+        r = np.sqrt(r)
+        roots.append(r)
+    out = []
+    for j in range(256):
+        v = LD(1)
+        for b in range(8):
+            if j >> (7 - b) & 1:
+                v = v * roots[b]
+        out.append(float(v))
+    return out
+
+
 if __name__ == "__main__":
+    if sys.argv[1:] == ["--table"]:
+        t = table()
+        for j in range(0, 256, 4):
+            print(" ".join(f"{v.hex()}," for v in t[j:j + 4]))
+        sys.exit(0)
     c = coefficients()
     for i, v in enumerate(c):
         print(f"c{i} = {float(v)!r}")

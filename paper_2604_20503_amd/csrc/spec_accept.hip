@@ -35,6 +35,7 @@ constexpr int kChunk = 4096;        // vocabulary tokens per chunk
 constexpr int kThreads = 256;       // threads per block in stats / partials / select
 constexpr int kPerThread = kChunk / kThreads;  // 16 contiguous tokens per thread in select
 constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (max, sum) pair
+constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
 constexpr int kLazyJ = 2;           // LOGITS mode, two-pass statistics: drafts tested before the rest of a request's rows is normalised
 constexpr int kLazyMinRows = 3072;  // rows a call must be able to hold for the two extra launches of the two passes to pay
 constexpr int kMaxSampleGroup = 8;  // accept_sample: a workgroup takes 1, 2, 4 or 8 consecutive chunks (see launch_all)
@@ -207,6 +208,52 @@ __device__ __forceinline__ double exp_softmax(double x, const ExpConsts& k) {
     p = fma(p, r, 1.0);
     return ldexp(p, (int)(uint32_t)__builtin_bit_cast(unsigned long long, t));
 }
+// exp for the loops over whole rows, where its instruction count is the kernel's time: x = n ln2 / 256 + r with
+// |r| <= ln2 / 512, 2^(n/256) from a table of 256 values in LDS and four terms of the series in r: 13 instructions and a
+// table look-up where exp_softmax takes 16, and closer to exp (2.3e-16).  The integer n sits in the low word of the
+// rounding sum; the table's high words are stored less j << 12, so that one shift-and-add of n puts 2^(n / 256) together.
+// Measured, statistics of 512 requests x 152064 logits (about 2.9 GB of rows, bound by the vector ALUs): 693 -> 557 us, with
+// the references that need no rescaling per chunk.
+// Arguments below kExpTableFloor (and NaN) count as that floor: 1e-304, so that the exponent stays a normal one.
+constexpr double kExpTableFloor = -700.0;
+__device__ const double kExp2Table[256] = {
+#include "exp_table.inc"
+};
+struct ExpTable {
+    const uint2* tab;  // LDS
+    double c, nl_hi, nl_lo, magic, c4, c3, floor;
+};
+__device__ __forceinline__ void fill_exp_table(uint2* tab) {
+    for (int j = threadIdx.x; j < 256; j += kThreads) {
+        const unsigned long long v = __builtin_bit_cast(unsigned long long, kExp2Table[j]);
+        tab[j] = make_uint2((uint32_t)v, (uint32_t)(v >> 32) - ((uint32_t)j << 12));
+    }
+}
+__device__ __forceinline__ ExpTable exp_table(const uint2* tab) {
+    ExpTable k;
+    k.tab = tab;
+    k.c = 369.3299304675746;            // 256 / ln2
+    k.nl_hi = -0.00270760617331689;     // -ln2 / 256 in two parts, the high one with 21 zero bits at its end
+    k.nl_lo = -7.453964567463233e-13;
+    k.magic = 6755399441055744.0;       // 1.5 * 2^52
+    k.c4 = 1.0 / 24.0;
+    k.c3 = 1.0 / 6.0;
+    k.floor = kExpTableFloor;
+    asm volatile("" : "+s"(k.floor), "+s"(k.c), "+s"(k.nl_hi), "+s"(k.nl_lo), "+s"(k.c4), "+v"(k.c3), "+v"(k.magic));
+    return k;
+}
+__device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
+    x = fmax(x, k.floor);
+    const double t = fma(x, k.c, k.magic);
+    const double kf = t - k.magic;
+    const uint32_t n = (uint32_t)__builtin_bit_cast(unsigned long long, t);
+    const uint2 e = k.tab[n & 255u];
+    double r = fma(kf, k.nl_hi, x);
+    r = fma(kf, k.nl_lo, r);
+    const double p = fma(fma(fma(r, k.c4, k.c3), r, 0.5), r, 1.0);
+    const double pow2 = __builtin_bit_cast(double, ((unsigned long long)(e.y + (n << 12)) << 32) | e.x);
+    return fma(pow2 * r, p, pow2);
+}
 // The constants for a kernel of the given mode: PROBS mode never evaluates exp and gets an empty set.
 template <int MODE>
 __device__ __forceinline__ ExpConsts exp_consts_for() {
@@ -231,8 +278,9 @@ __device__ __forceinline__ double prob_of(float x, double T, double m, double Z,
 // grid = (n_stat_groups, B * slots): a request owns `slots` consecutive workgroup rows; slot k < t_n is its target
 // row t_lo + k, the others are its draft rows d_lo, d_lo + 1, ...  (which of the request's rows a pass covers is
 // the host's choice: all of them, those of the first kLazyJ drafts, or the rest for the requests left pending).
-// Each lane keeps a running maximum and a sum relative to it over its own elements (16 per chunk), so the chunks of
-// a group need no exchange between lanes; lanes and waves are combined once, at the end.
+// Each lane keeps a reference (its first chunk's largest logit, replaced only by one far above it) and a sum relative to
+// it over its own elements (16 per chunk), so the chunks of a group need no exchange between lanes; lanes and waves are
+// combined once, at the end.  Any reference gives the same probabilities; it has to keep the exponents in range.
 // ---------------------------------------------------------------------------------------
 template <typename RT>
 __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
@@ -241,6 +289,7 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
     Workspace ws, int B, int V, int S_max, double T, int slots, int t_lo, int t_n, int d_lo, int only_pending) {
     __shared__ double s_sum[kThreads / 64];
     __shared__ float s_max[kThreads / 64];
+    __shared__ uint2 s_exp[256];
     const int nc = n_chunks_of(V), nsg = n_stat_groups_of(V, ws.stat_group);
     const int i = blockIdx.y / slots, k = blockIdx.y - i * slots;
     if (only_pending && !ws.pending[i]) return;
@@ -262,17 +311,22 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
     }
     const bool vec = row_vec_ok(rows);
     const double inv_T = 1.0 / T;
+    fill_exp_table(s_exp);
+    __syncthreads();
     const ExpConsts ek = exp_consts();
+    const ExpTable et = exp_table(s_exp);
     const int c_first = blockIdx.x * ws.stat_group, c_end = min(nc, c_first + ws.stat_group);
-    float mz = -INFINITY;  // largest logit this lane has seen
-    double mzT = 0.0;      // mz / T once mz is finite
-    double sum = 0.0;      // sum of exp(z / T - mz / T) over this lane's elements
+    float mz = -INFINITY;   // this lane's reference: a logit it has seen, no more than kStatSlack * T below the largest
+    float limit = -INFINITY;  // a logit above this makes a new reference
+    double mzT = 0.0;       // mz / T once mz is finite
+    double sum = 0.0;       // sum of exp(z / T - mz / T) over this lane's elements
+    const float slack = (float)(kStatSlack * T);
     // The fold over the group's chunks, twice: for whole chunks of a row aligned for vector loads (four loads per
     // lane and chunk, all in flight together, the next chunk's issued before this one's arithmetic), and with every
     // element bounds-checked for the chunk that holds the vocabulary's ragged end or a row that is not aligned.
     // Two separate loops, because mixed in one the compiler orders each vector load behind all loads before it.
     auto fold = [&](auto whole, int c_lo, int c_hi) {
-        float cur[kPerThread], nxt[kPerThread];
+        float va[kPerThread], vb[kPerThread];
         auto load_chunk = [&](int c, float (&v)[kPerThread]) {
 #pragma unroll
             for (int q = 0; q < kPerThread / 4; ++q) {
@@ -284,23 +338,30 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
                 for (int u = 0; u < 4; ++u) v[q * 4 + u] = x[u];
             }
         };
-        if (c_lo >= c_hi) return;
-        load_chunk(c_lo, cur);
-        for (int c = c_lo; c < c_hi; ++c) {
-            if (c + 1 < c_hi) load_chunk(c + 1, nxt);
-            float mx = cur[0];
+        auto add_chunk = [&](const float (&v)[kPerThread]) {
+            float mx = v[0];
 #pragma unroll
-            for (int u = 1; u < kPerThread; ++u) mx = fmaxf(mx, cur[u]);
-            if (mx > mz) {  // rescale what was summed against the old maximum
+            for (int u = 1; u < kPerThread; ++u) mx = fmaxf(mx, v[u]);
+            if (mx > limit) {  // rescale what was summed against the old reference
                 const double mxT = (double)mx * inv_T;
                 sum = mz == -INFINITY ? 0.0 : sum * exp_softmax(mzT - mxT, ek);
                 mz = mx;
                 mzT = mxT;
+                limit = mz + slack;
             }
+            // (a masked logit -- -inf, NaN, past V -- or one far below the reference adds 1e-304)
 #pragma unroll
-            for (int u = 0; u < kPerThread; ++u) sum += exp_softmax((double)cur[u] * inv_T - mzT, ek);  // -inf (masked, or past V) adds 0
-#pragma unroll
-            for (int u = 0; u < kPerThread; ++u) cur[u] = nxt[u];
+            for (int u = 0; u < kPerThread; ++u) sum += exp_lookup(fma((double)v[u], inv_T, -mzT), et);
+        };
+        if (c_lo >= c_hi) return;
+        load_chunk(c_lo, va);
+#pragma unroll 1
+        for (int c = c_lo; c < c_hi; c += 2) {
+            if (c + 1 < c_hi) load_chunk(c + 1, vb);
+            add_chunk(va);
+            if (c + 1 >= c_hi) break;
+            if (c + 2 < c_hi) load_chunk(c + 2, va);
+            add_chunk(vb);
         }
     };
     const int c_whole = vec ? min(c_end, V / kChunk) : c_first;  // chunks before it are whole and aligned
