@@ -217,17 +217,14 @@ def kernel_figures(b, st, times_us):
         norm_rows = 2 * tested + (acc == d)
         logits_bytes = int(((norm_rows + rows) * 4 * b.V + 8 * d).sum())
         all_rows_bytes = int((2 * d + 1).sum()) * 4 * b.V
-        if b.B * (2 * b.S_max + 1) >= 3072 and b.S_max > 3:  # two passes: rows of the first two drafts, then the rest of the undecided
-            pend = (np.minimum(acc, 2) == np.minimum(d, 2)) & (d > 2)
-            read_rows = np.minimum(d + 1, 3) + np.minimum(d, 2) + pend * ((d + 1 - 3) + (d - 2))
-        else:
-            read_rows = 2 * d + 1
+        # a large call leaves out rows behind a rejected draft (all but those already started: the least is norm_rows)
+        read_rows = norm_rows if b.B * (2 * b.S_max + 1) >= 2048 else 2 * d + 1
         read_bytes = int(((read_rows + rows) * 4 * b.V).sum())
         extra["spec_accept_logits"] = fig(
             times_us["accept_logits"], logits_bytes, 3,
-            "accept_stats_kernel (twice, with a first accept_decide_kernel in between, when the call holds 3072 rows or more) + accept_decide_kernel + "
+            "accept_stats_kernel (behind an accept_clear_kernel when the call holds 2048 rows or more) + accept_decide_kernel + "
             f"accept_sample_kernel, T = 1; normalising every row of the call would read {all_rows_bytes} bytes; "
-            f"this call reads {read_bytes} bytes; "
+            f"this call reads {read_bytes} bytes (or somewhat more); "
             f"not part of the timed step")
     if "attention_kv8" in times_us:
         L = st["variant_layers"]

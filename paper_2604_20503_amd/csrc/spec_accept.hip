@@ -8,12 +8,14 @@
 // Work split.  A verification batch has few requests (16 .. 512) but a vocabulary of
 // ~1.3e5, so one workgroup per request cannot fill the chip: every vocabulary row is cut
 // into chunks of kChunk tokens and the vocabulary-wide sums are two-level.
-//   stats    (LOGITS mode only) per row and group of 1-8 chunks: max of z / T and sum of exp(z / T - max) in
-//            fp64.  A large call takes two passes: the rows the first kLazyJ drafts of every request need,
-//            a first `decide` on those drafts, then the remaining rows of the requests still undecided and
-//            `decide` once more for those (only rows 0 .. n of a request, n = accepted drafts, are needed)
+//   stats    (LOGITS mode only) per row and group of 1-8 chunks: a reference and the sum of exp(z / T - reference) in
+//            fp64.  The rows of all requests' first drafts come first in the grid, then those of their second drafts
+//            and so on; the workgroup that finishes a draft's two rows last tests the draft, and rows behind a
+//            rejected draft that have not been started by then are left out (only rows 0 .. n of a request are
+//            needed, n = accepted drafts)
 //   decide   per request, one wave: the accept tests, one lane per draft with all gathers in flight
-//            together; picks the row pair to sample from and records it
+//            together (LOGITS mode: the outcome that `stats` has found); picks the row pair to sample from and
+//            records it
 //   sample   grid (chunks, requests): every workgroup sums the fp64 mass of its chunk of the residual
 //            and of the target row; the workgroup of a request that finishes last (found by an arrival
 //            counter that `decide` has zeroed) draws the token: prefix over the chunk masses -> chunk
@@ -35,9 +37,8 @@ constexpr int kChunk = 4096;        // vocabulary tokens per chunk
 constexpr int kThreads = 256;       // threads per block in stats / partials / select
 constexpr int kPerThread = kChunk / kThreads;  // 16 contiguous tokens per thread in select
 constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (max, sum) pair
+constexpr int kSkipMinRows = 2048;  // LOGITS mode: rows a call must be able to hold for rows behind a rejection to be left out
 constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
-constexpr int kLazyJ = 2;           // LOGITS mode, two-pass statistics: drafts tested before the rest of a request's rows is normalised
-constexpr int kLazyMinRows = 3072;  // rows a call must be able to hold for the two extra launches of the two passes to pay
 constexpr int kMaxSampleGroup = 8;  // accept_sample: a workgroup takes 1, 2, 4 or 8 consecutive chunks (see launch_all)
 constexpr int kMaxChunksLds = 256;  // chunk masses of a request that the selecting workgroup keeps in LDS (vocabularies up to 2^20)
 
@@ -61,7 +62,10 @@ struct Workspace {
     double* stat_d;      // [R_d_cap, n_stat_groups, 2]
     unsigned int* arrivals;  // [B] chunk workgroups of the request that have finished (zeroed by decide)
     int stat_group;          // chunks per (max, sum) pair in this call (set at launch)
-    int* pending;            // [B] (LOGITS, two-pass statistics) the request's first kLazyJ drafts were all accepted and more remain
+    // LOGITS mode, while the statistics of a large call are made (the memory is that of the chunk masses, which come
+    // later): 2 * n_chunks 32-bit words per request from mass_res on, word 0 the first rejected draft, word 1 + j the
+    // workgroups that have finished rows j (accept_clear_kernel sets them up).  0: `decide` tests the drafts.
+    int skip;
 };
 
 __host__ __device__ inline int n_chunks_of(int V) { return (V + kChunk - 1) / kChunk; }
@@ -80,10 +84,9 @@ size_t carve(const fsr_accept_params& p, char* base, Workspace* w) {
     tmp.mass_res = (double*)take(B * nc * sizeof(double));
     tmp.mass_tgt = (double*)take(B * nc * sizeof(double));
     tmp.arrivals = (unsigned int*)take(B * sizeof(unsigned int));
-    tmp.pending = nullptr;
+    tmp.skip = 0;
     tmp.stat_group = kMaxStatGroup;
     if (p.mode == FSR_LOGITS) {
-        tmp.pending = (int*)take(B * sizeof(int));
         const size_t nsg = nc;  // room for one pair per chunk; a call folds 1, 2, 4 or 8 chunks into a pair
         tmp.stat_t = (double*)take(B * (size_t)(p.S_max + 1) * nsg * 2 * sizeof(double));
         tmp.stat_d = (double*)take(B * (size_t)p.S_max * nsg * 2 * sizeof(double));
@@ -94,16 +97,14 @@ size_t carve(const fsr_accept_params& p, char* base, Workspace* w) {
     return off;
 }
 
-__device__ __forceinline__ double block_sum(double v, double* smem) {
-    v = wave_sum(v);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) smem[w] = v;
-    __syncthreads();
-    double t = 0.0;
-#pragma unroll
-    for (int k = 0; k < kThreads / 64; ++k) t += smem[k];
-    return t;
+constexpr unsigned kNoRejection = 0xffffffffu;
+// The request's words of the statistics (see Workspace::skip).
+__device__ __forceinline__ unsigned* stat_words(const Workspace& ws, int i, int nc) {
+    return reinterpret_cast<unsigned*>(ws.mass_res + (size_t)i * nc);
+}
+__global__ __launch_bounds__(kThreads) void accept_clear_kernel(Workspace ws, int n_words, int nc) {
+    const int w = blockIdx.x * kThreads + threadIdx.x;
+    if (w < n_words) stat_words(ws, 0, nc)[w] = w % (2 * nc) == 0 ? kNoRejection : 0u;
 }
 
 // Rows are fp32, or bf16 stored as 16-bit patterns (the upper half of an fp32).
@@ -273,42 +274,69 @@ __device__ __forceinline__ double prob_of(float x, double T, double m, double Z,
     }
 }
 
+// 8-byte values that another workgroup of the same launch reads: stored through to memory / loaded past the caches
+__device__ __forceinline__ void publish_f64(double* p, double v) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double fetch_f64(const double* p) {
+    return __builtin_bit_cast(double, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// Combine a row's chunk statistics into (max, partition sum); all lanes of the wave call it.  FRESH: the statistics were
+// made by other workgroups of this launch.
+template <bool FRESH>
+__device__ __forceinline__ void combine_stats(const double* __restrict__ stat, int nc, const ExpConsts& ek, double& m, double& Z) {
+    auto at = [&](int k) { return FRESH ? fetch_f64(stat + k) : stat[k]; };
+    const int lane = threadIdx.x & 63;
+    double mm = -INFINITY;
+    for (int c = lane; c < nc; c += 64) mm = fmax(mm, at(c * 2));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mm = fmax(mm, __shfl_xor(mm, o, 64));
+    double z = 0.0;
+    for (int c = lane; c < nc; c += 64) z += at(c * 2 + 1) * exp_softmax(at(c * 2) - mm, ek);
+    m = mm;
+    Z = wave_sum(z);
+}
 // ---------------------------------------------------------------------------------------
 // LOGITS mode: per row and group of ws.stat_group chunks, the maximum of z / T and the sum of exp(z / T - max), fp64.
-// grid = (n_stat_groups, B * slots): a request owns `slots` consecutive workgroup rows; slot k < t_n is its target
-// row t_lo + k, the others are its draft rows d_lo, d_lo + 1, ...  (which of the request's rows a pass covers is
-// the host's choice: all of them, those of the first kLazyJ drafts, or the rest for the requests left pending).
+// grid = (n_stat_groups, (2 * S_max + 1) * B): workgroup row k * B + i takes, of request i, target row k / 2 for even k and
+// draft row k / 2 for odd k, so that the rows of the first drafts are all started before any row of a second draft.
 // Each lane keeps a reference (its first chunk's largest logit, replaced only by one far above it) and a sum relative to
 // it over its own elements (16 per chunk), so the chunks of a group need no exchange between lanes; lanes and waves are
 // combined once, at the end.  Any reference gives the same probabilities; it has to keep the exponents in range.
 // ---------------------------------------------------------------------------------------
 template <typename RT>
 __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
-    const RT* __restrict__ z_target, const RT* __restrict__ z_draft, const int32_t* __restrict__ cu_t,
-    const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
-    Workspace ws, int B, int V, int S_max, double T, int slots, int t_lo, int t_n, int d_lo, int only_pending) {
+    const RT* __restrict__ z_target, const RT* __restrict__ z_draft, const int32_t* __restrict__ draft_tokens,
+    const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
+    const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, Workspace ws, int B, int V, int S_max, double T) {
     __shared__ double s_sum[kThreads / 64];
     __shared__ float s_max[kThreads / 64];
     __shared__ uint2 s_exp[256];
+    __shared__ int s_last;
     const int nc = n_chunks_of(V), nsg = n_stat_groups_of(V, ws.stat_group);
-    const int i = blockIdx.y / slots, k = blockIdx.y - i * slots;
-    if (only_pending && !ws.pending[i]) return;
+    const int k = blockIdx.y / B, i = blockIdx.y - k * B, j = k >> 1;
+    const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
     const RT* rows;
     double* stat;
-    if (k < t_n) {
-        const int j = t_lo + k, t0 = cu_t[i], t_i = cu_t[i + 1] - t0;
+    if ((k & 1) == 0) {
         const long long r = (long long)t0 + j;
         // no such row, or past what the workspace or the caller's row map holds (offsets of an invalid call)
         if (j >= t_i || t0 < 0 || r >= (long long)B * (S_max + 1) || r >= cu_t[B]) return;
         rows = z_target + (size_t)(t_rows ? t_rows[r] : r) * V;
-        stat = ws.stat_t + ((size_t)r * nsg + blockIdx.x) * 2;
+        stat = ws.stat_t + (size_t)r * nsg * 2;
     } else {
-        const int j = d_lo + (k - t_n), d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
         const long long r = (long long)d0 + j;
         if (j >= d_i || d0 < 0 || r >= (long long)B * S_max || r >= cu_d[B]) return;
         rows = z_draft + (size_t)(d_rows ? d_rows[r] : r) * V;
-        stat = ws.stat_d + ((size_t)r * nsg + blockIdx.x) * 2;
+        stat = ws.stat_d + (size_t)r * nsg * 2;
     }
+    // a draft before this row's has been rejected: nothing will read the row's statistics
+    if (ws.skip && j > 0 &&
+        __hip_atomic_load(stat_words(ws, i, nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned)j)
+        return;
     const bool vec = row_vec_ok(rows);
     const double inv_T = 1.0 / T;
     fill_exp_table(s_exp);
@@ -384,23 +412,29 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
 #pragma unroll
         for (int q = 0; q < kThreads / 64; ++q)
             if (s_max[q] != -INFINITY) tot += s_sum[q] * exp_softmax((double)s_max[q] * inv_T - mgT, ek);
-        stat[0] = mgT;  // -inf for a group of masked logits only
-        stat[1] = tot;
+        publish_f64(stat + blockIdx.x * 2, mgT);  // -inf for a group of masked logits only
+        publish_f64(stat + blockIdx.x * 2 + 1, tot);
+        s_last = 0;
+        if (ws.skip && j < d_i && j < S_max) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the pair is in memory before it is counted
+            s_last = atomicAdd(stat_words(ws, i, nc) + 1 + j, 1u) + 1 == 2u * nsg;
+        }
     }
+    if (!ws.skip || j >= d_i || j >= S_max) return;
+    __syncthreads();
+    if (!s_last || threadIdx.x >= 64) return;
+    // the draft's rows are done (both lie inside the workspace and the row maps: their workgroups have checked): test it
+    const long long rt = (long long)t0 + j, rd = (long long)d0 + j;
+    double m_t, Z_t, m_d, Z_d;
+    combine_stats<true>(ws.stat_t + (size_t)rt * nsg * 2, nsg, ek, m_t, Z_t);
+    combine_stats<true>(ws.stat_d + (size_t)rd * nsg * 2, nsg, ek, m_d, Z_d);
+    const long long tr = t_rows ? t_rows[rt] : rt, dr = d_rows ? d_rows[rd] : rd;
+    const int x = min(max(draft_tokens[dr], 0), V - 1);
+    const double px = prob_of<FSR_LOGITS>(to_float(z_target[(size_t)tr * V + x]), T, m_t, Z_t, ek);
+    const double qx = prob_of<FSR_LOGITS>(to_float(z_draft[(size_t)dr * V + x]), T, m_d, Z_d, ek);
+    if (threadIdx.x == 0 && !((double)u_accept[dr] * qx < px)) atomicMin(stat_words(ws, i, nc), (unsigned)j);
 }
 
-// Combine a row's chunk statistics into (max, partition sum); all lanes of the wave call it.
-__device__ __forceinline__ void combine_stats(const double* __restrict__ stat, int nc, const ExpConsts& ek, double& m, double& Z) {
-    const int lane = threadIdx.x & 63;
-    double mm = -INFINITY;
-    for (int c = lane; c < nc; c += 64) mm = fmax(mm, stat[c * 2]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mm = fmax(mm, __shfl_xor(mm, o, 64));
-    double z = 0.0;
-    for (int c = lane; c < nc; c += 64) z += stat[c * 2 + 1] * exp_softmax(stat[c * 2] - mm, ek);
-    m = mm;
-    Z = wave_sum(z);
-}
 // The same by one lane on its own (every lane of the wave works on a different row): the pairs four at a time, all
 // eight loads of a batch in flight together, folded with a running maximum.
 __device__ __forceinline__ void combine_stats_lane(const double* __restrict__ stat, int nc, const ExpConsts& ek, double& m,
@@ -463,30 +497,16 @@ __device__ __forceinline__ long long shfl_i64(long long v, int src) {
     const uint32_t lo = __shfl((uint32_t)v, src, 64), hi = __shfl((uint32_t)((unsigned long long)v >> 32), src, 64);
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
-// 8-byte values that another workgroup of the same launch reads: stored through to memory / loaded past the caches
-__device__ __forceinline__ void publish_f64(double* p, double v) {
-    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double fetch_f64(const double* p) {
-    return __builtin_bit_cast(double, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT));
-}
-
 // ---------------------------------------------------------------------------------------
 // decide: one wave per request; lane n tests draft n.
 // ---------------------------------------------------------------------------------------
-// PHASE 0: all drafts.  PHASE 1 (LOGITS, two-phase statistics): only the first kLazyJ drafts; a request whose first
-// kLazyJ drafts are all accepted and that has more is left pending, everything else is final.  PHASE 2: the pending
-// requests, from the start, now that all their rows are normalised.
-template <int MODE, typename RT, int PHASE>
+template <int MODE, typename RT>
 __global__ __launch_bounds__(64) void accept_decide_kernel(
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const int32_t* __restrict__ draft_tokens,
     const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
     const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, int32_t* __restrict__ accepted_len,
     int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int B, int V, int S_max, double T) {
     const int i = blockIdx.x, lane = threadIdx.x;
-    if (PHASE == 2 && !ws.pending[i]) return;
     const int nsg = n_stat_groups_of(V, ws.stat_group);
     const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
     int32_t* em = emitted + (size_t)i * (S_max + 1);
@@ -506,55 +526,60 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
             accepted_len[i] = -1;
             n_emitted[i] = -1;
             ws.dec[i] = dec;
-            if (PHASE == 1) ws.pending[i] = 0;
         }
         return;
     }
-    const int d_lim = PHASE == 1 ? min(d_i, kLazyJ) : d_i;  // drafts this pass tests
     const ExpConsts ek = exp_consts_for<MODE>();
-    int n = d_lim;  // accepted drafts
-    for (int n0 = 0; n0 < d_lim && n == d_lim; n0 += 64) {
-        const int k = n0 + lane;
-        const bool live = k < d_lim;
-        long long tr = 0, dr = 0;
-        double m_t = 0.0, Z_t = 1.0, m_d = 0.0, Z_d = 1.0;
-        int x = 0;
-        bool ok = true;
-        if (live) {
-            tr = t_rows ? t_rows[t0 + k] : t0 + k;
-            dr = d_rows ? d_rows[d0 + k] : d0 + k;
-            x = min(max(draft_tokens[dr], 0), V - 1);
-            const double u = (double)u_accept[dr];
-            if constexpr (MODE == FSR_LOGITS) {
-                combine_stats_lane(ws.stat_t + (size_t)(t0 + k) * nsg * 2, nsg, ek, m_t, Z_t);
-                combine_stats_lane(ws.stat_d + (size_t)(d0 + k) * nsg * 2, nsg, ek, m_d, Z_d);
-            }
-            const double px = prob_of<MODE>(to_float(p_target[(size_t)tr * V + x]), T, m_t, Z_t, ek);
-            const double qx = prob_of<MODE>(to_float(p_draft[(size_t)dr * V + x]), T, m_d, Z_d, ek);
-            ok = u * qx < px;
-        }
-        const unsigned long long rejected = __builtin_amdgcn_ballot_w64(live && !ok);
-        const int first = rejected ? (int)__builtin_ctzll(rejected) : 64;
-        if (live && lane < first) em[k] = x;  // accepted drafts of this round of 64
-        if (rejected) {
-            n = n0 + first;
+    int n = d_i;  // accepted drafts
+    if (MODE == FSR_LOGITS && ws.skip) {
+        n = (int)min(*stat_words(ws, i, n_chunks_of(V)), (unsigned)d_i);
+        for (int k = lane; k < n; k += 64) em[k] = min(max(draft_tokens[d_rows ? d_rows[d0 + k] : d0 + k], 0), V - 1);
+        if (n < d_i) {
             dec.kind = kCaseResidual;
-            dec.t_row = shfl_i64(tr, first);
-            dec.d_row = shfl_i64(dr, first);
-            dec.m_t = shfl_f64(m_t, first); dec.Z_t = shfl_f64(Z_t, first);
-            dec.m_d = shfl_f64(m_d, first); dec.Z_d = shfl_f64(Z_d, first);
+            dec.t_row = t_rows ? t_rows[t0 + n] : t0 + n;
+            dec.d_row = d_rows ? d_rows[d0 + n] : d0 + n;
+            combine_stats<false>(ws.stat_t + (size_t)(t0 + n) * nsg * 2, nsg, ek, dec.m_t, dec.Z_t);
+            combine_stats<false>(ws.stat_d + (size_t)(d0 + n) * nsg * 2, nsg, ek, dec.m_d, dec.Z_d);
         }
-    }
-    if (PHASE == 1) {
-        const bool pending = n == d_lim && d_i > d_lim;  // nothing rejected so far and drafts remain
-        if (lane == 0) ws.pending[i] = pending ? 1 : 0;
-        if (pending) return;
+    } else {
+        for (int n0 = 0; n0 < d_i && n == d_i; n0 += 64) {
+            const int k = n0 + lane;
+            const bool live = k < d_i;
+            long long tr = 0, dr = 0;
+            double m_t = 0.0, Z_t = 1.0, m_d = 0.0, Z_d = 1.0;
+            int x = 0;
+            bool ok = true;
+            if (live) {
+                tr = t_rows ? t_rows[t0 + k] : t0 + k;
+                dr = d_rows ? d_rows[d0 + k] : d0 + k;
+                x = min(max(draft_tokens[dr], 0), V - 1);
+                const double u = (double)u_accept[dr];
+                if constexpr (MODE == FSR_LOGITS) {
+                    combine_stats_lane(ws.stat_t + (size_t)(t0 + k) * nsg * 2, nsg, ek, m_t, Z_t);
+                    combine_stats_lane(ws.stat_d + (size_t)(d0 + k) * nsg * 2, nsg, ek, m_d, Z_d);
+                }
+                const double px = prob_of<MODE>(to_float(p_target[(size_t)tr * V + x]), T, m_t, Z_t, ek);
+                const double qx = prob_of<MODE>(to_float(p_draft[(size_t)dr * V + x]), T, m_d, Z_d, ek);
+                ok = u * qx < px;
+            }
+            const unsigned long long rejected = __builtin_amdgcn_ballot_w64(live && !ok);
+            const int first = rejected ? (int)__builtin_ctzll(rejected) : 64;
+            if (live && lane < first) em[k] = x;  // accepted drafts of this round of 64
+            if (rejected) {
+                n = n0 + first;
+                dec.kind = kCaseResidual;
+                dec.t_row = shfl_i64(tr, first);
+                dec.d_row = shfl_i64(dr, first);
+                dec.m_t = shfl_f64(m_t, first); dec.Z_t = shfl_f64(Z_t, first);
+                dec.m_d = shfl_f64(m_d, first); dec.Z_d = shfl_f64(Z_d, first);
+            }
+        }
     }
     dec.n = n;
     if (n == d_i && t_i == d_i + 1) {
         dec.kind = kCaseTarget;
         dec.t_row = t_rows ? t_rows[t0 + d_i] : t0 + d_i;
-        if constexpr (MODE == FSR_LOGITS) combine_stats(ws.stat_t + (size_t)(t0 + d_i) * nsg * 2, nsg, ek, dec.m_t, dec.Z_t);
+        if constexpr (MODE == FSR_LOGITS) combine_stats<false>(ws.stat_t + (size_t)(t0 + d_i) * nsg * 2, nsg, ek, dec.m_t, dec.Z_t);
     }
     for (int s = n + lane; s <= S_max; s += 64) em[s] = -1;
     if (lane == 0) {
@@ -801,9 +826,6 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
     const int nc = n_chunks_of(p.V);
     const double T = p.temperature;
     int rc;
-#define FSR_DECIDE(PHASE)                                                                                                    \
-    hipLaunchKernelGGL((accept_decide_kernel<MODE, RT, PHASE>), dim3(p.B), dim3(64), 0, s, p_target, p_draft, draft_tokens, u_accept, \
-                       cu_t, cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T)
     if (MODE == FSR_LOGITS) {
         const int rows_cap = p.B * (2 * p.S_max + 1);
         // chunks per workgroup: as many as leave the device a few thousand workgroups (a small call is a latency
@@ -811,33 +833,21 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
         int sg = kMaxStatGroup;
         while (sg > 1 && (long long)rows_cap * n_stat_groups_of(p.V, sg) < 4096) sg >>= 1;
         ws.stat_group = sg;
-        const int nsg = n_stat_groups_of(p.V, sg);
-    // rows of a request one pass covers: target rows T_LO .. T_LO + T_N - 1 and draft rows D_LO .. D_LO + D_N - 1
-#define FSR_STATS(T_LO, T_N, D_LO, D_N, ONLY_PENDING)                                                                        \
-    hipLaunchKernelGGL(accept_stats_kernel<RT>, dim3(nsg, p.B * ((T_N) + (D_N))), dim3(kThreads), 0, s, p_target, p_draft, cu_t, \
-                       cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T, (T_N) + (D_N), T_LO, T_N, D_LO, ONLY_PENDING)
-        // Only rows 0..n of a request (n = accepted drafts) have to be normalised.  With enough rows in the call to be
-        // worth two more launches, the rows the first kLazyJ drafts need are normalised and those drafts tested first;
-        // the remaining rows are read only for the requests that accepted all of them.
-        const bool two_phase = p.S_max > kLazyJ + 1 && rows_cap >= kLazyMinRows;
-        if (two_phase) {
-            FSR_STATS(0, kLazyJ + 1, 0, kLazyJ, 0);
-            if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
-            FSR_DECIDE(1);
-            if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
-            FSR_STATS(kLazyJ + 1, p.S_max - kLazyJ, kLazyJ, p.S_max - kLazyJ, 1);
-            if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
-            FSR_DECIDE(2);
-        } else {
-            FSR_STATS(0, p.S_max + 1, 0, p.S_max, 0);
-            if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
-            FSR_DECIDE(0);
+        // Leaving rows out is worth its clearing launch and the counting where there are many rows; a small call has all
+        // its rows in flight at once.  Vocabulary 128256, 1-8 drafts, fp32, us a call with / without: 16 requests 62.8 /
+        // 52.2, 64 requests (1088 rows) 103.5 / 102.3, 128 requests (2176 rows) 170.6 / 182.4, 256 requests 284 / 336.
+        if (rows_cap >= kSkipMinRows && p.S_max + 1 <= 2 * nc) {
+            ws.skip = 1;
+            const int n_words = p.B * 2 * nc;
+            hipLaunchKernelGGL(accept_clear_kernel, dim3((n_words + kThreads - 1) / kThreads), dim3(kThreads), 0, s, ws, n_words, nc);
+            if ((rc = check_launch("accept_clear_kernel")) != FSR_OK) return rc;
         }
-#undef FSR_STATS
-    } else {
-        FSR_DECIDE(0);
+        hipLaunchKernelGGL(accept_stats_kernel<RT>, dim3(n_stat_groups_of(p.V, sg), rows_cap), dim3(kThreads), 0, s, p_target, p_draft,
+                           draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T);
+        if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
     }
-#undef FSR_DECIDE
+    hipLaunchKernelGGL((accept_decide_kernel<MODE, RT>), dim3(p.B), dim3(64), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t,
+                       cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T);
     if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
     // chunks per workgroup: as many as leave the device about four workgroups per compute unit (a small batch
     // keeps one chunk per workgroup: there the call is a latency chain and parallelism is what shortens it)
