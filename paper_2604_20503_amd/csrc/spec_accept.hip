@@ -40,7 +40,6 @@ constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax st
 constexpr int kSkipMinRows = 2048;  // LOGITS mode: rows a call must be able to hold for rows behind a rejection to be left out
 constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
 constexpr int kMaxSampleGroup = 8;  // accept_sample: a workgroup takes 1, 2, 4 or 8 consecutive chunks (see launch_all)
-constexpr int kMaxChunksLds = 256;  // chunk masses of a request that the selecting workgroup keeps in LDS (vocabularies up to 2^20)
 
 enum : int { kCaseNone = 0, kCaseResidual = 1, kCaseTarget = 2 };
 
@@ -215,7 +214,8 @@ __device__ __forceinline__ double exp_softmax(double x, const ExpConsts& k) {
 // rounding sum; the table's high words are stored less j << 12, so that one shift-and-add of n puts 2^(n / 256) together.
 // Measured, statistics of 512 requests x 152064 logits (about 2.9 GB of rows, bound by the vector ALUs): 693 -> 557 us, with
 // the references that need no rescaling per chunk.
-// Arguments below kExpTableFloor (and NaN) count as that floor: 1e-304, so that the exponent stays a normal one.
+// CLAMP: arguments below kExpTableFloor (and NaN) count as that floor: 1e-304, so that the exponent stays a normal one;
+// without it the caller makes sure of the range (NaN gives NaN).
 constexpr double kExpTableFloor = -700.0;
 __device__ const double kExp2Table[256] = {
 #include "exp_table.inc"
@@ -243,8 +243,9 @@ __device__ __forceinline__ ExpTable exp_table(const uint2* tab) {
     asm volatile("" : "+s"(k.floor), "+s"(k.c), "+s"(k.nl_hi), "+s"(k.nl_lo), "+s"(k.c4), "+v"(k.c3), "+v"(k.magic));
     return k;
 }
+template <bool CLAMP = true>
 __device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
-    x = fmax(x, k.floor);
+    if constexpr (CLAMP) x = fmax(x, k.floor);
     const double t = fma(x, k.c, k.magic);
     const double kf = t - k.magic;
     const uint32_t n = (uint32_t)__builtin_bit_cast(unsigned long long, t);
@@ -465,11 +466,18 @@ __device__ __forceinline__ void combine_stats_lane(const double* __restrict__ st
     Z = z;
 }
 
+// p - q of two products, each rounded: fused into a multiply-add, equal probabilities would leave a rounding error behind
+// instead of 0.
+__device__ __forceinline__ double difference(double p, double q) {
+    asm("" : "+v"(p), "+v"(q));
+    return p - q;
+}
+
 // Masses of 4 consecutive tokens starting at e for the request's decision (bounds-checked).
 template <int MODE, typename RT>
 __device__ __forceinline__ void quad_masses(const Decision& dec, const RT* __restrict__ trow,
                                             const RT* __restrict__ drow, int e, int V, bool vec_t, bool vec_d,
-                                            double T, const ExpConsts& ek, double (&res)[4], double (&tgt)[4]) {
+                                            double T, const ExpConsts& ek, double (&mass)[4]) {
     float a[4], b[4];
     load_quad(trow, e, V, vec_t, a);
     if (dec.kind == kCaseResidual) load_quad(drow, e, V, vec_d, b);
@@ -477,13 +485,12 @@ __device__ __forceinline__ void quad_masses(const Decision& dec, const RT* __res
     for (int k = 0; k < 4; ++k) {
         const bool ok = e + k < V;
         const double pt = ok ? prob_of<MODE>(a[k], T, dec.m_t, dec.Z_t, ek) : 0.0;
-        tgt[k] = pt;
         if (dec.kind == kCaseResidual) {
             const double qd = ok ? prob_of<MODE>(b[k], T, dec.m_d, dec.Z_d, ek) : 0.0;
-            const double r = pt - qd;
-            res[k] = r > 0.0 ? r : 0.0;
+            const double r = difference(pt, qd);
+            mass[k] = r > 0.0 ? r : 0.0;
         } else {
-            res[k] = pt;
+            mass[k] = pt;
         }
     }
 }
@@ -592,182 +599,226 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
 // ---------------------------------------------------------------------------------------
 // sample: request i = blockIdx.y; this workgroup owns chunks kSampleGroup * blockIdx.x .. + kSampleGroup - 1 of the
 // vocabulary.  grid = (ceil(n_chunks / kSampleGroup), B)
+// A large call is bound by the rows' bytes (PROBS) or by fp64 instructions (LOGITS: exp by table look-up, see exp_lookup);
+// a small one is a latency chain (decision, rows, sums, arrival, chunk search, chunk scan), so what lies on it is kept
+// short: sums over a wave by DPP, the search over the chunk masses by one wave.  Measured, us a launch before / after:
+// PROBS 16 requests 17.6 / 13.4, chunks of 512 requests' drafts (mean of four) 47.5 / 39.3; LOGITS 16 requests in bf16
+// 20.8 / 16.4, 512 requests 183 / 148.
 // ---------------------------------------------------------------------------------------
 template <int MODE, typename RT, int kSampleGroup>
 __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const float* __restrict__ u_sample,
     int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int V, int S_max, double T) {
-    __shared__ double s_part[kThreads / 64][2 * kSampleGroup];
+    __shared__ double s_part[kThreads / 64][kSampleGroup];
     __shared__ double s_wave[kThreads / 64];
     __shared__ int s_i[kThreads / 64];
     __shared__ double s_base, s_thr;
     __shared__ int s_chunk, s_fallback, s_last;
-    __shared__ double s_mass[2 * kMaxChunksLds];
+    __shared__ uint2 s_exp[MODE == FSR_LOGITS ? 256 : 1];
     const int nc = n_chunks_of(V), i = blockIdx.y;
-    const ExpConsts ek = exp_consts_for<MODE>();
     const int c_first = blockIdx.x * kSampleGroup, n_here = min(kSampleGroup, nc - c_first);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int32_t* em = emitted + (size_t)i * (S_max + 1);
     Decision dec = ws.dec[i];
     dec.kind = __builtin_amdgcn_readfirstlane(dec.kind);  // the same in every lane: say so, branches on it stay scalar
     if (dec.kind == kCaseNone) return;
+    if constexpr (MODE == FSR_LOGITS) {
+        fill_exp_table(s_exp);
+        __syncthreads();
+    }
+    const ExpConsts ek = exp_consts_for<MODE>();
 
-    // ---- 2. fp64 mass of this chunk of the sampling distribution (and of the target row, for the fallback)
+    // ---- 2. fp64 mass of this workgroup's chunks of the sampling distribution
     const RT* trow = p_target + (size_t)dec.t_row * V;
     const RT* drow = p_draft + (size_t)dec.d_row * V;
     const bool vec_t = row_vec_ok(trow), vec_d = row_vec_ok(drow);
     // A workgroup takes kSampleGroup consecutive chunks: the chain every workgroup goes through (decision record,
-    // row loads, reduction, store-through, arrival count) is paid once per 128 KB instead of once per 32 KB.  Each
-    // chunk's mass is reduced exactly as if it had a workgroup to itself (thread sums, wave sums, waves in order).
+    // row loads, reduction, store-through, arrival count) is paid once per 128 KB instead of once per 32 KB.
+    auto chunk_mass_checked = [&](int c) __attribute__((always_inline)) {  // any chunk, element by element
+        double r = 0.0;
+#pragma unroll
+        for (int k = 0; k < kPerThread / 4; ++k) {
+            double m[4];
+            quad_masses<MODE, RT>(dec, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V, vec_t, vec_d, T, ek, m);
+            r += (m[0] + m[1]) + (m[2] + m[3]);
+        }
+        return r;
+    };
     {
         // whole chunks of aligned rows first, through code that has only vector loads (the next chunk's issued before
         // this chunk's arithmetic); then the chunk with the vocabulary's ragged end (or every chunk, if a row is not
-        // aligned), bounds-checked.  A chunk's two masses go to LDS as soon as the wave has them.
-        const bool vec_ok = vec_t && (dec.kind != kCaseResidual || vec_d);
-        const int n_whole = vec_ok ? min(n_here, max(0, V / kChunk - c_first)) : 0;
+        // aligned), bounds-checked.  A chunk's mass goes to LDS as soon as the wave has it.
         const bool residual = dec.kind == kCaseResidual;
+        const bool vec_ok = vec_t && (!residual || vec_d);
+        const int n_whole = vec_ok ? min(n_here, max(0, V / kChunk - c_first)) : 0;
+        const double inv_T = 1.0 / T, inv_Zt = 1.0 / dec.Z_t, inv_Zd = 1.0 / dec.Z_d;
+        auto load_rows = [&](int c, float (&t)[kPerThread], float (&d)[kPerThread]) {
+#pragma unroll
+            for (int k = 0; k < kPerThread / 4; ++k) {
+                const int e = c * kChunk + (k * kThreads + threadIdx.x) * 4;
+                float x[4], y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                load_quad_vec(trow, e, x);
+                if (residual) load_quad_vec(drow, e, y);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    t[4 * k + u] = x[u];
+                    d[4 * k + u] = y[u];
+                }
+            }
+        };
+        unsigned todo = ((1u << n_here) - 1u) & ~((1u << n_whole) - 1u);  // chunks left to the checked path, per wave
+        auto sum_chunk = [&](int cc, const float (&t)[kPerThread], const float (&d)[kPerThread]) {
+            double r = 0.0;
+            bool exact = true;  // (LOGITS) the table covers every logit of the wave
+            if constexpr (MODE == FSR_LOGITS) {
+                const ExpTable et = exp_table(s_exp);
+                float lo_t = t[0], lo_d = d[0];
+#pragma unroll
+                for (int u = 1; u < kPerThread; ++u) {
+                    lo_t = fminf(lo_t, t[u]);
+                    lo_d = fminf(lo_d, d[u]);
+                }
+                bool in = fma((double)lo_t, inv_T, -dec.m_t) >= kExpTableFloor;
+                if (residual) in = in && fma((double)lo_d, inv_T, -dec.m_d) >= kExpTableFloor;
+                exact = __builtin_amdgcn_ballot_w64(!in) == 0;
+                if (exact) {
+                    if (residual) {
+#pragma unroll
+                        for (int u = 0; u < kPerThread; ++u) {
+                            const double pt = exp_lookup<false>(fma((double)t[u], inv_T, -dec.m_t), et) * inv_Zt;
+                            const double qd = exp_lookup<false>(fma((double)d[u], inv_T, -dec.m_d), et) * inv_Zd;
+                            const double x = difference(pt, qd);
+                            r += x < 0.0 ? 0.0 : x;  // (keeps a NaN)
+                        }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < kPerThread; ++u) r += exp_lookup<false>(fma((double)t[u], inv_T, -dec.m_t), et);
+                        r *= inv_Zt;
+                    }
+                    exact = __builtin_amdgcn_ballot_w64(r != r) == 0;  // a NaN logit counts as masked
+                }
+                if (!exact) {
+                    todo |= 1u << cc;
+                    return;
+                }
+            } else if (residual) {
+#pragma unroll
+                for (int k = 0; k < kPerThread; k += 4) {
+                    double m[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const double x = (double)t[k + u] - (double)d[k + u];
+                        m[u] = x > 0.0 ? x : 0.0;
+                    }
+                    r += (m[0] + m[1]) + (m[2] + m[3]);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < kPerThread; k += 4)
+                    r += ((double)t[k] + (double)t[k + 1]) + ((double)t[k + 2] + (double)t[k + 3]);
+            }
+            r = wave_sum_to_last(r);
+            if (lane == 63) s_part[w][cc] = r;
+        };
         if (n_whole > 0) {
             float ta[kPerThread], da[kPerThread], tb[kPerThread], db[kPerThread];
-            auto load_rows = [&](int c, float (&t)[kPerThread], float (&d)[kPerThread]) {
-#pragma unroll
-                for (int k = 0; k < kPerThread / 4; ++k) {
-                    const int e = c * kChunk + (k * kThreads + threadIdx.x) * 4;
-                    float x[4], y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                    load_quad_vec(trow, e, x);
-                    if (residual) load_quad_vec(drow, e, y);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        t[4 * k + u] = x[u];
-                        d[4 * k + u] = y[u];
-                    }
-                }
-            };
             load_rows(c_first, ta, da);
-            for (int cc = 0; cc < n_whole; ++cc) {
+#pragma unroll 1
+            for (int cc = 0; cc < n_whole; cc += 2) {
                 if (cc + 1 < n_whole) load_rows(c_first + cc + 1, tb, db);
-                double r = 0.0, t = 0.0;
-#pragma unroll
-                for (int k = 0; k < kPerThread / 4; ++k) {
-                    double res[4], tgt[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const double pt = prob_of<MODE>(ta[4 * k + u], T, dec.m_t, dec.Z_t, ek);
-                        tgt[u] = pt;
-                        if (residual) {
-                            const double d = pt - prob_of<MODE>(da[4 * k + u], T, dec.m_d, dec.Z_d, ek);
-                            res[u] = d > 0.0 ? d : 0.0;
-                        } else {
-                            res[u] = pt;
-                        }
-                    }
-                    r += (res[0] + res[1]) + (res[2] + res[3]);
-                    t += (tgt[0] + tgt[1]) + (tgt[2] + tgt[3]);
-                }
-                r = wave_sum(r);
-                t = wave_sum(t);
-                if (lane == 0) {
-                    s_part[w][2 * cc] = r;
-                    s_part[w][2 * cc + 1] = t;
-                }
-#pragma unroll
-                for (int u = 0; u < kPerThread; ++u) {
-                    ta[u] = tb[u];
-                    da[u] = db[u];
-                }
+                sum_chunk(cc, ta, da);
+                if (cc + 1 >= n_whole) break;
+                if (cc + 2 < n_whole) load_rows(c_first + cc + 2, ta, da);
+                sum_chunk(cc + 1, tb, db);
             }
         }
 #pragma unroll 1
-        for (int cs = n_whole; cs < n_here; ++cs) {
-            const int e0 = (c_first + cs) * kChunk;
-            double r = 0.0, t = 0.0;
-#pragma unroll
-            for (int k = 0; k < kPerThread / 4; ++k) {
-                const int e = e0 + (k * kThreads + threadIdx.x) * 4;
-                double res[4], tgt[4];
-                quad_masses<MODE, RT>(dec, trow, drow, e, V, vec_t, vec_d, T, ek, res, tgt);
-                r += (res[0] + res[1]) + (res[2] + res[3]);
-                t += (tgt[0] + tgt[1]) + (tgt[2] + tgt[3]);
-            }
-            r = wave_sum(r);
-            t = wave_sum(t);
-            if (lane == 0) {
-                s_part[w][2 * cs] = r;
-                s_part[w][2 * cs + 1] = t;
-            }
+        while (todo) {
+            const int cs = __builtin_ctz(todo);
+            todo &= todo - 1;
+            const double r = wave_sum_to_last(chunk_mass_checked(c_first + cs));
+            if (lane == 63) s_part[w][cs] = r;
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int cc = 0; cc < n_here; ++cc) {
-                double tr = 0.0, tt = 0.0;
+        if (w == 0) {
+            if (lane < n_here) {
+                double r = 0.0;
 #pragma unroll
-                for (int k = 0; k < kThreads / 64; ++k) {
-                    tr += s_part[k][2 * cc];
-                    tt += s_part[k][2 * cc + 1];
-                }
-                publish_f64(ws.mass_res + (size_t)i * nc + c_first + cc, tr);
-                publish_f64(ws.mass_tgt + (size_t)i * nc + c_first + cc, tt);
+                for (int k = 0; k < kThreads / 64; ++k) r += s_part[k][lane];
+                publish_f64(ws.mass_res + (size_t)i * nc + c_first + lane, r);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // all are in memory before the arrivals are counted
-            s_last = atomicAdd(ws.arrivals + i, (unsigned)n_here) + (unsigned)n_here == (unsigned)nc;
+            if (lane == 0) s_last = atomicAdd(ws.arrivals + i, (unsigned)n_here) + (unsigned)n_here == (unsigned)nc;
         }
         __syncthreads();
         if (!s_last) return;
     }
 
-    // ---- 3. the request's last workgroup draws the token: total mass and the chunk that holds u * R.
-    // The chunk masses come from memory (other workgroups wrote them): all threads fetch them together
-    // into LDS, then one thread runs the sequential fp64 prefix over the <= a few dozen chunks.
-    double* l_res = reinterpret_cast<double*>(s_mass);
-    double* l_tgt = l_res + kMaxChunksLds;
-    const bool in_lds = nc <= kMaxChunksLds;
-    if (in_lds) {
-        for (int cc = threadIdx.x; cc < nc; cc += kThreads) {
-            l_res[cc] = fetch_f64(ws.mass_res + (size_t)i * nc + cc);
-            l_tgt[cc] = fetch_f64(ws.mass_tgt + (size_t)i * nc + cc);
+    // ---- 3. the request's last workgroup draws the token: total mass and the chunk that holds u * R, by one wave (lane
+    // l takes chunks l, l + 64, ...; the masses come from memory, other workgroups wrote them)
+    auto search = [&](const double* masses, bool last_resort) {  // false: no mass at all
+        double v0 = 0.0, inc0 = 0.0, R = 0.0;
+        for (int c0 = 0; c0 < nc; c0 += 64) {
+            const double v = c0 + lane < nc ? fetch_f64(masses + c0 + lane) : 0.0, inc = wave_inclusive_scan(v);
+            if (c0 == 0) {
+                v0 = v;
+                inc0 = inc;
+            }
+            R += shfl_f64(inc, 63);
         }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const double* gres = ws.mass_res + (size_t)i * nc;
-        const double* gtgt = ws.mass_tgt + (size_t)i * nc;
-        auto mres = [&](int cc) { return in_lds ? l_res[cc] : fetch_f64(gres + cc); };
-        auto mtgt = [&](int cc) { return in_lds ? l_tgt[cc] : fetch_f64(gtgt + cc); };
-        double R = 0.0;
-        for (int cc = 0; cc < nc; ++cc) R += mres(cc);
-        int fallback = 0;
-        if (!(R > 0.0)) {  // residual is all zero: sample from the target row itself
-            fallback = 1;
-            R = 0.0;
-            for (int cc = 0; cc < nc; ++cc) R += mtgt(cc);
-        }
+        if (!(R > 0.0) && !last_resort) return false;
         const double thr = (double)u_sample[i] * R;
-        double acc = 0.0, base = 0.0;
+        double carry = 0.0, base = 0.0;
         int chunk = -1, last_pos = 0;
         double last_base = 0.0;
-        for (int cc = 0; cc < nc; ++cc) {
-            const double prev = acc, mc = fallback ? mtgt(cc) : mres(cc);
-            acc += mc;
-            if (mc > 0.0) {
-                last_pos = cc;
-                last_base = prev;
-                if (acc > thr) {
-                    chunk = cc;
-                    base = prev;
-                    break;
-                }
+        for (int c0 = 0; c0 < nc; c0 += 64) {
+            const double v = c0 == 0 ? v0 : c0 + lane < nc ? fetch_f64(masses + c0 + lane) : 0.0;
+            const double inc = c0 == 0 ? inc0 : wave_inclusive_scan(v);
+            const double up = __shfl_up(inc, 1, 64), before = carry + (lane == 0 ? 0.0 : up);
+            const unsigned long long with_mass = __builtin_amdgcn_ballot_w64(v > 0.0);
+            const unsigned long long past = __builtin_amdgcn_ballot_w64(v > 0.0 && carry + inc > thr);
+            if (past) {
+                chunk = c0 + (int)__builtin_ctzll(past);
+                base = shfl_f64(before, chunk - c0);
+                break;
             }
+            if (with_mass) {
+                last_pos = c0 + 63 - (int)__builtin_clzll(with_mass);
+                last_base = shfl_f64(before, last_pos - c0);
+            }
+            carry += shfl_f64(inc, 63);
         }
         if (chunk < 0) {  // rounding left no chunk: the last chunk with mass
             chunk = last_pos;
             base = last_base;
         }
-        s_base = base;
-        s_thr = thr;
-        s_chunk = chunk;
-        s_fallback = fallback;
+        if (lane == 0) {
+            s_base = base;
+            s_thr = thr;
+            s_chunk = chunk;
+        }
+        return true;
+    };
+    if (w == 0) {
+        const bool found = search(ws.mass_res + (size_t)i * nc, false);
+        if (lane == 0) s_fallback = !found;
     }
     __syncthreads();
-    if (s_fallback) dec.kind = kCaseTarget;
+    if (s_fallback) {  // the residual is all zero: sample from the target row itself (its masses are made here and now)
+        dec.kind = kCaseTarget;
+        for (int c = 0; c < nc; ++c) {
+            const double r = wave_sum_to_last(chunk_mass_checked(c));
+            if (lane == 63) s_wave[w] = r;
+            __syncthreads();
+            if (threadIdx.x == 0) publish_f64(ws.mass_tgt + (size_t)i * nc + c, (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
+            __syncthreads();
+        }
+        if (w == 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            search(ws.mass_tgt + (size_t)i * nc, true);
+        }
+        __syncthreads();
+    }
     const double thr = s_thr;
     const int cs = s_chunk;
 
@@ -777,12 +828,12 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
     double local = 0.0;
 #pragma unroll
     for (int k = 0; k < kPerThread / 4; ++k) {
-        double res[4], tgt[4];
-        quad_masses<MODE, RT>(dec, trow, drow, e0 + 4 * k, V, vec_t, vec_d, T, ek, res, tgt);
+        double m[4];
+        quad_masses<MODE, RT>(dec, trow, drow, e0 + 4 * k, V, vec_t, vec_d, T, ek, m);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            mass[4 * k + j] = res[j];
-            local += res[j];
+            mass[4 * k + j] = m[j];
+            local += m[j];
         }
     }
     const double inc = wave_inclusive_scan(local);
@@ -850,7 +901,9 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
                        cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T);
     if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
     // chunks per workgroup: as many as leave the device about four workgroups per compute unit (a small batch
-    // keeps one chunk per workgroup: there the call is a latency chain and parallelism is what shortens it)
+    // keeps one chunk per workgroup: there the call is a latency chain and parallelism is what shortens it).
+    // PROBS, vocabulary 128256, us a call with 1024 / 2048 / 4096 workgroups as the line: 64 requests 21.9 / 28.3 / 28.1,
+    // 128 requests 28.5 / 30.6 / 38.6, 512 requests 92.8 / 94.8 / 95.5.
     int group = kMaxSampleGroup;
     while (group > 1 && (long long)p.B * ((nc + group - 1) / group) < 1024) group >>= 1;
 #define FSR_SAMPLE(G)                                                                                                          \
