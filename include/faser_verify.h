@@ -311,7 +311,7 @@ int fsr_accept_workspace_bytes(const fsr_accept_params* p /*host*/, size_t* out_
  * arg-max token of target row n (the lowest id among equal maxima); the token after the
  * accepted run is the arg-max of the next target row (the row of the first mismatch, or
  * the bonus row).  p_target may hold probabilities or logits; p_draft, u_accept and
- * u_sample are not read and may be null.  Every target row of the call is read once.
+ * u_sample are not read and may be null.  Rows behind a request's first mismatch may be left unread.
  */
 int fsr_spec_accept(const void* p_target, const void* p_draft, const int32_t* draft_tokens,
                     const float* u_accept, const float* u_sample, const int32_t* cu_t,

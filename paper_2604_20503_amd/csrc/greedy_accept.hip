@@ -2,12 +2,18 @@
 // an arg-max target.  A draft is accepted iff it is the arg-max token of its target row (lowest id
 // among equal maxima); the token after the accepted run is the arg-max of the next target row.
 //
-// The cost is one streaming pass over the target rows (4 V bytes each).  All rows are reduced in
-// parallel (a request's rows behind its first mismatch are read although not needed: the
-// alternative, row after row, would put one memory round trip per accepted draft on the critical
-// path).  greedy_argmax_kernel: grid (16 KB chunks, rows); every workgroup folds its chunk into a
-// 64-bit key (value made order-preserving << 32 | ~index) and merges it into the row's key with one
-// atomic max, which yields the largest value and, among equals, the lowest index.
+// The cost is one streaming pass over the target rows up to the first mismatch (4 V bytes each).  Row after row would put a
+// memory round trip per accepted draft on the critical path, all rows at once would read those behind the mismatch for
+// nothing; so the rows are started in the order of their positions, those of all requests' first drafts before any of a
+// second one, and a workgroup whose request is known to have a mismatch before its row leaves at once.  A mismatch is known
+// as soon as any workgroup of the row has met a score above the draft's own, long before the row is done.
+// greedy_argmax_kernel: every workgroup folds a 16 KB piece of a row into a 64-bit key (value made order-preserving << 32 |
+// ~index) and merges it into the row's key with one atomic max, which yields the largest value and, among equals, the
+// lowest index.
+// Measured, vocabulary 128256, 1-8 drafts of which about 40 % match, us a launch with all rows read / like this: 16 requests
+// 13.8 / 14.2, 64 requests 34.1 / 30.9, 128 requests 63.0 / 31.4, 384 requests 184 / 83.  Workgroups that go through a
+// request's positions one after the other read less but wait more: 39 us at 64 requests, 176 us at 384.
+#include <climits>
 #include <cstdint>
 
 #include "common.hpp"
@@ -18,9 +24,11 @@ namespace fsr {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kChunk = 4096;  // scores per workgroup
+constexpr int kChunk = 4096;  // scores of a piece
+constexpr int kQuads = kChunk / kThreads / 4;
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(4))) uint32_t gu32x4;  // at any element of a row
 
 // fp32 bits -> unsigned integer with the same order (-0 and +0 map to the same key; a NaN never wins
 // against a number: it takes the key of minus infinity).
@@ -42,46 +50,60 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long k)
     return k;
 }
 
-__global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long long* keys, int n) {
+// first_miss [B]: position of the first mismatch known so far (the accepted_len output serves until `decide` fills it)
+__global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long long* keys, int32_t* first_miss, int n, int B) {
     const int r = blockIdx.x * kThreads + threadIdx.x;
     if (r < n) keys[r] = 0ull;
+    if (r < B) first_miss[r] = INT_MAX;
 }
 
-__global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(const float* __restrict__ target,
-                                                                 const int32_t* __restrict__ cu_t,
-                                                                 const int32_t* __restrict__ t_rows,
-                                                                 unsigned long long* keys, int B, int V, int R_cap) {
+// grid (pieces, positions x requests): workgroup row y takes position y / B of request y % B
+__global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
+    const float* __restrict__ target, const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ cu_t,
+    const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
+    unsigned long long* keys, int32_t* first_miss, int B, int V, int R_cap) {
     __shared__ unsigned long long part[kThreads / 64];
-    const int r = blockIdx.y;  // call-row on the target side
-    if (r >= R_cap || r >= cu_t[B]) return;
-    const long long row = t_rows ? t_rows[r] : r;
-    const float* z = target + (size_t)row * V;
-    const int v0 = blockIdx.x * kChunk, v1 = min(v0 + kChunk, V);
-    unsigned long long best = 0ull;
-    // peel up to the first 16-byte boundary, then 16-byte loads, then the tail
-    const uintptr_t addr0 = (uintptr_t)(z + v0);
-    const int head = min((int)(((16 - (addr0 & 15)) & 15) / 4), v1 - v0);
-    if ((int)threadIdx.x < head) {
-        const int v = v0 + threadIdx.x;
-        best = make_key(__builtin_bit_cast(uint32_t, z[v]), v);
+    __shared__ int s_miss;
+    const int j = blockIdx.y / B, i = blockIdx.y - j * B;
+    const int t0 = cu_t[i], r = t0 + j;  // call-row on the target side
+    if (t0 < 0 || r >= cu_t[i + 1] || r >= R_cap || r >= cu_t[B]) return;
+    if (j > 0) {  // one lane asks: the words of all requests lie in a few cache lines that every workgroup wants
+        if (threadIdx.x == 0) s_miss = __hip_atomic_load(first_miss + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_miss < j) return;
     }
-    const int body0 = v0 + head, n_vec = (v1 - body0) / 4;
-    const u32x4* vec = reinterpret_cast<const u32x4*>(z + body0);
-    for (int k = threadIdx.x; k < n_vec; k += kThreads) {
-        const u32x4 w = __builtin_nontemporal_load(vec + k);  // a row is streamed once
-        const uint32_t w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
-        const int v = body0 + 4 * k;
+    const float* z = target + (size_t)(t_rows ? t_rows[r] : r) * V;
+    const int v0 = blockIdx.x * kChunk;
+    u32x4 x[kQuads];
+    if (v0 + kChunk <= V) {
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q)  // a row is streamed once
+            x[q] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v0 + (q * kThreads + threadIdx.x) * 4));
+    } else {  // past the end: minus infinity at an index that loses against every token
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) {
+            const int v = v0 + (q * kThreads + threadIdx.x) * 4;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[q][u] = v + u < V ? __builtin_bit_cast(uint32_t, z[v + u]) : 0xff800000u;
+        }
+    }
+    // the key of the draft this row verifies: larger than any if there is none, smaller for an id outside the vocabulary
+    const int d0 = cu_d[i];
+    unsigned long long drafted = ~0ull;
+    if (d0 >= 0 && d0 + j < cu_d[i + 1] && d0 + j < cu_d[B]) {
+        const int t = draft_tokens[d_rows ? d_rows[d0 + j] : d0 + j];
+        drafted = t < 0 || t >= V ? 0ull : make_key(__builtin_bit_cast(uint32_t, z[t]), t);
+    }
+    unsigned long long best = 0ull;
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q) {
+        const int v = v0 + (q * kThreads + threadIdx.x) * 4;
+        const uint32_t w0 = x[q][0], w1 = x[q][1], w2 = x[q][2], w3 = x[q][3];
         unsigned long long c = make_key(w0, v);
         const unsigned long long c1 = make_key(w1, v + 1), c2 = make_key(w2, v + 2), c3 = make_key(w3, v + 3);
         c = c1 > c ? c1 : c;
         c = c2 > c ? c2 : c;
         c = c3 > c ? c3 : c;
-        best = c > best ? c : best;
-    }
-    const int tail0 = body0 + n_vec * 4;
-    if (tail0 + (int)threadIdx.x < v1) {
-        const int v = tail0 + threadIdx.x;
-        const unsigned long long c = make_key(__builtin_bit_cast(uint32_t, z[v]), v);
         best = c > best ? c : best;
     }
     best = wave_max_u64(best);
@@ -90,6 +112,7 @@ __global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(const float* __
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int w = 1; w < kThreads / 64; ++w) best = part[w] > best ? part[w] : best;
+        if (best > drafted) atomicMin(first_miss + i, j);
         atomicMax(keys + r, best);
     }
 }
@@ -142,10 +165,10 @@ int greedy_accept_launch(const float* target, const int32_t* draft_tokens, const
     unsigned long long* keys = (unsigned long long*)workspace;
     const int R_cap = p.B * (p.S_max + 1);
     int rc;
-    hipLaunchKernelGGL(greedy_init_kernel, dim3((R_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, keys, R_cap);
+    hipLaunchKernelGGL(greedy_init_kernel, dim3((R_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, keys, accepted_len, R_cap, p.B);
     if ((rc = check_launch("greedy_init_kernel")) != FSR_OK) return rc;
-    hipLaunchKernelGGL(greedy_argmax_kernel, dim3((p.V + kChunk - 1) / kChunk, R_cap), dim3(kThreads), 0, s, target, cu_t,
-                       t_rows, keys, p.B, p.V, R_cap);
+    hipLaunchKernelGGL(greedy_argmax_kernel, dim3((p.V + kChunk - 1) / kChunk, R_cap), dim3(kThreads), 0, s, target, draft_tokens,
+                       cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, R_cap);
     if ((rc = check_launch("greedy_argmax_kernel")) != FSR_OK) return rc;
     hipLaunchKernelGGL(greedy_decide_kernel, dim3((p.B + kThreads - 1) / kThreads), dim3(kThreads), 0, s, draft_tokens, cu_t,
                        cu_d, d_rows, keys, accepted_len, n_emitted, emitted, p.B, p.S_max, R_cap);
