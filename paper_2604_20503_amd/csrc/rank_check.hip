@@ -4,8 +4,10 @@
 //
 // The work is one pass over the score row of every draft that still has an active row: count the
 // scores strictly above the draft's own.  That is HBM streaming with a trivial reduction, so the
-// kernels are laid out for bandwidth: a grid of (32 KB chunk of a row) x (draft), 16-byte loads,
-// one integer atomic per workgroup into the draft's rank.
+// kernels are laid out for bandwidth: a grid of (32 KB piece of a row) x (draft), a piece's 16-byte loads all in flight
+// together (at any alignment: the hardware takes vectors at element addresses), one integer atomic per workgroup into the
+// draft's rank.  Measured, 1400 drafts x 128256 bf16 scores: 59.8 us; with 16 KB pieces, a loop over aligned loads and a
+// binary search for the draft's request 65 us.
 //
 //   rank_init_kernel    rank[d] = 0 for drafts with an active row and a valid token id, -1 for
 //                       drafts without a row, V for ids outside the vocabulary
@@ -20,10 +22,12 @@ namespace fsr {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kChunk = 8192;  // scores per workgroup: 32 KB of fp32, 16 KB of bf16
+constexpr int kLoads = 8;                           // 16-byte loads of a thread, all in flight together
+constexpr int kChunkBytes = kThreads * kLoads * 16;  // a workgroup's piece of a row
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(2))) uint32_t gu32x4;  // at any element of a row
 
 struct RankArgs {
     const void* logits;
@@ -41,6 +45,21 @@ __device__ __forceinline__ int owner(const int32_t* __restrict__ cu, int B, int 
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (cu[mid] <= x) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// The same by a whole wave: every lane looks at one of 64 places at a time, so a search is one memory round trip per factor
+// of 64 instead of one per factor of two.
+__device__ __forceinline__ int owner_by_wave(const int32_t* __restrict__ cu, int B, int x) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = B;  // the answer lies in [lo, lo + n)
+    while (n > 1) {
+        const int step = (n + 63) / 64, at = lo + lane * step;
+        const unsigned long long below = __builtin_amdgcn_ballot_w64(lane * step < n && cu[at] <= x);
+        const int k = below ? 63 - (int)__builtin_clzll(below) : 0;  // the last such place (cu is non-decreasing)
+        n = min(step, n - k * step);
+        lo += k * step;
     }
     return lo;
 }
@@ -81,34 +100,42 @@ __global__ __launch_bounds__(kThreads) void rank_count_kernel(RankArgs a) {
     __shared__ int part[kThreads / 64];
     const int d = blockIdx.y;
     if (d >= a.cu_d[a.B]) return;
-    const int row = row_of_draft(a, d);
+    const int i = owner_by_wave(a.cu_d, a.B, d), j = d - a.cu_d[i];
+    const int row = j < a.cu_q[i + 1] - a.cu_q[i] ? a.cu_q[i] + j : -1;
     const int tok = a.draft_tokens[d];
     if (row < 0 || row >= a.N_cap || tok < 0 || tok >= a.V) return;  // uniform for the workgroup
-    const size_t base = (size_t)row * a.V;
-    const float mine = score<T>(a.logits, base + tok);
-    const int v0 = blockIdx.x * kChunk, v1 = min(v0 + kChunk, a.V);
     constexpr int kPer = 16 / sizeof(T);  // scores per 16-byte load
+    const T* z = reinterpret_cast<const T*>(a.logits) + (size_t)row * a.V;
+    const int v0 = blockIdx.x * (kChunkBytes / (int)sizeof(T));
+    u32x4 w[kLoads];
+    const bool whole = a.V - v0 >= kChunkBytes / (int)sizeof(T);
+    if (whole) {
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k)  // a row is streamed once
+            w[k] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v0 + (k * kThreads + threadIdx.x) * kPer));
+    }
+    const float mine = score<T>(z, tok);
     int count = 0;
-    // a row starts at any element offset: peel up to the first 16-byte boundary of the chunk
-    const uintptr_t addr0 = (uintptr_t)a.logits + (base + v0) * sizeof(T);
-    const int head = min((int)(((16 - (addr0 & 15)) & 15) / sizeof(T)), v1 - v0);
-    if ((int)threadIdx.x < head) count += score<T>(a.logits, base + v0 + threadIdx.x) > mine;
-    const int body0 = v0 + head, n_vec = (v1 - body0) / kPer;
-    const u32x4* vec = reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(a.logits) + base + body0);
-    for (int k = threadIdx.x; k < n_vec; k += kThreads) {
-        const u32x4 w = __builtin_nontemporal_load(vec + k);  // a row is streamed once
+    auto add = [&](u32x4 x) {
         // elements go to scalars first: __builtin_bit_cast applied to a vector-element expression was
         // seen to read element 0 for every index
-        const uint32_t w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+        const uint32_t w0 = x[0], w1 = x[1], w2 = x[2], w3 = x[3];
         if constexpr (sizeof(T) == 4) {
             count += (__builtin_bit_cast(float, w0) > mine) + (__builtin_bit_cast(float, w1) > mine) +
                      (__builtin_bit_cast(float, w2) > mine) + (__builtin_bit_cast(float, w3) > mine);
         } else {
             count += above_pair(w0, mine) + above_pair(w1, mine) + above_pair(w2, mine) + above_pair(w3, mine);
         }
+    };
+    if (whole) {
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) add(w[k]);
+    } else {  // the row's last piece
+        const int n_vec = (a.V - v0) / kPer;
+        for (int k = threadIdx.x; k < n_vec; k += kThreads) add(*reinterpret_cast<const gu32x4*>(z + v0 + k * kPer));
+        const int tail = v0 + n_vec * kPer + threadIdx.x;
+        if (tail < a.V) count += score<T>(z, tail) > mine;
     }
-    const int tail0 = body0 + n_vec * kPer;
-    if (tail0 + (int)threadIdx.x < v1) count += score<T>(a.logits, base + tail0 + threadIdx.x) > mine;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, kWave);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = count;
@@ -155,7 +182,8 @@ extern "C" int fsr_topk_rank_check(const void* logits, const int32_t* draft_toke
     a.B = p->B; a.V = p->V; a.K = p->K; a.N_cap = p->N_cap; a.D_cap = p->D_cap;
     if (p->D_cap > 0) {
         hipLaunchKernelGGL(rank_init_kernel, dim3((p->D_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
-        const dim3 grid((p->V + kChunk - 1) / kChunk, p->D_cap);
+        const int piece = kChunkBytes / (p->dtype == FSR_F32 ? 4 : 2);
+        const dim3 grid((p->V + piece - 1) / piece, p->D_cap);
         if (p->dtype == FSR_F32) hipLaunchKernelGGL(rank_count_kernel<float>, grid, dim3(kThreads), 0, s, a);
         else hipLaunchKernelGGL(rank_count_kernel<uint16_t>, grid, dim3(kThreads), 0, s, a);
     }
