@@ -104,8 +104,14 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor"):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _raw_stream() -> int:
+    """Handle of the current stream of the current device (torch.cuda.current_stream() builds a Python object around it
+    and costs ten times as much, which a call of a few microseconds notices)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream())
 
 
 def _code(dt: torch.dtype) -> int:
@@ -181,9 +187,9 @@ def _guard_workspace(workspace):
     if workspace is None or torch.cuda.is_current_stream_capturing():
         return None
     key = workspace.data_ptr()
-    stream = torch.cuda.current_stream()
+    stream = _raw_stream()
     last = _ws_last_use.get(key)
-    if last is not None and last[0] != stream.cuda_stream and not last[1].query():
+    if last is not None and last[0] != stream and not last[1].query():
         raise FsrError(EWS, "this attention workspace is still in use by a call on another stream: "
                                      "give every stream (and every graph that may replay concurrently) its own workspace")
     return key, stream
@@ -192,9 +198,11 @@ def _guard_workspace(workspace):
 def _note_workspace_use(token):
     if token is not None:
         key, stream = token
-        ev = torch.cuda.Event()
-        ev.record(stream)
-        _ws_last_use[key] = (stream.cuda_stream, ev)
+        last = _ws_last_use.get(key)
+        # calls that follow each other on one stream record the same event anew
+        ev, handle = (last[1], last[2]) if last is not None and last[0] == stream else (torch.cuda.Event(), torch.cuda.current_stream())
+        ev.record(handle)
+        _ws_last_use[key] = (stream, ev, handle)
 
 
 def verify_attention(q, k_cache, v_cache, block_tables, ctx_lens, spec_lens, cu_q, *, scale, out=None, lse=None,
@@ -213,11 +221,12 @@ def verify_attention(q, k_cache, v_cache, block_tables, ctx_lens, spec_lens, cu_
         raise ValueError("q, k_cache and v_cache must share dtype; caches must share shape")
     if cu_q.shape[0] != B + 1 or block_tables.shape[0] != B:
         raise ValueError("cu_q must have B+1 entries and block_tables B rows")
-    need = ctypes.c_size_t(0)
-    _check(lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
     token = _guard_workspace(workspace)
-    if workspace is None and need.value:
-        workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device)
+    if workspace is None:  # (one that the caller brings is checked by the call itself)
+        need = ctypes.c_size_t(0)
+        _check(lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
+        if need.value:
+            workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if plan is not None:
         _check(lib.fsr_verify_attention_planned(
@@ -270,10 +279,11 @@ def verify_attention_kv8(q, k_cache, v_cache, k_scale, v_scale, block_tables, ct
         raise ValueError("k_scale and v_scale need one entry per KV head")
     if cu_q.shape[0] != B + 1 or block_tables.shape[0] != B:
         raise ValueError("cu_q must have B+1 entries and block_tables B rows")
-    need = ctypes.c_size_t(0)
-    _check(lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
-    if workspace is None and need.value:
-        workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device)
+    if workspace is None:
+        need = ctypes.c_size_t(0)
+        _check(lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
+        if need.value:
+            workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if plan is not None:
         _check(lib.fsr_verify_attention_kv8_planned(
@@ -355,9 +365,9 @@ def spec_accept(p_target, p_draft, draft_tokens, u_accept, u_sample, cu_t, cu_d,
         raise ValueError("emitted must be [B, S_max+1]")
     if cu_t.shape[0] != B + 1 or cu_d.shape[0] != B + 1:
         raise ValueError("cu_t and cu_d must have B+1 entries")
-    need = ctypes.c_size_t(0)
-    _check(lib.fsr_accept_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
     if workspace is None:
+        need = ctypes.c_size_t(0)
+        _check(lib.fsr_accept_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
         workspace = torch.empty(max(need.value, 256), dtype=torch.uint8, device=dev)
     ws_bytes = workspace.numel() * workspace.element_size()
     _check(lib.fsr_spec_accept(
