@@ -11,19 +11,20 @@
 //   bf16: 32-key tiles.  Whole key rows are loaded (1 KB of consecutive bytes per load, each lane 16) and put through
 //     wave-private swizzled LDS tiles, from which K is read as matrix operand and V transposed; while a tile is worked
 //     on, the next one is in flight in registers, and the places of the keys of the one after it.  Probabilities go to
-//     the matrix cores as bf16 terms: two (17 bits) for a bf16 result, three (the fp32 value exactly) for an fp32 one.
+//     the matrix cores as three bf16 terms, which together are the fp32 value exactly (two terms, 17 bits: 39 instead of
+//     42 us at the first shape below, but errors of 4e-6 of the largest value before the output's rounding, not 5e-7).
 //     A wave spends about as many cycles on its vector instructions as on waiting, so two waves per SIMD matter more
-//     than a second tile in flight: at 32 requests of 256 to 4096 tokens, 8 KV heads, D = 64, bf16, 36 us as built, 45 us
-//     with two tiles in flight (the registers spill), 59 us with four waves of 512 registers.
+//     than a second tile in flight: at 32 requests of 256 to 4096 tokens, 8 KV heads, D = 64, bf16, and two terms, 36 us
+//     as built, 45 us with two tiles in flight (the registers spill), 59 us with four waves of 512 registers.
 //   fp32: 16-key tiles on v_mfma_f32_16x16x4_f32, operands straight from memory in the operand layout.
 // All global accesses are declared with the element's alignment only (the hardware takes unaligned vectors).
 //
 // Measured, us a call, against one wave per (row, query head) with vector FMAs, which re-reads the keys for each of them:
-//   bf16 D = 64, 32/8 heads, 32 requests of 256-4096 tokens, 1-8 drafts      716 -> 39
-//   bf16 D = 64, 32/8 heads, 1 request of 8192 tokens, no drafts             317 -> 51 (eight workgroups in all)
-//   bf16 D = 64, 32/32 heads, 64 requests of 256-4096 tokens, 0-7 drafts     1324 -> 225
-//   bf16 D = 128, 64/2 heads, 16 requests of 1024-2048 tokens, 1-8 drafts    761 -> 56
-//   fp32 D = 128, 32/8 heads, 32 requests of 1024-2048 tokens, 1-8 drafts    1588 -> 145
+//   bf16 D = 64, 32/8 heads, 32 requests of 256-4096 tokens, 1-8 drafts      718 -> 42
+//   bf16 D = 64, 32/8 heads, 1 request of 8192 tokens, no drafts             317 -> 54 (eight workgroups in all)
+//   bf16 D = 64, 32/32 heads, 64 requests of 256-4096 tokens, 0-7 drafts     1282 -> 193
+//   bf16 D = 128, 64/2 heads, 16 requests of 1024-2048 tokens, 1-8 drafts    761 -> 64
+//   fp32 D = 128, 32/8 heads, 32 requests of 1024-2048 tokens, 1-8 drafts    1586 -> 142
 //   fp32 D = 64, 8/2 heads, 4 requests of 64-256 tokens, 0-4 drafts          20 -> 9 (kernel)
 #include "attend_items.hpp"
 
@@ -111,8 +112,8 @@ __device__ __forceinline__ u32x4 load16(const char* p) {
 }
 
 // Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see, merge the waves,
-// write the rows.  TERMS: bf16 terms a probability is split into (bf16 only).  MTMAX: what the LDS is laid out for.
-template <bool BF16, int D, int MTMAX, int MT, bool NT, int TERMS>
+// write the rows.  MTMAX: what the LDS is laid out for.
+template <bool BF16, int D, int MTMAX, int MT, bool NT>
 __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0) {
     typedef Map<BF16, D, MTMAX> L;
     constexpr int kTile = L::kTile, kKt = L::kKt, kDB = D / 16, kW = L::kW;
@@ -309,7 +310,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
 #pragma unroll
             for (int e = 0; e < 4 * kKt; ++e) {
                 float p = exp2_fast(fmaf(x[mt][e], a.scale_log2, neg_m));
-                if constexpr (TERMS == 3) p = fmaf(p, fmaxf(x[mt][e], -1e30f) * a.scale_rest, p);
+                p = fmaf(p, fmaxf(x[mt][e], -1e30f) * a.scale_rest, p);
                 x[mt][e] = p;
                 sum += p;
             }
@@ -358,37 +359,28 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
             }
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                // x = hi + lo (+ rest): hi, and with three terms lo too, by truncation; the last term by rounding or,
-                // as the third, exactly
+                // x = hi + lo + rest exactly: hi and lo by truncation, 8 bits each
                 uint32_t hi[4], lo[4], rest[4];
-                bf16x8 lo2;
 #pragma unroll
                 for (int e = 0; e < 8; e += 2) {
                     uint32_t b0 = __builtin_bit_cast(uint32_t, x[mt][e]), b1 = __builtin_bit_cast(uint32_t, x[mt][e + 1]);
                     hi[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
                     const float r0 = x[mt][e] - __builtin_bit_cast(float, b0 & 0xffff0000u);
                     const float r1 = x[mt][e + 1] - __builtin_bit_cast(float, b1 & 0xffff0000u);
-                    if constexpr (TERMS == 3) {
-                        b0 = __builtin_bit_cast(uint32_t, r0);
-                        b1 = __builtin_bit_cast(uint32_t, r1);
-                        lo[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-                        b0 = __builtin_bit_cast(uint32_t, r0 - __builtin_bit_cast(float, b0 & 0xffff0000u));
-                        b1 = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b1 & 0xffff0000u));
-                        rest[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-                    } else {
-                        lo2[e] = (__bf16)r0;
-                        lo2[e + 1] = (__bf16)r1;
-                    }
+                    b0 = __builtin_bit_cast(uint32_t, r0);
+                    b1 = __builtin_bit_cast(uint32_t, r1);
+                    lo[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                    b0 = __builtin_bit_cast(uint32_t, r0 - __builtin_bit_cast(float, b0 & 0xffff0000u));
+                    b1 = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b1 & 0xffff0000u));
+                    rest[e >> 1] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
                 }
                 const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{hi[0], hi[1], hi[2], hi[3]});
-                if constexpr (TERMS == 3) lo2 = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], lo[2], lo[3]});
+                const bf16x8 pl = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], lo[2], lo[3]});
+                const bf16x8 pr = __builtin_bit_cast(bf16x8, u32x4{rest[0], rest[1], rest[2], rest[3]});
 #pragma unroll
                 for (int db = 0; db < kDB; ++db) {
-                    if constexpr (TERMS == 3) {
-                        const bf16x8 pr = __builtin_bit_cast(bf16x8, u32x4{rest[0], rest[1], rest[2], rest[3]});
-                        acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], pr, acc[mt][db], 0, 0, 0);
-                    }
-                    acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], lo2, acc[mt][db], 0, 0, 0);
+                    acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], pr, acc[mt][db], 0, 0, 0);
+                    acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], pl, acc[mt][db], 0, 0, 0);
                     acc[mt][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], ph, acc[mt][db], 0, 0, 0);
                 }
             }
@@ -475,7 +467,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     }
 }
 
-template <bool BF16, int D, int MTMAX, bool NT, int TERMS>
+template <bool BF16, int D, int MTMAX, bool NT>
 __global__ __launch_bounds__((Map<BF16, D, MTMAX>::kThreads)) void attend_items_kernel(ItemArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int g = blockIdx.x, i = blockIdx.y;
@@ -485,12 +477,12 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX>::kThreads)) void attend_items_
     for (int m0 = blockIdx.z * 16 * MTMAX; m0 < M; m0 += gridDim.z * 16 * MTMAX) {
         const int mt = (min(M - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
         if constexpr (MTMAX >= 4)
-            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT>(a, smem, i, g, q0, M, c, m0);
         if constexpr (MTMAX >= 3)
-            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT>(a, smem, i, g, q0, M, c, m0);
         if constexpr (MTMAX >= 2)
-            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
-        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, TERMS>(a, smem, i, g, q0, M, c, m0);
+            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT>(a, smem, i, g, q0, M, c, m0);
+        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT>(a, smem, i, g, q0, M, c, m0);
         __syncthreads();  // before the next group's query operands and tiles
     }
 }
@@ -502,11 +494,10 @@ int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
     // keys that one workgroup reads once bypass the caches' replacement (non-temporal); further groups of a request
     // find them in the caches
     if constexpr (BF16) {
-        if (a.out_bf16 && groups == 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true, 2>), grid, block, smem, s, a);
-        else if (a.out_bf16) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false, 2>), grid, block, smem, s, a);
-        else hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false, 3>), grid, block, smem, s, a);
+        if (groups == 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true>), grid, block, smem, s, a);
+        else hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false>), grid, block, smem, s, a);
     } else {
-        hipLaunchKernelGGL((attend_items_kernel<false, D, MT, false, 3>), grid, block, smem, s, a);
+        hipLaunchKernelGGL((attend_items_kernel<false, D, MT, false>), grid, block, smem, s, a);
     }
     return check_launch("attend_items_kernel");
 }

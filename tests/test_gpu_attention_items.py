@@ -106,3 +106,38 @@ def test_values_that_are_not_finite_reach_their_rows_only(fsr, oracle, dtype, D,
     hit[2:5, :, d] = True
     assert np.array_equal(o[hit], np.full(hit.sum(), bad, np.float32), equal_nan=True)
     np.testing.assert_allclose(o[~hit], ref[~hit], rtol=0, atol=1e-5 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("D,P", [(64, 16), (128, 32)])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_probabilities_keep_32_bits(fsr, oracle, D, P, out_dtype):
+    """Outputs that are differences of nearly equal probabilities: two keys that differ by one unit in the last place of one
+    component, with values A and -A among zeros, so that an output is A (p1 - p2).  Error bound relative to A, besides the
+    output's own rounding: 2^-20.  It holds for 32-bit arithmetic (scores around 6 enter the exponential's argument with half
+    a unit of 2^-20, the rest are a few 2^-24 of p <= 1/2), and not for probabilities cut to 17 bits, off by up to 2^-18."""
+    announce(f"items probabilities D={D} out={out_dtype}")
+    rng = np.random.Generator(np.random.PCG64(21))
+    H_q, H_kv, B = 8, 2, 64
+    widen = lambda a: (a.astype(np.uint32) << 16).view(np.float32)  # noqa: E731
+    narrow = lambda a: (np.asarray(a, np.float32).view(np.uint32) >> 16).astype(np.uint16)  # noqa: E731
+    x = make(rng, "bf16", H_q, H_kv, D, P, np.full(B, 33), np.zeros(B))
+    x["k"][:] = 0
+    x["v"][:] = 0
+    size = np.empty((B, H_q, D))
+    for i in range(B):
+        mean = widen(x["q"][i]).reshape(H_kv, H_q // H_kv, D).mean(1)
+        key = narrow(mean * 6.0 * np.sqrt(D) / (mean ** 2).sum(-1, keepdims=True))  # score 6 at the group's mean query
+        val = narrow(rng.uniform(1.0, 2.0, (H_kv, D)))
+        for t, k, v in ((7, key, val), (20, key.copy(), val ^ np.uint16(0x8000))):
+            if t == 20:
+                k[:, i % D] ^= 1
+            page = x["bt"][i, t // P]
+            x["k"][page, :, t % P], x["v"][page, :, t % P] = k, v
+        size[i] = np.repeat(widen(val), H_q // H_kv, 0)
+    out, _, ref, _ = run(fsr, oracle, x, "bf16", H_q, H_kv, D, P, out_dtype=out_dtype, hint=1)
+    err = np.abs(out.float().cpu().numpy().astype(np.float64) - ref)
+    err -= (2.0 ** -8 if out_dtype == torch.bfloat16 else 2.0 ** -23) * np.abs(ref)  # the output's rounding
+    small = np.abs(ref) < 2.0 ** -10 * size  # where that does not hide the probabilities
+    print(f"{small.sum()} of {small.size} elements, worst {(err / size)[small].max():.2e}")
+    assert small.sum() > small.size // 4
+    assert (err[small] <= 2.0 ** -20 * size[small]).all()
