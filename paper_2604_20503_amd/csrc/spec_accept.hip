@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
     __shared__ double s_sum[kThreads / 64];
     __shared__ float s_max[kThreads / 64];
     __shared__ uint2 s_exp[256];
-    __shared__ int s_last;
+    __shared__ int s_behind, s_last;
     const int nc = n_chunks_of(V), nsg = n_stat_groups_of(V, ws.stat_group);
     const int k = blockIdx.y / B, i = blockIdx.y - k * B, j = k >> 1;
     const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
@@ -334,14 +334,16 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
         rows = z_draft + (size_t)(d_rows ? d_rows[r] : r) * V;
         stat = ws.stat_d + (size_t)r * nsg * 2;
     }
-    // a draft before this row's has been rejected: nothing will read the row's statistics
-    if (ws.skip && j > 0 &&
-        __hip_atomic_load(stat_words(ws, i, nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned)j)
-        return;
-    const bool vec = row_vec_ok(rows);
-    const double inv_T = 1.0 / T;
+    // If a draft before this row's has been rejected, nothing will read the row's statistics.  One lane asks for the whole
+    // workgroup: other workgroups may lower the word at any time, and waves that asked for themselves could differ.
+    if (threadIdx.x == 0)
+        s_behind = ws.skip && j > 0 &&
+                   __hip_atomic_load(stat_words(ws, i, nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned)j;
     fill_exp_table(s_exp);
     __syncthreads();
+    if (s_behind) return;
+    const bool vec = row_vec_ok(rows);
+    const double inv_T = 1.0 / T;
     const ExpConsts ek = exp_consts();
     const ExpTable et = exp_table(s_exp);
     const int c_first = blockIdx.x * ws.stat_group, c_end = min(nc, c_first + ws.stat_group);

@@ -73,3 +73,31 @@ def test_rows_behind_a_rejection(fsr, oracle, B, V, spec_hi):
             call()
             torch.cuda.synchronize()
             check_accept(outs, refs[(k + 1) % 3], bs[(k + 1) % 3].u_sample)
+
+
+def test_statistics_are_whole_or_left_out(fsr):
+    """A row behind a rejection is left out by its whole workgroup or by none of it: whatever pair (reference, sum) a call
+    leaves in its workspace is that row's own, and the others keep their bytes."""
+    announce("accept statistics whole or left out")
+    B, V = 400, 9000  # 4400 rows: one pair a row
+    spec = np.random.default_rng(3).integers(4, 6, size=B).astype(np.int32)
+    b = batches(B, V, spec, 2)[1]  # (drafts of a distribution of their own: most first drafts are rejected)
+    S = b.S_max
+    d = DeviceBatch(b, kv=False, logits=True)
+    ws = torch.full((fsr.accept_workspace_bytes(B=B, V=V, S_max=S, mode=1),), 0xFF, dtype=torch.uint8, device="cuda")
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    at_t = up(B * 56) + 2 * up(B * 3 * 8) + up(B * 4)  # decisions, two arrays of chunk masses, arrivals
+    at_d = at_t + up(B * (S + 1) * 3 * 16)
+    lse_t, lse_d = (torch.logsumexp(z.double() / 0.8, dim=1) for z in (d.z_target, d.z_draft))
+    left_out = 0
+    for _ in range(20):
+        ws.fill_(0xFF)
+        fsr.spec_accept(d.z_target, d.z_draft, d.draft_tokens, d.u_accept, d.u_sample, d.cu_q, d.cu_d, S_max=S, mode=1,
+                        temperature=0.8, workspace=ws)
+        for at, lse in ((at_t, lse_t), (at_d, lse_d)):
+            raw = ws[at:at + len(lse) * 16].view(torch.float64).view(-1, 2)
+            untouched = (raw.view(torch.int64) == -1).all(1)
+            left_out += int(untouched.sum())
+            err = (raw[:, 0] + torch.log(raw[:, 1]) - lse)[~untouched].abs()
+            assert bool((err < 1e-12 * lse.abs().max()).all()), float(err.max())
+    assert left_out > 0
