@@ -50,6 +50,12 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long k)
     return k;
 }
 
+// A request whose row counts do not fit the call is flagged by `decide`; none of its rows or drafts is looked at (a call with
+// S_max = 0 has no drafts to read: draft_tokens may be null).
+__device__ __forceinline__ bool refused(int t0, int t_i, int d_i, int S_max, int R_cap) {
+    return d_i < 0 || d_i > S_max || t_i < d_i || t_i > d_i + 1 || t0 < 0 || t0 + t_i > R_cap;
+}
+
 // first_miss [B]: position of the first mismatch known so far (the accepted_len output serves until `decide` fills it)
 __global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long long* keys, int32_t* first_miss, int n, int B) {
     const int r = blockIdx.x * kThreads + threadIdx.x;
@@ -61,12 +67,13 @@ __global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long lon
 __global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
     const float* __restrict__ target, const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ cu_t,
     const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
-    unsigned long long* keys, int32_t* first_miss, int B, int V, int R_cap) {
+    unsigned long long* keys, int32_t* first_miss, int B, int V, int S_max, int R_cap) {
     __shared__ unsigned long long part[kThreads / 64];
     __shared__ int s_miss;
     const int j = blockIdx.y / B, i = blockIdx.y - j * B;
-    const int t0 = cu_t[i], r = t0 + j;  // call-row on the target side
-    if (t0 < 0 || r >= cu_t[i + 1] || r >= R_cap || r >= cu_t[B]) return;
+    const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
+    const int r = t0 + j;  // call-row on the target side
+    if (j >= t_i || r >= cu_t[B] || refused(t0, t_i, d_i, S_max, R_cap)) return;
     if (j > 0) {  // one lane asks: the words of all requests lie in a few cache lines that every workgroup wants
         if (threadIdx.x == 0) s_miss = __hip_atomic_load(first_miss + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -88,9 +95,8 @@ __global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
         }
     }
     // the key of the draft this row verifies: larger than any if there is none, smaller for an id outside the vocabulary
-    const int d0 = cu_d[i];
     unsigned long long drafted = ~0ull;
-    if (d0 >= 0 && d0 + j < cu_d[i + 1] && d0 + j < cu_d[B]) {
+    if (d0 >= 0 && j < d_i && d0 + j < cu_d[B]) {
         const int t = draft_tokens[d_rows ? d_rows[d0 + j] : d0 + j];
         drafted = t < 0 || t >= V ? 0ull : make_key(__builtin_bit_cast(uint32_t, z[t]), t);
     }
@@ -129,8 +135,7 @@ __global__ __launch_bounds__(kThreads) void greedy_decide_kernel(const int32_t* 
     const int d_i = cu_d[i + 1] - cu_d[i], t_i = cu_t[i + 1] - cu_t[i];
     int32_t* em = emitted + (size_t)i * (S_max + 1);
     for (int s = 0; s <= S_max; ++s) em[s] = -1;
-    // a request whose row counts do not fit the call is flagged, not processed
-    if (d_i < 0 || d_i > S_max || t_i < d_i || t_i > d_i + 1 || cu_t[i] < 0 || cu_t[i] + t_i > R_cap) {
+    if (refused(cu_t[i], t_i, d_i, S_max, R_cap)) {
         accepted_len[i] = -1;
         n_emitted[i] = -1;
         return;
@@ -168,7 +173,7 @@ int greedy_accept_launch(const float* target, const int32_t* draft_tokens, const
     hipLaunchKernelGGL(greedy_init_kernel, dim3((R_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, keys, accepted_len, R_cap, p.B);
     if ((rc = check_launch("greedy_init_kernel")) != FSR_OK) return rc;
     hipLaunchKernelGGL(greedy_argmax_kernel, dim3((p.V + kChunk - 1) / kChunk, R_cap), dim3(kThreads), 0, s, target, draft_tokens,
-                       cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, R_cap);
+                       cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
     if ((rc = check_launch("greedy_argmax_kernel")) != FSR_OK) return rc;
     hipLaunchKernelGGL(greedy_decide_kernel, dim3((p.B + kThreads - 1) / kThreads), dim3(kThreads), 0, s, draft_tokens, cu_t,
                        cu_d, d_rows, keys, accepted_len, n_emitted, emitted, p.B, p.S_max, R_cap);

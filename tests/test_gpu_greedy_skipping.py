@@ -42,3 +42,15 @@ def test_rows_behind_a_mismatch(fsr, oracle, B, V, S):
         torch.cuda.synchronize()
         for name, t in zip(("accepted_len", "n_emitted", "emitted"), outs):
             assert np.array_equal(t.cpu().numpy(), ref[name]), (name, match)
+
+
+def test_drafts_of_a_flagged_request_are_not_read(fsr):
+    """S_max = 0 and no draft array: a request whose offsets claim a draft is flagged, the others get their arg-max."""
+    announce("greedy S_max=0 with a draft claimed")
+    V = 5000
+    z = np.random.default_rng(1).standard_normal((3, V)).astype(np.float32)
+    cu_t, cu_d = np.array([0, 1, 2, 3], np.int32), np.array([0, 0, 1, 1], np.int32)
+    acc, n, em = fsr.spec_accept(dev(z), None, None, None, None, dev(cu_t), dev(cu_d), S_max=0, mode=2)
+    torch.cuda.synchronize()
+    assert acc.tolist() == [0, -1, 0] and n.tolist() == [1, -1, 1]
+    assert em[:, 0].tolist() == [int(z[0].argmax()), -1, int(z[2].argmax())]
