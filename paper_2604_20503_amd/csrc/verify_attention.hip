@@ -1361,9 +1361,12 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
             // only the last item of a share can have no tile in it
             if (!wk.clip(a, gr, base, max(wk.x, base), sg)) break;
             sg.i = lo; sg.kvh = g; sg.c = c; sg.q0 = q0; sg.q_len = q_len;
+            // more items than the capacity the host computes means offsets past N_cap: a share's count never exceeds the
+            // records that are written (and that fit the buffer)
+            if (l > 0 && o - 1 >= more_cap) break;
             n = l + 1;
             if (l == 0) write_record(first + (size_t)s * kRecInts, a, sg, 0, o0);
-            else if (o - 1 < more_cap) write_record(more + (size_t)(o - 1) * kRecInts, a, sg, 0, 0);
+            else write_record(more + (size_t)(o - 1) * kRecInts, a, sg, 0, 0);
         }
         n = wave_max_i(n);
     }

@@ -46,3 +46,26 @@ def test_many_segments_per_share(fsr, B, H_q, H_kv, spec_hi, max_workgroups, hin
         assert torch.isfinite(out).all()
         outs.append((out, lse))
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+def test_segment_count_stays_within_the_plan(fsr):
+    """Offsets past N_cap, one share: more segments than the buffer has records.  The share's count is the number of records
+    written, and nothing is written behind the buffer.  (Only the plan is built here: no attention call reads it.)"""
+    announce("plan segments beyond the buffer")
+    H_q, H_kv, N_cap = 32, 8, 16
+    i32 = dict(dtype=torch.int32, device="cuda")
+    q = torch.zeros((N_cap, H_q, 128), dtype=torch.bfloat16, device="cuda")
+    cache = torch.zeros((64, H_kv, 16, 128), dtype=torch.bfloat16, device="cuda")
+    bt = torch.arange(2 * 64, **i32).view(2, 64) % 64
+    ctx, cu = torch.tensor([5, 7], **i32), torch.tensor([0, 4, 4 + 600], **i32)  # 1 + 150 groups of four rows, 8 heads
+    kw = dict(scale=1.0, max_q_len=1, max_workgroups=1)
+    need = fsr.attn_plan(q, cache, bt, ctx, torch.tensor([0, 4, 8], **i32), **kw).numel()
+    room = torch.full((need + 65536,), 0x77, dtype=torch.uint8, device="cuda")
+    fsr.attn_plan(q, cache, bt, ctx, cu, plan=room[:need], **kw)
+    torch.cuda.synchronize()
+    rec = room[:need].view(torch.int32).view(-1, 32).cpu().numpy()
+    further = len(rec) - 1 - 1024  # records behind the header and the shares' first ones
+    assert further < 8 * 151 - 1
+    assert rec[1, 13] == 1 + further
+    assert (room[need:] == 0x77).all()
+    assert (rec[1 + 1024:, 0] < 2).all() and (rec[1 + 1024:, 1] < H_kv).all()
