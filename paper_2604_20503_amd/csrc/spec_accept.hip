@@ -256,6 +256,27 @@ __device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
     const double pow2 = __builtin_bit_cast(double, ((unsigned long long)(e.y + (n << 12)) << 32) | e.x);
     return fma(pow2 * r, p, pow2);
 }
+// exp for the masses of a draw, which are formed twice -- for the chunk sums, then token by token in the chunk that is drawn
+// from -- and must be the same values both times, or a chunk with mass might hold no token with any.  By the table, below its
+// range by exp_softmax; 0 for a masked token (-inf, NaN) and where fp64 has nothing smaller.  Four at a time: exp_softmax is
+// hardly ever needed, and one branch for the wave leaves the look-ups free to overlap.
+constexpr double kExpZero = -746.0;
+constexpr double kSpread = -1e5;  // a row's smallest exponent between this and the floor is far-spread logits, not a mask
+__device__ __forceinline__ double exp_in_table(double x, const ExpTable& et, bool& below) {
+    const bool in = x >= kExpTableFloor;
+    below |= !in && x > kExpZero;
+    const double e = exp_lookup(x, et);
+    return in ? e : 0.0;
+}
+__device__ __forceinline__ void exp_tokens(const double (&x)[4], const ExpTable& et, const ExpConsts& ek, double (&e)[4]) {
+    bool below = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) e[k] = exp_in_table(x[k], et, below);
+    if (__builtin_amdgcn_ballot_w64(below) != 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e[k] = x[k] < kExpTableFloor ? exp_softmax(x[k], ek) : e[k];
+    }
+}
 // The constants for a kernel of the given mode: PROBS mode never evaluates exp and gets an empty set.
 template <int MODE>
 __device__ __forceinline__ ExpConsts exp_consts_for() {
@@ -475,24 +496,42 @@ __device__ __forceinline__ double difference(double p, double q) {
     return p - q;
 }
 
-// Masses of 4 consecutive tokens starting at e for the request's decision (bounds-checked).
-template <int MODE, typename RT>
-__device__ __forceinline__ void quad_masses(const Decision& dec, const RT* __restrict__ trow,
-                                            const RT* __restrict__ drow, int e, int V, bool vec_t, bool vec_d,
-                                            double T, const ExpConsts& ek, double (&mass)[4]) {
-    float a[4], b[4];
-    load_quad(trow, e, V, vec_t, a);
-    if (dec.kind == kCaseResidual) load_quad(drow, e, V, vec_d, b);
+// Masses of four entries of a row in a draw: the probabilities themselves, or exp(z / T - m) / Z.
+struct RowScale {
+    double m, inv_Z;
+};
+template <int MODE>
+__device__ __forceinline__ void token_masses(const float (&z)[4], double inv_T, const RowScale& sc, const ExpTable& et,
+                                             const ExpConsts& ek, double (&mass)[4]) {
+    if constexpr (MODE == FSR_PROBS) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const bool ok = e + k < V;
-        const double pt = ok ? prob_of<MODE>(a[k], T, dec.m_t, dec.Z_t, ek) : 0.0;
-        if (dec.kind == kCaseResidual) {
-            const double qd = ok ? prob_of<MODE>(b[k], T, dec.m_d, dec.Z_d, ek) : 0.0;
-            const double r = difference(pt, qd);
+        for (int k = 0; k < 4; ++k) mass[k] = (double)z[k];
+    } else {
+        double x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = fma((double)z[k], inv_T, -sc.m);
+        exp_tokens(x, et, ek, mass);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mass[k] *= sc.inv_Z;
+    }
+}
+// Masses of 4 consecutive tokens starting at e for a draw from the row or from the residual (bounds-checked).
+template <int MODE, typename RT>
+__device__ __forceinline__ void quad_masses(bool residual, const RT* __restrict__ trow, const RT* __restrict__ drow, int e, int V,
+                                            bool vec_t, bool vec_d, double inv_T, const RowScale& sc_t, const RowScale& sc_d,
+                                            const ExpTable& et, const ExpConsts& ek, double (&mass)[4]) {
+    constexpr float kNothing = MODE == FSR_LOGITS ? -INFINITY : 0.0f;  // past the vocabulary
+    float a[4], b[4];
+    load_quad(trow, e, V, vec_t, a, kNothing);
+    if (residual) load_quad(drow, e, V, vec_d, b, kNothing);
+    token_masses<MODE>(a, inv_T, sc_t, et, ek, mass);
+    if (residual) {
+        double q[4];
+        token_masses<MODE>(b, inv_T, sc_d, et, ek, q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double r = difference(mass[k], q[k]);
             mass[k] = r > 0.0 ? r : 0.0;
-        } else {
-            mass[k] = pt;
         }
     }
 }
@@ -605,7 +644,9 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
 // a small one is a latency chain (decision, rows, sums, arrival, chunk search, chunk scan), so what lies on it is kept
 // short: sums over a wave by DPP, the search over the chunk masses by one wave.  Measured, us a launch before / after:
 // PROBS 16 requests 17.6 / 13.4, chunks of 512 requests' drafts (mean of four) 47.5 / 39.3; LOGITS 16 requests in bf16
-// 20.8 / 16.4, 512 requests 183 / 148.
+// 20.8 / 16.4, 512 requests 183 / 148.  LOGITS calls with masked logits, 128 requests x 128256 in fp32, us a call with such
+// chunks read again by the checked path / summed from the registers: all but 50 logits of a row masked 171 / 151, every
+// second one 164 / 140; exponents spread over several hundred (T = 0.02) 173 / 184, read again either way.
 // ---------------------------------------------------------------------------------------
 template <int MODE, typename RT, int kSampleGroup>
 __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
@@ -629,11 +670,16 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
         __syncthreads();
     }
     const ExpConsts ek = exp_consts_for<MODE>();
+    ExpTable et{};
+    if constexpr (MODE == FSR_LOGITS) et = exp_table(s_exp);
 
     // ---- 2. fp64 mass of this workgroup's chunks of the sampling distribution
     const RT* trow = p_target + (size_t)dec.t_row * V;
     const RT* drow = p_draft + (size_t)dec.d_row * V;
     const bool vec_t = row_vec_ok(trow), vec_d = row_vec_ok(drow);
+    const double inv_T = 1.0 / T;
+    // a draw from one row needs no normalisation: its masses are relative to each other only
+    const RowScale sc_t{dec.m_t, dec.kind == kCaseTarget ? 1.0 : 1.0 / dec.Z_t}, sc_d{dec.m_d, 1.0 / dec.Z_d};
     // A workgroup takes kSampleGroup consecutive chunks: the chain every workgroup goes through (decision record,
     // row loads, reduction, store-through, arrival count) is paid once per 128 KB instead of once per 32 KB.
     auto chunk_mass_checked = [&](int c) __attribute__((always_inline)) {  // any chunk, element by element
@@ -641,7 +687,8 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
 #pragma unroll
         for (int k = 0; k < kPerThread / 4; ++k) {
             double m[4];
-            quad_masses<MODE, RT>(dec, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V, vec_t, vec_d, T, ek, m);
+            quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V, vec_t, vec_d,
+                                  inv_T, sc_t, sc_d, et, ek, m);
             r += (m[0] + m[1]) + (m[2] + m[3]);
         }
         return r;
@@ -653,7 +700,6 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
         const bool residual = dec.kind == kCaseResidual;
         const bool vec_ok = vec_t && (!residual || vec_d);
         const int n_whole = vec_ok ? min(n_here, max(0, V / kChunk - c_first)) : 0;
-        const double inv_T = 1.0 / T, inv_Zt = 1.0 / dec.Z_t, inv_Zd = 1.0 / dec.Z_d;
         auto load_rows = [&](int c, float (&t)[kPerThread], float (&d)[kPerThread]) {
 #pragma unroll
             for (int k = 0; k < kPerThread / 4; ++k) {
@@ -668,40 +714,52 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
                 }
             }
         };
-        unsigned todo = ((1u << n_here) - 1u) & ~((1u << n_whole) - 1u);  // chunks left to the checked path, per wave
+        unsigned todo = ((1u << n_here) - 1u) & ~((1u << n_whole) - 1u);  // chunks left to the checked path
         auto sum_chunk = [&](int cc, const float (&t)[kPerThread], const float (&d)[kPerThread]) {
             double r = 0.0;
-            bool exact = true;  // (LOGITS) the table covers every logit of the wave
             if constexpr (MODE == FSR_LOGITS) {
-                const ExpTable et = exp_table(s_exp);
+                // Without a check per token where every logit of the wave lies in the table's range; with masked tokens
+                // (-inf, NaN, or so low that exp is 0) counted as 0 where some are masked; the checked path where a logit
+                // has a value below the table's range.  The values are those of exp_tokens throughout.
+                bool below = false;
+                auto sum = [&](auto masked) {
+                    auto mass = [&](float z, const RowScale& sc) {
+                        const double x = fma((double)z, inv_T, -sc.m);
+                        if constexpr (decltype(masked)::value) return exp_in_table(x, et, below);
+                        else return exp_lookup<false>(x, et);
+                    };
+                    double acc = 0.0;
+#pragma unroll
+                    for (int u = 0; u < kPerThread; ++u) {
+                        if (residual) {
+                            const double x = difference(mass(t[u], sc_t) * sc_t.inv_Z, mass(d[u], sc_d) * sc_d.inv_Z);
+                            acc += x < 0.0 ? 0.0 : x;  // (keeps a NaN)
+                        } else {
+                            acc += mass(t[u], sc_t);
+                        }
+                    }
+                    return acc;
+                };
                 float lo_t = t[0], lo_d = d[0];
 #pragma unroll
                 for (int u = 1; u < kPerThread; ++u) {
                     lo_t = fminf(lo_t, t[u]);
                     lo_d = fminf(lo_d, d[u]);
                 }
-                bool in = fma((double)lo_t, inv_T, -dec.m_t) >= kExpTableFloor;
-                if (residual) in = in && fma((double)lo_d, inv_T, -dec.m_d) >= kExpTableFloor;
-                exact = __builtin_amdgcn_ballot_w64(!in) == 0;
-                if (exact) {
-                    if (residual) {
-#pragma unroll
-                        for (int u = 0; u < kPerThread; ++u) {
-                            const double pt = exp_lookup<false>(fma((double)t[u], inv_T, -dec.m_t), et) * inv_Zt;
-                            const double qd = exp_lookup<false>(fma((double)d[u], inv_T, -dec.m_d), et) * inv_Zd;
-                            const double x = difference(pt, qd);
-                            r += x < 0.0 ? 0.0 : x;  // (keeps a NaN)
-                        }
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < kPerThread; ++u) r += exp_lookup<false>(fma((double)t[u], inv_T, -dec.m_t), et);
-                        r *= inv_Zt;
-                    }
-                    exact = __builtin_amdgcn_ballot_w64(r != r) == 0;  // a NaN logit counts as masked
+                double lo = fma((double)lo_t, inv_T, -sc_t.m);
+                if (residual) lo = fmin(lo, fma((double)lo_d, inv_T, -sc_d.m));
+                bool plain = __builtin_amdgcn_ballot_w64(!(lo >= kExpTableFloor)) == 0;
+                if (plain) {
+                    r = sum(std::false_type{});
+                    plain = __builtin_amdgcn_ballot_w64(r != r) == 0;  // a NaN logit counts as masked
                 }
-                if (!exact) {
-                    todo |= 1u << cc;
-                    return;
+                if (!plain) {
+                    below = lo < kExpTableFloor && lo > kSpread;  // far spread, not masked: some token will be below
+                    if (__builtin_amdgcn_ballot_w64(below) == 0) r = sum(std::true_type{});
+                    if (__builtin_amdgcn_ballot_w64(below) != 0) {
+                        todo |= 1u << cc;
+                        return;
+                    }
                 }
             } else if (residual) {
 #pragma unroll
@@ -831,7 +889,7 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
 #pragma unroll
     for (int k = 0; k < kPerThread / 4; ++k) {
         double m[4];
-        quad_masses<MODE, RT>(dec, trow, drow, e0 + 4 * k, V, vec_t, vec_d, T, ek, m);
+        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, vec_t, vec_d, inv_T, sc_t, sc_d, et, ek, m);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             mass[4 * k + j] = m[j];
@@ -864,7 +922,7 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
     last_pos = max(max(s_i[0], s_i[1]), max(s_i[2], s_i[3]));
     if (threadIdx.x == 0) {
         int tok = hit != INT_MAX ? hit : last_pos;
-        if (tok < 0) tok = 0;  // unreachable for a chunk with mass; keeps the id in range
+        if (tok < 0) tok = 0;  // only if no token of the row has any mass; keeps the id in range
         em[dec.n] = tok;
         n_emitted[i] = dec.n + 1;
     }

@@ -63,3 +63,53 @@ def test_masked_chunks_and_zero_uniforms(fsr, oracle, spec):
     gpu = fsr.spec_accept(x.z_target, x.z_draft, x.draft_tokens, x.u_accept, dev(b.u_sample), x.cu_q, x.cu_d, S_max=b.S_max, mode=1)
     torch.cuda.synchronize()
     check_accept(gpu, ref, b.u_sample)
+
+
+def test_a_chunk_with_mass_holds_a_token_with_mass(fsr):
+    """Draft logits = target logits + a constant: the distributions are equal, and what p - q leaves is rounding.  Rejected
+    (the drafted token is masked), such a request must still draw a token that has a probability.  All of them are in the
+    second chunk, which holds two values of logits only, so that its rounding errors are few and may all be negative."""
+    announce("accept residual of rounding errors")
+    B, V = 512, 8192
+    rng = np.random.default_rng(17)
+    z = np.full((2 * B, V), -np.inf, np.float32)  # rows 2 i: verifies the draft, 2 i + 1: bonus
+    grid = lambda lo, hi, n: rng.integers(int(lo * 1024), int(hi * 1024), n) / 1024.0  # noqa: E731  (sums are exact in fp32)
+    top, gap, shift = grid(-4, 4, B), grid(1, 30, B), grid(-3, 3, B)
+    z[0::2, 4096:] = (top - gap)[:, None]
+    z[np.arange(0, 2 * B, 2), 4096 + rng.integers(0, 4096, B)] = top
+    z[1::2, 4096:] = 0.0
+    q = z[0::2] + shift[:, None].astype(np.float32)
+    tok = rng.integers(0, 4096, B).astype(np.int32)
+    u = rng.random(B).astype(np.float32)
+    acc, n, em = fsr.spec_accept(dev(z), dev(q), dev(tok), dev(u), dev(u), dev(np.arange(0, 2 * B + 1, 2, dtype=np.int32)),
+                                 dev(np.arange(B + 1, dtype=np.int32)), S_max=1, mode=1, temperature=0.7)
+    torch.cuda.synchronize()
+    assert not acc.any() and (n == 1).all()
+    bad = (em[:, 0] < 4096).nonzero()[:, 0].tolist()
+    assert not bad, f"{len(bad)} requests drew a masked token, e.g. {bad[:5]}"
+
+
+@pytest.mark.parametrize("kind", ["top-50", "lowest", "far", "one"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_masked_and_far_spread_rows(fsr, oracle, kind, dtype):
+    """The ways through a whole chunk: most logits masked with -inf or with the type's lowest value, exponents from 0 to -900
+    (some in fp64's last range, where the table ends), a single masked token."""
+    announce(f"accept masked {kind} {dtype}")
+    V = 4 * 4096 + 100
+    b = workloads.make_batch(2, rep=9, with_kv=False, V=V, spec_lens=[3, 1, 0, 4, 2, 5], ctx_lens=[8] * 6, keep_logits=True,
+                             draft_mode="independent")
+    T = 0.01 if kind == "far" else 0.9
+    for z in (b.z_target, b.z_draft):
+        if kind in ("top-50", "lowest"):
+            z[z < np.sort(z, axis=1)[:, -50][:, None]] = -np.inf if kind == "top-50" else np.finfo(np.float32).min
+        if kind == "one":
+            z[:, 5000] = -np.inf
+    up = lambda a: torch.from_numpy(a).to(dtype)  # noqa: E731
+    zt, zd = up(b.z_target), up(b.z_draft)
+    b.u_sample[::2] = 0.0
+    ref = oracle.spec_accept(zt.float().numpy(), zd.float().numpy(), b.draft_tokens, b.u_accept, b.u_sample, b.cu_q, b.cu_d,
+                             S_max=b.S_max, mode=1, temperature=T)
+    gpu = fsr.spec_accept(zt.cuda(), zd.cuda(), dev(b.draft_tokens), dev(b.u_accept), dev(b.u_sample), dev(b.cu_q), dev(b.cu_d),
+                          S_max=b.S_max, mode=1, temperature=T)
+    torch.cuda.synchronize()
+    check_accept(gpu, ref, b.u_sample)
