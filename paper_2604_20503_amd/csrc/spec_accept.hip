@@ -16,10 +16,10 @@
 //   decide   per request, one wave: the accept tests, one lane per draft with all gathers in flight
 //            together (LOGITS mode: the outcome that `stats` has found); picks the row pair to sample from and
 //            records it
-//   sample   grid (chunks, requests): every workgroup sums the fp64 mass of its chunk of the residual
-//            and of the target row; the workgroup of a request that finishes last (found by an arrival
-//            counter that `decide` has zeroed) draws the token: prefix over the chunk masses -> chunk
-//            holding u * R -> scan inside that chunk
+//   sample   grid (chunks, requests): every workgroup sums the fp64 mass of its chunks of the residual or of the target
+//            row (of the target row too where there is no residual, for the draw if there is none anywhere); the
+//            workgroup of a request that finishes last (found by an arrival counter that `decide` has zeroed) draws the
+//            token: prefix over the chunk masses -> chunk holding u * R -> scan inside that chunk
 // Only the rows the outcome needs are streamed: one target row (bonus) or one target and
 // one draft row (rejection) per request -- the algorithmic minimum in PROBS mode.
 // All masses are accumulated in fp64 so that the chosen token matches a sequential fp64
@@ -515,16 +515,18 @@ __device__ __forceinline__ void token_masses(const float (&z)[4], double inv_T, 
         for (int k = 0; k < 4; ++k) mass[k] *= sc.inv_Z;
     }
 }
-// Masses of 4 consecutive tokens starting at e for a draw from the row or from the residual (bounds-checked).
+// Masses of 4 consecutive tokens starting at e for a draw from the row or from the residual (bounds-checked); their sum in
+// the target row is added to `target`.
 template <int MODE, typename RT>
 __device__ __forceinline__ void quad_masses(bool residual, const RT* __restrict__ trow, const RT* __restrict__ drow, int e, int V,
                                             bool vec_t, bool vec_d, double inv_T, const RowScale& sc_t, const RowScale& sc_d,
-                                            const ExpTable& et, const ExpConsts& ek, double (&mass)[4]) {
+                                            const ExpTable& et, const ExpConsts& ek, double (&mass)[4], double& target) {
     constexpr float kNothing = MODE == FSR_LOGITS ? -INFINITY : 0.0f;  // past the vocabulary
     float a[4], b[4];
     load_quad(trow, e, V, vec_t, a, kNothing);
     if (residual) load_quad(drow, e, V, vec_d, b, kNothing);
     token_masses<MODE>(a, inv_T, sc_t, et, ek, mass);
+    target += (mass[0] + mass[1]) + (mass[2] + mass[3]);
     if (residual) {
         double q[4];
         token_masses<MODE>(b, inv_T, sc_d, et, ek, q);
@@ -640,19 +642,23 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
 // ---------------------------------------------------------------------------------------
 // sample: request i = blockIdx.y; this workgroup owns chunks kSampleGroup * blockIdx.x .. + kSampleGroup - 1 of the
 // vocabulary.  grid = (ceil(n_chunks / kSampleGroup), B)
+// Where a wave meets no residual in a chunk it sums the target row's masses as well, in case there is none anywhere (a
+// drafted token without probability, rows that are equal otherwise); left to the request's last workgroup, such a call of
+// 16 requests took 57 us in place of 17 (PROBS) and 127 in place of 50 (LOGITS), one of 128 requests 76 in place of 31 and
+// 210 in place of 116.  LOGITS: four waves per SIMD, 128 registers (133 and three: 573 in place of 560 us a call of 512).
 // A large call is bound by the rows' bytes (PROBS) or by fp64 instructions (LOGITS: exp by table look-up, see exp_lookup);
 // a small one is a latency chain (decision, rows, sums, arrival, chunk search, chunk scan), so what lies on it is kept
 // short: sums over a wave by DPP, the search over the chunk masses by one wave.  Measured, us a launch before / after:
 // PROBS 16 requests 17.6 / 13.4, chunks of 512 requests' drafts (mean of four) 47.5 / 39.3; LOGITS 16 requests in bf16
 // 20.8 / 16.4, 512 requests 183 / 148.  LOGITS calls with masked logits, 128 requests x 128256 in fp32, us a call with such
-// chunks read again by the checked path / summed from the registers: all but 50 logits of a row masked 171 / 151, every
-// second one 164 / 140; exponents spread over several hundred (T = 0.02) 173 / 184, read again either way.
+// chunks read again by the checked path / summed from the registers: all but 50 logits of a row masked 171 / 158, every
+// second one 164 / 141; exponents spread over several hundred (T = 0.02) 173 / 176, read again either way.
 // ---------------------------------------------------------------------------------------
 template <int MODE, typename RT, int kSampleGroup>
-__global__ __launch_bounds__(kThreads) void accept_sample_kernel(
+__global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_sample_kernel(
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const float* __restrict__ u_sample,
     int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int V, int S_max, double T) {
-    __shared__ double s_part[kThreads / 64][kSampleGroup];
+    __shared__ double s_part[kThreads / 64][kSampleGroup], s_part_t[kThreads / 64][kSampleGroup];
     __shared__ double s_wave[kThreads / 64];
     __shared__ int s_i[kThreads / 64];
     __shared__ double s_base, s_thr;
@@ -682,13 +688,14 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
     const RowScale sc_t{dec.m_t, dec.kind == kCaseTarget ? 1.0 : 1.0 / dec.Z_t}, sc_d{dec.m_d, 1.0 / dec.Z_d};
     // A workgroup takes kSampleGroup consecutive chunks: the chain every workgroup goes through (decision record,
     // row loads, reduction, store-through, arrival count) is paid once per 128 KB instead of once per 32 KB.
-    auto chunk_mass_checked = [&](int c) __attribute__((always_inline)) {  // any chunk, element by element
+    auto chunk_mass_checked = [&](int c, double& target) __attribute__((always_inline)) {  // any chunk, element by element
         double r = 0.0;
+        target = 0.0;
 #pragma unroll
         for (int k = 0; k < kPerThread / 4; ++k) {
             double m[4];
             quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V, vec_t, vec_d,
-                                  inv_T, sc_t, sc_d, et, ek, m);
+                                  inv_T, sc_t, sc_d, et, ek, m, target);
             r += (m[0] + m[1]) + (m[2] + m[3]);
         }
         return r;
@@ -715,8 +722,19 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
             }
         };
         unsigned todo = ((1u << n_here) - 1u) & ~((1u << n_whole) - 1u);  // chunks left to the checked path
+        // A wave's masses of chunk cc to LDS.  Only a residual that is zero everywhere needs the target row's: a wave sums
+        // those where it has met no residual.
+        auto put = [&](int cc, double r, double target) {
+            const bool none = residual && __builtin_amdgcn_ballot_w64(r > 0.0) == 0;
+            r = wave_sum_to_last(r);
+            if (none) target = wave_sum_to_last(target);
+            if (lane == 63) {
+                s_part[w][cc] = r;
+                if (residual) s_part_t[w][cc] = none ? target : 0.0;
+            }
+        };
         auto sum_chunk = [&](int cc, const float (&t)[kPerThread], const float (&d)[kPerThread]) {
-            double r = 0.0;
+            double r = 0.0, target = 0.0;
             if constexpr (MODE == FSR_LOGITS) {
                 // Without a check per token where every logit of the wave lies in the table's range; with masked tokens
                 // (-inf, NaN, or so low that exp is 0) counted as 0 where some are masked; the checked path where a logit
@@ -761,6 +779,14 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
                         return;
                     }
                 }
+                if (residual && __builtin_amdgcn_ballot_w64(r > 0.0) == 0) {
+#pragma unroll
+                    for (int u = 0; u < kPerThread; ++u) {
+                        float z = t[u];
+                        asm volatile("" : "+v"(z));  // or the compiler keeps sixteen masses of the loop above in registers
+                        target += exp_in_table(fma((double)z, inv_T, -sc_t.m), et, below) * sc_t.inv_Z;
+                    }
+                }
             } else if (residual) {
 #pragma unroll
                 for (int k = 0; k < kPerThread; k += 4) {
@@ -771,14 +797,14 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
                         m[u] = x > 0.0 ? x : 0.0;
                     }
                     r += (m[0] + m[1]) + (m[2] + m[3]);
+                    target += ((double)t[k] + (double)t[k + 1]) + ((double)t[k + 2] + (double)t[k + 3]);
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < kPerThread; k += 4)
                     r += ((double)t[k] + (double)t[k + 1]) + ((double)t[k + 2] + (double)t[k + 3]);
             }
-            r = wave_sum_to_last(r);
-            if (lane == 63) s_part[w][cc] = r;
+            put(cc, r, target);
         };
         if (n_whole > 0) {
             float ta[kPerThread], da[kPerThread], tb[kPerThread], db[kPerThread];
@@ -796,8 +822,9 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
         while (todo) {
             const int cs = __builtin_ctz(todo);
             todo &= todo - 1;
-            const double r = wave_sum_to_last(chunk_mass_checked(c_first + cs));
-            if (lane == 63) s_part[w][cs] = r;
+            double target;
+            const double r = chunk_mass_checked(c_first + cs, target);
+            put(cs, r, target);
         }
         __syncthreads();
         if (w == 0) {
@@ -806,6 +833,9 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
 #pragma unroll
                 for (int k = 0; k < kThreads / 64; ++k) r += s_part[k][lane];
                 publish_f64(ws.mass_res + (size_t)i * nc + c_first + lane, r);
+                if (residual && !(r > 0.0))
+                    publish_f64(ws.mass_tgt + (size_t)i * nc + c_first + lane,
+                                (s_part_t[0][lane] + s_part_t[1][lane]) + (s_part_t[2][lane] + s_part_t[3][lane]));
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // all are in memory before the arrivals are counted
             if (lane == 0) s_last = atomicAdd(ws.arrivals + i, (unsigned)n_here) + (unsigned)n_here == (unsigned)nc;
@@ -864,19 +894,9 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
         if (lane == 0) s_fallback = !found;
     }
     __syncthreads();
-    if (s_fallback) {  // the residual is all zero: sample from the target row itself (its masses are made here and now)
+    if (s_fallback) {  // the residual is all zero: sample from the target row itself
+        if (w == 0) search((dec.kind == kCaseResidual ? ws.mass_tgt : ws.mass_res) + (size_t)i * nc, true);
         dec.kind = kCaseTarget;
-        for (int c = 0; c < nc; ++c) {
-            const double r = wave_sum_to_last(chunk_mass_checked(c));
-            if (lane == 63) s_wave[w] = r;
-            __syncthreads();
-            if (threadIdx.x == 0) publish_f64(ws.mass_tgt + (size_t)i * nc + c, (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
-            __syncthreads();
-        }
-        if (w == 0) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            search(ws.mass_tgt + (size_t)i * nc, true);
-        }
         __syncthreads();
     }
     const double thr = s_thr;
@@ -885,11 +905,11 @@ __global__ __launch_bounds__(kThreads) void accept_sample_kernel(
     // scan inside the chunk: thread t owns tokens [16 t, 16 t + 16) of the chunk
     const int e0 = cs * kChunk + threadIdx.x * kPerThread;
     double mass[kPerThread];
-    double local = 0.0;
+    double local = 0.0, unused = 0.0;
 #pragma unroll
     for (int k = 0; k < kPerThread / 4; ++k) {
         double m[4];
-        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, vec_t, vec_d, inv_T, sc_t, sc_d, et, ek, m);
+        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, vec_t, vec_d, inv_T, sc_t, sc_d, et, ek, m, unused);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             mass[4 * k + j] = m[j];

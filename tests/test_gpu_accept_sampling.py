@@ -17,19 +17,23 @@ def fsr():
     return f
 
 
-@pytest.mark.parametrize("V", [4096, 9001, 300000])  # one chunk; unaligned rows; more chunks (74) than a wave has lanes
+# one chunk; unaligned rows; more chunks (74) than a wave has lanes; several chunks a workgroup
+@pytest.mark.parametrize("V,B", [(4096, 4), (9001, 4), (300000, 4), (8196, 1024)])
 @pytest.mark.parametrize("mode", ["probs", "logits"])
-def test_residual_that_is_zero_everywhere(fsr, oracle, V, mode):
+def test_residual_that_is_zero_everywhere(fsr, oracle, V, B, mode):
     """Draft and target rows are equal and the drafted token has no probability: it is rejected, p - q is zero for every
-    token, and the recovery token is drawn from the target row."""
-    announce(f"accept zero residual {mode} V={V}")
-    b = workloads.make_batch(2, rep=3, with_kv=False, V=V, spec_lens=[3, 1, 2, 4], ctx_lens=[8] * 4, keep_logits=True,
-                             draft_mode="noise")
+    token, and the recovery token is drawn from the target row (whose masses every workgroup leaves for this)."""
+    announce(f"accept zero residual {mode} V={V} B={B}")
+    b = workloads.make_batch(2, rep=3, with_kv=False, V=V, spec_lens=[3, 1, 2, 4] if B == 4 else [1] * B, ctx_lens=[8] * B,
+                             keep_logits=True, draft_mode="noise")
     for i in range(b.B):
         for n in range(int(b.spec_lens[i])):
             t, d = int(b.cu_q[i]) + n, int(b.cu_d[i]) + n
             x = int(b.draft_tokens[d])
             b.p_target[t, x], b.z_target[t, x] = 0.0, -np.inf
+            if B > 4:  # masked tokens in some of the rows, whole chunks of them in a few
+                lo, step = (0, 1) if d % 8 == 0 else (d % 4096, 3)
+                b.p_target[t, lo:5000:step], b.z_target[t, lo:5000:step] = 0.0, -np.inf
             b.p_draft[d], b.z_draft[d] = b.p_target[t], b.z_target[t]
     b.u_sample[0] = 0.0
     x = DeviceBatch(b, kv=False, logits=True)
