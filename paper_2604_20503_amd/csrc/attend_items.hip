@@ -5,7 +5,7 @@
 // What bounds it is reading K and V (bf16) or the fp32 matrix instructions (fp32), so the work is laid out to read a
 // request's keys once per KV head: one workgroup per (request, KV head, group of up to 16 * MT query rows), its waves
 // take the keys' tiles in turn and are merged through LDS at the end.  Longer suffixes than a group holds are further
-// workgroups (grid.z), or further rounds of the same one where the caller has not said how long they are.  A ragged
+// workgroups (grid.z), or further rounds of the same one where there are more groups than workgroups.  A ragged
 // batch loads the compute units unevenly, but a compute unit draws about twice its even share of the HBM bandwidth
 // when others are idle, which covers a longest context of twice the mean.
 //   bf16: 32-key tiles.  Whole key rows are loaded (1 KB of consecutive bytes per load, each lane 16) and put through
@@ -506,9 +506,13 @@ template <bool BF16, int D>
 int launch_mt(const ItemArgs& a, long long rows, bool bounded, hipStream_t s) {
     constexpr int kMost = D == 64 ? 4 : 3;  // query tiles a wave holds without spilling
     const int mt = (int)std::min<long long>(kMost, (rows + 15) / 16);
-    // an item gets as many workgroups as its rows need groups; with a bound too small, or none given, a workgroup may
-    // have to take several
-    const unsigned groups = (unsigned)std::min<long long>(bounded ? 64 : 4, (rows + 16 * mt - 1) / (16 * mt));
+    // An item gets as many workgroups as its rows need groups, up to 64; each may take several, and one without rows leaves
+    // at once.  Where the caller has not said how many rows a request has, one may have all of the call's, and the bound is
+    // as many as leave the call some thousands (at least four an item).  Without a hint, us a call with four an item / like
+    // this: 32/1 heads of 64, one request of 64 rows and 8192 tokens 1039 / 141, 32/8 heads, one of 256 rows and 4096 tokens
+    // 283 / 77, one of 1024 rows 1207 / 165, 128 of 2 to 9 rows 114 / 114; fp32, 8/2 heads, 512 of 2 to 9 rows 57 / 57.
+    const long long items = (long long)a.B * a.H_kv, most = bounded ? 64 : std::max(4LL, std::min(64LL, 4096 / items));
+    const unsigned groups = (unsigned)std::min(most, (rows + 16 * mt - 1) / (16 * mt));
     switch (mt) {
         case 1: return launch<BF16, D, 1>(a, groups, s);
         case 2: return launch<BF16, D, 2>(a, groups, s);

@@ -75,6 +75,22 @@ def test_shapes_outside_the_stream_kernel(fsr, oracle, dtype, H_q, H_kv, D, P, t
         print(f"max rel err {err:.2e}")
 
 
+@pytest.mark.parametrize("dtype,D,P,out_dtype", [("bf16", 64, 16, torch.bfloat16), ("bf16", 128, 8, torch.float32),
+                                                 ("f32", 64, 16, torch.float32)])
+def test_more_row_groups_than_workgroups(fsr, oracle, dtype, D, P, out_dtype):
+    """One request of 241 rows with 20 query heads: 4820 rows of a KV head, in groups of 64 (D = 64) or 48, of which an item
+    has at most 64 in flight; beside it requests of few rows and of none at all."""
+    rng = np.random.Generator(np.random.PCG64(77))
+    x = make(rng, dtype, 20, 1, D, P, [70, 0, 33, 5], [240, 0, 2, 3])
+    x["cu"] = np.concatenate([x["cu"][:2], x["cu"][1:2], x["cu"][2:-1]]).astype(np.int32)  # request 1 has no rows, 2 one
+    for hint in (0, 241, 3):
+        announce(f"items many groups {dtype} D={D} hint={hint}")
+        out, lse, ref, lse_ref = run(fsr, oracle, x, dtype, 20, 1, D, P, out_dtype=out_dtype, hint=hint)
+        n = int(x["cu"][-1])
+        check_attention(out[:n], ref[:n], "f32", n)
+        np.testing.assert_allclose(lse[:n].cpu().numpy(), lse_ref[:n], rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("dtype,D,shift,out_dtype", [("f32", 64, 1, torch.float32), ("bf16", 64, 1, torch.bfloat16),
                                                      ("bf16", 64, 3, torch.float32)])
 def test_inputs_aligned_to_their_elements_only(fsr, oracle, dtype, D, shift, out_dtype):
