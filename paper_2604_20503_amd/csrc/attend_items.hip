@@ -214,7 +214,8 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     };
     // One tile.  masked: some row does not see all of its keys.  careful: V may hold Inf or NaN, which must reach
     // exactly the rows that see their key, and an infinite value must meet the whole probability and not its zero
-    // parts: the sum is formed without the matrix cores.
+    // parts: the sum is formed without the matrix cores.  V may also be so large that it must not meet a probability
+    // above 1: the references are the largest scores.
     auto tile = [&](int t, auto masked_, auto careful_) {
         constexpr bool masked = decltype(masked_)::value, careful = decltype(careful_)::value;
         const int kb = kb0 + t * step;
@@ -287,7 +288,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
                     top[mt] = fmaxf(top[mt], z);
                 }
             top[mt] *= a.scale_log2;
-            raise |= top[mt] > m_run[mt] + 8.0f;
+            raise |= top[mt] > m_run[mt] + (careful ? 0.0f : 8.0f);
         }
         if (__builtin_amdgcn_ballot_w64(raise) != 0) {
 #pragma unroll
@@ -402,14 +403,15 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     for (; t < n_plain; ++t) tile(t, std::false_type{}, std::false_type{});
 #pragma unroll 1
     for (; t < nw; ++t) tile(t, std::true_type{}, std::false_type{});
-    // an accumulator that is not finite: once more from the start, with care (0 * x is NaN for exactly those)
+    // an accumulator that is not finite, or so large that the sum over the waves might not be (each may lie 2^8 above what
+    // references without slack give): once more from the start, with care (0 * x is NaN for exactly those)
     float zero = 0.0f;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) zero = fmaf(acc[mt][db][u], 0.0f, zero);
+            for (int u = 0; u < 4; ++u) zero = fmaf(acc[mt][db][u] * 0x1p14f, 0.0f, zero);
     if (__builtin_amdgcn_ballot_w64(!(zero == 0.0f)) != 0) {
         start();
 #pragma unroll 1

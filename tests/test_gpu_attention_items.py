@@ -91,6 +91,28 @@ def test_more_row_groups_than_workgroups(fsr, oracle, dtype, D, P, out_dtype):
         np.testing.assert_allclose(lse[:n].cpu().numpy(), lse_ref[:n], rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("dtype,D,P", [("f32", 64, 16), ("bf16", 64, 16), ("bf16", 128, 32)])
+@pytest.mark.parametrize("size", [1e37, 4e35])
+def test_values_near_the_end_of_the_range(fsr, oracle, dtype, D, P, size):
+    """Two keys of score 0 and 5 with large values among others of score -20 and ordinary values: an exponent's reference may
+    lag behind by 5.5, but a probability of e^5 must not meet such values (the result, about the value itself, is finite)."""
+    announce(f"items large values {dtype} D={D} {size}")
+    rng = np.random.Generator(np.random.PCG64(3))
+    ctx = [1000, 700]
+    x = make(rng, dtype, 4, 1, D, P, ctx, [0, 2])
+    code = (lambda a: np.asarray(a, np.float32)) if dtype == "f32" else (lambda a: (np.asarray(a, np.float32).view(np.uint32) >> 16).astype(np.uint16))
+    unit = np.zeros(D, np.float32)
+    unit[3] = np.sqrt(D)
+    x["q"][:] = code(unit / np.sqrt(D))
+    x["k"][:] = code(-20.0 * unit)
+    for i, c in enumerate(ctx):
+        for t, score in ((1, 0.0), (1 + 512 + i * 128, 5.0)):
+            x["k"][x["bt"][i, t // P], 0, t % P] = code(score * unit)
+            x["v"][x["bt"][i, t // P], 0, t % P] = code(rng.uniform(0.5, 1.0, D).astype(np.float32) * size)
+    out, _, ref, _ = run(fsr, oracle, x, dtype, 4, 1, D, P, hint=3)
+    check_attention(out, ref, "f32", len(ref))
+
+
 @pytest.mark.parametrize("dtype,D,shift,out_dtype", [("f32", 64, 1, torch.float32), ("bf16", 64, 1, torch.bfloat16),
                                                      ("bf16", 64, 3, torch.float32)])
 def test_inputs_aligned_to_their_elements_only(fsr, oracle, dtype, D, shift, out_dtype):
