@@ -104,14 +104,16 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor"):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _raw_stream() -> int:
-    """Handle of the current stream of the current device (torch.cuda.current_stream() builds a Python object around it
-    and costs ten times as much, which a call of a few microseconds notices)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _device_and_stream() -> tuple:
+    """The current device and the handle of its current stream (torch.cuda.current_stream() builds a Python object around
+    it and costs ten times as much, which a call of a few microseconds notices).  A handle alone does not name a stream:
+    the default stream's is 0 on every device."""
+    device = torch._C._cuda_getDevice()
+    return device, torch._C._cuda_getCurrentRawStream(device)
 
 
 def _stream():
-    return ctypes.c_void_p(_raw_stream())
+    return ctypes.c_void_p(_device_and_stream()[1])
 
 
 def _code(dt: torch.dtype) -> int:
@@ -187,7 +189,7 @@ def _guard_workspace(workspace):
     if workspace is None or torch.cuda.is_current_stream_capturing():
         return None
     key = workspace.data_ptr()
-    stream = _raw_stream()
+    stream = _device_and_stream()
     last = _ws_last_use.get(key)
     if last is not None and last[0] != stream and not last[1].query():
         raise FsrError(EWS, "this attention workspace is still in use by a call on another stream: "
