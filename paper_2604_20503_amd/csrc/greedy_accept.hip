@@ -2,17 +2,21 @@
 // an arg-max target.  A draft is accepted iff it is the arg-max token of its target row (lowest id
 // among equal maxima); the token after the accepted run is the arg-max of the next target row.
 //
-// The cost is one streaming pass over the target rows up to the first mismatch (4 V bytes each).  Row after row would put a
-// memory round trip per accepted draft on the critical path, all rows at once would read those behind the mismatch for
-// nothing; so the rows are started in the order of their positions, those of all requests' first drafts before any of a
-// second one, and a workgroup whose request is known to have a mismatch before its row leaves at once.  A mismatch is known
-// as soon as any workgroup of the row has met a score above the draft's own, long before the row is done.
+// The cost is one streaming pass over the target rows (4 V bytes each).  Row after row would put a memory round trip per
+// accepted draft on the critical path, so all rows are read at once; but a large call starts them in the order of their
+// positions, those of all requests' first drafts before any of a second one, and a workgroup whose request is known to have a
+// mismatch before its row leaves at once.  A mismatch is known as soon as any workgroup of the row has met a score above the
+// draft's own, long before the row is done.  A small call has most rows in flight before anything is known, and the asking
+// and telling costs it more than the rows (kSkipMinPieces).
 // greedy_argmax_kernel: every workgroup folds a 16 KB piece of a row into a 64-bit key (value made order-preserving << 32 |
 // ~index) and merges it into the row's key with one atomic max, which yields the largest value and, among equals, the
 // lowest index.
-// Measured, vocabulary 128256, 1-8 drafts of which about 40 % match, us a launch with all rows read / like this: 16 requests
-// 13.8 / 14.2, 64 requests 34.1 / 30.9, 128 requests 63.0 / 31.4, 384 requests 184 / 83.  Workgroups that go through a
-// request's positions one after the other read less but wait more: 39 us at 64 requests, 176 us at 384.
+// Measured, us a call (three launches in a graph), 1-8 drafts of which about 40 % match, all rows read / rows left out, by the
+// pieces the call can hold: vocabulary 152064: 32 requests (10.9 k) 24.0 / 25.4, 48 (16.4 k) 34.0 / 30.0, 128 81 / 38;
+// 128256: 16 requests 16.1 / 17.7, 48 (13.8 k) 28.9 / 31.4, 64 (18.4 k) 34.3 / 33.0, 256 123 / 60; 64000: 32 requests 13.2 /
+// 22.8, 96 (13.8 k) 27.4 / 29.0, 128 (18.4 k) 33.8 / 26.5; 32000: 64 requests 14.9 / 24.0, 192 (13.8 k) 28.6 / 27.7, 256
+// (18.4 k) 36.0 / 26.6.  Workgroups that go through a request's positions one after the other read less but wait more: 39 us
+// at 64 requests, 176 us at 384.
 #include <climits>
 #include <cstdint>
 
@@ -26,6 +30,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kChunk = 4096;  // scores of a piece
 constexpr int kQuads = kChunk / kThreads / 4;
+constexpr int kSkipMinPieces = 16384;  // pieces a call must be able to hold for rows behind a mismatch to be left out
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(4))) uint32_t gu32x4;  // at any element of a row
@@ -63,21 +68,31 @@ __global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long lon
     if (r < B) first_miss[r] = INT_MAX;
 }
 
-// grid (pieces, positions x requests): workgroup row y takes position y / B of request y % B
+// grid (pieces, B (S_max + 1)).  SKIP: workgroup row y takes position y / B of request y % B and leaves out what lies behind a
+// known mismatch; else it takes the call's row y.
+template <bool SKIP>
 __global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
     const float* __restrict__ target, const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ cu_t,
     const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
     unsigned long long* keys, int32_t* first_miss, int B, int V, int S_max, int R_cap) {
     __shared__ unsigned long long part[kThreads / 64];
     __shared__ int s_miss;
-    const int j = blockIdx.y / B, i = blockIdx.y - j * B;
-    const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
-    const int r = t0 + j;  // call-row on the target side
-    if (j >= t_i || r >= cu_t[B] || refused(t0, t_i, d_i, S_max, R_cap)) return;
-    if (j > 0) {  // one lane asks: the words of all requests lie in a few cache lines that every workgroup wants
-        if (threadIdx.x == 0) s_miss = __hip_atomic_load(first_miss + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (s_miss < j) return;
+    int r = blockIdx.y, i = 0, j = 0, d0 = 0, d_i = 0;  // r: call-row on the target side
+    if constexpr (SKIP) {
+        j = r / B;
+        i = r - j * B;
+        const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0;
+        d0 = cu_d[i];
+        d_i = cu_d[i + 1] - d0;
+        r = t0 + j;
+        if (j >= t_i || r >= cu_t[B] || refused(t0, t_i, d_i, S_max, R_cap)) return;
+        if (j > 0) {  // one lane asks: the words of all requests lie in a few cache lines that every workgroup wants
+            if (threadIdx.x == 0) s_miss = __hip_atomic_load(first_miss + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if (s_miss < j) return;
+        }
+    } else if (r >= cu_t[B]) {
+        return;
     }
     const float* z = target + (size_t)(t_rows ? t_rows[r] : r) * V;
     const int v0 = blockIdx.x * kChunk;
@@ -90,13 +105,22 @@ __global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
 #pragma unroll
         for (int q = 0; q < kQuads; ++q) {
             const int v = v0 + (q * kThreads + threadIdx.x) * 4;
+            if (v + 3 < V) x[q] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v));
+            else x[q] = u32x4{0xff800000u, 0xff800000u, 0xff800000u, 0xff800000u};
+        }
+        const int tail = V & ~3;  // (v0 is a multiple of four, so only the row's last quad is not whole)
+        if (tail < V && (tail - v0) / 4 % kThreads == (int)threadIdx.x) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[q][u] = v + u < V ? __builtin_bit_cast(uint32_t, z[v + u]) : 0xff800000u;
+            for (int q = 0; q < kQuads; ++q)
+                if (v0 + (q * kThreads + (int)threadIdx.x) * 4 == tail)
+#pragma unroll
+                    for (int u = 0; u < 3; ++u)
+                        if (tail + u < V) x[q][u] = __builtin_bit_cast(uint32_t, z[tail + u]);
         }
     }
     // the key of the draft this row verifies: larger than any if there is none, smaller for an id outside the vocabulary
     unsigned long long drafted = ~0ull;
-    if (d0 >= 0 && j < d_i && d0 + j < cu_d[B]) {
+    if (SKIP && d0 >= 0 && j < d_i && d0 + j < cu_d[B]) {
         const int t = draft_tokens[d_rows ? d_rows[d0 + j] : d0 + j];
         drafted = t < 0 || t >= V ? 0ull : make_key(__builtin_bit_cast(uint32_t, z[t]), t);
     }
@@ -118,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int w = 1; w < kThreads / 64; ++w) best = part[w] > best ? part[w] : best;
-        if (best > drafted) atomicMin(first_miss + i, j);
+        if (SKIP && best > drafted) atomicMin(first_miss + i, j);
         atomicMax(keys + r, best);
     }
 }
@@ -172,8 +196,10 @@ int greedy_accept_launch(const float* target, const int32_t* draft_tokens, const
     int rc;
     hipLaunchKernelGGL(greedy_init_kernel, dim3((R_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, keys, accepted_len, R_cap, p.B);
     if ((rc = check_launch("greedy_init_kernel")) != FSR_OK) return rc;
-    hipLaunchKernelGGL(greedy_argmax_kernel, dim3((p.V + kChunk - 1) / kChunk, R_cap), dim3(kThreads), 0, s, target, draft_tokens,
-                       cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
+    const int pieces = (p.V + kChunk - 1) / kChunk;
+    const bool skip = (long long)R_cap * pieces >= kSkipMinPieces;
+    hipLaunchKernelGGL(skip ? greedy_argmax_kernel<true> : greedy_argmax_kernel<false>, dim3(pieces, R_cap), dim3(kThreads), 0, s, target,
+                       draft_tokens, cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
     if ((rc = check_launch("greedy_argmax_kernel")) != FSR_OK) return rc;
     hipLaunchKernelGGL(greedy_decide_kernel, dim3((p.B + kThreads - 1) / kThreads), dim3(kThreads), 0, s, draft_tokens, cu_t,
                        cu_d, d_rows, keys, accepted_len, n_emitted, emitted, p.B, p.S_max, R_cap);

@@ -17,7 +17,9 @@ def fsr():
     return f
 
 
-@pytest.mark.parametrize("B,V,S", [(1, 4095, 70), (200, 4097, 8), (64, 30003, 6), (700, 100, 3)])
+# rows are left out from 16384 pieces on: B * (S + 1) rows of ceil(V / 4096) pieces
+@pytest.mark.parametrize("B,V,S", [(1, 4095, 70), (200, 4097, 8), (64, 30003, 6), (700, 100, 3),
+                                   (2500, 100, 7), (1100, 4097, 7), (64, 150001, 6), (2048, 20, 7), (2047, 20, 7)])
 def test_rows_behind_a_mismatch(fsr, oracle, B, V, S):
     announce(f"greedy skipping B={B} V={V} S={S}")
     rng = np.random.default_rng(V)
@@ -44,13 +46,17 @@ def test_rows_behind_a_mismatch(fsr, oracle, B, V, S):
             assert np.array_equal(t.cpu().numpy(), ref[name]), (name, match)
 
 
-def test_drafts_of_a_flagged_request_are_not_read(fsr):
+@pytest.mark.parametrize("B", [3, 16400])  # without and with rows left out
+def test_drafts_of_a_flagged_request_are_not_read(fsr, B):
     """S_max = 0 and no draft array: a request whose offsets claim a draft is flagged, the others get their arg-max."""
-    announce("greedy S_max=0 with a draft claimed")
-    V = 5000
-    z = np.random.default_rng(1).standard_normal((3, V)).astype(np.float32)
-    cu_t, cu_d = np.array([0, 1, 2, 3], np.int32), np.array([0, 0, 1, 1], np.int32)
-    acc, n, em = fsr.spec_accept(dev(z), None, None, None, None, dev(cu_t), dev(cu_d), S_max=0, mode=2)
+    announce(f"greedy S_max=0 with a draft claimed B={B}")
+    V = 501
+    z = np.random.default_rng(1).standard_normal((B, V)).astype(np.float32)
+    cu_d = np.zeros(B + 1, np.int32)
+    cu_d[2:] = 1
+    acc, n, em = fsr.spec_accept(dev(z), None, None, None, None, dev(np.arange(B + 1, dtype=np.int32)), dev(cu_d), S_max=0, mode=2)
     torch.cuda.synchronize()
-    assert acc.tolist() == [0, -1, 0] and n.tolist() == [1, -1, 1]
-    assert em[:, 0].tolist() == [int(z[0].argmax()), -1, int(z[2].argmax())]
+    want = z.argmax(1)
+    want[1] = -1
+    assert acc.tolist() == [0, -1] + [0] * (B - 2) and n.tolist() == [1, -1] + [1] * (B - 2)
+    assert np.array_equal(em[:, 0].cpu().numpy(), want)
