@@ -506,7 +506,7 @@ int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
 
 template <bool BF16, int D>
 int launch_mt(const ItemArgs& a, long long rows, bool bounded, hipStream_t s) {
-    constexpr int kMost = D == 64 ? 4 : 3;  // query tiles a wave holds without spilling
+    constexpr int kMost = D == 64 ? 4 : 3;  // query tiles a wave holds (three at D = 128 spill some 30 registers, outside the loops' sums)
     const int mt = (int)std::min<long long>(kMost, (rows + 15) / 16);
     // An item gets as many workgroups as its rows need groups, up to 64; each may take several, and one without rows leaves
     // at once.  Where the caller has not said how many rows a request has, one may have all of the call's, and the bound is

@@ -36,7 +36,7 @@ namespace {
 constexpr int kChunk = 4096;        // vocabulary tokens per chunk
 constexpr int kThreads = 256;       // threads per block in stats / partials / select
 constexpr int kPerThread = kChunk / kThreads;  // 16 contiguous tokens per thread in select
-constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (max, sum) pair
+constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (reference, sum) pair
 constexpr int kSkipMinRows = 2048;  // LOGITS mode: rows a call must be able to hold for rows behind a rejection to be left out
 constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
 constexpr int kMaxSampleGroup = 8;  // accept_sample: a workgroup takes 1, 2, 4 or 8 consecutive chunks (see launch_all)
@@ -47,7 +47,7 @@ enum : int { kCaseNone = 0, kCaseResidual = 1, kCaseTarget = 2 };
 struct Decision {
     long long t_row;  // storage row of the target distribution to sample from
     long long d_row;  // storage row of the draft distribution (residual case)
-    double m_t, Z_t;  // LOGITS mode: max and partition sum of the target row
+    double m_t, Z_t;  // LOGITS mode: exponent reference (at most kStatSlack below the maximum) and partition sum of the target row
     double m_d, Z_d;  // ... of the draft row
     int kind;         // kCase*
     int n;            // accepted drafts
@@ -60,7 +60,7 @@ struct Workspace {
     double* stat_t;      // [R_t_cap, n_stat_groups, 2]  (LOGITS)
     double* stat_d;      // [R_d_cap, n_stat_groups, 2]
     unsigned int* arrivals;  // [B] chunk workgroups of the request that have finished (zeroed by decide)
-    int stat_group;          // chunks per (max, sum) pair in this call (set at launch)
+    int stat_group;          // chunks per (reference, sum) pair in this call (set at launch)
     // LOGITS mode, while the statistics of a large call are made (the memory is that of the chunk masses, which come
     // later): 2 * n_chunks 32-bit words per request from mass_res on, word 0 the first rejected draft, word 1 + j the
     // workgroups that have finished rows j (accept_clear_kernel sets them up).  0: `decide` tests the drafts.
@@ -183,8 +183,8 @@ __device__ __forceinline__ ExpConsts exp_consts() {
     return k;
 }
 
-// exp(x) in fp64 for the arguments a softmax produces (x <= 0 after the row maximum is taken off; x up to a few
-// hundred works too; x below -745, -inf included, gives 0, and so does NaN: such a logit counts as masked).
+// exp(x) in fp64 for the arguments a softmax produces (x up to about 100 after the row's reference is taken off; a few
+// hundred work too; x below -745, -inf included, gives 0, and so does NaN: such a logit counts as masked).
 // x = k ln2 + r with |r| <= ln2 / 2: k by adding 1.5 * 2^52 to x log2(e), which rounds to the integer and leaves it
 // in the sum's low word; ln2 in two parts so that r is exact to the last bit; exp(r) by a polynomial of degree 10
 // (5e-16 relative); times 2^k by ldexp, which also makes the subnormal results and the final 0.  16 instructions,
@@ -285,8 +285,8 @@ __device__ __forceinline__ ExpConsts exp_consts_for() {
 }
 
 // Probability of one entry in fp64: the value itself, or exp(z / T - m) / Z with the two divisions as products
-// by 1 / T and 1 / Z (loop invariants the compiler hoists).  m is a maximum of values z * (1 / T) formed the same
-// way, so the row's largest entry gives exp(0) exactly.
+// by 1 / T and 1 / Z (loop invariants the compiler hoists).  m is a reference that the row's statistics have kept, at most
+// kStatSlack below the largest z / T, and Z the sum relative to the same m.
 template <int MODE>
 __device__ __forceinline__ double prob_of(float x, double T, double m, double Z, const ExpConsts& ek) {
     if constexpr (MODE == FSR_PROBS) {
@@ -306,7 +306,7 @@ __device__ __forceinline__ double fetch_f64(const double* p) {
                                                          __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// Combine a row's chunk statistics into (max, partition sum); all lanes of the wave call it.  FRESH: the statistics were
+// Combine a row's chunk statistics into (largest reference, partition sum relative to it); all lanes of the wave call it.  FRESH: the statistics were
 // made by other workgroups of this launch.
 template <bool FRESH>
 __device__ __forceinline__ void combine_stats(const double* __restrict__ stat, int nc, const ExpConsts& ek, double& m, double& Z) {
@@ -322,7 +322,7 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ stat, i
     Z = wave_sum(z);
 }
 // ---------------------------------------------------------------------------------------
-// LOGITS mode: per row and group of ws.stat_group chunks, the maximum of z / T and the sum of exp(z / T - max), fp64.
+// LOGITS mode: per row and group of ws.stat_group chunks, a reference and the sum of exp(z / T - reference), fp64.
 // grid = (n_stat_groups, (2 * S_max + 1) * B): workgroup row k * B + i takes, of request i, target row k / 2 for even k and
 // draft row k / 2 for odd k, so that the rows of the first drafts are all started before any row of a second draft.
 // Each lane keeps a reference (its first chunk's largest logit, replaced only by one far above it) and a sum relative to

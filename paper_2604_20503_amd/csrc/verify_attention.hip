@@ -403,10 +403,8 @@ __device__ __forceinline__ int share_of_block(int w, int n) {  // w < n workgrou
     return die * full + min(die, extra) + idx;
 }
 
-// Walks a share [x, x1) of the cost line and hands out its segments in order.  UNI: the walker runs
-// in all lanes of a wave alike (the attention kernel), so what it looks up is moved to scalar
-// registers; the plan kernel walks a different share in every lane.
-template <bool UNI>
+// A share [x, x1) of the cost line.  The attention kernel walks it segment by segment (next), all lanes of a wave alike, so
+// that what is looked up is moved to scalar registers; the plan kernel clips an item in every lane.
 struct ShareWalker {
     const long long* pref;
     const int* lds_cu;   // LDS copies of cu_q (B + 1 entries) and of max(ctx_lens, 0)
@@ -414,7 +412,6 @@ struct ShareWalker {
     long long x, x1, T, q;
     int nb, r, b, mt_max;
 
-    static __device__ __forceinline__ int uni(int v) { return UNI ? uniform(v) : v; }
     // nb shares of q or q + 1 units (the first r are the longer ones)
     __device__ void set_shares(long long total, int n) {
         T = total; nb = n;
@@ -428,7 +425,7 @@ struct ShareWalker {
         return min(bb, nb - 1);
     }
     // The part of item (gr, base) that the share owns from cost position `from` on: tile range, slot and pieces of
-    // sg.  False if that is no tile (phantom tiles only).
+    // sg.  False if that is no tile: phantom tiles only, or a share that ends inside the item's first tile.
     __device__ bool clip(const FastArgs& a, const Group& gr, long long base, long long from, Segment& sg) const {
         const long long iend = base + (long long)gr.nt * gr.cost;
         // tiles [xt_a, xt_e) of the item, phantom tiles included, are this share's
@@ -454,8 +451,8 @@ struct ShareWalker {
         while (x < x1) {
             // scalar loads (constant address space, uniform index): they must not queue behind the K/V
             // tile loads that are in flight while the next segment is being looked up
-            const int ri = uni(locate_request(pref, a.B, a.H_kv, x));
-            const int q0 = uni(lds_cu[ri]), q_len = uni(lds_cu[ri + 1]) - q0, c = uni(lds_ctx[ri]);
+            const int ri = uniform(locate_request(pref, a.B, a.H_kv, x));
+            const int q0 = uniform(lds_cu[ri]), q_len = uniform(lds_cu[ri + 1]) - q0, c = uniform(lds_ctx[ri]);
             // the KV head, then the row group, that hold position x
             const long long per_head = pref[ri + 1] - pref[ri], req_base = pref[ri] * a.H_kv;
             const int g = (int)div_u(x - req_base, per_head);
@@ -469,7 +466,7 @@ struct ShareWalker {
             const long long from = x;
             x = x1 >= iend ? iend : x1;
             if (clip(a, gr, base, from, sg)) {
-                sg.i = ri; sg.kvh = uni(g); sg.c = c; sg.q0 = q0; sg.q_len = q_len;
+                sg.i = ri; sg.kvh = uniform(g); sg.c = c; sg.q0 = q0; sg.q_len = q_len;
                 return true;
             }
         }
@@ -1231,7 +1228,7 @@ __global__ __launch_bounds__(kThreads) void attn_stream_kernel(FastArgs a) {
     const int cmax = build_cost_prefix<false>(a, MTMAX, pref, reinterpret_cast<long long*>(tables + scan_off(a.B)),
                                               reinterpret_cast<int*>(tables + cu_off(a.B)),
                                               reinterpret_cast<int*>(tables + ctx_off(a.B)), nullptr);
-    ShareWalker<true> wk;
+    ShareWalker wk;
     wk.pref = pref;
     wk.lds_cu = reinterpret_cast<const int*>(tables + cu_off(a.B));
     wk.lds_ctx = reinterpret_cast<const int*>(tables + ctx_off(a.B));
@@ -1303,7 +1300,7 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
     int* lds_cu = reinterpret_cast<int*>(smem + cu_off(a.B));
     int* lds_ctx = reinterpret_cast<int*>(smem + ctx_off(a.B));
     const int cmax = build_cost_prefix<true>(a, mt_max, pref, scratch, lds_cu, lds_ctx, gpref);
-    ShareWalker<false> wk;
+    ShareWalker wk;
     wk.pref = pref;
     wk.lds_cu = lds_cu;
     wk.lds_ctx = lds_ctx;
@@ -1358,7 +1355,7 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
             }
             if (base >= wk.x1) break;
             Segment sg;
-            // only the last item of a share can have no tile in it
+            // (only the last item of a share can have none)
             if (!wk.clip(a, gr, base, max(wk.x, base), sg)) break;
             sg.i = lo; sg.kvh = g; sg.c = c; sg.q0 = q0; sg.q_len = q_len;
             // more items than the capacity the host computes means offsets past N_cap: a share's count never exceeds the

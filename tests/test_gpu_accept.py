@@ -128,10 +128,10 @@ def test_logits_mode(fsr, oracle, T):
 @pytest.mark.parametrize("draft_mode", ["independent", "noise", "equal"])
 @pytest.mark.parametrize("T", [1.0, 0.8])
 def test_logits_mode_with_enough_rows_for_two_passes(fsr, oracle, draft_mode, T):
-    """A call with room for several thousand rows: the library normalises the rows of the first two drafts, tests them, and
-    reads the later rows only of the requests still undecided.  Requests rejected at draft 0, 1, 2 and later, requests
+    """A call with room for several thousand rows: rows behind a rejected draft are left out where they have not been started
+    by the time it is known.  Requests rejected at draft 0, 1, 2 and later, requests
     accepted whole, with 0, 1, 2 and 3 drafts, with and without a bonus row, and rows reached through maps."""
-    announce(f"accept LOGITS two passes {draft_mode} T={T}")
+    announce(f"accept LOGITS many rows {draft_mode} T={T}")
     B = 189
     spec = np.array(([0, 1, 2, 3, 4, 5, 6, 7, 8] * 21), np.int32)
     b = workloads.make_batch(2, rep=11, with_kv=False, V=33001, B=B, spec_lens=spec.tolist(), ctx_lens=[10] * B,

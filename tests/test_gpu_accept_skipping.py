@@ -101,3 +101,27 @@ def test_statistics_are_whole_or_left_out(fsr):
             err = (raw[:, 0] + torch.log(raw[:, 1]) - lse)[~untouched].abs()
             assert bool((err < 1e-12 * lse.abs().max()).all()), float(err.max())
     assert left_out > 0
+
+
+@pytest.mark.parametrize("steps", [(0, 130, 260, 390), (390, 260, 130, 0), (0, 95, 190, 90)])
+def test_logits_that_climb_far_above_a_reference(fsr, oracle, steps):
+    """Eight chunks a workgroup at most (4200 rows): from chunk to chunk a row's logits climb by more than the statistics let
+    an exponent grow (100), by less, or fall."""
+    announce(f"accept statistics steps={steps}")
+    B, V, T = 600, 4 * 4096, 0.7
+    spec = np.random.default_rng(5).integers(0, 4, size=B).astype(np.int32)
+    spec[0] = 3
+    b = batches(B, V, spec, 1)[0]
+    lift = (np.repeat(np.array(steps, np.float32), 4096) * T).astype(np.float32)
+    for z in (b.z_target, b.z_draft):
+        z += lift
+    best = int(np.argmax(steps)) * 4096
+    b.draft_tokens[::2] = best + b.draft_tokens[::2] % 4096  # drafts among the likely tokens and elsewhere
+    d = DeviceBatch(b, kv=False, logits=True)
+    ref = oracle.spec_accept(b.z_target, b.z_draft, b.draft_tokens, b.u_accept, b.u_sample, b.cu_q, b.cu_d, S_max=b.S_max, mode=1,
+                             temperature=T)
+    gpu = fsr.spec_accept(d.z_target, d.z_draft, d.draft_tokens, d.u_accept, d.u_sample, d.cu_q, d.cu_d, S_max=b.S_max, mode=1,
+                          temperature=T)
+    torch.cuda.synchronize()
+    check_accept(gpu, ref, b.u_sample)
+    assert 0 < ref["accepted_len"].sum() < spec.sum()

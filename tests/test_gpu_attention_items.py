@@ -75,6 +75,19 @@ def test_shapes_outside_the_stream_kernel(fsr, oracle, dtype, H_q, H_kv, D, P, t
         print(f"max rel err {err:.2e}")
 
 
+@pytest.mark.parametrize("H_q,H_kv,D,P,token_major", [(8, 2, 64, 16, False), (14, 2, 64, 24, True), (20, 1, 64, 1, False),
+                                                      (6, 6, 128, 32, False), (34, 2, 128, 16, True), (80, 1, 128, 16, False)])
+def test_bf16_output(fsr, oracle, H_q, H_kv, D, P, token_major):
+    """One to four query tiles, one and several row groups, page sizes and wide query groups, with the result in bf16."""
+    rng = np.random.Generator(np.random.PCG64(13 * H_q + D + P))
+    x = make(rng, "bf16", H_q, H_kv, D, P, CTX, SPEC)
+    for hint in (max(SPEC) + 1, 2, 0):
+        announce(f"items bf16 output heads={H_q}/{H_kv} D={D} P={P} token_major={token_major} hint={hint}")
+        out, lse, ref, lse_ref = run(fsr, oracle, x, "bf16", H_q, H_kv, D, P, token_major=token_major, out_dtype=torch.bfloat16, hint=hint)
+        check_attention(out, ref, "f32", len(ref))
+        np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("dtype,D,P,out_dtype", [("bf16", 64, 16, torch.bfloat16), ("bf16", 128, 8, torch.float32),
                                                  ("f32", 64, 16, torch.float32)])
 def test_more_row_groups_than_workgroups(fsr, oracle, dtype, D, P, out_dtype):
