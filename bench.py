@@ -165,7 +165,7 @@ def build_step(fsr, torch, b, n_layers, seed, cache_budget_bytes=16e9, use_plan=
         def append_kv8_only():
             fsr.kv_append_kv8(k_new, v_new, k8[0], v8[0], sc8, sc8, bt, ctx, cu_q)
 
-        # greedy acceptance (arg-max of every target row) and the restore of the compacted rows to their old places
+        # greedy acceptance (arg-max of the target rows) and the restore of the compacted rows to their old places
         ws_gr = torch.empty(max(256, fsr.accept_workspace_bytes(B=b.B, V=b.V, S_max=S_max, mode=2)), dtype=torch.uint8,
                             device="cuda")
         acc_g, nem_g, em_g = torch.empty_like(acc), torch.empty_like(nem), torch.empty_like(em)
@@ -186,7 +186,7 @@ def build_step(fsr, torch, b, n_layers, seed, cache_budget_bytes=16e9, use_plan=
     state = dict(q=q, k0=k0, v0=v0, out=out, acc=acc, nem=nem, em=em, prune=prune_out, packed=packed, variant_layers=extra_layers,
                  n_caches=n_caches, kv_bytes=kv_bytes, k_caches=k_caches, v_caches=v_caches,
                  dev=dict(bt=bt, ctx=ctx, spec=spec, cu_q=cu_q, cu_d=cu_d, p_t=p_t, p_d=p_d, toks=toks, u_a=u_a, u_s=u_s),
-                 calls=calls)
+                 calls=calls, acc_greedy=acc_g if variants else None)
     return step, attention_all_layers, tail, state
 
 
@@ -235,8 +235,11 @@ def kernel_figures(b, st, times_us):
         extra["kv_append"] = fig(times_us["kv_append"], 2 * rows_bytes, 1, "kv_append_kernel: the call's bf16 K and V rows in, the same bytes into the pages")
         extra["kv_append_kv8"] = fig(times_us["kv_append_kv8"], rows_bytes + rows_bytes // 2, 1,
                                      "kv_append8_kernel: bf16 rows in, E4M3 bytes into the pages")
-        extra["greedy_accept"] = fig(times_us["greedy_accept"], b.N * 4 * b.V + 4 * int(d.sum()), 3,
-                                     "greedy_init_kernel + greedy_argmax_kernel + greedy_decide_kernel: every target row of the call once")
+        # the rows up to the first mismatch (every request has its bonus row) have to be read
+        needed = int(st["acc_greedy"].sum().item()) + b.B
+        extra["greedy_accept"] = fig(times_us["greedy_accept"], needed * 4 * b.V + 4 * int(d.sum()), 3,
+                                     "greedy_init_kernel + greedy_argmax_kernel + greedy_decide_kernel: the rows up to each request's first "
+                                     f"mismatch; all target rows of the call (a small call reads them) are {b.N * 4 * b.V} bytes")
         extra["prune_restore"] = fig(times_us["prune_restore"], (n_new + b.N) * row_bytes + 5 * b.N, 1,
                                      "restore_rows_kernel: surviving rows back to their old places, filler elsewhere")
     return {
