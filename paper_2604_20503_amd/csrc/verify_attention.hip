@@ -99,15 +99,21 @@ __host__ __device__ constexpr int ctx_off(int B) { return cu_off(B) + (B + 4) * 
 __host__ __device__ constexpr int tables_bytes(int B) { return ctx_off(B) + (B + 4) * 4; }
 // Measured: a tile takes 2.0 / 2.4 / 2.5 us per wave with 1 / 2 / 3 query tiles riding on it (bandwidth, not the
 // matrix work, sets the pace), and taking up an item costs a workgroup 6 to 10 us of merge, count and refill.
-// Swept on four batches of the 16-request shape and on the 128- and 512-request shapes: base 3..6 with 12..20
-// phantom tiles is a plateau, 5 to 9 % under base 1 with 8.
+// Swept on four batches of the 16-request shape and on the 128- and 512-request shapes: base 3..6 with heads of 12..20
+// tiles is a plateau, 5 to 9 % under base 1 with 8.
 // With many items per workgroup the per-item costs average out and time follows the bytes, i.e. the tile count:
 // the 256- and 512-request shapes keep gaining up to base 16 (another 8 % and 5 %), while the 16-request shape,
 // where a workgroup holds one or two long items whose fixed costs grow with the query tiles, is best at 4.  The
 // host therefore sets the base to twice the items per workgroup, between kCostBase and kCostBaseMax.
 constexpr int kCostBase = 4;   // a tile costs cost_base + (16-row query tiles riding on it)
 constexpr int kCostBaseMax = 16;
-constexpr int kSegTiles = 16;  // what starting an item costs a workgroup (merge, refill), in tiles of that item
+constexpr int kSegTiles = 16;  // what starting an item costs a workgroup (merge, refill), in one team's tiles of that item
+// A tile that two teams take, in tiles of one team with as many query tiles: its four waves have two distinct tiles in
+// flight instead of four.  Measured per workgroup in a batch of both kinds (256 requests, 64/8 heads, 2 to 11 rows): 0.80
+// against 0.49 us a tile.  Counted by their query tiles alone, 22 to 19, workgroups with one-team items were done after
+// 480 us and others after 750; launch time for ratios of 1.2 / 1.4 / 1.5 / 1.6 / 1.7 / 1.85 / 2.0: 729 / 698 / 677 / 668 /
+// 674 / 682 / 710 us (738 before), 64 requests 190 -> 166 us, 8-bit caches, 128 requests, 373 -> 335 us.
+constexpr int kTwoTeamNum = 8, kTwoTeamDen = 5;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -134,8 +140,9 @@ struct FastArgs {
     float scale_log2;
     const float* k_scale;  // 8-bit caches: per KV head, cached key = decode(byte) * k_scale[head]; else unused
     const float* v_scale;  // the same for values
-    int cost_base;   // fixed part of a tile's cost (see tile_cost)
-    int seg_tiles;   // phantom tiles in front of every item on the cost line (see the schedule)
+    int cost_base;   // fixed part of a tile's cost (see group_at)
+    int seg_tiles;   // what taking up an item costs, in tiles that one team takes (see the schedule)
+    int two_cost;    // cost of a tile that two teams take
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -161,16 +168,19 @@ __device__ __forceinline__ int vtile_off(int key, int ch) { return key * 256 + (
 // mt_max / G positions), so that a group's accumulators fit the kernel's registers.  Nearly always
 // a request is one group.  Work is measured in cost units: a 32-key tile of a group costs
 // cost_base + (16-row query tiles riding on it), so that shares of equal cost take about equal
-// time whether a request has one suffix row or nine.  In front of its real tiles every item carries
-// seg_tiles phantom tiles: they stand for what it costs a workgroup to take up an item at all
-// (merging its waves, refilling the load pipeline), so a workgroup whose share spans an item
-// boundary is handed fewer real tiles than one that streams a single item throughout.
+// time whether a request has one suffix row or nine, or two_cost where two teams take it.  In front of
+// its tiles every item has a head that is as long as seg_tiles of one team's tiles: it stands for what
+// it costs a workgroup to take up an item at all (merging its waves, refilling the load pipeline), so a
+// workgroup whose share spans an item boundary is handed fewer tiles than one that streams a single
+// item throughout.
 // pref[i] = cost of the items of requests 0..i-1 for one KV head; on the flattened cost line the
 // request's items follow each other head by head, and inside a head group by group.
 // ---------------------------------------------------------------------------------------
 struct Group {
     int j0, rows_g;  // suffix positions j0 .. j0 + rows_g - 1 of the request
-    int nt, cost;    // tiles (phantom ones included) and cost of one tile
+    int nt, cost;    // key tiles and the cost of one
+    int head;        // cost of taking the group up, in front of its tiles
+    __device__ long long total() const { return head + (long long)nt * cost; }
 };
 
 // Group of request (context c, q_len rows) that starts at suffix position j0.
@@ -183,9 +193,10 @@ __device__ __forceinline__ Group group_at(const FastArgs& a, int mt_max, int c, 
     gr.j0 = j0;
     gr.rows_g = min(rows_per_group(a, mt_max), q_len - j0);
     const int visible = min(c + j0 + gr.rows_g, a.max_pages * kP);  // keys the group's last row sees
-    gr.nt = (visible + kTile - 1) / kTile + a.seg_tiles;
-    const int rows_a = min(gr.rows_g, per_team), rows_b = gr.rows_g - rows_a;
-    gr.cost = a.cost_base + min((a.G * rows_a + 15) >> 4, mt_max) + ((a.G * rows_b + 15) >> 4);
+    gr.nt = (visible + kTile - 1) / kTile;
+    const int one = a.cost_base + min((a.G * min(gr.rows_g, per_team) + 15) >> 4, mt_max);
+    gr.cost = gr.rows_g > per_team ? a.two_cost : one;
+    gr.head = a.seg_tiles * one;
     return gr;
 }
 
@@ -209,7 +220,7 @@ __device__ int build_cost_prefix(const FastArgs& a, int mt_max, long long* pref,
             lds_ctx[i] = c;
             for (int j0 = 0; j0 < ql; j0 += rows_per_group(a, mt_max)) {
                 const Group gr = group_at(a, mt_max, c, ql, j0);
-                units += (long long)gr.nt * gr.cost;
+                units += gr.total();
                 cmax = max(cmax, gr.cost);
                 ++groups;
             }
@@ -425,23 +436,21 @@ struct ShareWalker {
         return min(bb, nb - 1);
     }
     // The part of item (gr, base) that the share owns from cost position `from` on: tile range, slot and pieces of
-    // sg.  False if that is no tile: phantom tiles only, or a share that ends inside the item's first tile.
+    // sg.  False if that is no tile: a share that ends before the item's first tile does.
     __device__ bool clip(const FastArgs& a, const Group& gr, long long base, long long from, Segment& sg) const {
-        const long long iend = base + (long long)gr.nt * gr.cost;
-        // tiles [xt_a, xt_e) of the item, phantom tiles included, are this share's
-        const int xt_a = (int)div_u(from - base, gr.cost);
-        const int xt_e = x1 >= iend ? gr.nt : (int)div_u(x1 - base, gr.cost);
-        const int nt = gr.nt - a.seg_tiles, tile_a = max(xt_a - a.seg_tiles, 0), tile_e = max(xt_e - a.seg_tiles, 0);
+        const long long first = base + gr.head, iend = base + gr.total();
+        const int tile_a = from <= first ? 0 : (int)div_u(from - first, gr.cost);
+        const int tile_e = x1 >= iend ? gr.nt : x1 <= first ? 0 : (int)div_u(x1 - first, gr.cost);
         if (tile_e <= tile_a) return false;
         sg.j0 = gr.j0; sg.rows_g = gr.rows_g; sg.tile_a = tile_a; sg.tile_e = tile_e;
-        sg.final_out = tile_a == 0 && tile_e == nt;
+        sg.final_out = tile_a == 0 && tile_e == gr.nt;
         sg.slot = b * 2 + (tile_a > 0 ? 0 : 1);
         sg.cut = !sg.final_out;
         sg.b_first = sg.b_last = b;
         if (sg.cut) {
             // pieces of this item: the shares that own its first .. last tile; share bb owns
-            // tile k iff share_start(bb) < base + (k + 1) * cost <= share_start(bb + 1)
-            sg.b_first = owner_of(base + (long long)(a.seg_tiles + 1) * gr.cost);
+            // tile k iff share_start(bb) < first + (k + 1) * cost <= share_start(bb + 1)
+            sg.b_first = owner_of(first + gr.cost);
             sg.b_last = owner_of(iend);
         }
         return true;
@@ -458,11 +467,11 @@ struct ShareWalker {
             const int g = (int)div_u(x - req_base, per_head);
             long long base = req_base + g * per_head;
             Group gr = group_at(a, mt_max, c, q_len, 0);
-            while (x >= base + (long long)gr.nt * gr.cost && gr.j0 + gr.rows_g < q_len) {
-                base += (long long)gr.nt * gr.cost;
+            while (x >= base + gr.total() && gr.j0 + gr.rows_g < q_len) {
+                base += gr.total();
                 gr = group_at(a, mt_max, c, q_len, gr.j0 + gr.rows_g);
             }
-            const long long iend = base + (long long)gr.nt * gr.cost;
+            const long long iend = base + gr.total();
             const long long from = x;
             x = x1 >= iend ? iend : x1;
             if (clip(a, gr, base, from, sg)) {
@@ -1213,7 +1222,7 @@ __device__ __forceinline__ void finish_piece(const FastArgs& a, const Segment& s
 
 // Persistent grid: nb workgroups of 256 threads; the cost line [0, T) is cut into nb' = min(nb,
 // T / dearest tile) shares whose lengths differ by at most one unit, every workgroup takes one share.  A
-// share owns the tiles that END inside it (phantom tiles are owned and skipped).  An item that lies
+// share owns the tiles that END inside it.  An item that lies
 // inside one share is finished by that workgroup; an item cut by share boundaries leaves one
 // partial per piece, and the workgroup whose piece arrives last combines them (no workgroup ever
 // waits for another).
@@ -1331,8 +1340,8 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
             long long base = pref[ri] * a.H_kv + g * per_head;
             o0 = gpref[ri] * a.H_kv + g * (gpref[ri + 1] - gpref[ri]);
             Group gr = group_at(a, mt_max, c, q_len, 0);
-            while (wk.x >= base + (long long)gr.nt * gr.cost && gr.j0 + gr.rows_g < q_len) {
-                base += (long long)gr.nt * gr.cost;
+            while (wk.x >= base + gr.total() && gr.j0 + gr.rows_g < q_len) {
+                base += gr.total();
                 gr = group_at(a, mt_max, c, q_len, gr.j0 + gr.rows_g);
                 ++o0;
             }
@@ -1350,7 +1359,7 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
             long long base = pref[lo] * a.H_kv + g * (pref[lo + 1] - pref[lo]);
             Group gr = group_at(a, mt_max, c, q_len, 0);
             for (int k = rem - g * ng; k > 0; --k) {
-                base += (long long)gr.nt * gr.cost;
+                base += gr.total();
                 gr = group_at(a, mt_max, c, q_len, gr.j0 + gr.rows_g);
             }
             if (base >= wk.x1) break;
@@ -1555,6 +1564,7 @@ void fill_common(FastArgs& a, const fsr_attn_params* p, const Setup& su, const i
     a.nb = su.nb; a.m_cap = su.m_cap; a.wide = su.wide ? 1 : 0;
     a.seg_tiles = kSegTiles;
     a.cost_base = cost_base_for(*p, su);
+    a.two_cost = (a.cost_base + kWideMT) * kTwoTeamNum / kTwoTeamDen;
     a.plan = nullptr; a.plan_key = 0;
 }
 
