@@ -282,8 +282,9 @@ struct KVTile {
     bf16x8 k[2][4];
     s16x8 v[8];
 };
-// The same tile of an 8-bit cache: a key row is 128 bytes.  k[page][c]: key li of the page, the 16
-// bytes d = 64 c + 16 lg .. +15; v[r]: key 8 r + lane / 8 of the tile, the 16 bytes d = 16 (lane % 8) .. +15.
+// The same tile of an 8-bit cache: a key row is 128 bytes.  k[page][h]: key 8 h + li % 8 of the page, the 16 bytes
+// d = 64 (li / 8) + 16 lg .. +15 (whole rows per load; rows_to_operands turns the pair into key li, d = 64 c + 16 lg
+// .. +15); v[r]: key 8 r + lane / 8 of the tile, the 16 bytes d = 16 (lane % 8) .. +15.
 struct KVTile8 {
     u32x4 k[2][2];
     u32x4 v[4];
@@ -308,6 +309,19 @@ __device__ __forceinline__ void e4m3x16_to_bf16(u32x4 w, u32x4& first8, u32x4& n
     e4m3x4_to_bf16(w3, b2, b3);
     first8 = u32x4{a0, a1, a2, a3};
     next8 = u32x4{b0, b1, b2, b3};
+}
+
+// The pair of K loads of an 8-bit page, eight whole rows each, as the matrix operand's layout: lane (li, lg) of a load has
+// key 8 h + li % 8, half li / 8 of its row, and needs both halves of key li.  Lanes li < 8 take the second half of row li
+// from lane li + 8 of the first load, lanes li >= 8 the first half of row li from lane li - 8 of the second: one rotation
+// by eight lanes inside each sixteen, masked to the half that receives.
+__device__ __forceinline__ void rows_to_operands(const u32x4 (&rows)[2], u32x4 (&c)[2]) {
+    constexpr int kRowRor8 = 0x128;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        c[0][e] = (uint32_t)__builtin_amdgcn_update_dpp((int)rows[0][e], (int)rows[1][e], kRowRor8, 0xf, 0xc, false);
+        c[1][e] = (uint32_t)__builtin_amdgcn_update_dpp((int)rows[1][e], (int)rows[0][e], kRowRor8, 0xf, 0x3, false);
+    }
 }
 
 // What a workgroup processes between two merges: tiles [tile_a, tile_e) of item (i, kvh) for the
@@ -530,12 +544,12 @@ __device__ __forceinline__ void issue_tile(const FastArgs& a, const KVStream& sv
     gmem_char* vp0 = st.v_head + (size_t)pg0 * page_bytes;
     gmem_char* vp1 = st.v_head + (size_t)pg1 * page_bytes;
     if constexpr (KV8) {
-        const int kl = real ? li * ks + lg * 16 : 0;                  // K: key li, bytes 16 lg (+ 64 c)
-        const int vl = real ? (lane >> 3) * ks + (lane & 7) * 16 : 0;  // V: key lane / 8 (+ 8 per r), chunk lane % 8
+        const int kl = real ? (li & 7) * ks + (li >> 3) * 64 + lg * 16 : 0;  // K: key li % 8 (+ 8 h), bytes 64 (li / 8) + 16 lg
+        const int vl = real ? (lane >> 3) * ks + (lane & 7) * 16 : 0;        // V: key lane / 8 (+ 8 per r), chunk lane % 8
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            t.k[0][c] = tile_load<NT>((gmem_u32x4*)(kp0 + kl + 64 * c));
-            t.k[1][c] = tile_load<NT>((gmem_u32x4*)(kp1 + kl + 64 * c));
+        for (int h = 0; h < 2; ++h) {
+            t.k[0][h] = tile_load<NT>((gmem_u32x4*)(kp0 + kl + 8 * h * ks));
+            t.k[1][h] = tile_load<NT>((gmem_u32x4*)(kp1 + kl + 8 * h * ks));
         }
         t.v[0] = tile_load<NT>((gmem_u32x4*)(vp0 + vl));
         t.v[1] = tile_load<NT>((gmem_u32x4*)(vp0 + vl + 8 * ks));
@@ -698,14 +712,17 @@ __device__ void attend_segment(const FastArgs& a, const Segment& sg, const KVStr
                 *reinterpret_cast<u32x4*>(vbuf + v8_off[r] + 16) = hi8;
             }
 #pragma unroll
-            for (int pg = 0; pg < 2; ++pg)
+            for (int pg = 0; pg < 2; ++pg) {
+                u32x4 half[2];
+                rows_to_operands(t.k[pg], half);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     u32x4 lo8, hi8;
-                    e4m3x16_to_bf16(t.k[pg][c], lo8, hi8);
+                    e4m3x16_to_bf16(half[c], lo8, hi8);
                     kop[pg][2 * c] = __builtin_bit_cast(bf16x8, lo8);
                     kop[pg][2 * c + 1] = __builtin_bit_cast(bf16x8, hi8);
                 }
+            }
         } else {
             if (kb + kTile > kv_total) {  // slots past the request's last token may hold anything: zero them
 #pragma unroll
