@@ -3,17 +3,22 @@
 // building the set of the K best).
 //
 // The work is one pass over the score row of every draft that still has an active row: count the
-// scores strictly above the draft's own.  That is HBM streaming with a trivial reduction, so the
-// kernels are laid out for bandwidth: a grid of (32 KB piece of a row) x (draft), a piece's 16-byte loads all in flight
-// together (at any alignment: the hardware takes vectors at element addresses), one integer atomic per workgroup into the
-// draft's rank.  Measured, 1400 drafts x 128256 bf16 scores: 59.8 us; with 16 KB pieces, a loop over aligned loads and a
-// binary search for the draft's request 65 us.  The piece with the row's end too: one request x 32000 bf16 scores 7.4 us a
-// call, with a loop there 8.0.
-//
-//   rank_init_kernel    rank[d] = 0 for drafts with an active row and a valid token id, -1 for
-//                       drafts without a row, V for ids outside the vocabulary
-//   rank_count_kernel   rank[d] += #{v in chunk : z[row][v] > z[row][draft]}
-//   rank_mask_kernel    keep[row] from the ranks (first row of a request always kept)
+// scores strictly above the draft's own.  That is HBM streaming with a trivial reduction.
+//   rank_check_kernel   one launch, one workgroup per draft: it streams the row with 16-byte loads (at any alignment: the
+//                       hardware takes vectors at element addresses), the next four of every thread in flight while four
+//                       are counted, and writes the draft's rank and its row's mask itself.  Few drafts get the largest
+//                       workgroups, so that a compute unit has enough loads in flight with one or two of them, many drafts
+//                       small ones, so that all run at once.
+//   rank_init_kernel    rank[d] = 0 for drafts with an active row and a valid token id, -1 for drafts without a row, V for
+//                       ids outside the vocabulary;
+//   rank_count_kernel   rank[d] += #{v in chunk : z[row][v] > z[row][draft]}, grid (32 KB piece of a row) x (draft), a piece's
+//                       loads all in flight together, one integer atomic per workgroup;
+//   rank_mask_kernel    keep[row] from the ranks (first row of a request always kept): three launches, for a few hundred
+//                       drafts with long rows, where some compute units would have two rows to stream and others one (see
+//                       the rule at the launch).
+// Measured, kernel time of 1400 drafts x 128256 bf16 scores: 60.3 us; in three launches 4.2 + 59.3 + 4.8.
+// us a rank check, compaction and restore, one launch / three: 70 drafts x 128256 bf16 24.4 / 31.6, 576 x 32000 bf16 23.8 /
+// 30.4, 290 x 128256 fp32 41.0 / 38.7, 540 x 152063 fp32 71.5 / 71.5, 1100 x 128256 fp32 107 / 110, 2100 x 152064 fp32 213 / 217.
 #include <cstdint>
 
 #include "common.hpp"
@@ -22,11 +27,13 @@
 namespace fsr {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kLoads = 8;                           // 16-byte loads of a thread, all in flight together
-constexpr int kChunkBytes = kThreads * kLoads * 16;  // a workgroup's piece of a row
+constexpr int kLoads = 4;       // 16-byte loads of a thread that are counted together; as many more are in flight
+constexpr int kThreads = 256;   // of the three launches
+constexpr int kPieceLoads = 8;  // 16-byte loads of a thread, all in flight together
+constexpr int kChunkBytes = kThreads * kPieceLoads * 16;  // a workgroup's piece of a row
+constexpr long long kSplitMinBytes = 96LL << 20;  // score bytes from which a few hundred rows are cut into pieces
+constexpr int kMaskRows = 256;  // rows without a draft that one of the further workgroups looks after
 
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(2))) uint32_t gu32x4;  // at any element of a row
 
@@ -65,13 +72,6 @@ __device__ __forceinline__ int owner_by_wave(const int32_t* __restrict__ cu, int
     return lo;
 }
 
-// Score row of draft d, or -1 if the draft has no active row (its rows were pruned earlier).
-__device__ __forceinline__ int row_of_draft(const RankArgs& a, int d) {
-    const int i = owner(a.cu_d, a.B, d);
-    const int j = d - a.cu_d[i];
-    return j < a.cu_q[i + 1] - a.cu_q[i] ? a.cu_q[i] + j : -1;
-}
-
 template <typename T>
 __device__ __forceinline__ float score(const void* base, size_t idx);
 template <>
@@ -86,6 +86,13 @@ __device__ __forceinline__ float score<uint16_t>(const void* base, size_t idx) {
 // How many of the two bf16 scores packed in w exceed x.
 __device__ __forceinline__ int above_pair(uint32_t w, float x) {
     return (__builtin_bit_cast(float, w << 16) > x) + (__builtin_bit_cast(float, w & 0xffff0000u) > x);
+}
+
+// Score row of draft d, or -1 if the draft has no active row (its rows were pruned earlier).
+__device__ __forceinline__ int row_of_draft(const RankArgs& a, int d) {
+    const int i = owner(a.cu_d, a.B, d);
+    const int j = d - a.cu_d[i];
+    return j < a.cu_q[i + 1] - a.cu_q[i] ? a.cu_q[i] + j : -1;
 }
 
 __global__ __launch_bounds__(kThreads) void rank_init_kernel(RankArgs a) {
@@ -108,18 +115,18 @@ __global__ __launch_bounds__(kThreads) void rank_count_kernel(RankArgs a) {
     constexpr int kPer = 16 / sizeof(T);  // scores per 16-byte load
     const T* z = reinterpret_cast<const T*>(a.logits) + (size_t)row * a.V;
     const int v0 = blockIdx.x * (kChunkBytes / (int)sizeof(T));
-    u32x4 w[kLoads];
+    u32x4 w[kPieceLoads];
     const bool whole = a.V - v0 >= kChunkBytes / (int)sizeof(T);
     const int last = a.V - v0 - kPer;  // of the row's last piece: where its last whole load may start
     if (whole) {
 #pragma unroll
-        for (int k = 0; k < kLoads; ++k)  // a row is streamed once
+        for (int k = 0; k < kPieceLoads; ++k)  // a row is streamed once
             w[k] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v0 + (k * kThreads + threadIdx.x) * kPer));
     } else if (a.V >= kPer) {
         // loads past the row's end are moved back to its last whole one, so that all are unconditional and in flight
         // together here too, and what they bring is left out
 #pragma unroll
-        for (int k = 0; k < kLoads; ++k)
+        for (int k = 0; k < kPieceLoads; ++k)
             w[k] = *reinterpret_cast<const gu32x4*>(z + (v0 + min((k * kThreads + (int)threadIdx.x) * kPer, last)));
     }
     const float mine = score<T>(z, tok);
@@ -137,10 +144,10 @@ __global__ __launch_bounds__(kThreads) void rank_count_kernel(RankArgs a) {
     };
     if (whole) {
 #pragma unroll
-        for (int k = 0; k < kLoads; ++k) add(w[k]);
+        for (int k = 0; k < kPieceLoads; ++k) add(w[k]);
     } else {
 #pragma unroll
-        for (int k = 0; k < kLoads; ++k)
+        for (int k = 0; k < kPieceLoads; ++k)
             if ((k * kThreads + (int)threadIdx.x) * kPer <= last) add(w[k]);
     }
     const int tail = a.V - a.V % kPer + (int)threadIdx.x;  // (pieces are whole loads: what is left over ends the row's last one)
@@ -167,6 +174,91 @@ __global__ __launch_bounds__(kThreads) void rank_mask_kernel(RankArgs a) {
     a.keep[row] = keep;
 }
 
+// Workgroup d < D_cap: rank[d], and keep[row] of the row that carries the draft.  The workgroups behind those: keep = 1 for
+// the rows that carry no draft (a request's first row; rows past its last draft).
+template <typename T, int THREADS>
+__global__ __launch_bounds__(THREADS) void rank_check_kernel(RankArgs a) {
+    __shared__ int part[THREADS / 64];
+    if (blockIdx.x >= (unsigned)a.D_cap) {
+        const int row = (blockIdx.x - a.D_cap) * kMaskRows + threadIdx.x;
+        if (threadIdx.x >= kMaskRows || row >= a.N_cap || row >= a.cu_q[a.B]) return;
+        const int i = owner(a.cu_q, a.B, row);
+        const int j = row - a.cu_q[i];  // the row's input is draft j - 1 of the request
+        if (j < 1 || j - 1 >= a.cu_d[i + 1] - a.cu_d[i]) a.keep[row] = 1;
+        return;
+    }
+    const int d = blockIdx.x;
+    if (d >= a.cu_d[a.B]) return;
+    const int i = owner_by_wave(a.cu_d, a.B, d), j = d - a.cu_d[i];
+    const int q0 = a.cu_q[i], q1 = a.cu_q[i + 1];
+    const int row = j < q1 - q0 ? q0 + j : -1;
+    const int tok = a.draft_tokens[d];
+    // -1 without an active row (its rows were pruned earlier), V for an id outside the vocabulary, 0 for a row past N_cap
+    int rank = row < 0 ? -1 : (tok < 0 || tok >= a.V) ? a.V : 0;
+    if (rank == 0 && row < a.N_cap) {  // uniform for the workgroup
+        constexpr int kPer = 16 / sizeof(T);                 // scores per 16-byte load
+        constexpr int kPiece = THREADS * kLoads * kPer;      // scores the workgroup counts between two waits
+        const T* z = reinterpret_cast<const T*>(a.logits) + (size_t)row * a.V;
+        const float mine = score<T>(z, tok);
+        int count = 0;
+        auto add = [&](u32x4 x) {
+            // elements go to scalars first: __builtin_bit_cast applied to a vector-element expression was
+            // seen to read element 0 for every index
+            const uint32_t w0 = x[0], w1 = x[1], w2 = x[2], w3 = x[3];
+            if constexpr (sizeof(T) == 4) {
+                count += (__builtin_bit_cast(float, w0) > mine) + (__builtin_bit_cast(float, w1) > mine) +
+                         (__builtin_bit_cast(float, w2) > mine) + (__builtin_bit_cast(float, w3) > mine);
+            } else {
+                count += above_pair(w0, mine) + above_pair(w1, mine) + above_pair(w2, mine) + above_pair(w3, mine);
+            }
+        };
+        const int n_vec = a.V / kPer;  // whole loads of the row
+        u32x4 w[2][kLoads];
+        // loads past the row's last whole one are moved back to it, so that all are unconditional, and what they bring is
+        // left out
+        auto issue = [&](u32x4 (&x)[kLoads], int p) {
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k)  // a row is streamed once
+                x[k] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(
+                    z + (size_t)min(p * THREADS * kLoads + k * THREADS + (int)threadIdx.x, n_vec - 1) * kPer));
+        };
+        auto take = [&](const u32x4 (&x)[kLoads], int p) {
+            if ((p + 1) * THREADS * kLoads <= n_vec) {
+#pragma unroll
+                for (int k = 0; k < kLoads; ++k) add(x[k]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kLoads; ++k)
+                    if (p * THREADS * kLoads + k * THREADS + (int)threadIdx.x < n_vec) add(x[k]);
+            }
+        };
+        if (n_vec > 0) {
+            const int n_piece = (a.V + kPiece - 1) / kPiece;
+            issue(w[0], 0);
+            for (int p = 0; p < n_piece; p += 2) {
+                if (p + 1 < n_piece) issue(w[1], p + 1);
+                take(w[0], p);
+                if (p + 1 >= n_piece) break;
+                if (p + 2 < n_piece) issue(w[0], p + 2);
+                take(w[1], p + 1);
+            }
+        }
+        const int tail = n_vec * kPer + (int)threadIdx.x;
+        if (tail < a.V) count += score<T>(z, tail) > mine;  // (fewer than kPer scores)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, kWave);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = count;
+        __syncthreads();
+#pragma unroll
+        for (int w_ = 0; w_ < THREADS / 64; ++w_) rank += part[w_];
+    }
+    if (threadIdx.x == 0) {
+        a.rank[d] = rank;
+        const int own = q0 + j + 1;  // the row whose input the draft is
+        if (own < q1 && own < a.N_cap) a.keep[own] = rank < a.K ? 1 : 0;
+    }
+}
+
 }  // namespace
 }  // namespace fsr
 
@@ -189,13 +281,30 @@ extern "C" int fsr_topk_rank_check(const void* logits, const int32_t* draft_toke
     RankArgs a;
     a.logits = logits; a.draft_tokens = draft_tokens; a.cu_q = cu_q; a.cu_d = cu_d; a.rank = rank; a.keep = keep_mask;
     a.B = p->B; a.V = p->V; a.K = p->K; a.N_cap = p->N_cap; a.D_cap = p->D_cap;
-    if (p->D_cap > 0) {
+    const bool f32 = p->dtype == FSR_F32;
+    const long long bytes = (long long)p->D_cap * p->V * (f32 ? 4 : 2);
+    // Between one and two rows a compute unit, the units with two end the one launch late; from some 100 MB on that costs more
+    // than the two further launches (both sides measured at the top).
+    if (p->D_cap > 256 && p->D_cap < 512 && bytes >= kSplitMinBytes) {
         hipLaunchKernelGGL(rank_init_kernel, dim3((p->D_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
-        const int piece = kChunkBytes / (p->dtype == FSR_F32 ? 4 : 2);
-        const dim3 grid((p->V + piece - 1) / piece, p->D_cap);
-        if (p->dtype == FSR_F32) hipLaunchKernelGGL(rank_count_kernel<float>, grid, dim3(kThreads), 0, s, a);
-        else hipLaunchKernelGGL(rank_count_kernel<uint16_t>, grid, dim3(kThreads), 0, s, a);
+        const int piece = kChunkBytes / (f32 ? 4 : 2);
+        const dim3 pieces((p->V + piece - 1) / piece, p->D_cap);
+        if (f32) hipLaunchKernelGGL(rank_count_kernel<float>, pieces, dim3(kThreads), 0, s, a);
+        else hipLaunchKernelGGL(rank_count_kernel<uint16_t>, pieces, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(rank_mask_kernel, dim3((p->N_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
+        return check_launch("fsr_topk_rank_check");
     }
-    hipLaunchKernelGGL(rank_mask_kernel, dim3((p->N_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
+    const dim3 grid((unsigned)p->D_cap + (p->N_cap + kMaskRows - 1) / kMaskRows);
+    // workgroups of a size at which as many as there are drafts run at once (2048 threads a compute unit), if any
+    const int threads = p->D_cap <= 512 ? 1024 : p->D_cap <= 1024 ? 512 : 256;
+#define FSR_RANK(T) hipLaunchKernelGGL((T), grid, dim3(threads), 0, s, a)
+    if (threads == 1024) {
+        if (f32) FSR_RANK((rank_check_kernel<float, 1024>)); else FSR_RANK((rank_check_kernel<uint16_t, 1024>));
+    } else if (threads == 512) {
+        if (f32) FSR_RANK((rank_check_kernel<float, 512>)); else FSR_RANK((rank_check_kernel<uint16_t, 512>));
+    } else {
+        if (f32) FSR_RANK((rank_check_kernel<float, 256>)); else FSR_RANK((rank_check_kernel<uint16_t, 256>));
+    }
+#undef FSR_RANK
     return check_launch("fsr_topk_rank_check");
 }

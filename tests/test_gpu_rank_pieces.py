@@ -1,4 +1,5 @@
-"""Rank check at the edges of its pieces (8192 fp32 / 16384 bf16 scores) and of the wave's search for a draft's request
+"""Rank check at the edges of its pieces (8192 fp32 / 16384 bf16 scores; per workgroup size 4096 to 32768), of the workgroup
+sizes (512, 1024 drafts), of the rule that cuts rows into pieces (256 to 512 drafts, 96 MiB) and of the wave's search for a draft's request
 (64 requests, 64 x 64 requests, runs of requests without drafts), bit-exact against the oracle."""
 import numpy as np
 import pytest
@@ -11,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("B,V", [(1, 8192), (64, 8199), (65, 16384), (300, 16391), (4097, 33)])
+@pytest.mark.parametrize("B,V", [(1, 8192), (64, 8199), (65, 16384), (300, 16391), (4097, 33), (512, 4096), (700, 2051), (1024, 2047),
+                                 (330, 100003)])
 def test_pieces_and_search(oracle, B, V, dtype):
     import paper_2604_20503_amd as fsr
     announce(f"rank pieces B={B} V={V} {dtype}")
