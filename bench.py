@@ -246,9 +246,9 @@ def kernel_figures(b, st, times_us):
         **extra,
         "spec_accept": fig(times_us["accept"], accept_bytes, 2, "accept_decide_kernel + accept_sample_kernel"),
         "survivor_compact": fig(times_us["compact"], compact_bytes, 2,
-                                f"prune_scan_kernel + gather_rows_kernel; {n_new} of {b.N} rows of {row_bytes} bytes survive"),
+                                f"prune_compact_kernel; {n_new} of {b.N} rows of {row_bytes} bytes survive"),
         "topk_rank_check": fig(times_us["rank"], rank_bytes, 3,
-                               "rank_init + rank_count + rank_mask over the target rows, K = 10; not part of the timed step"),
+                               "rank check over the target rows, K = 10; not part of the timed step"),
     }
 
 

@@ -3,8 +3,11 @@
 // The ragged metadata of a verification batch is a few KB (B <= a few thousand requests,
 // N <= a few thousand rows), so the offsets and row maps are produced by ONE workgroup that
 // walks the requests in tiles of 1024 with a running carry: latency-bound, no inter-block
-// synchronisation.  The optional payload gather is the only part that moves real bytes and
-// runs as a separate grid over rows with 16-byte accesses.
+// synchronisation.  The optional payload gather is the only part that moves real bytes: its workgroups
+// (a window of output rows each) work the offsets out once more for themselves, which takes as long as
+// it takes the one that writes the maps, instead of waiting for that one in a second launch.
+#include <algorithm>
+
 #include "common.hpp"
 #include "device_utils.hpp"
 
@@ -14,98 +17,162 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 
-// Exclusive scan of one value per thread over the block; returns the exclusive prefix and
-// sets `total`.  smem must hold kScanThreads / 64 + 1 ints.
-__device__ __forceinline__ int block_exclusive_scan(int v, int* smem, int& total) {
+// Exclusive scan of one value per thread over the block; returns the exclusive prefix and sets `total`.  smem holds two
+// buffers of kScanThreads / 64 values; `turn` says which one is used (a buffer is written again two scans later at the
+// earliest, with a barrier in between).  Lanes move data by DPP and every wave adds up the waves before it for itself: one
+// barrier and no LDS round trips but one.
+__device__ __forceinline__ int dpp_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // lanes 1, 2, 4, 8 to the left in a row of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // lane 15 of a row to the next row
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // lane 31 to the upper half
+    return v;
+}
+__device__ __forceinline__ int block_exclusive_scan(int v, int (*smem)[kScanThreads / 64], int& turn, int& total) {
+    constexpr int kW = kScanThreads / 64;
+    static_assert(kW == 16, "the waves' sums are one row of lanes");
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int inc = wave_inclusive_scan(v);
-    if (lane == 63) smem[w] = inc;
+    const int inc = dpp_inclusive_scan(v);
+    int* sums = smem[turn];
+    turn ^= 1;
+    if (lane == 63) sums[w] = inc;
     __syncthreads();
-    if (w == 0) {
-        int s = lane < (kScanThreads / 64) ? smem[lane] : 0;
-        int si = wave_inclusive_scan(s);
-        if (lane < (kScanThreads / 64)) smem[lane] = si - s;
-        if (lane == (kScanThreads / 64) - 1) smem[kScanThreads / 64] = si;
-    }
-    __syncthreads();
-    const int base = smem[w];
-    total = smem[kScanThreads / 64];
-    __syncthreads();
+    const int before = dpp_inclusive_scan(lane < kW ? sums[lane] : 0);
+    total = __builtin_amdgcn_readlane(before, kW - 1);
+    const int wu = __builtin_amdgcn_readfirstlane(w);
+    const int base = wu > 0 ? __builtin_amdgcn_readlane(before, max(wu - 1, 0)) : 0;
     return base + inc - v;
 }
 
-// keep: the mask; or, when accepted_len is given instead, request i keeps its rows 0 .. accepted_len[i]
-// (the survivors of an accept step; always suffix-closed) and keep_out, if not null, receives that mask.
-__global__ __launch_bounds__(kScanThreads) void prune_scan_kernel(
-    const uint8_t* __restrict__ keep, const int32_t* __restrict__ accepted_len, uint8_t* __restrict__ keep_out,
-    const int32_t* __restrict__ cu_q, int32_t* __restrict__ new_cu_q,
-    int32_t* __restrict__ new_q_lens, int32_t* __restrict__ src_row, int32_t* __restrict__ dst_row,
-    int32_t* __restrict__ n_active, int32_t* __restrict__ active_ids, int B, int N_cap, int suffix_close) {
-    __shared__ int smem[kScanThreads / 64 + 1];
+// Whether rows r0 .. r1 - 1 (mask bytes) are kept; the bytes of eight rows are sent for together.
+template <typename F>
+__device__ __forceinline__ void for_kept(const uint8_t* __restrict__ keep, int r0, int r1, F&& f) {
+    for (int r = r0; r < r1; r += 8) {
+        uint8_t k[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) k[u] = keep[min(r + u, r1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (r + u < r1) f(r + u, k[u] != 0);
+    }
+}
+
+struct CompactArgs {
+    // keep: the mask; or, when accepted_len is given instead, request i keeps its rows 0 .. accepted_len[i]
+    // (the survivors of an accept step; always suffix-closed) and keep_out, if not null, receives that mask.
+    const uint8_t* keep;
+    const int32_t* accepted_len;
+    uint8_t* keep_out;
+    const int32_t* cu_q;
+    int32_t* new_cu_q;
+    int32_t* new_q_lens;
+    int32_t* src_row;
+    int32_t* dst_row;
+    int32_t* n_active;
+    int32_t* active_ids;
+    int B, N_cap, suffix_close;
+    const void* in;  // payload rows of row_vecs vectors, or null
+    void* out;
+    size_t row_vecs;
+    int window;      // output rows of a copying workgroup
+};
+
+constexpr int kMaxWindow = 4096;
+constexpr int kMinWindow = 8;
+constexpr int kCopyGroups = 511;  // copying workgroups a call is cut into at most: as many as run at once, with the maps' own
+
+// Workgroup 0 writes the maps; workgroup 1 + k copies the output rows k * window .. of the payload.
+template <typename VecT>
+__global__ __launch_bounds__(kScanThreads) void prune_compact_kernel(CompactArgs a) {
+    __shared__ int smem[2][kScanThreads / 64];
+    int turn = 0;
+    __shared__ int src_of[kMaxWindow];  // input row of the window's output rows
+    const bool maps = blockIdx.x == 0;
+    const long long lo = maps ? 0 : (long long)(blockIdx.x - 1) * a.window;  // (N_cap < 2^31: past the end it may exceed an int)
+    const int B = a.B, N_cap = a.N_cap;
     int row_carry = 0, act_carry = 0;
-    const int N = B > 0 ? min(max(cu_q[B], 0), N_cap) : 0;
+    const int N = B > 0 ? min(max(a.cu_q[B], 0), N_cap) : 0;
+    if (lo > N) return;
     for (int base = 0; base < B; base += kScanThreads) {
         const int i = base + threadIdx.x;
         int kept = 0, r0 = 0, r1 = 0;
         if (i < B) {
-            r0 = min(max(cu_q[i], 0), N_cap);  // offsets beyond the allocated rows are cut off
-            r1 = min(max(cu_q[i + 1], r0), N_cap);
-            if (accepted_len) {
-                kept = min(max(accepted_len[i] + 1, 0), r1 - r0);
-            } else if (suffix_close) {
-                int r = r0;
-                while (r < r1 && keep[r] != 0) ++r;
-                kept = r - r0;
+            r0 = min(max(a.cu_q[i], 0), N_cap);  // offsets beyond the allocated rows are cut off
+            r1 = min(max(a.cu_q[i + 1], r0), N_cap);
+            if (a.accepted_len) {
+                kept = min(max(a.accepted_len[i] + 1, 0), r1 - r0);
             } else {
-                for (int r = r0; r < r1; ++r) kept += keep[r] != 0;
+                bool open = true;  // suffix_close: no row so far was dropped
+                for_kept(a.keep, r0, r1, [&](int, bool k) {
+                    kept += k && open;
+                    open = open && (k || !a.suffix_close);
+                });
             }
         }
-        int tile_rows, tile_act;
-        const int off = row_carry + block_exclusive_scan(kept, smem, tile_rows);
-        const int aoff = act_carry + block_exclusive_scan(kept > 0 ? 1 : 0, smem, tile_act);
-        if (i < B) {
-            new_cu_q[i] = off;
-            new_q_lens[i] = kept;
-            if (kept > 0) active_ids[aoff] = i;
+        int tile_rows, tile_act = 0;
+        const int off = row_carry + block_exclusive_scan(kept, smem, turn, tile_rows);
+        if (maps) {
+            const int aoff = act_carry + block_exclusive_scan(kept > 0 ? 1 : 0, smem, turn, tile_act);
+            if (i < B) {
+                a.new_cu_q[i] = off;
+                a.new_q_lens[i] = kept;
+                if (kept > 0) a.active_ids[aoff] = i;
+            }
+        }
+        const bool wanted = i < B && (maps || (off < lo + a.window && off + kept > lo));
+        if (wanted) {
             int o = off;
-            for (int r = r0; r < r1; ++r) {
-                const bool k = suffix_close ? (r - r0 < kept) : (keep[r] != 0);
-                if (keep_out) keep_out[r] = k ? 1 : 0;
-                if (k) {
-                    src_row[o] = r;
-                    dst_row[r] = o;
-                    ++o;
-                } else {
-                    dst_row[r] = -1;
+            auto put = [&](int r, bool k) {
+                if (maps) {
+                    if (a.keep_out) a.keep_out[r] = k ? 1 : 0;
+                    if (k) a.src_row[o] = r;
+                    a.dst_row[r] = k ? o : -1;
+                } else if (k && o >= lo && o < lo + a.window) {
+                    src_of[o - lo] = r;
                 }
+                o += k;
+            };
+            if (a.accepted_len || a.suffix_close) {
+                for (int r = r0; r < r1; ++r) put(r, r - r0 < kept);
+            } else {
+                for_kept(a.keep, r0, r1, put);
             }
         }
         row_carry += tile_rows;
         act_carry += tile_act;
+        if (!maps && row_carry >= lo + a.window) break;  // the window is complete
     }
-    if (threadIdx.x == 0) {
-        new_cu_q[B] = row_carry;
-        n_active[0] = act_carry;
+    if (maps) {
+        if (threadIdx.x == 0) {
+            a.new_cu_q[B] = row_carry;
+            a.n_active[0] = act_carry;
+        }
+        for (int r = row_carry + threadIdx.x; r < N_cap; r += kScanThreads) a.src_row[r] = -1;
+        for (int r = N + threadIdx.x; r < N_cap; r += kScanThreads) a.dst_row[r] = -1;
+        for (int k = act_carry + threadIdx.x; k < B; k += kScanThreads) a.active_ids[k] = -1;
+        return;
     }
-    for (int r = row_carry + threadIdx.x; r < N_cap; r += kScanThreads) src_row[r] = -1;
-    for (int r = N + threadIdx.x; r < N_cap; r += kScanThreads) dst_row[r] = -1;
-    for (int a = act_carry + threadIdx.x; a < B; a += kScanThreads) active_ids[a] = -1;
-}
-
-// payload_out[r'] = payload_in[src_row[r']] for r' < n_new[0]; one block per output row slice.
-template <typename VecT>
-__global__ __launch_bounds__(256) void gather_rows_kernel(const VecT* __restrict__ in, VecT* __restrict__ out,
-                                                          const int32_t* __restrict__ src_row,
-                                                          const int32_t* __restrict__ n_new, size_t row_vecs,
-                                                          int N_cap) {
-    const int n = min(n_new[0], N_cap);
-    for (int r = blockIdx.x; r < n; r += gridDim.x) {
-        const int s = src_row[r];
-        if (s < 0 || s >= N_cap) continue;
-        const VecT* src = in + (size_t)s * row_vecs;
-        VecT* dst = out + (size_t)r * row_vecs;
-        for (size_t v = (size_t)blockIdx.y * blockDim.x + threadIdx.x; v < row_vecs; v += (size_t)gridDim.y * blockDim.x)
-            dst[v] = src[v];
+    __syncthreads();
+    const int n = (int)min(max(min(row_carry, N_cap) - lo, 0LL), (long long)a.window);
+    // a wave takes pieces of four vectors a lane, all in flight together
+    constexpr int kPer = 4, kPiece = 64 * kPer, kWavesCopy = kScanThreads / 64;
+    const size_t pieces = (a.row_vecs + kPiece - 1) / kPiece;
+    const int lane = threadIdx.x & 63;
+    for (size_t u = threadIdx.x >> 6; u < (size_t)n * pieces; u += kWavesCopy) {
+        const size_t r = u / pieces, v0 = (u - r * pieces) * kPiece + lane;
+        const VecT* src = reinterpret_cast<const VecT*>(a.in) + (size_t)src_of[r] * a.row_vecs;
+        VecT* dst = reinterpret_cast<VecT*>(a.out) + (size_t)(lo + r) * a.row_vecs;
+        if (v0 - lane + kPiece <= a.row_vecs) {
+            VecT x[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) x[e] = src[v0 + 64 * e];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) dst[v0 + 64 * e] = x[e];
+        } else {
+            for (size_t v = v0; v < a.row_vecs; v += 64) dst[v] = src[v];
+        }
     }
 }
 
@@ -240,22 +307,21 @@ int compact_call(const char* who, const uint8_t* keep_mask, const int32_t* accep
     if (payload_in && (row_bytes == 0 || row_bytes % 4 != 0)) return fail(FSR_ESHAPE, "%s: row_bytes=%zu must be a positive multiple of 4", who, row_bytes);
     if (payload_in && payload_in == payload_out) return fail(FSR_EINVAL, "%s: payload gather cannot run in place", who);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(prune_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, keep_mask, accepted_len, keep_out, cu_q, new_cu_q,
-                       new_q_lens, src_row, dst_row, n_active, active_ids, p->B, p->N_cap, accepted_len ? 1 : p->suffix_close);
-    int rc = check_launch("prune_scan_kernel");
-    if (rc != FSR_OK) return rc;
-    if (payload_in && p->N_cap > 0) {
-        const int N_cap = p->N_cap;
-        rc = launch_by_width(row_bytes, payload_in, payload_out, [&](auto tag, size_t row_vecs) {
-            using VecT = decltype(tag);
-            const unsigned gy = (unsigned)std::min<size_t>(std::max<size_t>(1, (row_vecs + 255) / 256), 64);
-            const unsigned gx = (unsigned)std::min(N_cap, 65535);
-            hipLaunchKernelGGL(gather_rows_kernel<VecT>, dim3(gx, gy), dim3(256), 0, s, (const VecT*)payload_in,
-                               (VecT*)payload_out, src_row, new_cu_q + p->B, row_vecs, N_cap);
-            return check_launch("gather_rows_kernel");
-        });
+    CompactArgs a{keep_mask, accepted_len, keep_out, cu_q, new_cu_q, new_q_lens, src_row, dst_row, n_active, active_ids, p->B, p->N_cap,
+                  accepted_len ? 1 : p->suffix_close, nullptr, nullptr, 0, 0};
+    if (!payload_in || p->N_cap == 0) {
+        hipLaunchKernelGGL(prune_compact_kernel<uint32_t>, dim3(1), dim3(kScanThreads), 0, s, a);
+        return check_launch("prune_compact_kernel");
     }
-    return rc;
+    a.in = payload_in;
+    a.out = payload_out;
+    a.window = std::min(std::max(kMinWindow, p->N_cap / kCopyGroups + 1), kMaxWindow);
+    return launch_by_width(row_bytes, payload_in, payload_out, [&](auto tag, size_t row_vecs) {
+        using VecT = decltype(tag);
+        a.row_vecs = row_vecs;
+        hipLaunchKernelGGL(prune_compact_kernel<VecT>, dim3(1 + (p->N_cap - 1) / a.window + 1), dim3(kScanThreads), 0, s, a);
+        return check_launch("prune_compact_kernel");
+    });
 }
 }  // namespace
 

@@ -46,6 +46,29 @@ def _compare(fsr, oracle, keep, cu, suffix_close, pay, N_cap):
     assert np.array_equal(base.cpu().numpy(), exp)
 
 
+@pytest.mark.parametrize("width", [4, 1023, 1024, 1028, 1025])  # words: 16-byte rows, one vector short of, exactly and past a lane's four
+@pytest.mark.parametrize("B,maxlen", [(1, 8), (1025, 5), (1500, 9)])  # one window; a second tile of requests; windows of more than 8 rows
+def test_survivor_windows(fsr, oracle, B, maxlen, width):
+    announce(f"survivor_windows B={B} width={width}")
+    rng = np.random.default_rng(B + width)
+    lens = rng.integers(1, maxlen + 1, size=B)
+    acc = np.minimum(rng.integers(-1, maxlen, size=B), lens - 1).astype(np.int32)
+    cu = workloads.exclusive_offsets(lens)
+    N = int(cu[-1])
+    keep = np.concatenate([np.arange(n) <= a for n, a in zip(lens, acc)]).astype(np.uint8)
+    pay = rng.integers(-1000, 1000, size=(N, width)).astype(np.int32)
+    ref = oracle.prune_compact(keep, cu, suffix_close=True, payload=pay)
+    mask = dev(np.full(N, 7, np.uint8))
+    r = fsr.survivor_compact(dev(acc), dev(cu), N, keep_mask=mask, payload=dev(pay), payload_out=torch.full((N, width), -7, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    n_new = int(ref["new_cu_q"][-1])
+    for name in ("new_cu_q", "new_q_lens", "src_row", "dst_row", "active_ids"):
+        assert np.array_equal(r[name].cpu().numpy(), ref[name]), name
+    assert np.array_equal(mask.cpu().numpy(), keep)
+    got = r["payload"].cpu().numpy()
+    assert np.array_equal(got[:n_new], ref["payload"]) and (got[n_new:] == -7).all()
+
+
 @pytest.mark.parametrize("suffix_close", [True, False])
 @pytest.mark.parametrize("seed,B,maxlen,width", [(0, 1, 5, 4), (1, 37, 9, 6), (2, 512, 11, 64), (3, 2500, 4, 3), (4, 300, 0, 4)])
 def test_prune_random(fsr, oracle, suffix_close, seed, B, maxlen, width):
