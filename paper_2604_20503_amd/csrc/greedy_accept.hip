@@ -8,15 +8,16 @@
 // mismatch before its row leaves at once.  A mismatch is known as soon as any workgroup of the row has met a score above the
 // draft's own, long before the row is done.  A small call has most rows in flight before anything is known, and the asking
 // and telling costs it more than the rows (kSkipMinPieces).
-// greedy_argmax_kernel: every workgroup folds a 16 KB piece of a row into a 64-bit key (value made order-preserving << 32 |
-// ~index) and merges it into the row's key with one atomic max, which yields the largest value and, among equals, the
-// lowest index.
-// Measured, us a call (three launches in a graph), 1-8 drafts of which about 40 % match, all rows read / rows left out, by the
-// pieces the call can hold: vocabulary 152064: 32 requests (10.9 k) 24.0 / 25.4, 48 (16.4 k) 34.0 / 30.0, 128 81 / 38;
-// 128256: 16 requests 16.1 / 17.7, 48 (13.8 k) 28.9 / 31.4, 64 (18.4 k) 34.3 / 33.0, 256 123 / 60; 64000: 32 requests 13.2 /
-// 22.8, 96 (13.8 k) 27.4 / 29.0, 128 (18.4 k) 33.8 / 26.5; 32000: 64 requests 14.9 / 24.0, 192 (13.8 k) 28.6 / 27.7, 256
-// (18.4 k) 36.0 / 26.6.  Workgroups that go through a request's positions one after the other read less but wait more: 39 us
-// at 64 requests, 176 us at 384.
+// greedy_argmax_kernel: every workgroup finds the largest score of a 64 KB piece of a row and its lowest place, and merges them
+// as a 64-bit key (value made order-preserving << 32 | ~index) into the row's key with one atomic max, which yields the largest
+// value and, among equals, the lowest index.  Pieces of 64 KB: most workgroups of a large call are those of rows that are left
+// out, and each costs two memory round trips before it may leave.
+// Measured, us a call with the compaction behind it, 1-8 drafts of which about 40 % match, all rows read / rows left out, by the
+// pieces the call can hold: vocabulary 128256: 32 requests (2304) 27 / 30, 64 (4608) 43 / 36; 32000: 192 requests (3456) 34.5 /
+// 32.3; 152064: 128 requests (11520) 79 / 47; 128256: 384 requests (30720) 209 / 88.  With 16 KB pieces of 256 threads: 64
+// requests 39.8, 128 requests 46.3, 384 requests 107.  At 64 requests 50 MB are read: what is left is the chain of workgroups,
+// not the bytes.  Workgroups that go through a request's positions one after the other read less but wait more: 45 us at 64
+// requests, 139 us at 384.
 #include <climits>
 #include <cstdint>
 
@@ -28,9 +29,10 @@ namespace fsr {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kChunk = 4096;  // scores of a piece
-constexpr int kQuads = kChunk / kThreads / 4;
-constexpr int kSkipMinPieces = 16384;  // pieces a call must be able to hold for rows behind a mismatch to be left out
+constexpr int kRowThreads = 512;                  // threads that take a piece of a row
+constexpr int kQuads = 8;                         // 16-byte loads of such a thread, all in flight together
+constexpr int kChunk = kRowThreads * kQuads * 4;  // scores of a piece
+constexpr int kSkipMinPieces = 3072;  // pieces a call must be able to hold for rows behind a mismatch to be left out
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(4))) uint32_t gu32x4;  // at any element of a row
@@ -45,16 +47,6 @@ __device__ __forceinline__ uint32_t ordered_bits(uint32_t b) {
 __device__ __forceinline__ unsigned long long make_key(uint32_t bits, int idx) {
     return ((unsigned long long)ordered_bits(bits) << 32) | (uint32_t)(0xffffffffu - (uint32_t)idx);
 }
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)k, o, kWave), hi = __shfl_xor((uint32_t)(k >> 32), o, kWave);
-        const unsigned long long other = ((unsigned long long)hi << 32) | lo;
-        k = other > k ? other : k;
-    }
-    return k;
-}
-
 // A request whose row counts do not fit the call is flagged by `decide`; none of its rows or drafts is looked at (a call with
 // S_max = 0 has no drafts to read: draft_tokens may be null).
 __device__ __forceinline__ bool refused(int t0, int t_i, int d_i, int S_max, int R_cap) {
@@ -68,80 +60,111 @@ __global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long lon
     if (r < B) first_miss[r] = INT_MAX;
 }
 
-// grid (pieces, B (S_max + 1)).  SKIP: workgroup row y takes position y / B of request y % B and leaves out what lies behind a
-// known mismatch; else it takes the call's row y.
-template <bool SKIP>
-__global__ __launch_bounds__(kThreads) void greedy_argmax_kernel(
-    const float* __restrict__ target, const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ cu_t,
-    const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
-    unsigned long long* keys, int32_t* first_miss, int B, int V, int S_max, int R_cap) {
-    __shared__ unsigned long long part[kThreads / 64];
-    __shared__ int s_miss;
-    int r = blockIdx.y, i = 0, j = 0, d0 = 0, d_i = 0;  // r: call-row on the target side
-    if constexpr (SKIP) {
-        j = r / B;
-        i = r - j * B;
-        const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0;
-        d0 = cu_d[i];
-        d_i = cu_d[i + 1] - d0;
-        r = t0 + j;
-        if (j >= t_i || r >= cu_t[B] || refused(t0, t_i, d_i, S_max, R_cap)) return;
-        if (j > 0) {  // one lane asks: the words of all requests lie in a few cache lines that every workgroup wants
-            if (threadIdx.x == 0) s_miss = __hip_atomic_load(first_miss + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            if (s_miss < j) return;
-        }
-    } else if (r >= cu_t[B]) {
-        return;
-    }
-    const float* z = target + (size_t)(t_rows ? t_rows[r] : r) * V;
-    const int v0 = blockIdx.x * kChunk;
-    u32x4 x[kQuads];
+typedef u32x4 Piece[kQuads];  // a thread's scores of a piece: quads q * kRowThreads + thread
+
+// Send for the scores v0 .. v0 + kChunk - 1 of row z.
+__device__ __forceinline__ void load_piece(const float* __restrict__ z, int v0, int V, Piece& x) {
     if (v0 + kChunk <= V) {
 #pragma unroll
         for (int q = 0; q < kQuads; ++q)  // a row is streamed once
-            x[q] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v0 + (q * kThreads + threadIdx.x) * 4));
+            x[q] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v0 + (q * kRowThreads + threadIdx.x) * 4));
     } else {  // past the end: minus infinity at an index that loses against every token
 #pragma unroll
         for (int q = 0; q < kQuads; ++q) {
-            const int v = v0 + (q * kThreads + threadIdx.x) * 4;
+            const int v = v0 + (q * kRowThreads + threadIdx.x) * 4;
             if (v + 3 < V) x[q] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v));
             else x[q] = u32x4{0xff800000u, 0xff800000u, 0xff800000u, 0xff800000u};
         }
         const int tail = V & ~3;  // (v0 is a multiple of four, so only the row's last quad is not whole)
-        if (tail < V && (tail - v0) / 4 % kThreads == (int)threadIdx.x) {
+        if (tail < V && (tail - v0) / 4 % kRowThreads == (int)threadIdx.x) {
 #pragma unroll
             for (int q = 0; q < kQuads; ++q)
-                if (v0 + (q * kThreads + (int)threadIdx.x) * 4 == tail)
+                if (v0 + (q * kRowThreads + (int)threadIdx.x) * 4 == tail)
 #pragma unroll
                     for (int u = 0; u < 3; ++u)
                         if (tail + u < V) x[q][u] = __builtin_bit_cast(uint32_t, z[tail + u]);
         }
     }
+}
+
+// Key of the piece's largest score and its lowest place, valid in thread 0; ends behind a barrier.  The largest value first (a
+// NaN counts as minus infinity, -0 equals +0), by plain maxima, and only then, in the waves that hold it, the lowest place: one
+// or two instructions a score where folding (value, place) keys took ten.
+__device__ __forceinline__ unsigned long long piece_key(const Piece& x, int v0, float* s_top, int* s_at) {
+    constexpr int kW = kRowThreads / 64;
+    float top = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q) {
+        const uint32_t w0 = x[q][0], w1 = x[q][1], w2 = x[q][2], w3 = x[q][3];
+        top = fmaxf(top, fmaxf(__builtin_bit_cast(float, w0), __builtin_bit_cast(float, w1)));
+        top = fmaxf(top, fmaxf(__builtin_bit_cast(float, w2), __builtin_bit_cast(float, w3)));
+    }
+    top = wave_max(top);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((threadIdx.x & 63) == 0) s_top[w] = top;
+    __syncthreads();
+    float most = s_top[0];
+#pragma unroll
+    for (int k = 1; k < kW; ++k) most = fmaxf(most, s_top[k]);
+    int at = INT_MAX;
+    if (top == most) {
+#pragma unroll
+        for (int q = kQuads - 1; q >= 0; --q) {
+            const uint32_t wq[4] = {x[q][0], x[q][1], x[q][2], x[q][3]};
+#pragma unroll
+            for (int u = 3; u >= 0; --u) {  // (nothing but minus infinities and NaN: the first place)
+                const float f = __builtin_bit_cast(float, wq[u]);
+                if (f == most || most == -INFINITY) at = v0 + (q * kRowThreads + (int)threadIdx.x) * 4 + u;
+            }
+        }
+        at = wave_min_i(at);
+    }
+    if ((threadIdx.x & 63) == 0) s_at[w] = at;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kW; ++k) at = min(at, s_at[k]);
+    return make_key(__builtin_bit_cast(uint32_t, most), at);
+}
+
+// grid (pieces, B (S_max + 1)).  SKIP: workgroup row y takes position y / B of request y % B and leaves out what lies behind a
+// known mismatch; else it takes the call's row y.
+template <bool SKIP>
+__global__ __launch_bounds__(kRowThreads) void greedy_argmax_kernel(
+    const float* __restrict__ target, const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ cu_t,
+    const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
+    unsigned long long* keys, int32_t* first_miss, int B, int V, int S_max, int R_cap) {
+    __shared__ float s_top[kRowThreads / 64];
+    __shared__ int s_at[kRowThreads / 64];
+    __shared__ int s_miss;
+    int r = blockIdx.y, i = 0, j = 0, d0 = 0, d_i = 0;  // r: call-row on the target side
+    if constexpr (SKIP) {
+        j = r / B;
+        i = r - j * B;
+        // one lane asks (the words of all requests lie in a few cache lines that every workgroup wants), with the offsets
+        // still on their way: most workgroups of a large call do nothing else
+        if (threadIdx.x == 0) s_miss = __hip_atomic_load(first_miss + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0;
+        d0 = cu_d[i];
+        d_i = cu_d[i + 1] - d0;
+        r = t0 + j;
+        if (j >= t_i || r >= cu_t[B] || refused(t0, t_i, d_i, S_max, R_cap)) return;
+        __syncthreads();
+        if (s_miss < j) return;
+    } else if (r >= cu_t[B]) {
+        return;
+    }
+    const float* z = target + (size_t)(t_rows ? t_rows[r] : r) * V;
+    const int v0 = blockIdx.x * kChunk;
+    Piece x;
+    load_piece(z, v0, V, x);
     // the key of the draft this row verifies: larger than any if there is none, smaller for an id outside the vocabulary
     unsigned long long drafted = ~0ull;
     if (SKIP && d0 >= 0 && j < d_i && d0 + j < cu_d[B]) {
         const int t = draft_tokens[d_rows ? d_rows[d0 + j] : d0 + j];
         drafted = t < 0 || t >= V ? 0ull : make_key(__builtin_bit_cast(uint32_t, z[t]), t);
     }
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int q = 0; q < kQuads; ++q) {
-        const int v = v0 + (q * kThreads + threadIdx.x) * 4;
-        const uint32_t w0 = x[q][0], w1 = x[q][1], w2 = x[q][2], w3 = x[q][3];
-        unsigned long long c = make_key(w0, v);
-        const unsigned long long c1 = make_key(w1, v + 1), c2 = make_key(w2, v + 2), c3 = make_key(w3, v + 3);
-        c = c1 > c ? c1 : c;
-        c = c2 > c ? c2 : c;
-        c = c3 > c ? c3 : c;
-        best = c > best ? c : best;
-    }
-    best = wave_max_u64(best);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = best;
-    __syncthreads();
+    const unsigned long long best = piece_key(x, v0, s_top, s_at);
     if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) best = part[w] > best ? part[w] : best;
         if (SKIP && best > drafted) atomicMin(first_miss + i, j);
         atomicMax(keys + r, best);
     }
@@ -154,32 +177,40 @@ __global__ __launch_bounds__(kThreads) void greedy_decide_kernel(const int32_t* 
                                                                  const unsigned long long* __restrict__ keys,
                                                                  int32_t* accepted_len, int32_t* n_emitted,
                                                                  int32_t* emitted, int B, int S_max, int R_cap) {
-    const int i = blockIdx.x * kThreads + threadIdx.x;
+    // one wave per request, lane n tests draft n: what they read is in flight together
+    const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= B) return;
-    const int d_i = cu_d[i + 1] - cu_d[i], t_i = cu_t[i + 1] - cu_t[i];
+    const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
     int32_t* em = emitted + (size_t)i * (S_max + 1);
-    for (int s = 0; s <= S_max; ++s) em[s] = -1;
-    if (refused(cu_t[i], t_i, d_i, S_max, R_cap)) {
-        accepted_len[i] = -1;
-        n_emitted[i] = -1;
+    if (refused(t0, t_i, d_i, S_max, R_cap)) {
+        for (int s = lane; s <= S_max; s += 64) em[s] = -1;
+        if (lane == 0) {
+            accepted_len[i] = -1;
+            n_emitted[i] = -1;
+        }
         return;
     }
-    auto choice = [&](int n) { return (int)(0xffffffffu - (uint32_t)keys[cu_t[i] + n]); };
-    int n = 0, tok = -1;
-    while (n < d_i) {
-        const long long dr = d_rows ? d_rows[cu_d[i] + n] : cu_d[i] + n;
-        const int c = choice(n);
-        if (draft_tokens[dr] != c) {
-            tok = c;
+    int n = d_i, tok = -1;  // accepted drafts, and the token behind them
+    for (int n0 = 0; n0 < t_i; n0 += 64) {
+        const int k = n0 + lane;
+        int choice = -1, drafted = -1;
+        if (k < t_i) choice = (int)(0xffffffffu - (uint32_t)keys[t0 + k]);
+        if (k < d_i) drafted = draft_tokens[d_rows ? d_rows[d0 + k] : d0 + k];
+        // the run ends at the first mismatch, or at the row behind the last draft
+        const unsigned long long ends = __builtin_amdgcn_ballot_w64(k < t_i && (k >= d_i || choice != drafted));
+        const int first = ends ? (int)__builtin_ctzll(ends) : 64;
+        if (k < t_i && lane < first) em[k] = choice;
+        if (ends) {
+            n = n0 + first;
+            tok = __shfl(choice, first, 64);
             break;
         }
-        em[n] = c;
-        ++n;
     }
-    if (n == d_i && t_i == d_i + 1) tok = choice(d_i);
-    if (tok >= 0) em[n] = tok;
-    accepted_len[i] = n;
-    n_emitted[i] = n + (tok >= 0 ? 1 : 0);
+    for (int s = n + lane; s <= S_max; s += 64) em[s] = s == n ? tok : -1;
+    if (lane == 0) {
+        accepted_len[i] = n;
+        n_emitted[i] = n + (tok >= 0 ? 1 : 0);
+    }
 }
 
 }  // namespace
@@ -198,10 +229,10 @@ int greedy_accept_launch(const float* target, const int32_t* draft_tokens, const
     if ((rc = check_launch("greedy_init_kernel")) != FSR_OK) return rc;
     const int pieces = (p.V + kChunk - 1) / kChunk;
     const bool skip = (long long)R_cap * pieces >= kSkipMinPieces;
-    hipLaunchKernelGGL(skip ? greedy_argmax_kernel<true> : greedy_argmax_kernel<false>, dim3(pieces, R_cap), dim3(kThreads), 0, s, target,
-                       draft_tokens, cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
+    hipLaunchKernelGGL(skip ? greedy_argmax_kernel<true> : greedy_argmax_kernel<false>, dim3(pieces, R_cap), dim3(kRowThreads), 0, s,
+                       target, draft_tokens, cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
     if ((rc = check_launch("greedy_argmax_kernel")) != FSR_OK) return rc;
-    hipLaunchKernelGGL(greedy_decide_kernel, dim3((p.B + kThreads - 1) / kThreads), dim3(kThreads), 0, s, draft_tokens, cu_t,
+    hipLaunchKernelGGL(greedy_decide_kernel, dim3((p.B + kThreads / 64 - 1) / (kThreads / 64)), dim3(kThreads), 0, s, draft_tokens, cu_t,
                        cu_d, d_rows, keys, accepted_len, n_emitted, emitted, p.B, p.S_max, R_cap);
     return check_launch("greedy_decide_kernel");
 }
