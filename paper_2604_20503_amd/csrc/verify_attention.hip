@@ -143,6 +143,7 @@ struct FastArgs {
     int cost_base;   // fixed part of a tile's cost (see group_at)
     int seg_tiles;   // what taking up an item costs, in tiles that one team takes (see the schedule)
     int two_cost;    // cost of a tile that two teams take
+    int aligned;     // a share is a piece of one item (see aligned_share); else the cost line is cut evenly
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -496,6 +497,85 @@ struct ShareWalker {
         return false;
     }
 };
+
+// The schedule of calls with few items: every share is one piece of one item.  An item is cut into as many even pieces as it
+// takes for none of them to last longer than a common time, and that time is the shortest of 64 candidates -- from an even split
+// of the work to the longest whole item, in equal ratios -- that leaves no more pieces than there are workgroups.  Pieces are
+// numbered request by request, head by head.  Against the cost line no workgroup takes up a second item, short items are not cut
+// at all, and nothing has to be built in LDS: each wave works its share out from the lengths in its lanes.
+// Segment of share b; returns the number of shares, 0 if this schedule does not do (a request of several row groups, or items so
+// uneven and so many that the longest would end late).  have: the share is one of them.
+// Measured, us of a plan and 8 layers, 32/8 heads, cost line / this: one request of 257 tokens 147 / 104, of 1200 230 / 139, of
+// 8192 326 / 210; 16 requests of 1024 to 4096 tokens and 2 to 9 rows, seven batches, 343 to 384 / 314 to 357; 30 of 100 to 600
+// 214 / 180.
+constexpr int kAlignedMaxB = 64;   // a request per lane
+// Items are not cut into shorter pieces: a cut costs its count, write-through and combine.  Least pieces of 16 / 24 / 40 tiles:
+// one request of 1200 tokens 136 / 139 / 155, of 8192 233 / 210 / 216, 4 layers of 4 requests of 200 to 2000 97 / 99 / 115.
+constexpr int kAlignedTiles = 24;
+// What an item costs a workgroup besides its tiles, in tiles: whole, and as a piece.  0 and 0 / 8 and 14 / 16 and 24: mean of the
+// seven batches above 334 / 331 / 333; with all tiles alike 344.
+constexpr float kHeadWhole = 8.0f, kHeadPiece = 14.0f;
+// The longest piece against a share of the cost line.  Where it is 1.3 to 1.42 times as long this schedule gains 1 to 12 %, at 1.73
+// (32 requests of 256 to 4096 tokens) and 1.85 (28 with log-normal contexts) it loses 1 to 6 %.
+constexpr float kLineMargin = 1.55f;
+__device__ int aligned_share(const FastArgs& a, int mt_max, int b, Segment& sg, bool& have) {
+    const int lane = threadIdx.x & 63;
+    int q0 = 0, ql = 0, c = 0, nt = 0;
+    float cost = 1.0f;
+    if (lane < a.B) {
+        q0 = a.cu_q[lane];
+        ql = a.cu_q[lane + 1] - q0;
+        c = max(a.ctx[lane], 0);
+        if (ql > 0) {
+            const Group gr = group_at(a, mt_max, c, ql, 0);
+            nt = gr.nt;
+            cost = (float)gr.cost;
+        }
+    }
+    if (__builtin_amdgcn_ballot_w64(ql > rows_per_group(a, mt_max)) != 0) return 0;
+    auto pieces = [](int tiles, float per_tile, float time) {
+        const float len = time / per_tile - kHeadPiece;
+        if (tiles <= 0) return 0;
+        if ((float)tiles <= len + (kHeadPiece - kHeadWhole)) return 1;
+        return max(1, min((int)__builtin_ceilf((float)tiles / fmaxf(len, 1.0f) - 1e-4f), (tiles + kAlignedTiles - 1) / kAlignedTiles));
+    };
+    float work = (float)nt * cost, line = nt > 0 ? ((float)nt + (float)a.seg_tiles) * cost : 0.0f;
+    float longest = nt > 0 ? ((float)nt + kHeadWhole) * cost : 0.0f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        work += __shfl_xor(work, o, 64);
+        line += __shfl_xor(line, o, 64);
+        longest = fmaxf(longest, __shfl_xor(longest, o, 64));
+    }
+    if (longest == 0.0f) return 0;
+    const float per_group = (float)a.H_kv / (float)a.nb, least = fminf(longest, work * per_group);
+    float time = lane == 63 ? longest * 1.0001f : least * fast_exp2(__builtin_amdgcn_logf(longest / least) * ((float)lane / 63.0f));
+    int sum = 0;
+    for (int i = 0; i < a.B; ++i)
+        sum += pieces(__builtin_amdgcn_readlane(nt, i), __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cost), i)), time);
+    const unsigned long long fits = __builtin_amdgcn_ballot_w64((long long)sum * a.H_kv <= a.nb);
+    if (fits == 0) return 0;
+    time = __shfl(time, __builtin_ctzll(fits), 64);
+    if (time > kLineMargin * line * per_group) return 0;
+    const int k = pieces(nt, cost, time);
+    const int upto = wave_inclusive_scan(k * a.H_kv);
+    const unsigned long long mine = __builtin_amdgcn_ballot_w64(b < upto && b >= upto - k * a.H_kv);
+    have = mine != 0;
+    const int n_shares = __shfl(upto, 63, 64);
+    if (!have) return n_shares;
+    const int i = __builtin_ctzll(mine), ki = uniform(__shfl(k, i, 64)), first = uniform(__shfl(upto - k * a.H_kv, i, 64));
+    const int g = (b - first) / ki, piece = (b - first) - g * ki, tiles = uniform(__shfl(nt, i, 64));
+    sg.i = i; sg.kvh = uniform(g); sg.c = uniform(__shfl(c, i, 64)); sg.q0 = uniform(__shfl(q0, i, 64)); sg.q_len = uniform(__shfl(ql, i, 64));
+    sg.j0 = 0; sg.rows_g = sg.q_len;
+    sg.tile_a = (int)((long long)tiles * piece / ki);
+    sg.tile_e = (int)((long long)tiles * (piece + 1) / ki);
+    sg.final_out = ki == 1;
+    sg.cut = ki > 1;
+    sg.b_first = first + g * ki;
+    sg.b_last = sg.b_first + ki - 1;
+    sg.slot = b * 2 + (piece > 0 ? 0 : 1);
+    return n_shares;
+}
 
 // Issue the global loads of the wave's tile ti (no waiting); bt = the table in which the tile's pages
 // are looked up.  Tiles past the wave's last one are "issued" too, so that the number of loads in
@@ -1249,28 +1329,32 @@ template <int MTMAX, bool TM, bool KV8, bool WIDE>
 __global__ __launch_bounds__(kThreads) void attn_stream_kernel(FastArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ int s_last;
-    char* tables = smem + stream_fixed_smem(WIDE);
-    long long* pref = reinterpret_cast<long long*>(tables);
-    const int cmax = build_cost_prefix<false>(a, MTMAX, pref, reinterpret_cast<long long*>(tables + scan_off(a.B)),
-                                              reinterpret_cast<int*>(tables + cu_off(a.B)),
-                                              reinterpret_cast<int*>(tables + ctx_off(a.B)), nullptr);
-    ShareWalker wk;
-    wk.pref = pref;
-    wk.lds_cu = reinterpret_cast<const int*>(tables + cu_off(a.B));
-    wk.lds_ctx = reinterpret_cast<const int*>(tables + ctx_off(a.B));
-    // every share is at least as wide as the dearest tile: a workgroup whose share lies inside an
-    // item then owns at least one of its tiles
-    const long long total = pref[a.B] * a.H_kv;
-    const int nbx = (int)min((long long)a.nb, div_u(total, cmax));
-    wk.b = share_of_block(blockIdx.x, a.nb);
-    if (wk.b >= nbx) return;
-    wk.set_shares(total, nbx);
-    wk.mt_max = MTMAX;
-    wk.x = wk.share_start(wk.b);
-    wk.x1 = wk.share_start(wk.b + 1);
-
     Segment cur;
-    while (wk.next(a, cur)) {
+    bool have = false;
+    const bool aligned = a.aligned && aligned_share(a, MTMAX, blockIdx.x, cur, have) > 0;
+    ShareWalker wk;
+    if (!aligned) {
+        char* tables = smem + stream_fixed_smem(WIDE);
+        long long* pref = reinterpret_cast<long long*>(tables);
+        const int cmax = build_cost_prefix<false>(a, MTMAX, pref, reinterpret_cast<long long*>(tables + scan_off(a.B)),
+                                                  reinterpret_cast<int*>(tables + cu_off(a.B)),
+                                                  reinterpret_cast<int*>(tables + ctx_off(a.B)), nullptr);
+        wk.pref = pref;
+        wk.lds_cu = reinterpret_cast<const int*>(tables + cu_off(a.B));
+        wk.lds_ctx = reinterpret_cast<const int*>(tables + ctx_off(a.B));
+        // every share is at least as wide as the dearest tile: a workgroup whose share lies inside an
+        // item then owns at least one of its tiles
+        const long long total = pref[a.B] * a.H_kv;
+        const int nbx = (int)min((long long)a.nb, div_u(total, cmax));
+        wk.b = share_of_block(blockIdx.x, a.nb);
+        if (wk.b >= nbx) return;
+        wk.set_shares(total, nbx);
+        wk.mt_max = MTMAX;
+        wk.x = wk.share_start(wk.b);
+        wk.x1 = wk.share_start(wk.b + 1);
+        have = wk.next(a, cur);
+    }
+    for (; have; have = !aligned && wk.next(a, cur)) {
         attend_dispatch<MTMAX, TM, KV8, kStreamRT, WIDE>(a, cur, smem, false, 0);
         if (cur.cut) finish_piece<MTMAX>(a, cur, &s_last);
     }
@@ -1325,6 +1409,25 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
     int* gpref = reinterpret_cast<int*>(smem + tables_bytes(a.B));  // [B + 1] row groups of the requests before
     int* lds_cu = reinterpret_cast<int*>(smem + cu_off(a.B));
     int* lds_ctx = reinterpret_cast<int*>(smem + ctx_off(a.B));
+    if (a.aligned) {
+        const int s = blockIdx.x * kWaves + (threadIdx.x >> 6);
+        Segment sg;
+        bool have = false;
+        const int n_shares = aligned_share(a, mt_max, s, sg, have);
+        if (n_shares > 0) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                plan[2] = n_shares;
+                plan[1] = (int32_t)a.plan_key;
+                plan[0] = kPlanMagic;
+            }
+            if (s < a.nb && (threadIdx.x & 63) == 0) {
+                int32_t* rec = plan + (size_t)(1 + s) * kRecInts;
+                if (have) write_record(rec, a, sg, 1, 0);
+                else rec[13] = 0;
+            }
+            return;
+        }
+    }
     const int cmax = build_cost_prefix<true>(a, mt_max, pref, scratch, lds_cu, lds_ctx, gpref);
     ShareWalker wk;
     wk.pref = pref;
@@ -1401,7 +1504,7 @@ __global__ __launch_bounds__(kThreads) void attn_planned_kernel(FastArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ int s_last;
     const const_i32* plan = (const const_i32*)a.plan;
-    const int share = share_of_block(blockIdx.x, a.nb);
+    const int share = a.aligned ? (int)blockIdx.x : share_of_block(blockIdx.x, a.nb);
     const const_i32* rec = plan + (size_t)(1 + share) * kRecInts;
     // Header and first record are sent for together, before anything is known about either (the record's
     // address lies inside the plan buffer whatever the buffer holds): the fields through the scalar cache,
@@ -1581,6 +1684,7 @@ void fill_common(FastArgs& a, const fsr_attn_params* p, const Setup& su, const i
     a.nb = su.nb; a.m_cap = su.m_cap; a.wide = su.wide ? 1 : 0;
     a.seg_tiles = kSegTiles;
     a.cost_base = cost_base_for(*p, su);
+    a.aligned = p->B <= kAlignedMaxB && (long long)p->B * p->H_kv <= su.nb;
     a.two_cost = (a.cost_base + kWideMT) * kTwoTeamNum / kTwoTeamDen;
     a.plan = nullptr; a.plan_key = 0;
 }

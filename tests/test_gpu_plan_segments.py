@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads
-from gpu_utils import announce, dev
+from gpu_utils import announce, check_attention, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +44,35 @@ def test_many_segments_per_share(fsr, B, H_q, H_kv, spec_hi, max_workgroups, hin
         fsr.verify_attention(q, k, v, bt, ctx_d, None, cu_d, out=out, lse=lse, plan=plan, **kw)
         torch.cuda.synchronize()
         assert torch.isfinite(out).all()
+        outs.append((out, lse))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+@pytest.mark.parametrize("H_q,H_kv,ctx,spec,max_workgroups,hint", [
+    (32, 8, [765, 766, 767, 768, 1535], [0, 1, 2, 3, 8], 0, 9),      # around the least piece of 24 tiles; 1 to 3 query tiles
+    (32, 8, [5000], [3], 0, 4), (8, 1, [9000, 1], [0, 1], 9, 2),     # few workgroups: 9 for two items
+    (4, 4, list(range(1, 1280, 20)), [1] * 64, 0, 2),                # 64 requests x 4 heads: as many items as workgroups
+    (4, 4, [40] * 60 + [4000] * 4, [1] * 64, 0, 2),                  # ... too uneven: the cost line
+    (4, 4, [300] * 65, [1] * 65, 0, 2),                              # a request more than a wave has lanes: the cost line
+    (64, 8, [900, 2000, 33], [10, 1, 5], 0, 11),                     # two-team groups beside ordinary ones
+    (32, 8, [100, 700, 900], [2, 8, 0], 0, 0),                       # no bound on the rows
+    (32, 8, [100, 900], [8, 8], 0, 2)])                              # a bound that is too small: the cost line
+def test_a_piece_of_an_item_per_share(fsr, oracle, H_q, H_kv, ctx, spec, max_workgroups, hint):
+    announce(f"plan pieces heads={H_q}/{H_kv} B={len(ctx)} workgroups={max_workgroups} hint={hint}")
+    b = workloads.make_batch(2, with_probs=False, H_q=H_q, H_kv=H_kv, ctx_lens=np.array(ctx), spec_lens=np.array(spec))
+    q, k, v = dev(b.q, True), dev(b.k_cache, True), dev(b.v_cache, True)
+    bt, ctx_d, cu = dev(b.block_tables), dev(b.ctx_lens), dev(b.cu_q)
+    kw = dict(scale=b.scale, max_q_len=hint, max_workgroups=max_workgroups)
+    ref, lse_ref = oracle.verify_attention(b.q, b.k_cache, b.v_cache, b.block_tables, b.ctx_lens, b.cu_q, H_q=H_q, H_kv=H_kv, D=b.D,
+                                           P=b.P, dtype=b.dtype, scale=b.scale)
+    outs = []
+    for plan in (None, fsr.attn_plan(q, k, bt, ctx_d, cu, **kw)):
+        out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+        lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+        fsr.verify_attention(q, k, v, bt, ctx_d, None, cu, out=out, lse=lse, plan=plan, **kw)
+        torch.cuda.synchronize()
+        check_attention(out, ref, "bf16", b.N)
+        np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-4, atol=1e-4)
         outs.append((out, lse))
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
 
