@@ -1,6 +1,7 @@
 // Verification attention (Sec. 2.1 / 3.1) for the shapes the stream kernel of verify_attention.hip is not built for:
 // fp32 inputs, heads of 64, page sizes other than 16, more than 16 query heads per KV head, very large batches.
-// Nothing is handed from one workgroup to another, so the call needs no workspace.
+// Nothing is handed from one workgroup to another, so the call needs no workspace, except that bf16 items of a small call
+// are cut into pieces of their keys where the caller brings scratch memory for them.
 //
 // What bounds it is reading K and V (bf16) or the fp32 matrix instructions (fp32), so the work is laid out to read a
 // request's keys once per KV head: one workgroup per (request, KV head, group of up to 16 * MT query rows), its waves
@@ -49,6 +50,9 @@ typedef __attribute__((__vector_size__(16), __aligned__(4))) float gf32x4;
 
 constexpr double kLog2e = 1.4426950408889634074;
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr int kMaxSplits = 8;
+constexpr int kSplitKeys = 512;            // an item is not cut into pieces of fewer keys
+constexpr long long kSplitGroups = 256;    // workgroups a call is brought up to by cutting items: one per compute unit
 
 struct ItemArgs {
     const void* q;
@@ -62,6 +66,12 @@ struct ItemArgs {
     int B, N_cap, H_q, H_kv, G, P, p_shift, max_pages, n_pages;  // p_shift: log2(P), or -1 if P is no power of two
     int out_bf16;
     long long page_stride, slot_stride, head_stride;  // of the caches, in bytes
+    // bf16: an item is cut into up to `splits` pieces of at least kSplitKeys keys, handed over through the workspace
+    int splits;
+    float* part_o;   // [items * splits][16 * MTMAX][D] unnormalised sums of the pieces
+    float* part_ml;  // [items * splits][16 * MTMAX][4] exponent reference (log2), sum, call tag, unused
+    unsigned long long* arrivals;  // [items] (call id << 16 | pieces that have arrived)
+    unsigned long long call_id;
     float scale_log2, scale_rest;  // softmax scale times log2(e), and (times ln 2) what rounding took off it
 };
 
@@ -111,10 +121,62 @@ __device__ __forceinline__ u32x4 load16(const char* p) {
     else return *reinterpret_cast<const gu32x4*>(p);
 }
 
-// Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see, merge the waves,
-// write the rows.  MTMAX: what the LDS is laid out for.
-template <bool BF16, int D, int MTMAX, int MT, bool NT>
-__device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0) {
+// Stores through to memory, past the die's L2, for what another workgroup of the launch reads.
+__device__ __forceinline__ void store_device(float* base, long long at, f32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000),
+                                           (int)(at * 4), 0, 16);
+}
+
+__device__ __forceinline__ void write_out(const ItemArgs& a, size_t at, float x) {
+    if (a.out_bf16) reinterpret_cast<uint16_t*>(a.out)[at] = to_bf16(x);
+    else reinterpret_cast<float*>(a.out)[at] = x;
+}
+
+// The pieces of an item's rows m0 .. m0 + rows - 1, slots slot0 .. slot0 + n - 1, to the rows themselves: four values of a row
+// to a thread at a time.  Ordinary loads: a slot was stored through to memory before its piece was counted, is written and
+// read once per launch, and caches start a launch without older copies.  A slot that this call did not write makes its rows NaN.
+template <int D, int ROWS>
+__device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0, int m0, int rows, long long slot0, int n) {
+    for (int e = threadIdx.x; e < rows * (D / 4); e += blockDim.x) {
+        const int m = e / (D / 4), d0 = (e % (D / 4)) * 4;
+        f32x4 ml[kMaxSplits], o[kMaxSplits];
+#pragma unroll
+        for (int k = 0; k < kMaxSplits; ++k) {  // past the last piece: it again, left out below
+            const long long row = (slot0 + min(k, n - 1)) * ROWS + m;
+            ml[k] = *reinterpret_cast<const f32x4*>(a.part_ml + row * 4);
+            o[k] = *reinterpret_cast<const f32x4*>(a.part_o + row * D + d0);
+        }
+        float top = -INFINITY, sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kMaxSplits; ++k)
+            if (k < n) top = fmaxf(top, ml[k][0]);
+        const float ref = top == -INFINITY ? 0.0f : top;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kMaxSplits; ++k) {
+            const float tag = ml[k][2];
+            float w = exp2_fast(ml[k][0] - ref);
+            if (__builtin_bit_cast(uint32_t, tag) != (uint32_t)a.call_id) w = __builtin_nanf("");
+            if (k < n) {
+                sum = fmaf(ml[k][1], w, sum);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[u] = fmaf(o[k][u], w, acc[u]);
+            }
+        }
+        const int j = (m0 + m) / a.G, h = g * a.G + (m0 + m) % a.G;
+        const size_t at = ((size_t)(q0 + j) * a.H_q + h) * D + d0;
+        const float inv = 1.0f / sum;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) write_out(a, at + u, acc[u] * inv);
+        if (a.lse && d0 == 0) a.lse[(size_t)(q0 + j) * a.H_q + h] = top * kLn2 + logf(sum);
+    }
+}
+
+// Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see (piece sp of n_sp of
+// them), merge the waves, write the rows (or the piece's sums to slot slot0 + sp).  MTMAX: what the LDS is laid out for.
+template <bool BF16, int D, int MTMAX, int MT, bool NT, bool SPLIT>
+__device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0, int sp, int n_sp,
+                                             long long slot0) {
     typedef Map<BF16, D, MTMAX> L;
     constexpr int kTile = L::kTile, kKt = L::kKt, kDB = D / 16, kW = L::kW;
     const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6), lg = lane >> 4, li = lane & 15;
@@ -130,8 +192,14 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
 
     const int rows = min(16 * MT, M - m0);
     const int first_lim = c + m0 / a.G;                           // last key the group's first row sees
-    const int kend = min(c + (m0 + rows - 1) / a.G + 1, kv_cap);  // keys any row of the group sees
-    const int kb0 = w * kTile, step = kW * kTile;
+    int kend = min(c + (m0 + rows - 1) / a.G + 1, kv_cap);  // keys any row of the group sees
+    int kb0 = w * kTile;
+    if constexpr (SPLIT) {  // the piece's even share of their tiles
+        const long long n_tiles = (kend + kTile - 1) / kTile;
+        kb0 += (int)(n_tiles * sp / n_sp) * kTile;
+        if (sp + 1 < n_sp) kend = (int)(n_tiles * (sp + 1) / n_sp) * kTile;
+    }
+    const int step = kW * kTile;
     const int nw = kb0 < kend ? (kend - kb0 + step - 1) / step : 0;
     // the wave's first n_plain tiles lie wholly below every row's causal limit
     const int below = min(first_lim + 1, kend) - kTile - kb0;
@@ -455,43 +523,74 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
                 o[u] = fmaf(part, e, o[u]);
             }
         }
-        if (m < rows) {
+        if (SPLIT && n_sp > 1 && m < rows) {
+            const long long row = (slot0 + sp) * (16 * MTMAX) + m;
+            if constexpr (kPer >= 4) {
+#pragma unroll
+                for (int u = 0; u < kPer; u += 4) store_device(a.part_o, row * D + d0 + u, f32x4{o[u], o[u + 1], o[u + 2], o[u + 3]});
+            } else {  // two neighbours make a vector
+                static_assert(kPer == 2 || kPer >= 4, "a thread's values are whole vectors or half of one");
+                const float o2 = __shfl_down(o[0], 1, 64), o3 = __shfl_down(o[1], 1, 64);
+                if (d0 % 4 == 0) store_device(a.part_o, row * D + d0, f32x4{o[0], o[1], o2, o3});
+            }
+            if (d0 == 0) store_device(a.part_ml, row * 4, f32x4{top, sum, __builtin_bit_cast(float, (uint32_t)a.call_id), 0.0f});
+        } else if (m < rows) {
             const int j = (m0 + m) / a.G, h = g * a.G + (m0 + m) % a.G;
             const size_t at = ((size_t)(q0 + j) * a.H_q + h) * D + d0;
             const float inv = 1.0f / sum;
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                if (a.out_bf16) reinterpret_cast<uint16_t*>(a.out)[at + u] = to_bf16(o[u] * inv);
-                else reinterpret_cast<float*>(a.out)[at + u] = o[u] * inv;
-            }
+            for (int u = 0; u < kPer; ++u) write_out(a, at + u, o[u] * inv);
             if (a.lse && d0 == 0) a.lse[(size_t)(q0 + j) * a.H_q + h] = top * kLn2 + logf(sum);
         }
     }
 }
 
-template <bool BF16, int D, int MTMAX, bool NT>
+// SPLIT: one group per item, grid.z counts the pieces its keys are cut into; else grid.z counts the groups.
+template <bool BF16, int D, int MTMAX, bool NT, bool SPLIT>
 __global__ __launch_bounds__((Map<BF16, D, MTMAX>::kThreads)) void attend_items_kernel(ItemArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int g = blockIdx.x, i = blockIdx.y;
     const int q0 = a.cu_q[i], q_len = min(a.cu_q[i + 1], a.N_cap) - q0, c = a.ctx[i];
     const int M = q_len * a.G;
     if (q_len <= 0) return;
-    for (int m0 = blockIdx.z * 16 * MTMAX; m0 < M; m0 += gridDim.z * 16 * MTMAX) {
+    int n_sp = 1, sp = 0, z = blockIdx.z, nz = gridDim.z;
+    if constexpr (SPLIT) {
+        // (rows beyond the caller's bound are further rounds: a slot would be written twice, so no pieces then)
+        const int seen = (int)min((long long)c + q_len, min((long long)a.max_pages * a.P, 1LL << 30));
+        if (M <= 16 * MTMAX) n_sp = max(1, min((int)gridDim.z, seen / kSplitKeys));
+        sp = blockIdx.z;
+        if (sp >= n_sp) return;
+        z = 0;
+        nz = 1;
+    }
+    const long long word = (long long)i * gridDim.x + g, slot0 = word * gridDim.z;
+    for (int m0 = z * 16 * MTMAX; m0 < M; m0 += nz * 16 * MTMAX) {
         const int mt = (min(M - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
         if constexpr (MTMAX >= 4)
-            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT>(a, smem, i, g, q0, M, c, m0);
+            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
         if constexpr (MTMAX >= 3)
-            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT>(a, smem, i, g, q0, M, c, m0);
+            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
         if constexpr (MTMAX >= 2)
-            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT>(a, smem, i, g, q0, M, c, m0);
-        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT>(a, smem, i, g, q0, M, c, m0);
+            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
+        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
         __syncthreads();  // before the next group's query operands and tiles
+    }
+    if constexpr (SPLIT) {
+        __shared__ int s_last;
+        if (n_sp == 1) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the piece is in memory once every wave's stores are acknowledged
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = count_arrival(a.arrivals + word, a.call_id) == n_sp;
+        __syncthreads();
+        if (!s_last) return;
+        combine_pieces<D, 16 * MTMAX>(a, g, q0, 0, M, slot0, n_sp);
+        if (threadIdx.x == 0) __atomic_store_n(a.arrivals + word, a.call_id << 16, __ATOMIC_RELAXED);  // for a graph's next replay
     }
 }
 
 template <bool BF16, int D, int MT>
 int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
-    const dim3 grid((unsigned)a.H_kv, (unsigned)a.B, groups), block(Map<BF16, D, MT>::kThreads);
+    const dim3 grid((unsigned)a.H_kv, (unsigned)a.B, a.splits > 1 ? (unsigned)a.splits : groups), block(Map<BF16, D, MT>::kThreads);
     const size_t smem = Map<BF16, D, MT>::kSmem;
     // keys that one workgroup reads once bypass the caches' replacement (non-temporal); further groups of a request
     // find them in the caches.  D = 64, 32/8 heads, 256 to 4096 tokens, us a call over the caches of 24 layers in turn,
@@ -499,38 +598,74 @@ int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
     // request of 8192 tokens 55.2 / 55.7.  (Called again and again on one pair of caches that the last level holds, the
     // plain loads win at the small end: one request of 8192 tokens 54.0 / 47.3.)
     if constexpr (BF16) {
-        if (groups == 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true>), grid, block, smem, s, a);
-        else hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false>), grid, block, smem, s, a);
+        if (a.splits > 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true, true>), grid, block, smem, s, a);
+        else if (groups == 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true, false>), grid, block, smem, s, a);
+        else hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false, false>), grid, block, smem, s, a);
     } else {
-        hipLaunchKernelGGL((attend_items_kernel<false, D, MT, false>), grid, block, smem, s, a);
+        hipLaunchKernelGGL((attend_items_kernel<false, D, MT, false, false>), grid, block, smem, s, a);
     }
     return check_launch("attend_items_kernel");
 }
 
-template <bool BF16, int D>
-int launch_mt(const ItemArgs& a, long long rows, bool bounded, hipStream_t s) {
-    constexpr int kMost = D == 64 ? 4 : 3;  // query tiles a wave holds (three at D = 128 spill some 30 registers, outside the loops' sums)
-    const int mt = (int)std::min<long long>(kMost, (rows + 15) / 16);
+// How a call is laid out.
+struct Layout {
+    int mt;           // query tiles of a group
+    unsigned groups;  // workgroups an item's rows are dealt to
+    int splits;       // pieces an item's keys are cut into at most
+    size_t bytes_o, bytes_ml, bytes_cnt;
+};
+Layout layout_of(const fsr_attn_params& p) {
+    // query rows a KV head of one request can have: the caller's bound on its rows, or all rows of the call
+    const bool bounded = p.max_q_len > 0;
+    const long long rows = (long long)(p.H_q / p.H_kv) * (bounded ? std::min(p.max_q_len, p.N_cap) : p.N_cap);
+    const int most_tiles = p.D == 64 ? 4 : 3;  // query tiles a wave holds (three at D = 128 spill some 30 registers, outside the loops' sums)
+    Layout l{};
+    l.mt = (int)std::max(1LL, std::min<long long>(most_tiles, (rows + 15) / 16));
     // An item gets as many workgroups as its rows need groups, up to 64; each may take several, and one without rows leaves
     // at once.  Where the caller has not said how many rows a request has, one may have all of the call's, and the bound is
     // as many as leave the call some thousands (at least four an item).  Without a hint, us a call with four an item / like
     // this: 32/1 heads of 64, one request of 64 rows and 8192 tokens 1039 / 141, 32/8 heads, one of 256 rows and 4096 tokens
     // 283 / 77, one of 1024 rows 1207 / 165, 128 of 2 to 9 rows 114 / 114; fp32, 8/2 heads, 512 of 2 to 9 rows 57 / 57.
-    const long long items = (long long)a.B * a.H_kv, most = bounded ? 64 : std::max(4LL, std::min(64LL, 4096 / items));
-    const unsigned groups = (unsigned)std::min(most, (rows + 16 * mt - 1) / (16 * mt));
-    switch (mt) {
-        case 1: return launch<BF16, D, 1>(a, groups, s);
-        case 2: return launch<BF16, D, 2>(a, groups, s);
-        case 3: return launch<BF16, D, 3>(a, groups, s);
-        default: return launch<BF16, D, kMost>(a, groups, s);
+    const long long items = std::max(1LL, (long long)p.B * p.H_kv), most = bounded ? 64 : std::max(4LL, std::min(64LL, 4096 / items));
+    l.groups = (unsigned)std::max(1LL, std::min(most, (rows + 16 * l.mt - 1) / (16 * l.mt)));
+    // Pieces of an item's keys, where a call has fewer items than the device has compute units.  Not more: one workgroup runs on
+    // a compute unit at a time, and a second one waits for the first before it sends for anything.  D = 64, 32/8 heads, us of 3
+    // layers with no pieces / up to 256 / 512 / 1024 workgroups: one request of 8192 tokens 164 / 66 / 66 / 66, 4 of 256 to 4096
+    // 89 / 62 / 62 / 62, 16 of 256 to 8192 194 / 132 / 143 / 174, 32 of 256 to 4096 128 / 128 / 144 / 176.
+    l.splits = 1;
+    if (p.dtype == FSR_BF16 && l.groups == 1) {
+        const long long keys = (long long)p.max_pages * p.P;
+        l.splits = (int)std::max(1LL, std::min({(long long)kMaxSplits, keys / kSplitKeys, kSplitGroups / items}));
+    }
+    const size_t slots = (size_t)items * l.splits, row = (size_t)16 * l.mt;
+    if (l.splits > 1) {
+        l.bytes_o = align_up(slots * row * p.D * sizeof(float), 256);
+        l.bytes_ml = align_up(slots * row * 4 * sizeof(float), 256);
+        l.bytes_cnt = align_up((size_t)items * sizeof(unsigned long long), 256);
+    }
+    return l;
+}
+
+template <bool BF16, int D>
+int launch_mt(const ItemArgs& a, const Layout& l, hipStream_t s) {
+    switch (l.mt) {
+        case 1: return launch<BF16, D, 1>(a, l.groups, s);
+        case 2: return launch<BF16, D, 2>(a, l.groups, s);
+        case 3: return launch<BF16, D, 3>(a, l.groups, s);
+        default: return launch<BF16, D, D == 64 ? 4 : 3>(a, l.groups, s);
     }
 }
 
 }  // namespace
 
+size_t attend_items_workspace_bytes(const fsr_attn_params& p) {
+    const Layout l = layout_of(p);
+    return l.bytes_o + l.bytes_ml + l.bytes_cnt;
+}
+
 int attend_items_launch(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_tables,
                         const int32_t* ctx_lens, const int32_t* cu_q, void* out, float* lse, const fsr_attn_params* p,
-                        hipStream_t s, const char* who) {
+                        void* workspace, size_t ws_bytes, hipStream_t s, const char* who) {
     if (p->N_cap > 65535) return fail(FSR_EUNSUP, "%s: the scratch-free path is limited to N_cap <= 65535 rows", who);
     ItemArgs a;
     const long long e = p->dtype == FSR_BF16 ? 2 : 4, row = p->D * e;
@@ -545,11 +680,16 @@ int attend_items_launch(const void* q, const void* k_cache, const void* v_cache,
     a.head_stride = token_major ? row : p->P * row;
     a.scale_log2 = p->scale * (float)kLog2e;
     a.scale_rest = (float)(p->scale - a.scale_log2 / kLog2e);
-    // query rows a KV head of one request can have: the caller's bound on its rows, or all rows of the call
-    const bool bounded = p->max_q_len > 0;
-    const long long rows = (long long)a.G * (bounded ? std::min(p->max_q_len, p->N_cap) : p->N_cap);
-    if (p->dtype == FSR_BF16) return p->D == 64 ? launch_mt<true, 64>(a, rows, bounded, s) : launch_mt<true, 128>(a, rows, bounded, s);
-    return p->D == 64 ? launch_mt<false, 64>(a, rows, bounded, s) : launch_mt<false, 128>(a, rows, bounded, s);
+    Layout l = layout_of(*p);
+    // a caller without (enough) scratch memory gets one workgroup per group
+    if (l.splits > 1 && (!workspace || ((uintptr_t)workspace & 255) || ws_bytes < l.bytes_o + l.bytes_ml + l.bytes_cnt)) l.splits = 1;
+    a.splits = l.splits;
+    a.part_o = (float*)workspace;
+    a.part_ml = (float*)((char*)workspace + l.bytes_o);
+    a.arrivals = (unsigned long long*)((char*)workspace + l.bytes_o + l.bytes_ml);
+    a.call_id = l.splits > 1 ? next_call_id() : 0;
+    if (p->dtype == FSR_BF16) return p->D == 64 ? launch_mt<true, 64>(a, l, s) : launch_mt<true, 128>(a, l, s);
+    return p->D == 64 ? launch_mt<false, 64>(a, l, s) : launch_mt<false, 128>(a, l, s);
 }
 
 }  // namespace fsr

@@ -1656,7 +1656,7 @@ extern "C" int fsr_attn_workspace_bytes(const fsr_attn_params* p, size_t* out_by
     if (rc != FSR_OK) return rc;
     if (!out_bytes) return fail(FSR_EINVAL, "fsr_attn_workspace_bytes: out_bytes is null");
     const Setup su = make_setup(*p);
-    *out_bytes = su.fast ? su.ws_bytes() : 0;
+    *out_bytes = su.fast ? su.ws_bytes() : attend_items_workspace_bytes(*p);
     return FSR_OK;
 }
 
@@ -1765,7 +1765,7 @@ int attention_call(const void* q, const void* k_cache, const void* v_cache, cons
 #undef FSR_LAUNCH_K
         return check_launch(plan ? "attn_planned_kernel" : "attn_stream_kernel");
     }
-    return attend_items_launch(q, k_cache, v_cache, block_tables, ctx_lens, cu_q, out, lse, p, s, who);
+    return attend_items_launch(q, k_cache, v_cache, block_tables, ctx_lens, cu_q, out, lse, p, workspace, ws_bytes, s, who);
 }
 }  // namespace
 

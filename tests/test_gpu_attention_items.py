@@ -75,6 +75,37 @@ def test_shapes_outside_the_stream_kernel(fsr, oracle, dtype, H_q, H_kv, D, P, t
         print(f"max rel err {err:.2e}")
 
 
+@pytest.mark.parametrize("H_q,H_kv,D,P,hint", [(8, 2, 64, 16, 16), (40, 4, 64, 8, 4), (6, 6, 128, 32, 16), (17, 1, 128, 16, 2), (32, 2, 128, 24, 3)])
+@pytest.mark.parametrize("scratch", ["own", "none", "short", "misaligned"])
+def test_items_in_pieces(fsr, oracle, H_q, H_kv, D, P, hint, scratch):
+    """Contexts around the multiples of the least piece (512 keys), more rows than the bound says, one to four query tiles; the
+    same without scratch memory that holds the pieces."""
+    announce(f"items in pieces heads={H_q}/{H_kv} D={D} P={P} hint={hint} scratch={scratch}")
+    rng = np.random.Generator(np.random.PCG64(H_q + D))
+    ctx, spec = [1022, 510, 1023, 1024, 4100, 0, 2600, 1535], [0, 1, 2, 0, 1, 1, 0, 3]
+    x = make(rng, "bf16", H_q, H_kv, D, P, ctx, spec)
+    q, k, v = (dev(x[n], True) for n in "qkv")
+    need = fsr.attn_workspace_bytes(B=len(ctx), N_cap=q.shape[0], H_q=H_q, H_kv=H_kv, D=D, P=P, max_pages=x["bt"].shape[1],
+                                    n_pages=k.shape[0], dtype=torch.bfloat16, out_dtype=torch.float32, max_q_len=hint)
+    assert need > 0
+    room = torch.full((need + 256,), 0x55, dtype=torch.uint8, device="cuda")
+    ws = {"own": None, "none": room[:0], "short": room[:need - 1], "misaligned": room[16:16 + need]}[scratch]
+    scale = 1.0 / np.sqrt(D)
+    ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=H_q, H_kv=H_kv, D=D, P=P,
+                                           dtype="bf16", scale=float(np.float32(scale)))
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+    for _ in range(2):  # the second call finds the first one's counts
+        out.fill_(float("nan"))
+        fsr.verify_attention(q, k, v, dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=scale, out=out, lse=lse,
+                             max_q_len=hint, workspace=ws)
+        torch.cuda.synchronize()
+        check_attention(out, ref, "f32", len(ref))
+        np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+    if scratch != "own":
+        assert (room == 0x55).all()
+
+
 @pytest.mark.parametrize("H_q,H_kv,D,P,token_major", [(8, 2, 64, 16, False), (14, 2, 64, 24, True), (20, 1, 64, 1, False),
                                                       (6, 6, 128, 32, False), (34, 2, 128, 16, True), (80, 1, 128, 16, False)])
 def test_bf16_output(fsr, oracle, H_q, H_kv, D, P, token_major):
