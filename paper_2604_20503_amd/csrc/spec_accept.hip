@@ -24,6 +24,7 @@
 // one draft row (rejection) per request -- the algorithmic minimum in PROBS mode.
 // All masses are accumulated in fp64 so that the chosen token matches a sequential fp64
 // scan except when u * R lies within rounding of a CDF step.
+#include <algorithm>
 #include <climits>
 
 #include "common.hpp"
@@ -306,20 +307,64 @@ __device__ __forceinline__ double fetch_f64(const double* p) {
                                                          __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// Combine a row's chunk statistics into (largest reference, partition sum relative to it); all lanes of the wave call it.  FRESH: the statistics were
-// made by other workgroups of this launch.
+// One step of a reduction over each half of the wave by DPP (see wave_sum_to_last): the lane's value, or `none` where the
+// control has no lane to take one from.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v, double none) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v), z = __builtin_bit_cast(unsigned long long, none);
+    const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)z, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(z >> 32), (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+// Lane 31 ends with the fold of lanes 0 .. 31, lane 63 with that of lanes 32 .. 63.
+template <typename F>
+__device__ __forceinline__ double fold_halves(double v, double none, F&& f) {
+    v = f(v, dpp_f64<0x111, 0xf>(v, none));
+    v = f(v, dpp_f64<0x112, 0xf>(v, none));
+    v = f(v, dpp_f64<0x114, 0xf>(v, none));
+    v = f(v, dpp_f64<0x118, 0xf>(v, none));
+    return f(v, dpp_f64<0x142, 0xa>(v, none));
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+struct RowStat {
+    double m, Z;  // largest reference, partition sum relative to it
+};
+// Combine the chunk statistics of two rows, one in each half of the wave (all lanes call it; stat_b may be stat_a).  FRESH: the
+// statistics were made by other workgroups of this launch.
 template <bool FRESH>
-__device__ __forceinline__ void combine_stats(const double* __restrict__ stat, int nc, const ExpConsts& ek, double& m, double& Z) {
+__device__ __forceinline__ void combine_stats(const double* __restrict__ stat_a, const double* __restrict__ stat_b, int nc,
+                                              const ExpConsts& ek, RowStat& ra, RowStat& rb) {
+    const int lane = threadIdx.x & 63, l = lane & 31;
+    const double* stat = lane < 32 ? stat_a : stat_b;
     auto at = [&](int k) { return FRESH ? fetch_f64(stat + k) : stat[k]; };
-    const int lane = threadIdx.x & 63;
-    double mm = -INFINITY;
-    for (int c = lane; c < nc; c += 64) mm = fmax(mm, at(c * 2));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mm = fmax(mm, __shfl_xor(mm, o, 64));
+    // the first two pairs of a lane stay in registers (rows of up to 64 groups, i.e. nearly all)
+    double m0 = -INFINITY, m1 = -INFINITY, s0 = 0.0, s1 = 0.0;
+    if (l < nc) {
+        m0 = at(2 * l);
+        s0 = at(2 * l + 1);
+    }
+    if (l + 32 < nc) {
+        m1 = at(2 * (l + 32));
+        s1 = at(2 * (l + 32) + 1);
+    }
+    double mm = fmax(m0, m1);
+    for (int c = l + 64; c < nc; c += 32) mm = fmax(mm, at(c * 2));
+    mm = fold_halves(mm, -INFINITY, [](double x, double y) { return fmax(x, y); });
+    ra.m = lane_f64(mm, 31);
+    rb.m = lane_f64(mm, 63);
+    mm = lane < 32 ? ra.m : rb.m;
     double z = 0.0;
-    for (int c = lane; c < nc; c += 64) z += at(c * 2 + 1) * exp_softmax(at(c * 2) - mm, ek);
-    m = mm;
-    Z = wave_sum(z);
+    if (l < nc) z = s0 * exp_softmax(m0 - mm, ek);
+    if (l + 32 < nc) z += s1 * exp_softmax(m1 - mm, ek);
+    for (int c = l + 64; c < nc; c += 32) z += at(c * 2 + 1) * exp_softmax(at(c * 2) - mm, ek);
+    z = fold_halves(z, 0.0, [](double x, double y) { return x + y; });
+    ra.Z = lane_f64(z, 31);
+    rb.Z = lane_f64(z, 63);
 }
 // ---------------------------------------------------------------------------------------
 // LOGITS mode: per row and group of ws.stat_group chunks, a reference and the sum of exp(z / T - reference), fp64.
@@ -449,44 +494,13 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
     if (!s_last || threadIdx.x >= 64) return;
     // the draft's rows are done (both lie inside the workspace and the row maps: their workgroups have checked): test it
     const long long rt = (long long)t0 + j, rd = (long long)d0 + j;
-    double m_t, Z_t, m_d, Z_d;
-    combine_stats<true>(ws.stat_t + (size_t)rt * nsg * 2, nsg, ek, m_t, Z_t);
-    combine_stats<true>(ws.stat_d + (size_t)rd * nsg * 2, nsg, ek, m_d, Z_d);
+    RowStat st, sd;
+    combine_stats<true>(ws.stat_t + (size_t)rt * nsg * 2, ws.stat_d + (size_t)rd * nsg * 2, nsg, ek, st, sd);
     const long long tr = t_rows ? t_rows[rt] : rt, dr = d_rows ? d_rows[rd] : rd;
     const int x = min(max(draft_tokens[dr], 0), V - 1);
-    const double px = prob_of<FSR_LOGITS>(to_float(z_target[(size_t)tr * V + x]), T, m_t, Z_t, ek);
-    const double qx = prob_of<FSR_LOGITS>(to_float(z_draft[(size_t)dr * V + x]), T, m_d, Z_d, ek);
+    const double px = prob_of<FSR_LOGITS>(to_float(z_target[(size_t)tr * V + x]), T, st.m, st.Z, ek);
+    const double qx = prob_of<FSR_LOGITS>(to_float(z_draft[(size_t)dr * V + x]), T, sd.m, sd.Z, ek);
     if (threadIdx.x == 0 && !((double)u_accept[dr] * qx < px)) atomicMin(stat_words(ws, i, nc), (unsigned)j);
-}
-
-// The same by one lane on its own (every lane of the wave works on a different row): the pairs four at a time, all
-// eight loads of a batch in flight together, folded with a running maximum.
-__device__ __forceinline__ void combine_stats_lane(const double* __restrict__ stat, int nc, const ExpConsts& ek, double& m,
-                                                   double& Z) {
-    double mm = -INFINITY, z = 0.0;
-    for (int c0 = 0; c0 < nc; c0 += 4) {
-        double mc[4], sc[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = min(c0 + u, nc - 1);
-            mc[u] = stat[c * 2];
-            sc[u] = stat[c * 2 + 1];
-        }
-        double mb = mc[0];
-#pragma unroll
-        for (int u = 1; u < 4; ++u) mb = fmax(mb, c0 + u < nc ? mc[u] : -INFINITY);
-        if (mb > mm) {
-            z = mm == -INFINITY ? 0.0 : z * exp_softmax(mm - mb, ek);
-            mm = mb;
-        }
-        if (mm != -INFINITY) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (c0 + u < nc) z += sc[u] * exp_softmax(mc[u] - mm, ek);
-        }
-    }
-    m = mm;
-    Z = z;
 }
 
 // p - q of two products, each rounded: fused into a multiply-add, equal probabilities would leave a rounding error behind
@@ -548,15 +562,25 @@ __device__ __forceinline__ long long shfl_i64(long long v, int src) {
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
 // ---------------------------------------------------------------------------------------
-// decide: one wave per request; lane n tests draft n.
+// decide: PROBS mode, and where the statistics have found the outcome: one wave per request, lane n tests draft n.  LOGITS mode
+// otherwise: one wave per draft (in rounds of the workgroup's waves, one more for the row behind the last draft), its lanes hold
+// the row pair's statistics, so that a test is one memory round trip and two reductions; a lane per draft folded them four at a
+// time, one round trip each (a call of 16 requests in bf16 45.7 -> 42.9 us, of 4 requests in fp32 36.7 -> 26.5).
 // ---------------------------------------------------------------------------------------
+constexpr int kDecideWaves = 12;
+// What a wave finds out about a draft, or (test unused) the row behind the last one.
+struct DraftTest {
+    long long t_row, d_row;
+    double m_t, Z_t, m_d, Z_d;
+    int x, ok;
+};
 template <int MODE, typename RT>
-__global__ __launch_bounds__(64) void accept_decide_kernel(
+__global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void accept_decide_kernel(
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const int32_t* __restrict__ draft_tokens,
     const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
     const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, int32_t* __restrict__ accepted_len,
     int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int B, int V, int S_max, double T) {
-    const int i = blockIdx.x, lane = threadIdx.x;
+    const int i = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int nsg = n_stat_groups_of(V, ws.stat_group);
     const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
     int32_t* em = emitted + (size_t)i * (S_max + 1);
@@ -566,13 +590,13 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
     dec.t_row = dec.d_row = 0;
     dec.m_t = dec.m_d = 0.0;
     dec.Z_t = dec.Z_d = 1.0;
-    if (lane == 0) ws.arrivals[i] = 0u;
+    if (threadIdx.x == 0) ws.arrivals[i] = 0u;
     // the per-row statistics hold B*(S_max+1) target and B*S_max draft rows: a call whose offsets
     // run past that (only possible after an invalid request) is refused for the requests beyond
     const bool fits = (long long)t0 + t_i <= (long long)B * (S_max + 1) && (long long)d0 + d_i <= (long long)B * S_max;
     if (d_i < 0 || d_i > S_max || t_i < d_i || t_i > d_i + 1 || t0 < 0 || d0 < 0 || !fits) {
-        for (int s = lane; s <= S_max; s += 64) em[s] = -1;
-        if (lane == 0) {
+        for (int s = threadIdx.x; s <= S_max; s += blockDim.x) em[s] = -1;
+        if (threadIdx.x == 0) {
             accepted_len[i] = -1;
             n_emitted[i] = -1;
             ws.dec[i] = dec;
@@ -588,29 +612,67 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
             dec.kind = kCaseResidual;
             dec.t_row = t_rows ? t_rows[t0 + n] : t0 + n;
             dec.d_row = d_rows ? d_rows[d0 + n] : d0 + n;
-            combine_stats<false>(ws.stat_t + (size_t)(t0 + n) * nsg * 2, nsg, ek, dec.m_t, dec.Z_t);
-            combine_stats<false>(ws.stat_d + (size_t)(d0 + n) * nsg * 2, nsg, ek, dec.m_d, dec.Z_d);
+            RowStat st, sd;
+            combine_stats<false>(ws.stat_t + (size_t)(t0 + n) * nsg * 2, ws.stat_d + (size_t)(d0 + n) * nsg * 2, nsg, ek, st, sd);
+            dec.m_t = st.m; dec.Z_t = st.Z;
+            dec.m_d = sd.m; dec.Z_d = sd.Z;
         }
+    } else if constexpr (MODE == FSR_LOGITS) {
+        __shared__ DraftTest s_test[kDecideWaves];
+        for (int n0 = 0; n0 < t_i && n == d_i; n0 += n_waves) {
+            const int k = n0 + w;
+            if (k < t_i) {
+                DraftTest t{};
+                t.t_row = t_rows ? t_rows[t0 + k] : t0 + k;
+                t.ok = 1;
+                const double* stat_t = ws.stat_t + (size_t)(t0 + k) * nsg * 2;
+                RowStat st, sd;
+                if (k < d_i) {
+                    t.d_row = d_rows ? d_rows[d0 + k] : d0 + k;
+                    t.x = min(max(draft_tokens[t.d_row], 0), V - 1);
+                    const double u = (double)u_accept[t.d_row];
+                    const float z_t = to_float(p_target[(size_t)t.t_row * V + t.x]), z_d = to_float(p_draft[(size_t)t.d_row * V + t.x]);
+                    combine_stats<false>(stat_t, ws.stat_d + (size_t)(d0 + k) * nsg * 2, nsg, ek, st, sd);
+                    t.ok = u * prob_of<MODE>(z_d, T, sd.m, sd.Z, ek) < prob_of<MODE>(z_t, T, st.m, st.Z, ek);
+                    t.m_d = sd.m; t.Z_d = sd.Z;
+                } else {
+                    combine_stats<false>(stat_t, stat_t, nsg, ek, st, sd);
+                }
+                t.m_t = st.m; t.Z_t = st.Z;
+                if (lane == 0) s_test[w] = t;
+            }
+            __syncthreads();
+            const int here = min(n_waves, t_i - n0);
+            for (int q = 0; q < here; ++q) {  // (the same in every wave)
+                const DraftTest& t = s_test[q];
+                if (n0 + q < d_i && t.ok) {
+                    if (threadIdx.x == 0) em[n0 + q] = t.x;
+                    continue;
+                }
+                dec.kind = n0 + q < d_i ? kCaseResidual : kCaseTarget;
+                n = n0 + q;
+                dec.t_row = t.t_row; dec.m_t = t.m_t; dec.Z_t = t.Z_t;
+                if (dec.kind == kCaseResidual) {
+                    dec.d_row = t.d_row; dec.m_d = t.m_d; dec.Z_d = t.Z_d;
+                }
+                break;
+            }
+            if (dec.kind != kCaseNone) break;
+            __syncthreads();  // before the next round's results
+        }
+        if (w != 0) return;
     } else {
         for (int n0 = 0; n0 < d_i && n == d_i; n0 += 64) {
             const int k = n0 + lane;
             const bool live = k < d_i;
             long long tr = 0, dr = 0;
-            double m_t = 0.0, Z_t = 1.0, m_d = 0.0, Z_d = 1.0;
             int x = 0;
             bool ok = true;
             if (live) {
                 tr = t_rows ? t_rows[t0 + k] : t0 + k;
                 dr = d_rows ? d_rows[d0 + k] : d0 + k;
                 x = min(max(draft_tokens[dr], 0), V - 1);
-                const double u = (double)u_accept[dr];
-                if constexpr (MODE == FSR_LOGITS) {
-                    combine_stats_lane(ws.stat_t + (size_t)(t0 + k) * nsg * 2, nsg, ek, m_t, Z_t);
-                    combine_stats_lane(ws.stat_d + (size_t)(d0 + k) * nsg * 2, nsg, ek, m_d, Z_d);
-                }
-                const double px = prob_of<MODE>(to_float(p_target[(size_t)tr * V + x]), T, m_t, Z_t, ek);
-                const double qx = prob_of<MODE>(to_float(p_draft[(size_t)dr * V + x]), T, m_d, Z_d, ek);
-                ok = u * qx < px;
+                ok = (double)u_accept[dr] * (double)to_float(p_draft[(size_t)dr * V + x]) < (double)to_float(p_target[(size_t)tr * V + x]);
             }
             const unsigned long long rejected = __builtin_amdgcn_ballot_w64(live && !ok);
             const int first = rejected ? (int)__builtin_ctzll(rejected) : 64;
@@ -620,16 +682,19 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(
                 dec.kind = kCaseResidual;
                 dec.t_row = shfl_i64(tr, first);
                 dec.d_row = shfl_i64(dr, first);
-                dec.m_t = shfl_f64(m_t, first); dec.Z_t = shfl_f64(Z_t, first);
-                dec.m_d = shfl_f64(m_d, first); dec.Z_d = shfl_f64(Z_d, first);
             }
         }
     }
     dec.n = n;
-    if (n == d_i && t_i == d_i + 1) {
+    if (dec.kind == kCaseNone && n == d_i && t_i == d_i + 1) {
         dec.kind = kCaseTarget;
         dec.t_row = t_rows ? t_rows[t0 + d_i] : t0 + d_i;
-        if constexpr (MODE == FSR_LOGITS) combine_stats<false>(ws.stat_t + (size_t)(t0 + d_i) * nsg * 2, nsg, ek, dec.m_t, dec.Z_t);
+        if constexpr (MODE == FSR_LOGITS) {
+            const double* stat_t = ws.stat_t + (size_t)(t0 + d_i) * nsg * 2;
+            RowStat st, sd;
+            combine_stats<false>(stat_t, stat_t, nsg, ek, st, sd);
+            dec.m_t = st.m; dec.Z_t = st.Z;
+        }
     }
     for (int s = n + lane; s <= S_max; s += 64) em[s] = -1;
     if (lane == 0) {
@@ -977,7 +1042,8 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
                            draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T);
         if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
     }
-    hipLaunchKernelGGL((accept_decide_kernel<MODE, RT>), dim3(p.B), dim3(64), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t,
+    const int decide_waves = MODE == FSR_LOGITS && !ws.skip ? std::min(kDecideWaves, p.S_max + 1) : 1;
+    hipLaunchKernelGGL((accept_decide_kernel<MODE, RT>), dim3(p.B), dim3(64 * decide_waves), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t,
                        cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T);
     if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
     // chunks per workgroup: as many as leave the device about four workgroups per compute unit (a small batch
