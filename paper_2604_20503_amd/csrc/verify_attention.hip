@@ -533,11 +533,12 @@ __device__ int aligned_share(const FastArgs& a, int mt_max, int b, Segment& sg, 
         }
     }
     if (__builtin_amdgcn_ballot_w64(ql > rows_per_group(a, mt_max)) != 0) return 0;
-    auto pieces = [](int tiles, float per_tile, float time) {
-        const float len = time / per_tile - kHeadPiece;
+    // (approximate reciprocals: any count of pieces is a valid one, and all workgroups find the same)
+    auto pieces = [](int tiles, float tiles_per_cost, float time) {
+        const float len = time * tiles_per_cost - kHeadPiece;
         if (tiles <= 0) return 0;
         if ((float)tiles <= len + (kHeadPiece - kHeadWhole)) return 1;
-        return max(1, min((int)__builtin_ceilf((float)tiles / fmaxf(len, 1.0f) - 1e-4f), (tiles + kAlignedTiles - 1) / kAlignedTiles));
+        return max(1, min((int)__builtin_ceilf((float)tiles * __builtin_amdgcn_rcpf(fmaxf(len, 1.0f)) - 1e-4f), (tiles + kAlignedTiles - 1) / kAlignedTiles));
     };
     float work = (float)nt * cost, line = nt > 0 ? ((float)nt + (float)a.seg_tiles) * cost : 0.0f;
     float longest = nt > 0 ? ((float)nt + kHeadWhole) * cost : 0.0f;
@@ -549,15 +550,18 @@ __device__ int aligned_share(const FastArgs& a, int mt_max, int b, Segment& sg, 
     }
     if (longest == 0.0f) return 0;
     const float per_group = (float)a.H_kv / (float)a.nb, least = fminf(longest, work * per_group);
+    const float rate = __builtin_amdgcn_rcpf(cost), most = kLineMargin * line * per_group;
+    // no candidate up to the margin will do if the margin itself does not
+    if (most < longest && (long long)wave_sum_i(pieces(nt, rate, most)) * a.H_kv > a.nb) return 0;
     float time = lane == 63 ? longest * 1.0001f : least * fast_exp2(__builtin_amdgcn_logf(longest / least) * ((float)lane / 63.0f));
     int sum = 0;
     for (int i = 0; i < a.B; ++i)
-        sum += pieces(__builtin_amdgcn_readlane(nt, i), __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cost), i)), time);
+        sum += pieces(__builtin_amdgcn_readlane(nt, i), __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rate), i)), time);
     const unsigned long long fits = __builtin_amdgcn_ballot_w64((long long)sum * a.H_kv <= a.nb);
     if (fits == 0) return 0;
     time = __shfl(time, __builtin_ctzll(fits), 64);
-    if (time > kLineMargin * line * per_group) return 0;
-    const int k = pieces(nt, cost, time);
+    if (time > most) return 0;
+    const int k = pieces(nt, rate, time);
     const int upto = wave_inclusive_scan(k * a.H_kv);
     const unsigned long long mine = __builtin_amdgcn_ballot_w64(b < upto && b >= upto - k * a.H_kv);
     have = mine != 0;
