@@ -15,6 +15,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfaser_verify.so")
 _lib = None
+_calls = None  # entry point -> its native call object
 
 F32, BF16 = 0, 1
 PROBS, LOGITS, GREEDY = 0, 1, 2
@@ -28,6 +29,29 @@ SYMBOLS = [
     "fsr_prune_scatter", "fsr_survivor_mask", "fsr_survivor_compact", "fsr_topk_rank_check", "fsr_frontier_init", "fsr_frontier_plan", "fsr_frontier_commit",
     "fsr_hbm_read_probe",
 ]
+
+
+# What the entry points that a serving loop calls take, argument by argument: (kind, name), see csrc/marshal.cpp.
+_ATTENTION = "t:q t:k_cache t:v_cache"
+_LENGTHS = "i:block_tables i:ctx_lens"
+_MAPS = "i:new_cu_q i:new_q_lens i:src_row i:dst_row i:n_active i:active_ids t:payload t:payload_out n:row_bytes S:params n:stream"
+_ARGUMENTS = {
+    "fsr_attn_plan": f"{_LENGTHS} i:cu_q S:params t:plan n:plan_bytes n:stream",
+    "fsr_verify_attention": f"{_ATTENTION} {_LENGTHS} i:spec_lens i:cu_q t:out f:lse S:params t:workspace n:ws_bytes n:stream",
+    "fsr_verify_attention_planned": f"{_ATTENTION} {_LENGTHS} i:cu_q t:out f:lse S:params t:plan t:workspace n:ws_bytes n:stream",
+    "fsr_verify_attention_kv8": f"{_ATTENTION} f:k_scale f:v_scale {_LENGTHS} i:cu_q t:out f:lse S:params t:workspace n:ws_bytes n:stream",
+    "fsr_verify_attention_kv8_planned":
+        f"{_ATTENTION} f:k_scale f:v_scale {_LENGTHS} i:cu_q t:out f:lse S:params t:plan t:workspace n:ws_bytes n:stream",
+    "fsr_kv_append": f"t:k_new t:v_new t:k_cache t:v_cache {_LENGTHS} i:cu_q S:params n:stream",
+    "fsr_kv_append_kv8": f"t:k_new t:v_new t:k_cache t:v_cache f:k_scale f:v_scale {_LENGTHS} i:cu_q S:params n:stream",
+    "fsr_spec_accept": "t:p_target t:p_draft i:draft_tokens f:u_accept f:u_sample i:cu_t i:cu_d i:t_rows i:d_rows i:accepted_len "
+                       "i:n_emitted i:emitted S:params t:workspace n:ws_bytes n:stream",
+    "fsr_prune_compact": f"b:keep_mask i:cu_q {_MAPS}",
+    "fsr_survivor_compact": f"i:accepted_len i:cu_q b:keep_mask {_MAPS}",
+    "fsr_topk_rank_check": "t:logits i:draft_tokens i:cu_q i:cu_d i:rank b:keep_mask S:params n:stream",
+    "fsr_prune_restore": "t:compact i:dst_row t:restored b:has_value n:row_bytes n:N n:pad_word n:stream",
+    "fsr_prune_scatter": "t:compact i:src_row i:n_rows t:out n:row_bytes n:N_cap n:stream",
+}
 
 
 class FsrError(RuntimeError):
@@ -63,7 +87,7 @@ def library_path() -> str:
 
 def load_library():
     """Load ``libfaser_verify.so``; raises if it has not been built."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise FileNotFoundError(
@@ -75,6 +99,13 @@ def load_library():
         for name in SYMBOLS[2:]:
             getattr(lib, name).restype = ctypes.c_int
         lib.fsr_static_scratch_bytes.restype = ctypes.c_size_t
+        from . import _marshal
+
+        calls = {}
+        for name, arguments in _ARGUMENTS.items():
+            kinds, names = zip(*(a.split(":") for a in arguments.split()))
+            calls[name] = _marshal.make(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, "".join(kinds), names)
+        _calls = calls
         _lib = lib
     return _lib
 
@@ -102,6 +133,15 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor"):
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     return ctypes.c_void_p(t.data_ptr())
+
+
+def _call(name: str, *args):
+    """Check and hand over the arguments of an entry point (see _ARGUMENTS), the current stream behind them."""
+    if _calls is None:
+        load_library()
+    rc = _calls[name](*args, _device_and_stream()[1])
+    if rc != 0:
+        raise FsrError(rc, last_error())
 
 
 def _device_and_stream() -> tuple:
@@ -173,9 +213,7 @@ def attn_plan(q, k_cache, block_tables, ctx_lens, cu_q, *, scale, out_dtype=None
     _check(lib.fsr_attn_plan_bytes(ctypes.byref(p), ctypes.byref(need)))
     if plan is None:
         plan = torch.empty(max(need.value, 16), dtype=torch.uint8, device=q.device)
-    _check(lib.fsr_attn_plan(_ptr(block_tables, torch.int32, "block_tables"), _ptr(ctx_lens, torch.int32, "ctx_lens"),
-                             _ptr(cu_q, torch.int32, "cu_q"), ctypes.byref(p), _ptr(plan, name="plan"),
-                             ctypes.c_size_t(plan.numel() * plan.element_size()), _stream()))
+    _call("fsr_attn_plan", block_tables, ctx_lens, cu_q, p, plan, plan.numel() * plan.element_size())
     return plan
 
 
@@ -197,12 +235,22 @@ def _guard_workspace(workspace):
     return key, stream
 
 
+def _new_event():
+    event = torch.cuda.Event()
+    if isinstance(event, torch._C._CudaEventBase):  # recorded behind every call: without a fence for the host's memory
+        load_library()
+        from . import _marshal
+
+        _marshal.without_system_fence(event)
+    return event
+
+
 def _note_workspace_use(token):
     if token is not None:
         key, stream = token
         last = _ws_last_use.get(key)
         # calls that follow each other on one stream record the same event anew
-        ev, handle = (last[1], last[2]) if last is not None and last[0] == stream else (torch.cuda.Event(), torch.cuda.current_stream())
+        ev, handle = (last[1], last[2]) if last is not None and last[0] == stream else (_new_event(), torch.cuda.current_stream())
         ev.record(handle)
         _ws_last_use[key] = (stream, ev, handle)
 
@@ -231,19 +279,12 @@ def verify_attention(q, k_cache, v_cache, block_tables, ctx_lens, spec_lens, cu_
             workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if plan is not None:
-        _check(lib.fsr_verify_attention_planned(
-            _ptr(q, name="q"), _ptr(k_cache, name="k_cache"), _ptr(v_cache, name="v_cache"),
-            _ptr(block_tables, torch.int32, "block_tables"), _ptr(ctx_lens, torch.int32, "ctx_lens"),
-            _ptr(cu_q, torch.int32, "cu_q"), _ptr(out, name="out"), _ptr(lse, torch.float32, "lse"), ctypes.byref(p),
-            _ptr(plan, name="plan"), _ptr(workspace, name="workspace"), ctypes.c_size_t(ws_bytes), _stream()))
+        _call("fsr_verify_attention_planned", q, k_cache, v_cache, block_tables, ctx_lens, cu_q, out, lse, p, plan,
+              workspace, ws_bytes)
         _note_workspace_use(token)
         return out, lse
-    _check(lib.fsr_verify_attention(
-        _ptr(q, name="q"), _ptr(k_cache, name="k_cache"), _ptr(v_cache, name="v_cache"),
-        _ptr(block_tables, torch.int32, "block_tables"), _ptr(ctx_lens, torch.int32, "ctx_lens"),
-        _ptr(spec_lens, torch.int32, "spec_lens"), _ptr(cu_q, torch.int32, "cu_q"), _ptr(out, name="out"),
-        _ptr(lse, torch.float32, "lse"), ctypes.byref(p), _ptr(workspace, name="workspace"),
-        ctypes.c_size_t(ws_bytes), _stream()))
+    _call("fsr_verify_attention", q, k_cache, v_cache, block_tables, ctx_lens, spec_lens, cu_q, out, lse, p, workspace,
+          ws_bytes)
     _note_workspace_use(token)
     return out, lse
 
@@ -288,19 +329,11 @@ def verify_attention_kv8(q, k_cache, v_cache, k_scale, v_scale, block_tables, ct
             workspace = torch.empty(need.value, dtype=torch.uint8, device=q.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if plan is not None:
-        _check(lib.fsr_verify_attention_kv8_planned(
-            _ptr(q, name="q"), _ptr(k_cache, name="k_cache"), _ptr(v_cache, name="v_cache"),
-            _ptr(k_scale, torch.float32, "k_scale"), _ptr(v_scale, torch.float32, "v_scale"),
-            _ptr(block_tables, torch.int32, "block_tables"), _ptr(ctx_lens, torch.int32, "ctx_lens"),
-            _ptr(cu_q, torch.int32, "cu_q"), _ptr(out, name="out"), _ptr(lse, torch.float32, "lse"), ctypes.byref(p),
-            _ptr(plan, name="plan"), _ptr(workspace, name="workspace"), ctypes.c_size_t(ws_bytes), _stream()))
+        _call("fsr_verify_attention_kv8_planned", q, k_cache, v_cache, k_scale, v_scale, block_tables, ctx_lens, cu_q,
+              out, lse, p, plan, workspace, ws_bytes)
         return out, lse
-    _check(lib.fsr_verify_attention_kv8(
-        _ptr(q, name="q"), _ptr(k_cache, name="k_cache"), _ptr(v_cache, name="v_cache"),
-        _ptr(k_scale, torch.float32, "k_scale"), _ptr(v_scale, torch.float32, "v_scale"),
-        _ptr(block_tables, torch.int32, "block_tables"), _ptr(ctx_lens, torch.int32, "ctx_lens"),
-        _ptr(cu_q, torch.int32, "cu_q"), _ptr(out, name="out"), _ptr(lse, torch.float32, "lse"), ctypes.byref(p),
-        _ptr(workspace, name="workspace"), ctypes.c_size_t(ws_bytes), _stream()))
+    _call("fsr_verify_attention_kv8", q, k_cache, v_cache, k_scale, v_scale, block_tables, ctx_lens, cu_q, out, lse, p,
+          workspace, ws_bytes)
     return out, lse
 
 
@@ -319,10 +352,7 @@ def kv_append(k_new, v_new, k_cache, v_cache, block_tables, ctx_lens, cu_q, *, k
     p = AttnParams(B=B, N_cap=k_new.shape[0], H_q=H_kv, H_kv=H_kv, D=D, P=P, max_pages=block_tables.shape[1],
                    n_pages=n_pages, dtype=_code(k_new.dtype), out_dtype=_code(k_new.dtype), scale=1.0, max_q_len=0,
                    max_workgroups=0, kv_layout=int(kv_layout))
-    _check(lib.fsr_kv_append(_ptr(k_new, name="k_new"), _ptr(v_new, name="v_new"), _ptr(k_cache, name="k_cache"),
-                             _ptr(v_cache, name="v_cache"), _ptr(block_tables, torch.int32, "block_tables"),
-                             _ptr(ctx_lens, torch.int32, "ctx_lens"), _ptr(cu_q, torch.int32, "cu_q"), ctypes.byref(p),
-                             _stream()))
+    _call("fsr_kv_append", k_new, v_new, k_cache, v_cache, block_tables, ctx_lens, cu_q, p)
 
 
 def kv_append_kv8(k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_tables, ctx_lens, cu_q, *, kv_layout=KV_HEAD_MAJOR):
@@ -332,11 +362,7 @@ def kv_append_kv8(k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_tables
     p = _attn_params(k_new, k_cache, block_tables, B, k_new.dtype, 1.0, 0, 0, kv_layout)
     if v_new.shape != k_new.shape or v_cache.shape != k_cache.shape or k_cache.dtype != torch.uint8 or v_cache.dtype != torch.uint8:
         raise ValueError("rows must share a shape; caches must be uint8 tensors of one shape")
-    _check(lib.fsr_kv_append_kv8(
-        _ptr(k_new, name="k_new"), _ptr(v_new, name="v_new"), _ptr(k_cache, name="k_cache"), _ptr(v_cache, name="v_cache"),
-        _ptr(k_scale, torch.float32, "k_scale"), _ptr(v_scale, torch.float32, "v_scale"),
-        _ptr(block_tables, torch.int32, "block_tables"), _ptr(ctx_lens, torch.int32, "ctx_lens"),
-        _ptr(cu_q, torch.int32, "cu_q"), ctypes.byref(p), _stream()))
+    _call("fsr_kv_append_kv8", k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_tables, ctx_lens, cu_q, p)
 
 
 def accept_workspace_bytes(*, B, V, S_max, mode=PROBS, temperature=1.0) -> int:
@@ -372,14 +398,8 @@ def spec_accept(p_target, p_draft, draft_tokens, u_accept, u_sample, cu_t, cu_d,
         _check(lib.fsr_accept_workspace_bytes(ctypes.byref(p), ctypes.byref(need)))
         workspace = torch.empty(max(need.value, 256), dtype=torch.uint8, device=dev)
     ws_bytes = workspace.numel() * workspace.element_size()
-    _check(lib.fsr_spec_accept(
-        _ptr(p_target, name="p_target"), _ptr(p_draft, name="p_draft"),
-        _ptr(draft_tokens, torch.int32, "draft_tokens"), _ptr(u_accept, torch.float32, "u_accept"),
-        _ptr(u_sample, torch.float32, "u_sample"), _ptr(cu_t, torch.int32, "cu_t"), _ptr(cu_d, torch.int32, "cu_d"),
-        _ptr(t_rows, torch.int32, "t_rows"), _ptr(d_rows, torch.int32, "d_rows"),
-        _ptr(accepted_len, torch.int32, "accepted_len"), _ptr(n_emitted, torch.int32, "n_emitted"),
-        _ptr(emitted, torch.int32, "emitted"), ctypes.byref(p), _ptr(workspace, name="workspace"),
-        ctypes.c_size_t(ws_bytes), _stream()))
+    _call("fsr_spec_accept", p_target, p_draft, draft_tokens, u_accept, u_sample, cu_t, cu_d, t_rows, d_rows,
+          accepted_len, n_emitted, emitted, p, workspace, ws_bytes)
     return accepted_len, n_emitted, emitted
 
 
@@ -418,24 +438,15 @@ def prune_compact(keep_mask, cu_q, *, suffix_close=True, payload=None, payload_o
         if payload_out is None:
             payload_out = torch.empty_like(payload)
     if accepted_len is not None:
-        _check(lib.fsr_survivor_compact(
-            _ptr(accepted_len, torch.int32, "accepted_len"), _ptr(cu_q, torch.int32, "cu_q"),
-            _ptr(keep_mask, torch.uint8, "keep_mask"), _ptr(new_cu_q, torch.int32),
-            _ptr(new_q_lens, torch.int32), _ptr(src_row, torch.int32), _ptr(dst_row, torch.int32),
-            _ptr(n_active, torch.int32), _ptr(active_ids, torch.int32),
-            _ptr(payload if row_bytes else None, name="payload"), _ptr(payload_out if row_bytes else None, name="payload_out"),
-            ctypes.c_size_t(row_bytes), ctypes.byref(p), _stream()))
+        _call("fsr_survivor_compact", accepted_len, cu_q, keep_mask, new_cu_q, new_q_lens, src_row, dst_row, n_active,
+              active_ids, payload if row_bytes else None, payload_out if row_bytes else None, row_bytes, p)
         res = dict(new_cu_q=new_cu_q, new_q_lens=new_q_lens, src_row=src_row, dst_row=dst_row, n_active=n_active,
                    active_ids=active_ids)
         if payload is not None:
             res["payload"] = payload_out
         return res
-    _check(lib.fsr_prune_compact(
-        _ptr(keep_mask, torch.uint8, "keep_mask"), _ptr(cu_q, torch.int32, "cu_q"), _ptr(new_cu_q, torch.int32),
-        _ptr(new_q_lens, torch.int32), _ptr(src_row, torch.int32), _ptr(dst_row, torch.int32),
-        _ptr(n_active, torch.int32), _ptr(active_ids, torch.int32),
-        _ptr(payload if row_bytes else None, name="payload"), _ptr(payload_out if row_bytes else None, name="payload_out"),
-        ctypes.c_size_t(row_bytes), ctypes.byref(p), _stream()))
+    _call("fsr_prune_compact", keep_mask, cu_q, new_cu_q, new_q_lens, src_row, dst_row, n_active, active_ids,
+          payload if row_bytes else None, payload_out if row_bytes else None, row_bytes, p)
     res = dict(new_cu_q=new_cu_q, new_q_lens=new_q_lens, src_row=src_row, dst_row=dst_row, n_active=n_active,
                active_ids=active_ids)
     if payload is not None:
@@ -456,10 +467,8 @@ def topk_rank_check(logits, draft_tokens, cu_q, cu_d, *, K, rank=None, keep_mask
     if keep_mask is None:
         keep_mask = torch.empty(N_cap, dtype=torch.uint8, device=logits.device)
     p = RankParams(B=B, N_cap=N_cap, D_cap=D_cap, V=V, K=int(K), dtype=_code(logits.dtype), reserved=0)
-    _check(lib.fsr_topk_rank_check(
-        _ptr(logits, name="logits"), _ptr(draft_tokens if D_cap else None, torch.int32, "draft_tokens"),
-        _ptr(cu_q, torch.int32, "cu_q"), _ptr(cu_d, torch.int32, "cu_d"), _ptr(rank if D_cap else None, torch.int32, "rank"),
-        _ptr(keep_mask, torch.uint8, "keep_mask"), ctypes.byref(p), _stream()))
+    _call("fsr_topk_rank_check", logits, draft_tokens if D_cap else None, cu_q, cu_d, rank if D_cap else None,
+          keep_mask, p)
     return rank, keep_mask
 
 
@@ -476,9 +485,7 @@ def prune_restore(compact, dst_row, *, pad_word=0, restored=None, has_value=None
     for s in row_shape:
         row_elems *= s
     row_bytes = row_elems * compact.element_size()
-    _check(lib.fsr_prune_restore(_ptr(compact, name="compact"), _ptr(dst_row, torch.int32, "dst_row"),
-                                 _ptr(restored, name="restored"), _ptr(has_value, torch.uint8, "has_value"),
-                                 ctypes.c_size_t(row_bytes), ctypes.c_int32(N), ctypes.c_uint32(pad_word), _stream()))
+    _call("fsr_prune_restore", compact, dst_row, restored, has_value, row_bytes, N, pad_word)
     return restored, has_value
 
 
@@ -488,9 +495,7 @@ def prune_scatter(compact, src_row, n_rows, out):
     if compact.shape[0] != N_cap or out.shape != compact.shape or out.dtype != compact.dtype:
         raise ValueError("compact and out must be [N_cap, ...] of the same shape and dtype")
     row_bytes = (compact.numel() // max(N_cap, 1)) * compact.element_size()
-    _check(load_library().fsr_prune_scatter(_ptr(compact, name="compact"), _ptr(src_row, torch.int32, "src_row"),
-                                            _ptr(n_rows, torch.int32, "n_rows"), _ptr(out, name="out"),
-                                            ctypes.c_size_t(row_bytes), ctypes.c_int32(N_cap), _stream()))
+    _call("fsr_prune_scatter", compact, src_row, n_rows, out, row_bytes, N_cap)
     return out
 
 
