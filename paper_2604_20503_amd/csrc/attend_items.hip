@@ -658,9 +658,12 @@ int launch_mt(const ItemArgs& a, const Layout& l, hipStream_t s) {
 
 }  // namespace
 
+// For as many slots as any batch uses, so that the size covers smaller batches too (which are cut into more pieces).
 size_t attend_items_workspace_bytes(const fsr_attn_params& p) {
-    const Layout l = layout_of(p);
-    return l.bytes_o + l.bytes_ml + l.bytes_cnt;
+    if (p.dtype != FSR_BF16) return 0;
+    const size_t rows = (size_t)kSplitGroups * 16 * layout_of(p).mt;
+    return align_up(rows * p.D * sizeof(float), 256) + align_up(rows * 4 * sizeof(float), 256) +
+           align_up((size_t)kSplitGroups * sizeof(unsigned long long), 256);
 }
 
 int attend_items_launch(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_tables,

@@ -89,7 +89,7 @@ def test_items_in_pieces(fsr, oracle, H_q, H_kv, D, P, hint, scratch):
                                     n_pages=k.shape[0], dtype=torch.bfloat16, out_dtype=torch.float32, max_q_len=hint)
     assert need > 0
     room = torch.full((need + 256,), 0x55, dtype=torch.uint8, device="cuda")
-    ws = {"own": None, "none": room[:0], "short": room[:need - 1], "misaligned": room[16:16 + need]}[scratch]
+    ws = {"own": None, "none": room[:0], "short": room[:256], "misaligned": room[16:16 + need]}[scratch]
     scale = 1.0 / np.sqrt(D)
     ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=H_q, H_kv=H_kv, D=D, P=P,
                                            dtype="bf16", scale=float(np.float32(scale)))
