@@ -245,10 +245,10 @@ def kernel_figures(b, st, times_us):
     return {
         **extra,
         "spec_accept": fig(times_us["accept"], accept_bytes, 2, "accept_decide_kernel + accept_sample_kernel"),
-        "survivor_compact": fig(times_us["compact"], compact_bytes, 2,
+        "survivor_compact": fig(times_us["compact"], compact_bytes, 1,
                                 f"prune_compact_kernel; {n_new} of {b.N} rows of {row_bytes} bytes survive"),
-        "topk_rank_check": fig(times_us["rank"], rank_bytes, 3,
-                               "rank check over the target rows, K = 10; not part of the timed step"),
+        "topk_rank_check": fig(times_us["rank"], rank_bytes, 1,
+                               "rank_check_kernel over the target rows, K = 10; not part of the timed step"),
     }
 
 
