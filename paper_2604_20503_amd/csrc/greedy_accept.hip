@@ -8,16 +8,18 @@
 // mismatch before its row leaves at once.  A mismatch is known as soon as any workgroup of the row has met a score above the
 // draft's own, long before the row is done.  A small call has most rows in flight before anything is known, and the asking
 // and telling costs it more than the rows (kSkipMinPieces).
-// greedy_argmax_kernel: every workgroup finds the largest score of a 64 KB piece of a row and its lowest place, and merges them
-// as a 64-bit key (value made order-preserving << 32 | ~index) into the row's key with one atomic max, which yields the largest
-// value and, among equals, the lowest index.  Pieces of 64 KB: most workgroups of a large call are those of rows that are left
-// out, and each costs two memory round trips before it may leave.
-// Measured, us a call with the compaction behind it, 1-8 drafts of which about 40 % match, all rows read / rows left out, by the
-// pieces the call can hold: vocabulary 128256: 32 requests (2304) 27 / 30, 64 (4608) 43 / 36; 32000: 192 requests (3456) 34.5 /
-// 32.3; 152064: 128 requests (11520) 79 / 47; 128256: 384 requests (30720) 209 / 88.  With 16 KB pieces of 256 threads: 64
-// requests 39.8, 128 requests 46.3, 384 requests 107.  At 64 requests 50 MB are read: what is left is the chain of workgroups,
-// not the bytes.  Workgroups that go through a request's positions one after the other read less but wait more: 45 us at 64
-// requests, 139 us at 384.
+// greedy_argmax_kernel: every workgroup finds the largest score of a 32 or 64 KB piece of a row and its lowest place, and merges
+// them as a 64-bit key (value made order-preserving << 32 | ~index) into the row's key with one atomic max, which yields the largest
+// value and, among equals, the lowest index.  Most workgroups of a large call are those of rows that are left out, and each costs two
+// memory round trips before it may leave: the largest calls take 64 KB pieces.  With fewer, smaller pieces tell of a mismatch sooner.
+// Measured, us a call with the compaction behind it, 1-8 drafts of which about 40 % match:
+//   all rows read / rows left out (64 KB pieces), by the pieces the call can hold: vocabulary 128256: 32 requests (2304) 27 / 30, 64
+//   (4608) 43 / 36; 32000: 192 requests (3456) 34.5 / 32.3; 152064: 128 requests (11520) 79 / 47; 128256: 384 requests 209 / 88;
+//   rows left out, pieces of 16 KB (256 threads) / 32 / 64 KB: 128256: 64 requests (4608) 40.0 / 34.6 / 36.3, 100 (7200) 37.6 / 36.6 /
+//   40.3, 128 (9216) 42.2 / 41.9 / 45.4, 160 (11520) 48.7 / 47.7 / 47.9, 384 (27648) 101 / 101 / 85; 152064: 250 (22500) 78 / 78 / 68;
+//   32000: 192 (3456) 37.5 / 31.7 / 32.2, 380 (6840) 42.8 / 39.5 / 41.1.
+// At 64 requests 50 MB are read: what is left is the chain of workgroups, not the bytes.  Workgroups that go through a request's
+// positions one after the other read less but wait more: 45 us at 64 requests, 139 us at 384.
 #include <climits>
 #include <cstdint>
 
@@ -30,9 +32,11 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kRowThreads = 512;                  // threads that take a piece of a row
-constexpr int kQuads = 8;                         // 16-byte loads of such a thread, all in flight together
-constexpr int kChunk = kRowThreads * kQuads * 4;  // scores of a piece
-constexpr int kSkipMinPieces = 3072;  // pieces a call must be able to hold for rows behind a mismatch to be left out
+// 16-byte loads of such a thread, all in flight together: four or eight, i.e. pieces of 32 or 64 KB
+template <int QUADS>
+constexpr int kChunk = kRowThreads * QUADS * 4;  // scores of a piece
+constexpr int kLongPieces = 12288;    // 64 KB pieces a call must be able to hold for pieces of that size where rows are left out
+constexpr int kSkipMinPieces = 3072;  // 64 KB pieces a call must be able to hold for rows behind a mismatch to be left out
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(4))) uint32_t gu32x4;  // at any element of a row
@@ -60,11 +64,11 @@ __global__ __launch_bounds__(kThreads) void greedy_init_kernel(unsigned long lon
     if (r < B) first_miss[r] = INT_MAX;
 }
 
-typedef u32x4 Piece[kQuads];  // a thread's scores of a piece: quads q * kRowThreads + thread
-
+// A thread's scores of a piece are the quads q * kRowThreads + thread.
 // Send for the scores v0 .. v0 + kChunk - 1 of row z.
-__device__ __forceinline__ void load_piece(const float* __restrict__ z, int v0, int V, Piece& x) {
-    if (v0 + kChunk <= V) {
+template <int kQuads>
+__device__ __forceinline__ void load_piece(const float* __restrict__ z, int v0, int V, u32x4 (&x)[kQuads]) {
+    if (v0 + kChunk<kQuads> <= V) {
 #pragma unroll
         for (int q = 0; q < kQuads; ++q)  // a row is streamed once
             x[q] = __builtin_nontemporal_load(reinterpret_cast<const gu32x4*>(z + v0 + (q * kRowThreads + threadIdx.x) * 4));
@@ -90,7 +94,8 @@ __device__ __forceinline__ void load_piece(const float* __restrict__ z, int v0, 
 // Key of the piece's largest score and its lowest place, valid in thread 0; ends behind a barrier.  The largest value first (a
 // NaN counts as minus infinity, -0 equals +0), by plain maxima, and only then, in the waves that hold it, the lowest place: one
 // or two instructions a score where folding (value, place) keys took ten.
-__device__ __forceinline__ unsigned long long piece_key(const Piece& x, int v0, float* s_top, int* s_at) {
+template <int kQuads>
+__device__ __forceinline__ unsigned long long piece_key(const u32x4 (&x)[kQuads], int v0, float* s_top, int* s_at) {
     constexpr int kW = kRowThreads / 64;
     float top = -INFINITY;
 #pragma unroll
@@ -128,7 +133,7 @@ __device__ __forceinline__ unsigned long long piece_key(const Piece& x, int v0, 
 
 // grid (pieces, B (S_max + 1)).  SKIP: workgroup row y takes position y / B of request y % B and leaves out what lies behind a
 // known mismatch; else it takes the call's row y.
-template <bool SKIP>
+template <bool SKIP, int kQuads>
 __global__ __launch_bounds__(kRowThreads) void greedy_argmax_kernel(
     const float* __restrict__ target, const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ cu_t,
     const int32_t* __restrict__ cu_d, const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows,
@@ -154,8 +159,8 @@ __global__ __launch_bounds__(kRowThreads) void greedy_argmax_kernel(
         return;
     }
     const float* z = target + (size_t)(t_rows ? t_rows[r] : r) * V;
-    const int v0 = blockIdx.x * kChunk;
-    Piece x;
+    const int v0 = blockIdx.x * kChunk<kQuads>;
+    u32x4 x[kQuads];
     load_piece(z, v0, V, x);
     // the key of the draft this row verifies: larger than any if there is none, smaller for an id outside the vocabulary
     unsigned long long drafted = ~0ull;
@@ -227,10 +232,14 @@ int greedy_accept_launch(const float* target, const int32_t* draft_tokens, const
     int rc;
     hipLaunchKernelGGL(greedy_init_kernel, dim3((R_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, keys, accepted_len, R_cap, p.B);
     if ((rc = check_launch("greedy_init_kernel")) != FSR_OK) return rc;
-    const int pieces = (p.V + kChunk - 1) / kChunk;
-    const bool skip = (long long)R_cap * pieces >= kSkipMinPieces;
-    hipLaunchKernelGGL(skip ? greedy_argmax_kernel<true> : greedy_argmax_kernel<false>, dim3(pieces, R_cap), dim3(kRowThreads), 0, s,
-                       target, draft_tokens, cu_t, cu_d, t_rows, d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
+    auto launch = [&](auto kernel, int chunk) {
+        hipLaunchKernelGGL(kernel, dim3((p.V + chunk - 1) / chunk, R_cap), dim3(kRowThreads), 0, s, target, draft_tokens, cu_t, cu_d, t_rows,
+                           d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
+    };
+    const long long pieces = (long long)R_cap * ((p.V + kChunk<8> - 1) / kChunk<8>);
+    if (pieces < kSkipMinPieces) launch(greedy_argmax_kernel<false, 8>, kChunk<8>);
+    else if (pieces < kLongPieces) launch(greedy_argmax_kernel<true, 4>, kChunk<4>);
+    else launch(greedy_argmax_kernel<true, 8>, kChunk<8>);
     if ((rc = check_launch("greedy_argmax_kernel")) != FSR_OK) return rc;
     hipLaunchKernelGGL(greedy_decide_kernel, dim3((p.B + kThreads / 64 - 1) / (kThreads / 64)), dim3(kThreads), 0, s, draft_tokens, cu_t,
                        cu_d, d_rows, keys, accepted_len, n_emitted, emitted, p.B, p.S_max, R_cap);

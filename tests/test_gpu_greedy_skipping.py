@@ -17,8 +17,8 @@ def fsr():
     return f
 
 
-# rows are left out from 3072 pieces on: B * (S + 1) rows of ceil(V / 16384) pieces
-@pytest.mark.parametrize("B,V,S", [(384, 16384, 7), (192, 16385, 7), (171, 32767, 8), (511, 501, 5), (512, 2048, 5),(1, 4095, 70), (200, 4097, 8), (64, 30003, 6), (700, 100, 3),
+# rows are left out from 3072 pieces on: B * (S + 1) rows of ceil(V / 16384) pieces; below 12288 the pieces are of 8192 scores
+@pytest.mark.parametrize("B,V,S", [(384, 8193, 7), (1536, 8192, 7), (1535, 8191, 7), (768, 16385, 7),(384, 16384, 7), (192, 16385, 7), (171, 32767, 8), (511, 501, 5), (512, 2048, 5),(1, 4095, 70), (200, 4097, 8), (64, 30003, 6), (700, 100, 3),
                                    (2500, 100, 7), (1100, 4097, 7), (64, 150001, 6), (2048, 20, 7), (2047, 20, 7)])
 def test_rows_behind_a_mismatch(fsr, oracle, B, V, S):
     announce(f"greedy skipping B={B} V={V} S={S}")
