@@ -333,7 +333,8 @@ int fsr_spec_accept(const void* p_target, const void* p_draft, const int32_t* dr
  *   n_active   [1] int32, active_ids [B] int32: ascending requests with >= 1 kept row, -1 after
  *   payload_in nullable [N_cap, row_bytes]; payload_out [N_cap, row_bytes] gets the kept
  *              rows as a dense prefix (rows beyond it are not written).  row_bytes % 4 == 0.
- * No workspace is needed.
+ * No workspace is needed.  The offsets may be re-packed in place: new_cu_q may be cu_q, and new_q_lens the
+ * accepted_len of fsr_survivor_compact.
  */
 int fsr_prune_compact(const uint8_t* keep_mask, const int32_t* cu_q, int32_t* new_cu_q,
                       int32_t* new_q_lens, int32_t* src_row, int32_t* dst_row, int32_t* n_active,

@@ -178,18 +178,18 @@ __global__ __launch_bounds__(kScanThreads) void prune_compact_kernel(CompactArgs
     }
 }
 
-// out[src_row[r']] = compact[r'] for r' < n_new[0]; rows of `out` that no r' maps to keep their contents.
-template <typename VecT>
-__global__ __launch_bounds__(256) void scatter_rows_kernel(const VecT* __restrict__ compact, VecT* __restrict__ out,
-                                                           const int32_t* __restrict__ src_row,
-                                                           const int32_t* __restrict__ n_new, size_t row_vecs,
-                                                           int N_cap) {
+// Rows 0 .. n_new[0] - 1 of the compact side: out[r'] = in[src_row[r']] (GATHER), or out[src_row[r']] = in[r'], where rows of
+// `out` that no r' maps to keep their contents.
+template <typename VecT, bool GATHER>
+__global__ __launch_bounds__(256) void move_rows_kernel(const VecT* __restrict__ in, VecT* __restrict__ out,
+                                                        const int32_t* __restrict__ src_row, const int32_t* __restrict__ n_new,
+                                                        size_t row_vecs, int N_cap) {
     const int n = min(n_new[0], N_cap);
     for (int r = blockIdx.x; r < n; r += gridDim.x) {
         const int d = src_row[r];
         if (d < 0 || d >= N_cap) continue;
-        const VecT* src = compact + (size_t)r * row_vecs;
-        VecT* dst = out + (size_t)d * row_vecs;
+        const VecT* src = in + (size_t)(GATHER ? d : r) * row_vecs;
+        VecT* dst = out + (size_t)(GATHER ? r : d) * row_vecs;
         for (size_t v = (size_t)blockIdx.y * blockDim.x + threadIdx.x; v < row_vecs; v += (size_t)gridDim.y * blockDim.x)
             dst[v] = src[v];
     }
@@ -287,6 +287,27 @@ int launch_by_width(size_t row_bytes, const void* a, const void* b, F&& f) {
     return f(uint32_t{}, row_bytes / 4);
 }
 
+template <bool GATHER>
+int move_rows(const void* in, void* out, const int32_t* src_row, const int32_t* n_new, size_t row_bytes, int N_cap, hipStream_t s) {
+    return launch_by_width(row_bytes, in, out, [&](auto tag, size_t row_vecs) {
+        using VecT = decltype(tag);
+        const unsigned gy = (unsigned)std::min<size_t>(std::max<size_t>(1, (row_vecs + 255) / 256), 64);
+        const unsigned gx = (unsigned)std::min(N_cap, 65535);
+        hipLaunchKernelGGL((move_rows_kernel<VecT, GATHER>), dim3(gx, gy), dim3(256), 0, s, (const VecT*)in, (VecT*)out, src_row, n_new,
+                           row_vecs, N_cap);
+        return check_launch("move_rows_kernel");
+    });
+}
+
+struct Span {
+    const void* at;
+    size_t bytes;
+};
+bool overlap(const Span& a, const Span& b) {
+    const uintptr_t x = (uintptr_t)a.at, y = (uintptr_t)b.at;
+    return x && y && x < y + b.bytes && y < x + a.bytes;
+}
+
 }  // namespace
 }  // namespace fsr
 
@@ -311,9 +332,22 @@ int compact_call(const char* who, const uint8_t* keep_mask, const int32_t* accep
     hipStream_t s = (hipStream_t)stream;
     CompactArgs a{keep_mask, accepted_len, keep_out, cu_q, new_cu_q, new_q_lens, src_row, dst_row, n_active, active_ids, p->B, p->N_cap,
                   accepted_len ? 1 : p->suffix_close, nullptr, nullptr, 0, 0};
-    if (!payload_in || p->N_cap == 0) {
+    const size_t B = p->B, N = p->N_cap;
+    // The copying workgroups read the offsets, the mask (or lengths) and the payload while the first one writes the maps: where
+    // these share memory (a batch re-packed in place: new_cu_q is cu_q, new_q_lens accepted_len) the maps come first, and the
+    // rows in a launch behind them that reads nothing but src_row.
+    const Span reads[] = {{cu_q, (B + 1) * 4}, {keep_mask, N}, {accepted_len, B * 4}, {payload_in, N * row_bytes}};
+    const Span maps[] = {{new_cu_q, (B + 1) * 4}, {new_q_lens, B * 4}, {src_row, N * 4}, {dst_row, N * 4}, {n_active, 4}, {active_ids, B * 4}, {keep_out, N}};
+    bool shared = false;
+    for (const Span& r : reads) {
+        for (const Span& w : maps) shared |= overlap(r, w);
+        if (r.at != payload_in) shared |= overlap(r, Span{payload_out, N * row_bytes});
+    }
+    if (!payload_in || N == 0 || shared) {
         hipLaunchKernelGGL(prune_compact_kernel<uint32_t>, dim3(1), dim3(kScanThreads), 0, s, a);
-        return check_launch("prune_compact_kernel");
+        const int rc = check_launch("prune_compact_kernel");
+        if (rc != FSR_OK || !payload_in || N == 0) return rc;
+        return move_rows<true>(payload_in, payload_out, src_row, new_cu_q + p->B, row_bytes, p->N_cap, s);
     }
     a.in = payload_in;
     a.out = payload_out;
@@ -372,15 +406,7 @@ extern "C" int fsr_prune_scatter(const void* compact, const int32_t* src_row, co
     if (!compact || !src_row || !n_rows || !out) return fail(FSR_EINVAL, "fsr_prune_scatter: null pointer");
     if (row_bytes == 0 || row_bytes % 4 != 0) return fail(FSR_ESHAPE, "fsr_prune_scatter: row_bytes=%zu must be a positive multiple of 4", row_bytes);
     if (compact == out) return fail(FSR_EINVAL, "fsr_prune_scatter: cannot run in place");
-    hipStream_t s = (hipStream_t)stream;
-    return launch_by_width(row_bytes, compact, out, [&](auto tag, size_t row_vecs) {
-        using VecT = decltype(tag);
-        const unsigned gy = (unsigned)std::min<size_t>(std::max<size_t>(1, (row_vecs + 255) / 256), 64);
-        const unsigned gx = (unsigned)std::min(N_cap, 65535);
-        hipLaunchKernelGGL(scatter_rows_kernel<VecT>, dim3(gx, gy), dim3(256), 0, s, (const VecT*)compact, (VecT*)out,
-                           src_row, n_rows, row_vecs, N_cap);
-        return check_launch("scatter_rows_kernel");
-    });
+    return move_rows<false>(compact, out, src_row, n_rows, row_bytes, N_cap, (hipStream_t)stream);
 }
 
 extern "C" int fsr_survivor_mask(const int32_t* accepted_len, const int32_t* cu_q, uint8_t* keep_mask, int32_t B,

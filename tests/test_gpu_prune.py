@@ -136,3 +136,30 @@ def test_survivor_compact_equals_mask_then_compact(fsr, oracle, seed, B, maxlen)
     r3 = fsr.survivor_compact(dev(acc), dev(cu), N_cap)
     torch.cuda.synchronize()
     assert torch.equal(r3["src_row"], r["src_row"])
+
+
+@pytest.mark.parametrize("width", [4, 1025, 5000])  # words of a payload row; 0 bytes of it would not need the offsets
+@pytest.mark.parametrize("B,maxlen", [(1, 8), (37, 9), (1500, 9)])
+def test_offsets_replaced_in_place(fsr, oracle, B, maxlen, width):
+    """new_cu_q is cu_q itself, new_q_lens accepted_len itself: the payload rows must come from the offsets as they were."""
+    announce(f"prune in place B={B} width={width}")
+    rng = np.random.default_rng(B + width)
+    lens = rng.integers(1, maxlen + 1, size=B)
+    acc = np.minimum(rng.integers(-1, maxlen, size=B), lens - 1).astype(np.int32)
+    cu = workloads.exclusive_offsets(lens)
+    N = int(cu[-1])
+    keep = np.concatenate([np.arange(n) <= a for n, a in zip(lens, acc)]).astype(np.uint8)
+    pay = rng.integers(-1000, 1000, size=(N, width)).astype(np.int32)
+    ref = oracle.prune_compact(keep, cu, suffix_close=True, payload=pay)
+    n_new = int(ref["new_cu_q"][-1])
+    for survivors in (True, False):
+        cu_d, acc_d = dev(cu), dev(acc)
+        if survivors:
+            r = fsr.survivor_compact(acc_d, cu_d, N, payload=dev(pay), out=dict(new_cu_q=cu_d, new_q_lens=acc_d))
+        else:
+            r = fsr.prune_compact(dev(keep), cu_d, payload=dev(pay), out=dict(new_cu_q=cu_d))
+        torch.cuda.synchronize()
+        assert r["new_cu_q"] is cu_d
+        for name in ("new_cu_q", "new_q_lens", "src_row", "dst_row", "active_ids"):
+            assert np.array_equal(r[name].cpu().numpy(), ref[name]), name
+        assert np.array_equal(r["payload"].cpu().numpy()[:n_new], ref["payload"])
