@@ -6,8 +6,15 @@
 // synchronisation.  The optional payload gather is the only part that moves real bytes: its workgroups
 // (a window of output rows each) work the offsets out once more for themselves, which takes as long as
 // it takes the one that writes the maps, instead of waiting for that one in a second launch.
-// Measured, kernel time with rows of 8 KB, a scan and a gather in two launches / this: 64 requests 4.1 + 3.0 / 5.4 us, 256
-// requests 5.8 + 5.4 / 8.8 us; the chain of loads, scan and copy bounds it, not the bytes.
+// What bounds that is the chain of loads, scan and copy, so a call of up to 4096 rows gets one workgroup per compute unit
+// (255 beside the maps' own) and a small one a row to a workgroup; with more rows twice as many.  Where that is too much for
+// the workgroups the rows are moved by a second launch, which cuts wide ones across.
+// Measured, us a call, 45 % / 90 % of the rows kept, windows of at least 8 rows in up to 511 workgroups / this / in two launches:
+//   64 rows of 8 KB 6.5, 6.7 / 4.7, 4.9 / 6.2, 6.3;  700 7.0, 7.9 / 5.6, 6.7 / 6.6, 7.8;  1400 7.8, 9.1 / 7.4, 9.1 / 7.8, 9.3;
+//   64 of 16 KB 8.9, 9.1 / 5.0, 5.2 / 6.3, 6.4;  64 of 32 KB 13.6, 13.8 / 5.5, 5.9 / 6.4, 6.7;  20000 of 8 KB 42, 70 / 42, 70 / 47, 69.
+//   In two launches now: 3000 of 8 KB 10.4, 19.7 / 9.4, 16.3 (one launch of 255 10.2, 16.9, with 60 % kept 14.6 and in two 12.4);
+//   1400 of 16 KB 12.3, 17.2 / 9.7, 14.9;  64 of 64 KB 24.1, 24.3 / 6.8, 7.6;  64 of 513 KB, 80 % kept, 172 / 13.
+// 255 against 511 workgroups: 700 rows of 8 KB 5.6, 6.7 / 5.8, 8.3;  20000 rows of 4 KB 33.9, 39.5 / 26.5, 40.5.
 #include <algorithm>
 
 #include "common.hpp"
@@ -82,8 +89,15 @@ struct CompactArgs {
 };
 
 constexpr int kMaxWindow = 4096;
-constexpr int kMinWindow = 8;
-constexpr int kCopyGroups = 511;  // copying workgroups a call is cut into at most: as many as run at once, with the maps' own
+constexpr int kFewRows = 4096;  // up to so many rows one copying workgroup per compute unit, else as many as run at once
+
+// Whether a payload is copied by the launch that writes the maps: it saves the second launch, but copies at a workgroup's pace
+// and before anybody knows how many rows were kept (both sides measured at the top).
+constexpr size_t kOneLaunchBytes = 16 << 20, kOneLaunchRow = 32768;
+constexpr size_t kNarrowRow = 12288, kManyRows = 6144;  // many narrow rows: the second launch's workgroups per row cost more
+bool one_launch(size_t rows, size_t row_bytes) {
+    return (row_bytes <= kOneLaunchRow && rows * row_bytes <= kOneLaunchBytes) || (row_bytes <= kNarrowRow && rows > kManyRows);
+}
 
 // Workgroup 0 writes the maps; workgroup 1 + k copies the output rows k * window .. of the payload.
 template <typename VecT>
@@ -343,7 +357,7 @@ int compact_call(const char* who, const uint8_t* keep_mask, const int32_t* accep
         for (const Span& w : maps) shared |= overlap(r, w);
         if (r.at != payload_in) shared |= overlap(r, Span{payload_out, N * row_bytes});
     }
-    if (!payload_in || N == 0 || shared) {
+    if (!payload_in || N == 0 || shared || !one_launch(N, row_bytes)) {
         hipLaunchKernelGGL(prune_compact_kernel<uint32_t>, dim3(1), dim3(kScanThreads), 0, s, a);
         const int rc = check_launch("prune_compact_kernel");
         if (rc != FSR_OK || !payload_in || N == 0) return rc;
@@ -351,7 +365,7 @@ int compact_call(const char* who, const uint8_t* keep_mask, const int32_t* accep
     }
     a.in = payload_in;
     a.out = payload_out;
-    a.window = std::min(std::max(kMinWindow, p->N_cap / kCopyGroups + 1), kMaxWindow);
+    a.window = std::min(p->N_cap / (p->N_cap <= kFewRows ? 255 : 511) + 1, kMaxWindow);
     return launch_by_width(row_bytes, payload_in, payload_out, [&](auto tag, size_t row_vecs) {
         using VecT = decltype(tag);
         a.row_vecs = row_vecs;

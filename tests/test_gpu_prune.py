@@ -69,6 +69,17 @@ def test_survivor_windows(fsr, oracle, B, maxlen, width):
     assert np.array_equal(got[:n_new], ref["payload"]) and (got[n_new:] == -7).all()
 
 
+@pytest.mark.parametrize("N,width", [(255, 3), (256, 3), (4096, 8), (4097, 8), (512, 8192), (513, 8192), (5, 8193), (6144, 769), (6145, 769), (6145, 3073)])
+def test_copy_forms(fsr, oracle, N, width):
+    """Edges of the rules that deal the payload's rows out: windows of one row and of more, 4096 and 6144 rows, rows of 12 and 32 KB, 16 MB."""
+    announce(f"copy forms N={N} width={width}")
+    rng = np.random.default_rng(N + width)
+    cu = np.arange(0, N + 7, 7).clip(max=N).astype(np.int32)
+    pay = rng.integers(-2**31, 2**31 - 1, size=(N, width), dtype=np.int64).astype(np.int32)
+    for suffix_close in (True, False):
+        _compare(fsr, oracle, (rng.random(N) < 0.8).astype(np.uint8), cu, suffix_close, pay, N)
+
+
 @pytest.mark.parametrize("suffix_close", [True, False])
 @pytest.mark.parametrize("seed,B,maxlen,width", [(0, 1, 5, 4), (1, 37, 9, 6), (2, 512, 11, 64), (3, 2500, 4, 3), (4, 300, 0, 4)])
 def test_prune_random(fsr, oracle, suffix_close, seed, B, maxlen, width):
