@@ -175,8 +175,9 @@ int fsr_verify_attention_static(const void* q, const void* k_cache, const void* 
  * FSR_PATH_GENERIC, one workgroup per (request, KV head) for every other supported shape (fp32
  * inputs, D = 64, other page sizes, wider groups, larger batches): it needs no workspace and takes no
  * plan; keys are read once per KV head, but a batch of few or very uneven requests leaves compute
- * units idle.  With a workspace of fsr_attn_workspace_bytes the long contexts of a small bf16 batch are
- * shared by several workgroups.  Negative on invalid shapes.
+ * units idle.  With a workspace of fsr_attn_workspace_bytes (or the built-in one of
+ * fsr_verify_attention_static) the long contexts of a small bf16 batch are shared by several workgroups,
+ * whose fp32 sums are then added up in another order than without one.  Negative on invalid shapes.
  */
 #define FSR_PATH_GENERIC 0
 #define FSR_PATH_STREAM 1

@@ -192,7 +192,7 @@ PATH_GENERIC, PATH_STREAM = 0, 1
 
 
 def attn_path(*, B, N_cap, H_q, H_kv, D, P, max_pages, n_pages, dtype, out_dtype, max_q_len=0) -> int:
-    """fsr_attn_path: PATH_STREAM (the bandwidth kernel) or PATH_GENERIC (one workgroup per request and KV head, no scratch memory)."""
+    """fsr_attn_path: PATH_STREAM (the bandwidth kernel) or PATH_GENERIC (one workgroup per request and KV head)."""
     p = AttnParams(B=B, N_cap=N_cap, H_q=H_q, H_kv=H_kv, D=D, P=P, max_pages=max_pages, n_pages=n_pages,
                    dtype=_code(dtype), out_dtype=_code(out_dtype), scale=1.0, max_q_len=int(max_q_len),
                    max_workgroups=0, kv_layout=0)

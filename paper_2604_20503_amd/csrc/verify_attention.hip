@@ -28,7 +28,7 @@
 //     a share boundary leaves (reference, sum, accumulator) partials -- at most two per workgroup
 //     -- and the workgroup whose piece arrives last combines them, in the same launch.
 // Every other shape (fp32 inputs, D = 64, other page sizes, G > 16, B > 4096) is taken by
-// attend_items.hip, which needs no scratch memory.
+// attend_items.hip, which can do without scratch memory.
 #include <algorithm>
 #include <atomic>
 #include <map>
@@ -1887,14 +1887,13 @@ extern "C" int fsr_verify_attention_static(const void* q, const void* k_cache, c
     int rc = validate(p, "fsr_verify_attention_static");
     if (rc != FSR_OK) return rc;
     const Setup su = make_setup(*p, kStaticShares);
-    if (!su.fast)  // the other kernel uses no scratch buffer at all
-        return attention_call(q, k_cache, v_cache, nullptr, nullptr, false, block_tables, ctx_lens, cu_q, out, lse, p, nullptr, nullptr, 0,
-                              kStaticShares, stream, "fsr_verify_attention_static");
-    if (su.ws_bytes() > kStaticScratchBytes)
-        return fail(FSR_EWS, "fsr_verify_attention_static: these shapes need %zu bytes of scratch, the built-in buffer has %zu",
-                    su.ws_bytes(), kStaticScratchBytes);
-    void* ws = static_scratch();
-    if (!ws) return FSR_EHIP;
+    // (the other kernel's bf16 items are cut into pieces if there is scratch memory, as for fsr_verify_attention)
+    const size_t need = su.fast ? su.ws_bytes() : attend_items_workspace_bytes(*p);
+    if (need > kStaticScratchBytes)
+        return fail(FSR_EWS, "fsr_verify_attention_static: these shapes need %zu bytes of scratch, the built-in buffer has %zu", need,
+                    kStaticScratchBytes);
+    void* ws = need ? static_scratch() : nullptr;
+    if (need && !ws) return FSR_EHIP;
     return attention_call(q, k_cache, v_cache, nullptr, nullptr, false, block_tables, ctx_lens, cu_q, out, lse, p, nullptr, ws,
                           kStaticScratchBytes, kStaticShares, stream, "fsr_verify_attention_static");
 }

@@ -106,6 +106,23 @@ def test_items_in_pieces(fsr, oracle, H_q, H_kv, D, P, hint, scratch):
         assert (room == 0x55).all()
 
 
+@pytest.mark.parametrize("dtype,H_q,H_kv,D,P,ctx", [
+    ("bf16", 8, 2, 64, 16, [4100, 510, 1024, 2600]), ("bf16", 40, 4, 64, 8, [1023, 3000]), ("bf16", 17, 1, 128, 16, [8000]),
+    ("bf16", 32, 2, 128, 24, [2000] * 70), ("f32", 8, 2, 64, 16, [2000, 30])])
+def test_built_in_scratch_gives_the_same_bits(fsr, dtype, H_q, H_kv, D, P, ctx):
+    """fsr_verify_attention_static against fsr_verify_attention: items in pieces, too many of them for that, fp32."""
+    announce(f"items static {dtype} heads={H_q}/{H_kv} D={D} P={P} B={len(ctx)}")
+    rng = np.random.Generator(np.random.PCG64(H_q + D + len(ctx)))
+    x = make(rng, dtype, H_q, H_kv, D, P, ctx, [i % 3 for i in range(len(ctx))])
+    q, k, v = (dev(x[n], dtype == "bf16") for n in "qkv")
+    bt, c, cu = dev(x["bt"]), dev(x["ctx"]), dev(x["cu"])
+    outs, lses = ([torch.full(shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)] for shape in (q.shape, q.shape[:2]))
+    fsr.verify_attention(q, k, v, bt, c, None, cu, scale=0.1, out=outs[0], lse=lses[0], max_q_len=3)
+    fsr.verify_attention_static(q, k, v, bt, c, cu, scale=0.1, out=outs[1], lse=lses[1], max_q_len=3)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32)) and torch.equal(lses[0].view(torch.int32), lses[1].view(torch.int32))
+
+
 @pytest.mark.parametrize("H_q,H_kv,D,P,token_major", [(8, 2, 64, 16, False), (14, 2, 64, 24, True), (20, 1, 64, 1, False),
                                                       (6, 6, 128, 32, False), (34, 2, 128, 16, True), (80, 1, 128, 16, False)])
 def test_bf16_output(fsr, oracle, H_q, H_kv, D, P, token_major):
