@@ -631,11 +631,14 @@ Layout layout_of(const fsr_attn_params& p) {
     // Pieces of an item's keys, where a call has fewer items than the device has compute units.  Not more: one workgroup runs on
     // a compute unit at a time, and a second one waits for the first before it sends for anything.  D = 64, 32/8 heads, us of 3
     // layers with no pieces / up to 256 / 512 / 1024 workgroups: one request of 8192 tokens 164 / 66 / 66 / 66, 4 of 256 to 4096
-    // 89 / 62 / 62 / 62, 16 of 256 to 8192 194 / 132 / 143 / 174, 32 of 256 to 4096 128 / 128 / 144 / 176.
+    // 89 / 62 / 62 / 62, 16 of 256 to 8192 194 / 132 / 143 / 174, 32 of 256 to 4096 128 / 128 / 144 / 176.  On a stream that owns
+    // part of the device max_workgroups says how many units there are, us a layer with no pieces / up to 256 workgroups / up to the
+    // units owned: 32 units, 4 requests of 256 to 4096 37 / 76 / 35, 16 122 / 162 / 120, one of 8192 71 / 37 / 29; 128 units, 4 48 / 37 / 27.
     l.splits = 1;
     if (p.dtype == FSR_BF16 && l.groups == 1) {
         const long long keys = (long long)p.max_pages * p.P;
-        l.splits = (int)std::max(1LL, std::min({(long long)kMaxSplits, keys / kSplitKeys, kSplitGroups / items}));
+        const long long units = p.max_workgroups > 0 ? std::min<long long>(p.max_workgroups, kSplitGroups) : kSplitGroups;
+        l.splits = (int)std::max(1LL, std::min({(long long)kMaxSplits, keys / kSplitKeys, units / items}));
     }
     const size_t slots = (size_t)items * l.splits, row = (size_t)16 * l.mt;
     if (l.splits > 1) {

@@ -106,6 +106,21 @@ def test_items_in_pieces(fsr, oracle, H_q, H_kv, D, P, hint, scratch):
         assert (room == 0x55).all()
 
 
+@pytest.mark.parametrize("units,cut", [(0, True), (4, True), (3, False), (2, False)])
+def test_pieces_stay_within_the_callers_workgroups(fsr, units, cut):
+    """Two items on a stream that owns `units` compute units (0: the device): with fewer than four they are not cut, i.e. give the
+    bits of a call whose workspace is too small for pieces."""
+    announce(f"items max_workgroups={units}")
+    x = make(np.random.Generator(np.random.PCG64(17)), "bf16", 8, 2, 64, 16, [4000], [2])
+    q, k, v = (dev(x[n], True) for n in "qkv")
+    bt, c, cu, outs = dev(x["bt"]), dev(x["ctx"]), dev(x["cu"]), []
+    for ws in (None, torch.empty(256, dtype=torch.uint8, device="cuda")):
+        outs.append(torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda"))
+        fsr.verify_attention(q, k, v, bt, c, None, cu, scale=0.1, out=outs[-1], max_q_len=3, max_workgroups=units, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32)) != cut
+
+
 @pytest.mark.parametrize("dtype,H_q,H_kv,D,P,ctx", [
     ("bf16", 8, 2, 64, 16, [4100, 510, 1024, 2600]), ("bf16", 40, 4, 64, 8, [1023, 3000]), ("bf16", 17, 1, 128, 16, [8000]),
     ("bf16", 32, 2, 128, 24, [2000] * 70), ("f32", 8, 2, 64, 16, [2000, 30])])
