@@ -194,8 +194,8 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     const int first_lim = c + m0 / a.G;                           // last key the group's first row sees
     int kend = min(c + (m0 + rows - 1) / a.G + 1, kv_cap);  // keys any row of the group sees
     int kb0 = w * kTile;
-    if constexpr (SPLIT) {  // the piece's even share of their tiles
-        const long long n_tiles = (kend + kTile - 1) / kTile;
+    if (SPLIT && n_sp > 1) {  // the piece's even share of their tiles (at most 2^30 keys and eight pieces: the products fit 32 bits)
+        const unsigned n_tiles = (unsigned)(kend + kTile - 1) / kTile;
         kb0 += (int)(n_tiles * sp / n_sp) * kTile;
         if (sp + 1 < n_sp) kend = (int)(n_tiles * (sp + 1) / n_sp) * kTile;
     }
