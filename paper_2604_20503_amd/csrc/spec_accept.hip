@@ -564,10 +564,46 @@ __device__ __forceinline__ long long shfl_i64(long long v, int src) {
 // ---------------------------------------------------------------------------------------
 // decide: PROBS mode, and where the statistics have found the outcome: one wave per request, lane n tests draft n.  LOGITS mode
 // otherwise: one wave per draft (in rounds of the workgroup's waves, one more for the row behind the last draft), its lanes hold
-// the row pair's statistics, so that a test is one memory round trip and two reductions; a lane per draft folded them four at a
-// time, one round trip each (a call of 16 requests in bf16 45.7 -> 42.9 us, of 4 requests in fp32 36.7 -> 26.5).
+// the row pair's statistics, so that a test is one memory round trip and two reductions; or, where that would be many rounds
+// for rows of few pairs, a lane per draft that folds them four at a time, one round trip each (see decide_waves_of).
 // ---------------------------------------------------------------------------------------
+// The same by one lane on its own (every lane of the wave works on a different row): the pairs four at a time, all
+// eight loads of a batch in flight together, folded with a running maximum.
+__device__ __forceinline__ RowStat combine_stats_lane(const double* __restrict__ stat, int nc, const ExpConsts& ek) {
+    double mm = -INFINITY, z = 0.0;
+    for (int c0 = 0; c0 < nc; c0 += 4) {
+        double mc[4], sc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = min(c0 + u, nc - 1);
+            mc[u] = stat[c * 2];
+            sc[u] = stat[c * 2 + 1];
+        }
+        double mb = mc[0];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) mb = fmax(mb, c0 + u < nc ? mc[u] : -INFINITY);
+        if (mb > mm) {
+            z = mm == -INFINITY ? 0.0 : z * exp_softmax(mm - mb, ek);
+            mm = mb;
+        }
+        if (mm != -INFINITY) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (c0 + u < nc) z += sc[u] * exp_softmax(mc[u] - mm, ek);
+        }
+    }
+    return RowStat{mm, z};
+}
 constexpr int kDecideWaves = 12;
+// Waves of a request's workgroup (LOGITS mode, drafts not yet tested): twelve rows a round, or one wave with a lane per row.
+// Measured, us a call with a lane / a wave per draft: one round: 16 requests of 8 drafts x 128256 bf16 51.8 / 48.3, 4 of 4 x 152064
+// fp32 34.9 / 24.2, 2 of 8 x 32000 19.0 / 18.4; 32 pairs a row: two rounds, 8 of 12 x 128256 bf16 52.5 / 46.0, three, one of 24 31.4
+// / 28.8; 16 pairs, three rounds, 8 of 24 60.1 / 61.7; 8 pairs, vocabulary 32000: two rounds, 2 of 16 20.2 / 22.3, three, of 32
+// 22.4 / 28.8, six, of 64 27.9 / 43.5; one pair, one round, 60 of 11 x 4000 25.0 / 26.0.
+int decide_waves_of(int S_max, int pairs) {
+    const int rounds = (S_max + kDecideWaves) / kDecideWaves;
+    return (rounds == 1 && pairs > 4) || 8 * rounds <= pairs ? std::min(kDecideWaves, S_max + 1) : 1;
+}
 // What a wave finds out about a draft, or (test unused) the row behind the last one.
 struct DraftTest {
     long long t_row, d_row;
@@ -617,7 +653,7 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
             dec.m_t = st.m; dec.Z_t = st.Z;
             dec.m_d = sd.m; dec.Z_d = sd.Z;
         }
-    } else if constexpr (MODE == FSR_LOGITS) {
+    } else if (MODE == FSR_LOGITS && n_waves > 1) {
         __shared__ DraftTest s_test[kDecideWaves];
         for (int n0 = 0; n0 < t_i && n == d_i; n0 += n_waves) {
             const int k = n0 + w;
@@ -666,13 +702,21 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
             const int k = n0 + lane;
             const bool live = k < d_i;
             long long tr = 0, dr = 0;
+            RowStat st{0.0, 1.0}, sd{0.0, 1.0};
             int x = 0;
             bool ok = true;
             if (live) {
                 tr = t_rows ? t_rows[t0 + k] : t0 + k;
                 dr = d_rows ? d_rows[d0 + k] : d0 + k;
                 x = min(max(draft_tokens[dr], 0), V - 1);
-                ok = (double)u_accept[dr] * (double)to_float(p_draft[(size_t)dr * V + x]) < (double)to_float(p_target[(size_t)tr * V + x]);
+                const double u = (double)u_accept[dr];
+                if constexpr (MODE == FSR_LOGITS) {
+                    st = combine_stats_lane(ws.stat_t + (size_t)(t0 + k) * nsg * 2, nsg, ek);
+                    sd = combine_stats_lane(ws.stat_d + (size_t)(d0 + k) * nsg * 2, nsg, ek);
+                }
+                const double px = prob_of<MODE>(to_float(p_target[(size_t)tr * V + x]), T, st.m, st.Z, ek);
+                const double qx = prob_of<MODE>(to_float(p_draft[(size_t)dr * V + x]), T, sd.m, sd.Z, ek);
+                ok = u * qx < px;
             }
             const unsigned long long rejected = __builtin_amdgcn_ballot_w64(live && !ok);
             const int first = rejected ? (int)__builtin_ctzll(rejected) : 64;
@@ -682,6 +726,8 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
                 dec.kind = kCaseResidual;
                 dec.t_row = shfl_i64(tr, first);
                 dec.d_row = shfl_i64(dr, first);
+                dec.m_t = shfl_f64(st.m, first); dec.Z_t = shfl_f64(st.Z, first);
+                dec.m_d = shfl_f64(sd.m, first); dec.Z_d = shfl_f64(sd.Z, first);
             }
         }
     }
@@ -1042,7 +1088,7 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
                            draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T);
         if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
     }
-    const int decide_waves = MODE == FSR_LOGITS && !ws.skip ? std::min(kDecideWaves, p.S_max + 1) : 1;
+    const int decide_waves = MODE == FSR_LOGITS && !ws.skip ? decide_waves_of(p.S_max, n_stat_groups_of(p.V, ws.stat_group)) : 1;
     hipLaunchKernelGGL((accept_decide_kernel<MODE, RT>), dim3(p.B), dim3(64 * decide_waves), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t,
                        cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T);
     if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
