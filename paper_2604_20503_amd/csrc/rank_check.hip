@@ -6,19 +6,28 @@
 // scores strictly above the draft's own.  That is HBM streaming with a trivial reduction.
 //   rank_check_kernel   one launch, one workgroup per draft: it streams the row with 16-byte loads (at any alignment: the
 //                       hardware takes vectors at element addresses), the next four of every thread in flight while four
-//                       are counted, and writes the draft's rank and its row's mask itself.  Few drafts get the largest
-//                       workgroups, so that a compute unit has enough loads in flight with one or two of them, many drafts
-//                       small ones, so that all run at once.
+//                       are counted, and writes the draft's rank and its row's mask itself.  Long rows and those of few
+//                       drafts get 1024 threads, others, which a workgroup is through with in a few rounds, 512.
 //   rank_init_kernel    rank[d] = 0 for drafts with an active row and a valid token id, -1 for drafts without a row, V for
 //                       ids outside the vocabulary;
 //   rank_count_kernel   rank[d] += #{v in chunk : z[row][v] > z[row][draft]}, grid (32 KB piece of a row) x (draft), a piece's
 //                       loads all in flight together, one integer atomic per workgroup;
 //   rank_mask_kernel    keep[row] from the ranks (first row of a request always kept): three launches, for a few hundred
-//                       drafts with long rows, where some compute units would have two rows to stream and others one (see
-//                       the rule at the launch).
-// Measured, kernel time of 1400 drafts x 128256 bf16 scores: 60.3 us; in three launches 4.2 + 59.3 + 4.8.
-// us a rank check, compaction and restore, one launch / three: 70 drafts x 128256 bf16 24.4 / 31.6, 576 x 32000 bf16 23.8 /
-// 30.4, 290 x 128256 fp32 41.0 / 38.7, 540 x 152063 fp32 71.5 / 71.5, 1100 x 128256 fp32 107 / 110, 2100 x 152064 fp32 213 / 217.
+//                       rows of 384 KB or more, which one workgroup each would take too long, or on too few of the compute
+//                       units, to read (see the rule at the launch).
+// What bounds it is reading the rows once there are enough of them, and one row's stream through one workgroup where there are
+// few.  Drafts may have lost their rows to an earlier check, and the caller's capacities need not say so.
+// Measured, us a call in a graph, caches cold, drafts of the call and rows that are live, three launches / one of 1024 threads /
+// of 512:
+// (256 threads: 4032 all of 256 KB 160, of 513 KB 315; 2054, 508 live of 513 KB 75; 3976 all of 64 KB 43.5, 355 live 12.1, there with 512 13.9)
+//   64 KB rows (32000 bf16): 73, 57 live 8.0 / 4.8 / 4.9;  718 all 16.2 / 12.3 / 11.2;  718, 43 live 9.3 / 5.9 / 5.2;  3976 all 47.4 /
+//   51.0 / 41.7;  128 KB rows (32000 fp32): 493 all 17.3 / 13.4 / 13.4;  4006 all 82.3 / 79.9 / 79.1;  4006, 205 live 19.9 / 19.5 / 13.6;
+//   256 KB rows (128256 bf16): 83 all 11.2 / 10.5 / 10.7;  279, 69 live 10.9 / 9.5 / 10.2;  471 all 26.3 / 22.9 / 23.0;  716 all 35.4 / 32.0 /
+//   33.2;  716, 45 live 11.5 / 13.5 / 13.4;  1427 all 63.2 / 58.4 / 60.2;  1427, 416 live 26.3 / 24.6 / 26.1;  2040 all 85.0 / 79.9 / 82.7;
+//   513 KB rows (128256 fp32): 79 all 15.6 / 16.0 / 16.8;  79, 19 live 9.0 / 12.3 / 14.3;  289, 93 live 15.1 / 23.2 / 23.1;  491 all 48.7 /
+//   41.2 / 41.8;  491, 123 live 19.0 / 24.4 / 24.8;  722 all 66.6 / 58.9 / 61.2;  722, 183 live 24.3 / 26.0 / 26.1;  990, 247 live 30.2 / 28.5 /
+//   43.3;  1431 all 121 / 111 / 115;  2054 all 168 / 163 / 167;  2054, 508 live 51.5 / 47.2 / 53.6.
+#include <algorithm>
 #include <cstdint>
 
 #include "common.hpp"
@@ -31,7 +40,11 @@ constexpr int kLoads = 4;       // 16-byte loads of a thread that are counted to
 constexpr int kThreads = 256;   // of the three launches
 constexpr int kPieceLoads = 8;  // 16-byte loads of a thread, all in flight together
 constexpr int kChunkBytes = kThreads * kPieceLoads * 16;  // a workgroup's piece of a row
-constexpr long long kSplitMinBytes = 96LL << 20;  // score bytes from which a few hundred rows are cut into pieces
+constexpr int kPiecesRow = 384 << 10;  // bytes of a row from which few rows are cut into pieces
+constexpr int kPiecesRows = 512;       // ... in a call that can have fewer live rows than this, and no more drafts than
+constexpr int kPiecesDrafts = 1536;    // (the launches before and after look at every draft)
+constexpr int kLongRow = 192 << 10;    // bytes of a row from which it gets 1024 threads, ...
+constexpr int kFewDrafts = 512;        // ... and drafts up to which it does in any case
 constexpr int kMaskRows = 256;  // rows without a draft that one of the further workgroups looks after
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
@@ -282,10 +295,9 @@ extern "C" int fsr_topk_rank_check(const void* logits, const int32_t* draft_toke
     a.logits = logits; a.draft_tokens = draft_tokens; a.cu_q = cu_q; a.cu_d = cu_d; a.rank = rank; a.keep = keep_mask;
     a.B = p->B; a.V = p->V; a.K = p->K; a.N_cap = p->N_cap; a.D_cap = p->D_cap;
     const bool f32 = p->dtype == FSR_F32;
-    const long long bytes = (long long)p->D_cap * p->V * (f32 ? 4 : 2);
-    // Between one and two rows a compute unit, the units with two end the one launch late; from some 100 MB on that costs more
-    // than the two further launches (both sides measured at the top).
-    if (p->D_cap > 256 && p->D_cap < 512 && bytes >= kSplitMinBytes) {
+    const long long row_bytes = (long long)p->V * (f32 ? 4 : 2);
+    // (rows of logits that exist bound the live drafts; both sides measured at the top)
+    if (p->D_cap > 0 && row_bytes >= kPiecesRow && std::min(p->D_cap, p->N_cap) < kPiecesRows && p->D_cap <= kPiecesDrafts) {
         hipLaunchKernelGGL(rank_init_kernel, dim3((p->D_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
         const int piece = kChunkBytes / (f32 ? 4 : 2);
         const dim3 pieces((p->V + piece - 1) / piece, p->D_cap);
@@ -295,15 +307,11 @@ extern "C" int fsr_topk_rank_check(const void* logits, const int32_t* draft_toke
         return check_launch("fsr_topk_rank_check");
     }
     const dim3 grid((unsigned)p->D_cap + (p->N_cap + kMaskRows - 1) / kMaskRows);
-    // workgroups of a size at which as many as there are drafts run at once (2048 threads a compute unit), if any
-    const int threads = p->D_cap <= 512 ? 1024 : p->D_cap <= 1024 ? 512 : 256;
-#define FSR_RANK(T) hipLaunchKernelGGL((T), grid, dim3(threads), 0, s, a)
-    if (threads == 1024) {
-        if (f32) FSR_RANK((rank_check_kernel<float, 1024>)); else FSR_RANK((rank_check_kernel<uint16_t, 1024>));
-    } else if (threads == 512) {
-        if (f32) FSR_RANK((rank_check_kernel<float, 512>)); else FSR_RANK((rank_check_kernel<uint16_t, 512>));
+#define FSR_RANK(T, THREADS) hipLaunchKernelGGL((rank_check_kernel<T, THREADS>), grid, dim3(THREADS), 0, s, a)
+    if (row_bytes >= kLongRow || p->D_cap <= kFewDrafts) {
+        if (f32) FSR_RANK(float, 1024); else FSR_RANK(uint16_t, 1024);
     } else {
-        if (f32) FSR_RANK((rank_check_kernel<float, 256>)); else FSR_RANK((rank_check_kernel<uint16_t, 256>));
+        if (f32) FSR_RANK(float, 512); else FSR_RANK(uint16_t, 512);
     }
 #undef FSR_RANK
     return check_launch("fsr_topk_rank_check");
