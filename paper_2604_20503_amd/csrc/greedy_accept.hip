@@ -12,12 +12,19 @@
 // them as a 64-bit key (value made order-preserving << 32 | ~index) into the row's key with one atomic max, which yields the largest
 // value and, among equals, the lowest index.  Most workgroups of a large call are those of rows that are left out, and each costs two
 // memory round trips before it may leave: the largest calls take 64 KB pieces.  With fewer, smaller pieces tell of a mismatch sooner.
-// Measured, us a call with the compaction behind it, 1-8 drafts of which about 40 % match:
-//   all rows read / rows left out (64 KB pieces), by the pieces the call can hold: vocabulary 128256: 32 requests (2304) 27 / 30, 64
-//   (4608) 43 / 36; 32000: 192 requests (3456) 34.5 / 32.3; 152064: 128 requests (11520) 79 / 47; 128256: 384 requests 209 / 88;
-//   rows left out, pieces of 16 KB (256 threads) / 32 / 64 KB: 128256: 64 requests (4608) 40.0 / 34.6 / 36.3, 100 (7200) 37.6 / 36.6 /
-//   40.3, 128 (9216) 42.2 / 41.9 / 45.4, 160 (11520) 48.7 / 47.7 / 47.9, 384 (27648) 101 / 101 / 85; 152064: 250 (22500) 78 / 78 / 68;
-//   32000: 192 (3456) 37.5 / 31.7 / 32.2, 380 (6840) 42.8 / 39.5 / 41.1.
+// Telling costs too: the words of 32 requests share a cache line, and every atomic on one waits for those before it.  Below a bad
+// guess thousands of scores, in every piece, are larger than the draft's: such a piece (scores of several of its waves are) first
+// merges its key and tells only if the row's key of before was not above the draft's already.  A near miss is told at once.
+// Measured, us a call, 1-8 drafts of which 40 % match and the others are their row's second-best token / a random one:
+//   all rows read, by pieces of 64 KB the call can hold, pieces of 16 KB (256 threads) / 32 / 64 KB: vocabulary 32000: 1 request (18)
+//   7.4 / 7.3 / 8.1, 4 (72) 8.9 / 8.0 / 8.7, 24 (432) 10.9 / 9.8 / 10.8, 48 (864) 13.3 / 11.7 / 12.1;  64000: 1 (36) 8.1 / 7.7 / 8.4, 16 (576)
+//   12.8 / 11.1 / 11.4;  128256: 1 (72) 7.4 / 7.5 / 8.2, 2 (144) 10.4 / 9.0 / 8.8, 8 (576) 12.0 / 9.8 / 9.2, 16 (1152) 16.3 / 13.7 / 13.2, 24
+//   (1728) 22.4 / 18.9 / 18.6;
+//   all rows read in pieces of 32 KB / rows left out, near misses, bad guesses (told by every piece): 128256: 48 requests (3456) 29 / 23.1,
+//   26.7 (51), all match 29 / 31;  64 (4608) 35 / 24.9, 27.0 (51), all match 35 / 39;  100 (7200) 50 / 29.7, 30.5 (40);  152064: 128 (11520)
+//   76 / 39.7, 40.0 (51);  128256: 384 (27648) 167 / 67.4, 65.8 (68).  (Told after the merge by every piece: 64 requests 26.3, 25.0.)
+//   rows left out, pieces of 16 KB / 32 / 64 KB, with the compaction: 128256: 64 requests (4608) 40.0 / 34.6 / 36.3, 100 (7200) 37.6 / 36.6 /
+//   40.3, 160 (11520) 48.7 / 47.7 / 47.9, 384 (27648) 101 / 101 / 85; 152064: 250 (22500) 78 / 78 / 68; 32000: 380 (6840) 42.8 / 39.5 / 41.1.
 // At 64 requests 50 MB are read: what is left is the chain of workgroups, not the bytes.  Workgroups that go through a request's
 // positions one after the other read less but wait more: 45 us at 64 requests, 139 us at 384.
 #include <climits>
@@ -37,6 +44,8 @@ template <int QUADS>
 constexpr int kChunk = kRowThreads * QUADS * 4;  // scores of a piece
 constexpr int kLongPieces = 12288;    // 64 KB pieces a call must be able to hold for pieces of that size where rows are left out
 constexpr int kSkipMinPieces = 3072;  // 64 KB pieces a call must be able to hold for rows behind a mismatch to be left out
+constexpr int kShortRow = 98304;      // where none is left out: scores of a row up to which its pieces are of 32 KB, ...
+constexpr int kFewPieces = 128;       // ... and 64 KB pieces up to which a call's are
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)), __aligned__(4))) uint32_t gu32x4;  // at any element of a row
@@ -164,14 +173,25 @@ __global__ __launch_bounds__(kRowThreads) void greedy_argmax_kernel(
     load_piece(z, v0, V, x);
     // the key of the draft this row verifies: larger than any if there is none, smaller for an id outside the vocabulary
     unsigned long long drafted = ~0ull;
+    float guess = -INFINITY;
     if (SKIP && d0 >= 0 && j < d_i && d0 + j < cu_d[B]) {
         const int t = draft_tokens[d_rows ? d_rows[d0 + j] : d0 + j];
-        drafted = t < 0 || t >= V ? 0ull : make_key(__builtin_bit_cast(uint32_t, z[t]), t);
+        if (t >= 0 && t < V) guess = z[t];
+        drafted = t < 0 || t >= V ? 0ull : make_key(__builtin_bit_cast(uint32_t, guess), t);
     }
     const unsigned long long best = piece_key(x, v0, s_top, s_at);
     if (threadIdx.x == 0) {
-        if (SKIP && best > drafted) atomicMin(first_miss + i, j);
-        atomicMax(keys + r, best);
+        int above = 0;  // waves of the piece with a score above the draft's own
+        if (SKIP && best > drafted) {
+#pragma unroll
+            for (int k = 0; k < kRowThreads / 64; ++k) above += !(s_top[k] <= guess);
+        }
+        if (above > 1 && blockIdx.x != 0) {  // (a wait for the key of before, which a near miss is spared)
+            if (atomicMax(keys + r, best) <= drafted) atomicMin(first_miss + i, j);
+        } else {
+            if (SKIP && best > drafted) atomicMin(first_miss + i, j);
+            atomicMax(keys + r, best);
+        }
     }
 }
 
@@ -237,7 +257,8 @@ int greedy_accept_launch(const float* target, const int32_t* draft_tokens, const
                            d_rows, keys, accepted_len, p.B, p.V, p.S_max, R_cap);
     };
     const long long pieces = (long long)R_cap * ((p.V + kChunk<8> - 1) / kChunk<8>);
-    if (pieces < kSkipMinPieces) launch(greedy_argmax_kernel<false, 8>, kChunk<8>);
+    if (pieces < kSkipMinPieces && (p.V <= kShortRow || pieces <= kFewPieces)) launch(greedy_argmax_kernel<false, 4>, kChunk<4>);
+    else if (pieces < kSkipMinPieces) launch(greedy_argmax_kernel<false, 8>, kChunk<8>);
     else if (pieces < kLongPieces) launch(greedy_argmax_kernel<true, 4>, kChunk<4>);
     else launch(greedy_argmax_kernel<true, 8>, kChunk<8>);
     if ((rc = check_launch("greedy_argmax_kernel")) != FSR_OK) return rc;

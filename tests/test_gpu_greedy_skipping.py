@@ -17,9 +17,11 @@ def fsr():
     return f
 
 
-# rows are left out from 3072 pieces on: B * (S + 1) rows of ceil(V / 16384) pieces; below 12288 the pieces are of 8192 scores
+# rows are left out from 3072 pieces on: B * (S + 1) rows of ceil(V / 16384) pieces; below 12288 the pieces are of 8192 scores.  Where
+# none is, pieces are of 8192 scores for rows of up to 98304 and for calls of up to 128 pieces
 @pytest.mark.parametrize("B,V,S", [(384, 8193, 7), (1536, 8192, 7), (1535, 8191, 7), (768, 16385, 7),(384, 16384, 7), (192, 16385, 7), (171, 32767, 8), (511, 501, 5), (512, 2048, 5),(1, 4095, 70), (200, 4097, 8), (64, 30003, 6), (700, 100, 3),
-                                   (2500, 100, 7), (1100, 4097, 7), (64, 150001, 6), (2048, 20, 7), (2047, 20, 7)])
+                                   (2500, 100, 7), (1100, 4097, 7), (64, 150001, 6), (2048, 20, 7), (2047, 20, 7),
+                                   (383, 16384, 7), (64, 98309, 6), (3, 98304, 8), (3, 98305, 8), (2, 98305, 8), (1, 8191, 3), (1, 24577, 3)])
 def test_rows_behind_a_mismatch(fsr, oracle, B, V, S):
     announce(f"greedy skipping B={B} V={V} S={S}")
     rng = np.random.default_rng(V)
