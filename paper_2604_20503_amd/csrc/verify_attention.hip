@@ -522,6 +522,8 @@ constexpr float kHeadWhole = 8.0f, kHeadPiece = 14.0f;
 // (32 requests of 256 to 4096 tokens) and 1.85 (28 with log-normal contexts) it loses 1 to 6 %.
 constexpr float kLineMargin = 1.55f;
 __device__ int aligned_share(const FastArgs& a, int mt_max, int b, Segment& sg, bool& have) {
+    // The plan kernel and every stream kernel have to find the same pieces: what is rounded once is said, nothing else is fused.
+#pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
     int q0 = 0, ql = 0, c = 0, nt = 0;
     float cost = 1.0f;
@@ -538,10 +540,12 @@ __device__ int aligned_share(const FastArgs& a, int mt_max, int b, Segment& sg, 
     if (__builtin_amdgcn_ballot_w64(ql > rows_per_group(a, mt_max)) != 0) return 0;
     // (approximate reciprocals: any count of pieces is a valid one, and all workgroups find the same)
     auto pieces = [](int tiles, float tiles_per_cost, float time) {
-        const float len = time * tiles_per_cost - kHeadPiece;
+#pragma clang fp contract(off)
+        const float len = __builtin_fmaf(time, tiles_per_cost, -kHeadPiece);
         if (tiles <= 0) return 0;
         if ((float)tiles <= len + (kHeadPiece - kHeadWhole)) return 1;
-        return max(1, min((int)__builtin_ceilf((float)tiles * __builtin_amdgcn_rcpf(fmaxf(len, 1.0f)) - 1e-4f), (tiles + kAlignedTiles - 1) / kAlignedTiles));
+        const float n = __builtin_ceilf(__builtin_fmaf((float)tiles, __builtin_amdgcn_rcpf(fmaxf(len, 1.0f)), -1e-4f));
+        return max(1, min((int)n, (tiles + kAlignedTiles - 1) / kAlignedTiles));
     };
     float work = (float)nt * cost, line = nt > 0 ? ((float)nt + (float)a.seg_tiles) * cost : 0.0f;
     float longest = nt > 0 ? ((float)nt + kHeadWhole) * cost : 0.0f;

@@ -77,6 +77,31 @@ def test_a_piece_of_an_item_per_share(fsr, oracle, H_q, H_kv, ctx, spec, max_wor
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
 
 
+@pytest.mark.parametrize("B", [1, 2, 7, 12, 13, 16, 25, 40, 64])
+def test_plan_and_call_cut_items_alike(fsr, B):
+    """Where items are cut follows from quotients rounded at many places, by the plan kernel and by each stream kernel for itself:
+    40 batches of random lengths, on all and on some workgroups, give the same bits with a plan and without."""
+    announce(f"plan and call cut alike B={B}")
+    rng = np.random.Generator(np.random.PCG64(B))
+    H_q, H_kv, pages = 16, 4, 1200
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    k, v = (torch.randn((pages, H_kv, 16, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    for case in range(40):
+        hi = int(np.exp(rng.uniform(np.log(600), np.log(6000))))
+        ctx = np.minimum(rng.integers(0, hi, size=B) if case % 2 else np.exp(rng.normal(6.5, 1.2, size=B)), 10000).astype(np.int32)
+        spec = rng.integers(0, 10, size=B).astype(np.int32)
+        q = torch.randn((int((spec + 1).sum()), H_q, 128), generator=gen, device="cuda").to(torch.bfloat16)
+        bt = dev(rng.integers(0, pages, size=(B, int((ctx + spec).max()) // 16 + 1)).astype(np.int32))
+        c, cu = dev(ctx), dev(workloads.exclusive_offsets(spec + 1))
+        kw = dict(scale=0.09, max_q_len=10, max_workgroups=int(rng.choice([0, 0, 4 * B + 3])))
+        outs = []
+        for plan in (None, fsr.attn_plan(q, k, bt, c, cu, **kw)):
+            outs.append(torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda"))
+            fsr.verify_attention(q, k, v, bt, c, None, cu, out=outs[-1], plan=plan, **kw)
+        assert torch.isfinite(outs[0]).all() and torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32)), (case, ctx, spec)
+
+
+
 def test_segment_count_stays_within_the_plan(fsr):
     """Offsets past N_cap, one share: more segments than the buffer has records.  The share's count is the number of records
     written, and nothing is written behind the buffer.  (Only the plan is built here: no attention call reads it.)"""
