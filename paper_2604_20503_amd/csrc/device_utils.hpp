@@ -52,12 +52,6 @@ __device__ __forceinline__ int wave_max_i(int v) {
     return v;
 }
 
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-
 // Inclusive scan across the 64 lanes of a wave.
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v) {
@@ -69,6 +63,18 @@ __device__ __forceinline__ T wave_inclusive_scan(T v) {
     }
     return v;
 }
+
+// The same by DPP: no round trip through LDS per step.
+__device__ __forceinline__ int wave_inclusive_scan_dpp(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // lanes 1, 2, 4, 8 to the left in a row of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // lane 15 of a row to the next row
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // lane 31 to the upper half
+    return v;
+}
+__device__ __forceinline__ int wave_sum_i(int v) { return __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(v), kWave - 1); }
 
 // Count one more arrival on a 64-bit word that holds (call id << 16 | count).  A word left by another
 // call (or never written) counts as zero, so the memory it lives in needs no clearing between calls

@@ -30,25 +30,16 @@ constexpr int kScanThreads = 1024;
 // buffers of kScanThreads / 64 values; `turn` says which one is used (a buffer is written again two scans later at the
 // earliest, with a barrier in between).  Lanes move data by DPP and every wave adds up the waves before it for itself: one
 // barrier and no LDS round trips but one.
-__device__ __forceinline__ int dpp_inclusive_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // lanes 1, 2, 4, 8 to the left in a row of 16
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // lane 15 of a row to the next row
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // lane 31 to the upper half
-    return v;
-}
 __device__ __forceinline__ int block_exclusive_scan(int v, int (*smem)[kScanThreads / 64], int& turn, int& total) {
     constexpr int kW = kScanThreads / 64;
     static_assert(kW == 16, "the waves' sums are one row of lanes");
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int inc = dpp_inclusive_scan(v);
+    const int inc = wave_inclusive_scan_dpp(v);
     int* sums = smem[turn];
     turn ^= 1;
     if (lane == 63) sums[w] = inc;
     __syncthreads();
-    const int before = dpp_inclusive_scan(lane < kW ? sums[lane] : 0);
+    const int before = wave_inclusive_scan_dpp(lane < kW ? sums[lane] : 0);
     total = __builtin_amdgcn_readlane(before, kW - 1);
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const int base = wu > 0 ? __builtin_amdgcn_readlane(before, max(wu - 1, 0)) : 0;

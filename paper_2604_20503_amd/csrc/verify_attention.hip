@@ -512,6 +512,7 @@ struct ShareWalker {
 // 8192 326 / 210; 16 requests of 1024 to 4096 tokens and 2 to 9 rows, seven batches, 343 to 384 / 314 to 357; 30 of 100 to 600
 // 214 / 180.
 constexpr int kAlignedMaxB = 64;   // a request per lane
+constexpr int kCandidatesB = 8;    // requests up to which the candidates are tried side by side
 // Items are not cut into shorter pieces: a cut costs its count, write-through and combine.  Least pieces of 16 / 24 / 40 tiles:
 // one request of 1200 tokens 136 / 139 / 155, of 8192 233 / 210 / 216, 4 layers of 4 requests of 200 to 2000 97 / 99 / 115.
 constexpr int kAlignedTiles = 24;
@@ -561,12 +562,24 @@ __device__ int aligned_share(const FastArgs& a, int mt_max, int b, Segment& sg, 
     // no candidate up to the margin will do if the margin itself does not
     if (most < longest && (long long)wave_sum_i(pieces(nt, rate, most)) * a.H_kv > a.nb) return 0;
     float time = lane == 63 ? longest * 1.0001f : least * fast_exp2(__builtin_amdgcn_logf(longest / least) * ((float)lane / 63.0f));
-    int sum = 0;
-    for (int i = 0; i < a.B; ++i)
-        sum += pieces(__builtin_amdgcn_readlane(nt, i), __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rate), i)), time);
-    const unsigned long long fits = __builtin_amdgcn_ballot_w64((long long)sum * a.H_kv <= a.nb);
-    if (fits == 0) return 0;
-    time = __shfl(time, __builtin_ctzll(fits), 64);
+    if (a.B <= kCandidatesB) {  // every lane a candidate, request by request
+        int sum = 0;
+        for (int i = 0; i < a.B; ++i)
+            sum += pieces(__builtin_amdgcn_readlane(nt, i), __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rate), i)), time);
+        const unsigned long long fits = __builtin_amdgcn_ballot_w64((long long)sum * a.H_kv <= a.nb);
+        if (fits == 0) return 0;
+        time = __shfl(time, __builtin_ctzll(fits), 64);
+    } else {  // every lane a request, candidates by bisection: a longer time never takes more pieces
+        int lo = 0, hi = 64;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            const float t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, time), mid));
+            if ((long long)wave_sum_i(pieces(nt, rate, t)) * a.H_kv <= a.nb) hi = mid;
+            else lo = mid + 1;
+        }
+        if (lo == 64) return 0;
+        time = __shfl(time, lo, 64);
+    }
     if (time > most) return 0;
     const int k = pieces(nt, rate, time);
     const int upto = wave_inclusive_scan(k * a.H_kv);
