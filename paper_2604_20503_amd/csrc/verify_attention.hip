@@ -1391,8 +1391,8 @@ __global__ __launch_bounds__(kThreads) void attn_stream_kernel(FastArgs a) {
 // trip after they begin: a workgroup reads the record of its first segment, which also carries the
 // page ids of the first two tiles of each of its waves.
 //
-// Plan buffer (int32 words): header record, then one record per share (its first segment), then the
-// further segments of all shares, in the order of their items.  A record is kRecInts words:
+// Plan buffer (int32 words): header record, then one record per share (its first segment; of calls that may get the schedule of
+// single pieces in the order of the workgroups that take them), then the further segments of all shares, in the order of their items.  A record is kRecInts words:
 //   0 request  1 KV head  2 context  3 first row  4 rows of the request  5 first suffix position of
 //   the row group  6 positions in the group  7,8 tile range  9 flags (1 = whole item, 2 = cut)
 //   10,11 first / last share of the cut item  12 partial slot  13 segments of this share (first
@@ -1468,12 +1468,15 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(FastArgs a, int mt_
         plan[0] = kPlanMagic;
     }
     const int lane = threadIdx.x & 63;
-    const int s = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    const int s = blockIdx.x * kWaves + (threadIdx.x >> 6);  // place of the share's first record
     if (s >= a.nb) return;
+    // the records of a call of few items are read in the order of its workgroups: of the cost line's shares too, one die is to
+    // hold consecutive ones
+    const int b = a.aligned ? share_of_block(s, a.nb) : s;
     int n = 0;
-    if (s < nbx) {
+    if (b < nbx) {
         wk.set_shares(total, nbx);
-        wk.b = s; wk.x = wk.share_start(s); wk.x1 = wk.share_start(s + 1);
+        wk.b = b; wk.x = wk.share_start(b); wk.x1 = wk.share_start(b + 1);
         // number of the item that holds the share's start (items are numbered along the cost line)
         int o0;
         {

@@ -101,6 +101,28 @@ def test_plan_and_call_cut_items_alike(fsr, B):
         assert torch.isfinite(outs[0]).all() and torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32)), (case, ctx, spec)
 
 
+@pytest.mark.parametrize("max_workgroups", [20, 32, 0])
+def test_neighbouring_shares_of_the_cost_line_stay_on_one_die(fsr, max_workgroups):
+    """A batch of few items for which the cost line is cut all the same (more rows than the bound says): workgroup w takes the share
+    that it takes without a plan, i.e. the workgroups w, w + 8, w + 16, ... of one die take consecutive shares."""
+    announce(f"plan places workgroups={max_workgroups}")
+    b = workloads.make_batch(2, with_probs=False, H_q=32, H_kv=8, ctx_lens=np.array([3000, 2900]), spec_lens=np.array([8, 8]))
+    q, k = dev(b.q, True), dev(b.k_cache, True)
+    plan = fsr.attn_plan(q, k, dev(b.block_tables), dev(b.ctx_lens), dev(b.cu_q), scale=b.scale, max_q_len=2, max_workgroups=max_workgroups)
+    torch.cuda.synchronize()
+    rec = plan.view(torch.int32).view(-1, 32).cpu().numpy()
+    nb, used = max_workgroups or 256, rec[0, 2]
+    assert rec[1:1 + nb, 13].max() > 1  # the cost line: shares of several segments
+    cuts = 0
+    places = [w for die in range(8) for w in range(die, nb, 8)]  # workgroups in the order of their shares
+    for share, w in enumerate(places):
+        r = rec[1 + w]
+        assert r[13] == 0 or share < used
+        if r[13] > 0 and r[9] & 2:
+            assert r[12] // 2 == share and r[10] <= share <= r[11]
+            cuts += 1
+    assert cuts > nb // 4
+
 
 def test_segment_count_stays_within_the_plan(fsr):
     """Offsets past N_cap, one share: more segments than the buffer has records.  The share's count is the number of records
