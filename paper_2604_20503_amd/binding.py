@@ -14,6 +14,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfaser_verify.so")
+_MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 _lib = None
 _calls = None  # entry point -> its native call object
 
@@ -86,13 +87,14 @@ def library_path() -> str:
 
 
 def load_library():
-    """Load ``libfaser_verify.so``; raises if it has not been built."""
+    """Load ``libfaser_verify.so`` and the helper that hands arguments to it; raises if either has not been built."""
     global _lib, _calls
     if _lib is None:
-        if not os.path.exists(_LIB_PATH):
-            raise FileNotFoundError(
-                f"{_LIB_PATH} is missing: build it with `python paper_2604_20503_amd/build.py` "
-                "(there is no CPU or PyTorch fallback for the verification kernels)")
+        for path in (_LIB_PATH, _MARSHAL_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(
+                    f"{path} is missing: build it with `python paper_2604_20503_amd/build.py` "
+                    "(there is no CPU or PyTorch fallback for the verification kernels)")
         lib = ctypes.CDLL(_LIB_PATH)
         lib.fsr_last_error.restype = ctypes.c_char_p
         lib.fsr_version.restype = ctypes.c_char_p
@@ -339,7 +341,6 @@ def verify_attention_kv8(q, k_cache, v_cache, k_scale, v_scale, block_tables, ct
 
 def kv_append(k_new, v_new, k_cache, v_cache, block_tables, ctx_lens, cu_q, *, kv_layout=KV_HEAD_MAJOR):
     """fsr_kv_append: store the call's key / value rows [N_cap, H_kv, D] into the paged caches (in place)."""
-    lib = load_library()
     B = ctx_lens.shape[0]
     if kv_layout == KV_TOKEN_MAJOR:
         n_pages, P, H_kv, D = k_cache.shape
@@ -357,7 +358,6 @@ def kv_append(k_new, v_new, k_cache, v_cache, block_tables, ctx_lens, cu_q, *, k
 
 def kv_append_kv8(k_new, v_new, k_cache, v_cache, k_scale, v_scale, block_tables, ctx_lens, cu_q, *, kv_layout=KV_HEAD_MAJOR):
     """fsr_kv_append_kv8: quantise the call's bf16 key / value rows to E4M3 and store them into the uint8 caches."""
-    lib = load_library()
     B = ctx_lens.shape[0]
     p = _attn_params(k_new, k_cache, block_tables, B, k_new.dtype, 1.0, 0, 0, kv_layout)
     if v_new.shape != k_new.shape or v_cache.shape != k_cache.shape or k_cache.dtype != torch.uint8 or v_cache.dtype != torch.uint8:
@@ -414,7 +414,6 @@ def prune_compact(keep_mask, cu_q, *, suffix_close=True, payload=None, payload_o
                   N_cap=None):
     """fsr_prune_compact.  Returns dict(new_cu_q, new_q_lens, src_row, dst_row, n_active, active_ids[, payload]).
     With accepted_len (and N_cap) it is fsr_survivor_compact and keep_mask an optional output."""
-    lib = load_library()
     B = cu_q.shape[0] - 1
     if N_cap is None:
         N_cap = keep_mask.shape[0]
@@ -456,7 +455,6 @@ def prune_compact(keep_mask, cu_q, *, suffix_close=True, payload=None, payload_o
 
 def topk_rank_check(logits, draft_tokens, cu_q, cu_d, *, K, rank=None, keep_mask=None):
     """fsr_topk_rank_check.  logits [N_cap, V] fp32 or bf16; returns (rank [D_cap] int32, keep_mask [N_cap] uint8)."""
-    lib = load_library()
     N_cap, V = logits.shape
     D_cap = draft_tokens.shape[0]
     B = cu_q.shape[0] - 1
@@ -474,7 +472,6 @@ def topk_rank_check(logits, draft_tokens, cu_q, cu_d, *, K, rank=None, keep_mask
 
 def prune_restore(compact, dst_row, *, pad_word=0, restored=None, has_value=None):
     """fsr_prune_restore.  Returns (restored [N, ...], has_value [N] uint8)."""
-    lib = load_library()
     N = dst_row.shape[0]
     row_shape = tuple(compact.shape[1:])
     if restored is None:

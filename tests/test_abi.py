@@ -127,3 +127,12 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "_LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(FileNotFoundError):
         binding.load_library()
+
+
+def test_missing_argument_helper_fails_loudly(monkeypatch, tmp_path):
+    from paper_2604_20503_amd import binding
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_LIB_PATH", __file__)  # any file that is there: the helper is looked for before it is loaded
+    monkeypatch.setattr(binding, "_MARSHAL_PATH", str(tmp_path / "nope.so"))
+    with pytest.raises(FileNotFoundError, match="nope.so is missing: build it"):
+        binding.load_library()
