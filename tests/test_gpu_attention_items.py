@@ -106,6 +106,74 @@ def test_items_in_pieces(fsr, oracle, H_q, H_kv, D, P, hint, scratch):
         assert (room == 0x55).all()
 
 
+@pytest.mark.parametrize("D,P", [(64, 16), (128, 32)])
+def test_items_in_pieces_in_a_graph(fsr, D, P):
+    """A captured call whose items are cut, replayed over caches that change, with eager calls of another batch on the same
+    workspace between the replays: every replay gives the bits of an eager call on a workspace of its own."""
+    announce(f"items in pieces, graph D={D}")
+    rng = np.random.Generator(np.random.PCG64(D))
+    x = make(rng, "bf16", 8, 2, D, P, [4100, 30, 1500, 2600], [2, 0, 1, 3])
+    q, k, v = (dev(x[n], True) for n in "qkv")
+    bt, c, cu = dev(x["bt"]), dev(x["ctx"]), dev(x["cu"])
+    need = fsr.attn_workspace_bytes(B=4, N_cap=q.shape[0], H_q=8, H_kv=2, D=D, P=P, max_pages=bt.shape[1], n_pages=k.shape[0],
+                                    dtype=torch.bfloat16, out_dtype=torch.float32, max_q_len=4)
+    assert need > 0
+    room = [torch.full((need,), 0x55, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    out, other, want = (torch.zeros(q.shape, dtype=torch.float32, device="cuda") for _ in range(3))
+    c2 = dev(np.array([2000, 4000, 0, 700], np.int32))
+
+    def call(ctx, into, workspace):
+        fsr.verify_attention(q, k, v, bt, ctx, None, cu, scale=0.1, out=into, max_q_len=4, workspace=workspace)
+
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        call(c, out, room[0])
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            call(c, out, room[0])
+        for turn in range(4):
+            v.copy_(torch.randn(v.shape, device="cuda"))
+            out.fill_(float("nan"))
+            g.replay()
+            call(c2, other, room[0])
+            call(c, want, room[1])
+            torch.cuda.synchronize()
+            assert torch.isfinite(want).all() and torch.equal(out.view(torch.int32), want.view(torch.int32)), turn
+    torch.cuda.synchronize()
+    call(c, want, room[0])  # the calls of the other stream are done: its workspace may be used here
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("D,P", [(64, 16), (128, 32)])
+@pytest.mark.parametrize("bad", [(np.inf,), (-np.inf,), (np.nan,), (np.inf, -np.inf)])
+def test_values_that_are_not_finite_in_pieces(fsr, oracle, D, P, bad):
+    """V that is not finite on both sides of where an item of 4104 keys is cut into eight, and at a drafted token in the last piece:
+    the rows that see the key carry the value in that element, all else is untouched; +Inf and -Inf from two pieces make NaN."""
+    announce(f"items in pieces D={D} V={bad}")
+    rng = np.random.Generator(np.random.PCG64(12))
+    ctx, spec = [4100, 900], [3, 2]
+    x = make(rng, "bf16", 4, 1, D, P, ctx, spec)
+    ref, _ = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=4, H_kv=1, D=D, P=P, dtype="bf16",
+                                     scale=float(np.float32(1.0 / np.sqrt(D))))
+    tiles = (4104 + 31) // 32
+    code = lambda b: np.uint16(np.float32(b).view(np.uint32) >> 16)  # noqa: E731
+    want = ref.copy()
+    for d, at in ((3, 32 * (tiles // 8) - 1), (9, 32 * (tiles // 8)), (20, 32 * (tiles * 5 // 8)), (41, ctx[0] + 2)):
+        x["v"][x["bt"][0, at // P], 0, at % P, d] = code(bad[0])
+        first = max(0, at - ctx[0])
+        if len(bad) > 1:  # the other value in the first tile, i.e. in another piece
+            x["v"][x["bt"][0, 7 // P], 0, 7 % P, d] = code(bad[1])
+            want[0:first, :, d] = bad[1]
+        want[first:4, :, d] = bad[0] if len(bad) == 1 else np.nan
+    out, _, _, _ = run(fsr, oracle, x, "bf16", 4, 1, D, P, hint=4)
+    o = out.cpu().numpy()
+    odd = ~np.isfinite(want)
+    assert np.array_equal(o[odd], want[odd].astype(np.float32), equal_nan=True)
+    np.testing.assert_allclose(o[~odd], want[~odd], rtol=0, atol=1e-5 * np.abs(ref).max())
+
+
 @pytest.mark.parametrize("units,cut", [(0, True), (4, True), (3, False), (2, False)])
 def test_pieces_stay_within_the_callers_workgroups(fsr, units, cut):
     """Two items on a stream that owns `units` compute units (0: the device): with fewer than four they are not cut, i.e. give the
