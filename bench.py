@@ -203,6 +203,9 @@ def kernel_figures(b, st, times_us):
     row_bytes = b.H_q * b.D * 2
     compact_bytes = b.N + 4 * (b.B + 1) + 4 * (2 * b.N + 3 * b.B) + b.N + 2 * n_new * row_bytes
     rank_bytes = int(d.sum()) * 4 * b.V
+    # the forms that the library chooses for these sizes
+    one_launch = (row_bytes <= 32768 and b.N * row_bytes <= 16 << 20) or (row_bytes <= 12288 and b.N > 6144)
+    pieces = 4 * b.V >= 384 << 10 and int(d.sum()) < 512
 
     def fig(us, nbytes, launches, note):
         gbs = nbytes / us / 1e3
@@ -245,10 +248,12 @@ def kernel_figures(b, st, times_us):
     return {
         **extra,
         "spec_accept": fig(times_us["accept"], accept_bytes, 2, "accept_decide_kernel + accept_sample_kernel"),
-        "survivor_compact": fig(times_us["compact"], compact_bytes, 1,
-                                f"prune_compact_kernel; {n_new} of {b.N} rows of {row_bytes} bytes survive"),
-        "topk_rank_check": fig(times_us["rank"], rank_bytes, 1,
-                               "rank_check_kernel over the target rows, K = 10; not part of the timed step"),
+        "survivor_compact": fig(times_us["compact"], compact_bytes, 1 if one_launch else 2,
+                                ("prune_compact_kernel" if one_launch else "prune_compact_kernel + move_rows_kernel") +
+                                f"; {n_new} of {b.N} rows of {row_bytes} bytes survive"),
+        "topk_rank_check": fig(times_us["rank"], rank_bytes, 3 if pieces else 1,
+                               ("rank_init + rank_count + rank_mask" if pieces else "rank_check_kernel") +
+                               " over the target rows, K = 10; not part of the timed step"),
     }
 
 

@@ -567,7 +567,7 @@ __device__ __forceinline__ long long shfl_i64(long long v, int src) {
 // the row pair's statistics, so that a test is one memory round trip and two reductions; or, where that would be many rounds
 // for rows of few pairs, a lane per draft that folds them four at a time, one round trip each (see decide_waves_of).
 // ---------------------------------------------------------------------------------------
-// The same by one lane on its own (every lane of the wave works on a different row): the pairs four at a time, all
+// combine_stats by one lane on its own (every lane of the wave works on a different row): the pairs four at a time, all
 // eight loads of a batch in flight together, folded with a running maximum.
 __device__ __forceinline__ RowStat combine_stats_lane(const double* __restrict__ stat, int nc, const ExpConsts& ek) {
     double mm = -INFINITY, z = 0.0;

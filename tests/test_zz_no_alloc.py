@@ -54,7 +54,7 @@ def test_static_scratch_entry_point_matches_workspace_entry_point(oracle):
                                            D=b.D, P=b.P, dtype=b.dtype, scale=b.scale)
         check_attention(outs[1], o_ref, "bf16", b.N)
     # shapes whose scratch would not fit are refused before any launch... none exist for the built kernels:
-    # every stream-kernel shape needs at most the built-in size; the generic path needs no scratch
+    # every stream-kernel shape needs at most the built-in size; the generic path a few MB for the pieces of bf16 items, fp32 none
     g = B.AttnParams(B=2, N_cap=4, H_q=8, H_kv=2, D=64, P=16, max_pages=4, n_pages=8, dtype=B.F32, out_dtype=B.F32, scale=0.1,
                      max_q_len=2, max_workgroups=0, kv_layout=0)
     assert lib.fsr_verify_attention_static(None, None, None, None, None, None, None, None, ctypes.byref(g), stream) == -1
