@@ -14,6 +14,9 @@
 //   64 of 16 KB 8.9, 9.1 / 5.0, 5.2 / 6.3, 6.4;  64 of 32 KB 13.6, 13.8 / 5.5, 5.9 / 6.4, 6.7;  20000 of 8 KB 42, 70 / 42, 70 / 47, 69.
 //   In two launches now: 3000 of 8 KB 10.4, 19.7 / 9.4, 16.3 (one launch of 255 10.2, 16.9, with 60 % kept 14.6 and in two 12.4);
 //   1400 of 16 KB 12.3, 17.2 / 9.7, 14.9;  64 of 64 KB 24.1, 24.3 / 6.8, 7.6;  64 of 513 KB, 80 % kept, 172 / 13.
+// Requests of many rows, 70 % kept up to the first that is not, all mask bytes looked at / up to that row (and the copying workgroups
+// not going through rows that they do not take): 64 requests of 20 to 40 rows 11.0 / 8.4, with 8 KB rows 13.3 / 8.8, 250 12.6 / 10.8,
+// 19.6 / 15.4, 250 of 100 to 120 31 / 22, 43 / 24.
 // 255 against 511 workgroups: 700 rows of 8 KB 5.6, 6.7 / 5.8, 8.3;  20000 rows of 4 KB 33.9, 39.5 / 26.5, 40.5.
 #include <algorithm>
 
@@ -46,16 +49,18 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int (*smem)[kScanThre
     return base + inc - v;
 }
 
-// Whether rows r0 .. r1 - 1 (mask bytes) are kept; the bytes of eight rows are sent for together.
+// Whether rows r0 .. r1 - 1 (mask bytes) are kept, until f says that no further one matters; the bytes of eight rows are sent
+// for together.
 template <typename F>
 __device__ __forceinline__ void for_kept(const uint8_t* __restrict__ keep, int r0, int r1, F&& f) {
-    for (int r = r0; r < r1; r += 8) {
+    bool more = true;
+    for (int r = r0; r < r1 && more; r += 8) {
         uint8_t k[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) k[u] = keep[min(r + u, r1 - 1)];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (r + u < r1) f(r + u, k[u] != 0);
+            if (r + u < r1) more = f(r + u, k[u] != 0);
     }
 }
 
@@ -115,6 +120,7 @@ __global__ __launch_bounds__(kScanThreads) void prune_compact_kernel(CompactArgs
                 for_kept(a.keep, r0, r1, [&](int, bool k) {
                     kept += k && open;
                     open = open && (k || !a.suffix_close);
+                    return open;
                 });
             }
         }
@@ -129,23 +135,30 @@ __global__ __launch_bounds__(kScanThreads) void prune_compact_kernel(CompactArgs
             }
         }
         const bool wanted = i < B && (maps || (off < lo + a.window && off + kept > lo));
-        if (wanted) {
-            int o = off;
-            auto put = [&](int r, bool k) {
-                if (maps) {
+        if (wanted && (a.accepted_len || a.suffix_close)) {  // the request's first rows
+            if (maps) {
+                for (int r = r0; r < r1; ++r) {
+                    const bool k = r - r0 < kept;
                     if (a.keep_out) a.keep_out[r] = k ? 1 : 0;
+                    if (k) a.src_row[off + (r - r0)] = r;
+                    a.dst_row[r] = k ? off + (r - r0) : -1;
+                }
+            } else {
+                const int o1 = (int)min((long long)off + kept, lo + a.window);
+                for (int o = (int)max((long long)off, lo); o < o1; ++o) src_of[o - lo] = r0 + (o - off);
+            }
+        } else if (wanted) {
+            int o = off;
+            for_kept(a.keep, r0, r1, [&](int r, bool k) {
+                if (maps) {
                     if (k) a.src_row[o] = r;
                     a.dst_row[r] = k ? o : -1;
                 } else if (k && o >= lo && o < lo + a.window) {
                     src_of[o - lo] = r;
                 }
                 o += k;
-            };
-            if (a.accepted_len || a.suffix_close) {
-                for (int r = r0; r < r1; ++r) put(r, r - r0 < kept);
-            } else {
-                for_kept(a.keep, r0, r1, put);
-            }
+                return true;
+            });
         }
         row_carry += tile_rows;
         act_carry += tile_act;

@@ -81,6 +81,21 @@ def test_copy_forms(fsr, oracle, N, width):
 
 
 @pytest.mark.parametrize("suffix_close", [True, False])
+@pytest.mark.parametrize("drop", [0.0, 0.02, 0.3])
+@pytest.mark.parametrize("copies,width", [(1, 4), (1, 1025), (17, 3), (17, 1024)])
+def test_requests_of_many_rows(fsr, oracle, copies, width, drop, suffix_close):
+    """Requests around the multiples of 8 rows, which are read together, up to 49; 374 rows, and 6358, which take one launch or two by the size of a row."""
+    announce(f"many rows copies={copies} width={width} drop={drop} suffix_close={suffix_close}")
+    lens = np.tile([0, 1, 7, 8, 9, 15, 16, 17, 24, 31, 32, 33, 47, 48, 49, 2, 3, 0, 20, 2, 10], copies)
+    cu = workloads.exclusive_offsets(lens)
+    N = int(cu[-1])
+    assert N == 374 * copies
+    rng = np.random.default_rng(width + copies)
+    pay = rng.integers(-1000, 1000, size=(N, width)).astype(np.int32)
+    _compare(fsr, oracle, (rng.random(N) >= drop).astype(np.uint8), cu, suffix_close, pay, N)
+
+
+@pytest.mark.parametrize("suffix_close", [True, False])
 @pytest.mark.parametrize("seed,B,maxlen,width", [(0, 1, 5, 4), (1, 37, 9, 6), (2, 512, 11, 64), (3, 2500, 4, 3), (4, 300, 0, 4)])
 def test_prune_random(fsr, oracle, suffix_close, seed, B, maxlen, width):
     announce(f"prune_random seed={seed} B={B} suffix_close={suffix_close}")
