@@ -13,8 +13,8 @@
 //   rank_count_kernel   rank[d] += #{v in chunk : z[row][v] > z[row][draft]}, grid (32 KB piece of a row) x (draft), a piece's
 //                       loads all in flight together, one integer atomic per workgroup;
 //   rank_mask_kernel    keep[row] from the ranks (first row of a request always kept): three launches, for a few hundred
-//                       rows of 384 KB or more, which one workgroup each would take too long, or on too few of the compute
-//                       units, to read (see the rule at the launch).
+//                       rows of 384 KB or more, a few dozen of 320 KB or a few of 288, which one workgroup each would take too
+//                       long, or on too few of the compute units, to read (see pieces_below).
 // What bounds it is reading the rows once there are enough of them, and one row's stream through one workgroup where there are
 // few.  Drafts may have lost their rows to an earlier check, and the caller's capacities need not say so.
 // Measured, us a call in a graph, caches cold, drafts of the call and rows that are live, three launches / one of 1024 threads /
@@ -24,6 +24,9 @@
 //   51.0 / 41.7;  128 KB rows (32000 fp32): 493 all 17.3 / 13.4 / 13.4;  4006 all 82.3 / 79.9 / 79.1;  4006, 205 live 19.9 / 19.5 / 13.6;
 //   256 KB rows (128256 bf16): 83 all 11.2 / 10.5 / 10.7;  279, 69 live 10.9 / 9.5 / 10.2;  471 all 26.3 / 22.9 / 23.0;  716 all 35.4 / 32.0 /
 //   33.2;  716, 45 live 11.5 / 13.5 / 13.4;  1427 all 63.2 / 58.4 / 60.2;  1427, 416 live 26.3 / 24.6 / 26.1;  2040 all 85.0 / 79.9 / 82.7;
+//   304 KB rows (152064 bf16), three launches / one: 2 requests of 1 to 4 drafts 7.8 / 8.7, 4, half of them live, 8.2 / 9.1, 8 all 9.3 / 8.7, 16
+//   all 10.9 / 9.6;  340 KB (170000 bf16): 2 requests 7.8 / 9.1, 16 all 10.2 / 10.7, half live 8.8 / 10.1, 24 all 12.3 / 11.3;  380 KB: 2 requests
+//   7.9 / 9.8, 16 all 10.5 / 11.2, half live 9.0 / 11.5, 24 all 13.1 / 12.6;
 //   513 KB rows (128256 fp32): 79 all 15.6 / 16.0 / 16.8;  79, 19 live 9.0 / 12.3 / 14.3;  289, 93 live 15.1 / 23.2 / 23.1;  491 all 48.7 /
 //   41.2 / 41.8;  491, 123 live 19.0 / 24.4 / 24.8;  722 all 66.6 / 58.9 / 61.2;  722, 183 live 24.3 / 26.0 / 26.1;  990, 247 live 30.2 / 28.5 /
 //   43.3;  1431 all 121 / 111 / 115;  2054 all 168 / 163 / 167;  2054, 508 live 51.5 / 47.2 / 53.6.
@@ -40,9 +43,10 @@ constexpr int kLoads = 4;       // 16-byte loads of a thread that are counted to
 constexpr int kThreads = 256;   // of the three launches
 constexpr int kPieceLoads = 8;  // 16-byte loads of a thread, all in flight together
 constexpr int kChunkBytes = kThreads * kPieceLoads * 16;  // a workgroup's piece of a row
-constexpr int kPiecesRow = 384 << 10;  // bytes of a row from which few rows are cut into pieces
-constexpr int kPiecesRows = 512;       // ... in a call that can have fewer live rows than this, and no more drafts than
-constexpr int kPiecesDrafts = 1536;    // (the launches before and after look at every draft)
+// Live rows that a call can have, by the bytes of a row, below which its rows are cut into pieces, if it has no more drafts than
+// kPiecesDrafts (the launches before and after look at every draft).
+int pieces_below(long long row_bytes) { return row_bytes >= 384 << 10 ? 512 : row_bytes >= 320 << 10 ? 48 : row_bytes >= 288 << 10 ? 12 : 0; }
+constexpr int kPiecesDrafts = 1536;
 constexpr int kLongRow = 192 << 10;    // bytes of a row from which it gets 1024 threads, ...
 constexpr int kFewDrafts = 512;        // ... and drafts up to which it does in any case
 constexpr int kMaskRows = 256;  // rows without a draft that one of the further workgroups looks after
@@ -297,7 +301,7 @@ extern "C" int fsr_topk_rank_check(const void* logits, const int32_t* draft_toke
     const bool f32 = p->dtype == FSR_F32;
     const long long row_bytes = (long long)p->V * (f32 ? 4 : 2);
     // (rows of logits that exist bound the live drafts; both sides measured at the top)
-    if (p->D_cap > 0 && row_bytes >= kPiecesRow && std::min(p->D_cap, p->N_cap) < kPiecesRows && p->D_cap <= kPiecesDrafts) {
+    if (p->D_cap > 0 && std::min(p->D_cap, p->N_cap) < pieces_below(row_bytes) && p->D_cap <= kPiecesDrafts) {
         hipLaunchKernelGGL(rank_init_kernel, dim3((p->D_cap + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a);
         const int piece = kChunkBytes / (f32 ? 4 : 2);
         const dim3 pieces((p->V + piece - 1) / piece, p->D_cap);

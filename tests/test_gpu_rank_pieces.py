@@ -1,5 +1,5 @@
 """Rank check at the edges of its pieces (8192 fp32 / 16384 bf16 scores; of a workgroup that takes a row 8192 to 32768), of the
-rules that choose between three launches and one (rows of 384 KB, 512 rows, 1536 drafts) and between its workgroup sizes (rows of
+rules that choose between three launches and one (rows of 384 KB and 512 rows, of 320 KB and 48, of 288 KB and 12; 1536 drafts) and between its workgroup sizes (rows of
 192 KB), and of the wave's search for a draft's request (64 requests, 64 x 64 requests, runs of requests without drafts),
 bit-exact against the oracle."""
 import numpy as np
@@ -54,6 +54,7 @@ def check(oracle, spec, q_len, V, dtype, seed):
 @pytest.mark.parametrize("dtype,V,n,drafts", [
     ("f32", 98304, 128, 511), ("f32", 98303, 128, 511), ("f32", 98304, 128, 512), ("f32", 98305, 75, 300), ("f32", 100003, 16, 1),
     ("bf16", 196608, 100, 400), ("bf16", 196607, 100, 400), ("bf16", 196615, 128, 511), ("bf16", 196608, 128, 512),
+    ("f32", 81920, 12, 47), ("f32", 81919, 12, 47), ("bf16", 163840, 12, 48), ("bf16", 147456, 3, 11), ("bf16", 147457, 3, 12), ("f32", 73727, 3, 11),
     ("f32", 49151, 64, 257), ("f32", 49152, 64, 257), ("bf16", 98304, 64, 256), ("bf16", 98303, 64, 255)])
 def test_both_sides_of_the_launch_rules(oracle, dtype, V, n, drafts):
     announce(f"rank rules {dtype} V={V} drafts={drafts}")
@@ -61,7 +62,8 @@ def test_both_sides_of_the_launch_rules(oracle, dtype, V, n, drafts):
     spec[:drafts - spec.sum()] += 1
     N, D = check(oracle, spec, spec + 1, V, dtype, V + drafts)
     assert D == drafts and N == drafts + n
-    three = V * (4 if dtype == "f32" else 2) >= 384 << 10 and min(N, D) < 512
+    row = V * (4 if dtype == "f32" else 2) >> 10
+    three = min(N, D) < (512 if row >= 384 else 48 if row >= 320 else 12 if row >= 288 else 0)
     print("three launches" if three else "one launch")
 
 
