@@ -25,7 +25,9 @@
 // All masses are accumulated in fp64 so that the chosen token matches a sequential fp64
 // scan except when u * R lies within rounding of a CDF step.
 #include <algorithm>
+#include <cfloat>
 #include <climits>
+#include <cmath>
 
 #include "common.hpp"
 #include "device_utils.hpp"
@@ -53,6 +55,19 @@ struct Decision {
     int kind;         // kCase*
     int n;            // accepted drafts
 };
+// LOGITS mode, how the rows' masses in a draw are formed, in units that are each row's own: exp(z / T) where the rows' references
+// allow it (direct), else exp(z / T - m).  A direct row takes logits from `lowest` on as they are; one below that is masked
+// if exp(z / T - m) is 0 in fp64, and hardly ever anything else.
+struct RowScale {
+    float lowest;
+    float masked;  // below this a logit of a direct row is masked whatever the roundings
+};
+struct DrawScale {
+    RowScale t, d;
+    double ratio;  // one unit of the draft row's masses in those of the target row
+    int direct;
+    int unused;
+};
 
 struct Workspace {
     Decision* dec;       // [B]
@@ -60,6 +75,7 @@ struct Workspace {
     double* mass_tgt;    // [B, n_chunks]
     double* stat_t;      // [R_t_cap, n_stat_groups, 2]  (LOGITS)
     double* stat_d;      // [R_d_cap, n_stat_groups, 2]
+    DrawScale* scale;    // [B] (LOGITS)
     unsigned int* arrivals;  // [B] chunk workgroups of the request that have finished (zeroed by decide)
     int stat_group;          // chunks per (reference, sum) pair in this call (set at launch)
     // LOGITS mode, while the statistics of a large call are made (the memory is that of the chunk masses, which come
@@ -90,8 +106,10 @@ size_t carve(const fsr_accept_params& p, char* base, Workspace* w) {
         const size_t nsg = nc;  // room for one pair per chunk; a call folds 1, 2, 4 or 8 chunks into a pair
         tmp.stat_t = (double*)take(B * (size_t)(p.S_max + 1) * nsg * 2 * sizeof(double));
         tmp.stat_d = (double*)take(B * (size_t)p.S_max * nsg * 2 * sizeof(double));
+        tmp.scale = (DrawScale*)take(B * sizeof(DrawScale));
     } else {
         tmp.stat_t = tmp.stat_d = nullptr;
+        tmp.scale = nullptr;
     }
     if (w) *w = tmp;
     return off;
@@ -110,47 +128,35 @@ __global__ __launch_bounds__(kThreads) void accept_clear_kernel(Workspace ws, in
 // Rows are fp32, or bf16 stored as 16-bit patterns (the upper half of an fp32).
 __device__ __forceinline__ float to_float(float x) { return x; }
 __device__ __forceinline__ float to_float(uint16_t x) { return __builtin_bit_cast(float, (uint32_t)x << 16); }
-// May four consecutive values starting at a multiple of four be fetched with one vector load?
-__device__ __forceinline__ bool row_vec_ok(const float* row) { return ((uintptr_t)row & 15) == 0; }
-__device__ __forceinline__ bool row_vec_ok(const uint16_t* row) { return ((uintptr_t)row & 7) == 0; }
-
-// Four consecutive values of a row starting at token e (bounds-checked: `fill` stands for tokens past the
-// vocabulary; vector load when the row is aligned for it).
-__device__ __forceinline__ void load_quad(const float* __restrict__ row, int e, int V, bool vec, float (&x)[4],
-                                          float fill = 0.0f) {
-    if (vec && e + 3 < V) {
-        const float4 t = *reinterpret_cast<const float4*>(row + e);
-        x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
-    } else {
+// Four consecutive values of a row, wherever they start: the hardware takes vectors that are aligned to their elements only,
+// and most rows of an odd vocabulary start in the middle of one.  Against element by element for such rows, vocabulary
+// 152063, 1 to 7 drafts, us a call: PROBS 16 requests 23.2 / 17.0, 128 55.3 / 29.0, 384 120 / 83; LOGITS 16 in bf16 58 / 41.5, 128
+// in bf16 350 / 182, 384 in fp32 476 / 375.
+typedef __attribute__((__vector_size__(16), __aligned__(4))) float row_f32x4;
+typedef __attribute__((__vector_size__(8), __aligned__(2))) uint16_t row_u16x4;
+template <bool NT = false>  // with the non-temporal hint
+__device__ __forceinline__ void load_quad_vec(const float* __restrict__ row, int e, float (&x)[4]) {
+    const row_f32x4* p = reinterpret_cast<const row_f32x4*>(row + e);
+    const row_f32x4 t = NT ? __builtin_nontemporal_load(p) : *p;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = (e + k < V) ? row[e + k] : fill;
-    }
+    for (int k = 0; k < 4; ++k) x[k] = t[k];
 }
-__device__ __forceinline__ void load_quad(const uint16_t* __restrict__ row, int e, int V, bool vec, float (&x)[4],
-                                          float fill = 0.0f) {
-    if (vec && e + 3 < V) {
-        const uint2 t = *reinterpret_cast<const uint2*>(row + e);
-        x[0] = __builtin_bit_cast(float, t.x << 16);
-        x[1] = __builtin_bit_cast(float, t.x & 0xffff0000u);
-        x[2] = __builtin_bit_cast(float, t.y << 16);
-        x[3] = __builtin_bit_cast(float, t.y & 0xffff0000u);
+template <bool NT = false>
+__device__ __forceinline__ void load_quad_vec(const uint16_t* __restrict__ row, int e, float (&x)[4]) {
+    const row_u16x4* p = reinterpret_cast<const row_u16x4*>(row + e);
+    const row_u16x4 t = NT ? __builtin_nontemporal_load(p) : *p;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = to_float(t[k]);
+}
+// The same where some of the four may lie past the vocabulary: `fill` stands for those.
+template <typename RT>
+__device__ __forceinline__ void load_quad(const RT* __restrict__ row, int e, int V, float (&x)[4], float fill = 0.0f) {
+    if (e + 3 < V) {
+        load_quad_vec(row, e, x);
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k) x[k] = (e + k < V) ? to_float(row[e + k]) : fill;
     }
-}
-
-// The same where the caller has checked that the row is aligned and the four tokens exist: the load and nothing else.
-__device__ __forceinline__ void load_quad_vec(const float* __restrict__ row, int e, float (&x)[4]) {
-    const float4 t = *reinterpret_cast<const float4*>(row + e);
-    x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
-}
-__device__ __forceinline__ void load_quad_vec(const uint16_t* __restrict__ row, int e, float (&x)[4]) {
-    const uint2 t = *reinterpret_cast<const uint2*>(row + e);
-    x[0] = __builtin_bit_cast(float, t.x << 16);
-    x[1] = __builtin_bit_cast(float, t.x & 0xffff0000u);
-    x[2] = __builtin_bit_cast(float, t.y << 16);
-    x[3] = __builtin_bit_cast(float, t.y & 0xffff0000u);
 }
 
 // Constants of exp_softmax, made once per kernel.  The empty asm statements pin each one to a scalar register pair
@@ -215,8 +221,7 @@ __device__ __forceinline__ double exp_softmax(double x, const ExpConsts& k) {
 // rounding sum; the table's high words are stored less j << 12, so that one shift-and-add of n puts 2^(n / 256) together.
 // Measured, statistics of 512 requests x 152064 logits (about 2.9 GB of rows, bound by the vector ALUs): 693 -> 557 us, with
 // the references that need no rescaling per chunk.
-// CLAMP: arguments below kExpTableFloor (and NaN) count as that floor: 1e-304, so that the exponent stays a normal one;
-// without it the caller makes sure of the range (NaN gives NaN).
+// Arguments below kExpTableFloor (and NaN) count as that floor: 1e-304, so that the exponent stays a normal one.
 constexpr double kExpTableFloor = -700.0;
 __device__ const double kExp2Table[256] = {
 #include "exp_table.inc"
@@ -225,11 +230,12 @@ struct ExpTable {
     const uint2* tab;  // LDS
     double c, nl_hi, nl_lo, magic, c4, c3, floor;
 };
-__device__ __forceinline__ void fill_exp_table(uint2* tab) {
-    for (int j = threadIdx.x; j < 256; j += kThreads) {
-        const unsigned long long v = __builtin_bit_cast(unsigned long long, kExp2Table[j]);
-        tab[j] = make_uint2((uint32_t)v, (uint32_t)(v >> 32) - ((uint32_t)j << 12));
-    }
+// The thread's entry of the table that a workgroup keeps in LDS.  Loaded before the rows are sent for, stored behind that:
+// loads return in order, and the table must not wait for the rows, nor they for it.
+static_assert(kThreads == 256, "a thread brings one entry of the table");
+__device__ __forceinline__ uint2 exp_table_entry() {
+    const unsigned long long v = __builtin_bit_cast(unsigned long long, kExp2Table[threadIdx.x]);
+    return make_uint2((uint32_t)v, (uint32_t)(v >> 32) - (threadIdx.x << 12));
 }
 __device__ __forceinline__ ExpTable exp_table(const uint2* tab) {
     ExpTable k;
@@ -244,9 +250,8 @@ __device__ __forceinline__ ExpTable exp_table(const uint2* tab) {
     asm volatile("" : "+s"(k.floor), "+s"(k.c), "+s"(k.nl_hi), "+s"(k.nl_lo), "+s"(k.c4), "+v"(k.c3), "+v"(k.magic));
     return k;
 }
-template <bool CLAMP = true>
 __device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
-    if constexpr (CLAMP) x = fmax(x, k.floor);
+    x = fmax(x, k.floor);
     const double t = fma(x, k.c, k.magic);
     const double kf = t - k.magic;
     const uint32_t n = (uint32_t)__builtin_bit_cast(unsigned long long, t);
@@ -257,27 +262,81 @@ __device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
     const double pow2 = __builtin_bit_cast(double, ((unsigned long long)(e.y + (n << 12)) << 32) | e.x);
     return fma(pow2 * r, p, pow2);
 }
-// exp for the masses of a draw, which are formed twice -- for the chunk sums, then token by token in the chunk that is drawn
-// from -- and must be the same values both times, or a chunk with mass might hold no token with any.  By the table, below its
-// range by exp_softmax; 0 for a masked token (-inf, NaN) and where fp64 has nothing smaller.  Four at a time: exp_softmax is
-// hardly ever needed, and one branch for the wave leaves the look-ups free to overlap.
-constexpr double kExpZero = -746.0;
-constexpr double kSpread = -1e5;  // a row's smallest exponent between this and the floor is far-spread logits, not a mask
-__device__ __forceinline__ double exp_in_table(double x, const ExpTable& et, bool& below) {
-    const bool in = x >= kExpTableFloor;
-    below |= !in && x > kExpZero;
-    const double e = exp_lookup(x, et);
-    return in ? e : 0.0;
-}
-__device__ __forceinline__ void exp_tokens(const double (&x)[4], const ExpTable& et, const ExpConsts& ek, double (&e)[4]) {
-    bool below = false;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) e[k] = exp_in_table(x[k], et, below);
-    if (__builtin_amdgcn_ballot_w64(below) != 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) e[k] = x[k] < kExpTableFloor ? exp_softmax(x[k], ek) : e[k];
+// exp(z / T) for the logits themselves, with no reference taken off: z / T = n ln2 / 256 + r again, but in units of ln2 / 256, so
+// that one multiply-add rounds to n, one subtraction and two multiply-adds give r (256 / (T ln2) in two parts, the high one of 29
+// bits, whose product with a logit is exact), four the series and a fifth adds the value to a sum: 12 instructions and a
+// look-up where exp_lookup and its argument take 16.  Errors against exp(z / T), logits N(0, 2^2): 3.0e-16 at most, 8.3e-17
+// root mean square, at every T (by way of z * (1 / T) 1.9e-16 and 6.6e-17 at T = 1, 1.0e-15 and 1.9e-16 at 0.7, 7.9e-15 and 2.2e-15
+// at 0.05, where 1 / T is rounded).  For |z| <= reach only: |z / T| up to 600, where the value and 2^32 times it are normal numbers.
+struct TempScale {
+    double c, c_hi, c_lo;  // 256 / (T ln2); the same in two parts
+    float reach;
+};
+constexpr double kReach = 600.0;
+TempScale temp_scale(double T) {
+    TempScale t{};
+    const long double c = 256.0L / (0.693147180559945309417232121458L * (long double)T);
+    t.c = (double)c;
+    if (!std::isfinite(t.c) || t.c == 0.0) {
+        t.c = 0.0;
+        t.reach = -1.0f;  // no logit is within reach
+        return t;
     }
+    int e = 0;
+    const double m = std::frexp(t.c, &e);
+    t.c_hi = std::ldexp(std::floor(std::ldexp(m, 29)), e - 29);
+    t.c_lo = (double)(c - (long double)t.c_hi);
+    t.reach = (float)std::min(kReach * T, (double)FLT_MAX);
+    return t;
 }
+struct ExpDirect {
+    const uint2* tab;  // LDS
+    double c, c_hi, c_lo, magic, a4, a3, a2, a1;
+};
+__device__ __forceinline__ ExpDirect exp_direct(const uint2* tab, const TempScale& ts) {
+    ExpDirect k;
+    k.tab = tab;
+    k.c = ts.c;
+    k.c_hi = ts.c_hi;
+    k.c_lo = ts.c_lo;
+    k.magic = 6755399441055744.0;  // 1.5 * 2^52
+    k.a4 = 2.239395190875157e-12;  // (ln2 / 256)^n / n!
+    k.a3 = 3.3083026805413713e-09;
+    k.a2 = 3.6655655969101062e-06;
+    k.a1 = 0.0027076061740622863;
+    asm volatile("" : "+s"(k.c), "+s"(k.c_hi), "+s"(k.c_lo), "+s"(k.a4), "+v"(k.a3), "+s"(k.a2), "+s"(k.a1), "+v"(k.magic));
+    return k;
+}
+// exp(z / T) = power * series
+struct ExpParts {
+    double power, series;
+};
+__device__ __forceinline__ ExpParts exp_of_logit(float z, const ExpDirect& k) {
+    const double x = (double)z;
+    const double t = fma(x, k.c, k.magic);
+    const double n = t - k.magic;
+    const uint32_t low = (uint32_t)__builtin_bit_cast(unsigned long long, t);
+    const uint2 e = k.tab[low & 255u];
+    const double r = fma(x, k.c_lo, fma(x, k.c_hi, -n));
+    ExpParts p;
+    p.power = __builtin_bit_cast(double, ((unsigned long long)(e.y + (low << 12)) << 32) | e.x);
+    p.series = fma(fma(fma(fma(k.a4, r, k.a3), r, k.a2), r, k.a1), r, 1.0);
+    return p;
+}
+// Largest magnitude, largest and smallest of three (one instruction each; a NaN is passed over).
+__device__ __forceinline__ float max3_abs(float m, float x, float y) {
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x), "v"(y));
+    return m;
+}
+__device__ __forceinline__ float max3(float m, float x, float y) {
+    asm("v_max3_f32 %0, %1, %2, %0" : "+v"(m) : "v"(x), "v"(y));
+    return m;
+}
+__device__ __forceinline__ float min3(float m, float x, float y) {
+    asm("v_min3_f32 %0, %1, %2, %0" : "+v"(m) : "v"(x), "v"(y));
+    return m;
+}
+constexpr double kExpZero = -746.0;  // exp of it and of anything less is 0 in fp64
 // The constants for a kernel of the given mode: PROBS mode never evaluates exp and gets an empty set.
 template <int MODE>
 __device__ __forceinline__ ExpConsts exp_consts_for() {
@@ -370,16 +429,21 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ stat_a,
 // LOGITS mode: per row and group of ws.stat_group chunks, a reference and the sum of exp(z / T - reference), fp64.
 // grid = (n_stat_groups, (2 * S_max + 1) * B): workgroup row k * B + i takes, of request i, target row k / 2 for even k and
 // draft row k / 2 for odd k, so that the rows of the first drafts are all started before any row of a second draft.
-// Each lane keeps a reference (its first chunk's largest logit, replaced only by one far above it) and a sum relative to
-// it over its own elements (16 per chunk), so the chunks of a group need no exchange between lanes; lanes and waves are
+// Each lane sums exp(z / T) itself over its own elements (16 per chunk) where they are within reach (see exp_of_logit), and else
+// keeps a reference (its first chunk's largest logit, replaced only by one far above it) and a sum relative to
+// it, so the chunks of a group need no exchange between lanes; lanes and waves are
 // combined once, at the end.  Any reference gives the same probabilities; it has to keep the exponents in range.
+// The rows are read once here, with the non-temporal hint (512 requests x 152064 in fp32: call 533 us without, 508 with).  What
+// bounds it is both the rows' bytes and the fp64 instructions: 512 requests 455 us a launch with a reference taken off every logit
+// and ordinary loads, 394 like this (about 2.3 GB; vector ALUs 70 % busy); 16 requests x 128256 in bf16 24.1 / 20.6.
 // ---------------------------------------------------------------------------------------
 template <typename RT>
-__global__ __launch_bounds__(kThreads) void accept_stats_kernel(
+__global__ __launch_bounds__(kThreads, 5) void accept_stats_kernel(
     const RT* __restrict__ z_target, const RT* __restrict__ z_draft, const int32_t* __restrict__ draft_tokens,
     const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
-    const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, Workspace ws, int B, int V, int S_max, double T) {
-    __shared__ double s_sum[kThreads / 64];
+    const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, Workspace ws, int B, int V, int S_max, double T,
+    TempScale ts) {
+    __shared__ double s_sum[kThreads / 64], s_direct[kThreads / 64];
     __shared__ float s_max[kThreads / 64];
     __shared__ uint2 s_exp[256];
     __shared__ int s_behind, s_last;
@@ -400,42 +464,107 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
         rows = z_draft + (size_t)(d_rows ? d_rows[r] : r) * V;
         stat = ws.stat_d + (size_t)r * nsg * 2;
     }
+    const int c_first = blockIdx.x * ws.stat_group, c_end = min(nc, c_first + ws.stat_group);
+    const int c_whole = min(c_end, V / kChunk);  // chunks before it are whole
+    float va[kPerThread], vb[kPerThread];
+    auto load_chunk = [&](int c, float (&v)[kPerThread]) {
+#pragma unroll
+        for (int q = 0; q < kPerThread / 4; ++q) {
+            float x[4];
+            load_quad_vec<true>(rows, c * kChunk + (q * kThreads + threadIdx.x) * 4, x);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[q * 4 + u] = x[u];
+        }
+    };
+    auto load_checked = [&](int c, float (&v)[kPerThread]) {
+#pragma unroll
+        for (int q = 0; q < kPerThread / 4; ++q) {
+            float x[4];
+            load_quad(rows, c * kChunk + (q * kThreads + (int)threadIdx.x) * 4, V, x, -INFINITY);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[q * 4 + u] = x[u];
+        }
+    };
+    const uint2 entry = exp_table_entry();
+    if (!ws.skip && c_first < c_whole) load_chunk(c_first, va);  // (in flight while the table is filled)
     // If a draft before this row's has been rejected, nothing will read the row's statistics.  One lane asks for the whole
     // workgroup: other workgroups may lower the word at any time, and waves that asked for themselves could differ.
     if (threadIdx.x == 0)
         s_behind = ws.skip && j > 0 &&
                    __hip_atomic_load(stat_words(ws, i, nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned)j;
-    fill_exp_table(s_exp);
+    s_exp[threadIdx.x] = entry;
     __syncthreads();
     if (s_behind) return;
-    const bool vec = row_vec_ok(rows);
+    unsigned todo = (1u << (c_end - c_first)) - 1u;  // chunks (of the wave's tokens) that the first loop leaves to the second
+    // Chunks whose logits lie within reach, from exp(z / T) itself.  Whole ones: four vector loads per lane and chunk, all in
+    // flight together, the next chunk's issued before this one's arithmetic, and only such loads in the loop: mixed with
+    // bounds-checked ones the compiler orders each vector load behind all loads before it.
+    double direct = 0.0;  // sum of exp(z / T) over this lane's elements
+    {
+        const ExpDirect ed = exp_direct(s_exp, ts);
+        auto add_chunk = [&](const float (&v)[kPerThread], int c) {
+            float top = 0.0f;
+#pragma unroll
+            for (int u = 0; u < kPerThread; u += 2) top = max3_abs(top, v[u], v[u + 1]);
+            if (__builtin_amdgcn_ballot_w64(!(top <= ts.reach)) == 0) {
+#pragma unroll
+                for (int u = 0; u < kPerThread; ++u) {
+                    const ExpParts e = exp_of_logit(v[u], ed);
+                    direct = fma(e.power, e.series, direct);
+                }
+            } else {
+                float hi = -INFINITY;
+#pragma unroll
+                for (int u = 0; u < kPerThread; u += 2) hi = max3(hi, v[u], v[u + 1]);
+                if (__builtin_amdgcn_ballot_w64(hi > ts.reach) != 0) return;
+                // Masked logits (-inf, NaN), or some far below the rest: as such they add exp(-600) each, where one of the wave's
+                // is at least exp(-500).  A wave's masked logits alone add nothing; nor do finite ones as low, here.
+                if (__builtin_amdgcn_ballot_w64(hi >= ts.reach * (float)(-500.0 / kReach)) == 0) {
+                    if (__builtin_amdgcn_ballot_w64(hi != -INFINITY) != 0) return;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kPerThread; ++u) {
+                        const ExpParts e = exp_of_logit(fmaxf(v[u], -ts.reach), ed);
+                        direct = fma(e.power, e.series, direct);
+                    }
+                }
+            }
+            todo &= ~(1u << (c - c_first));
+        };
+        if (ws.skip && c_first < c_whole) load_chunk(c_first, va);
+#pragma unroll 1
+        for (int c = c_first; c < c_whole; c += 2) {
+            if (c + 1 < c_whole) load_chunk(c + 1, vb);
+            add_chunk(va, c);
+            if (c + 1 >= c_whole) break;
+            if (c + 2 < c_whole) load_chunk(c + 2, va);
+            add_chunk(vb, c + 1);
+        }
+        if (c_whole < c_end) {  // the chunk that holds the vocabulary's ragged end
+            load_checked(c_whole, va);
+            add_chunk(va, c_whole);
+        }
+        if (__builtin_amdgcn_ballot_w64(direct != direct) != 0) {  // a NaN logit counts as masked: all chunks again
+            direct = 0.0;
+            todo = (1u << (c_end - c_first)) - 1u;
+        }
+    }
+    // The others, with logits out of reach, against a reference of the lane's own.
     const double inv_T = 1.0 / T;
     const ExpConsts ek = exp_consts();
-    const ExpTable et = exp_table(s_exp);
-    const int c_first = blockIdx.x * ws.stat_group, c_end = min(nc, c_first + ws.stat_group);
     float mz = -INFINITY;   // this lane's reference: a logit it has seen, no more than kStatSlack * T below the largest
-    float limit = -INFINITY;  // a logit above this makes a new reference
     double mzT = 0.0;       // mz / T once mz is finite
     double sum = 0.0;       // sum of exp(z / T - mz / T) over this lane's elements
-    const float slack = (float)(kStatSlack * T);
-    // The fold over the group's chunks, twice: for whole chunks of a row aligned for vector loads (four loads per
-    // lane and chunk, all in flight together, the next chunk's issued before this one's arithmetic), and with every
-    // element bounds-checked for the chunk that holds the vocabulary's ragged end or a row that is not aligned.
-    // Two separate loops, because mixed in one the compiler orders each vector load behind all loads before it.
-    auto fold = [&](auto whole, int c_lo, int c_hi) {
-        float va[kPerThread], vb[kPerThread];
-        auto load_chunk = [&](int c, float (&v)[kPerThread]) {
-#pragma unroll
-            for (int q = 0; q < kPerThread / 4; ++q) {
-                float x[4];
-                const int e = c * kChunk + (q * kThreads + threadIdx.x) * 4;
-                if constexpr (decltype(whole)::value) load_quad_vec(rows, e, x);
-                else load_quad(rows, e, V, vec, x, -INFINITY);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[q * 4 + u] = x[u];
-            }
-        };
-        auto add_chunk = [&](const float (&v)[kPerThread]) {
+    if (todo != 0) {
+        const ExpTable et = exp_table(s_exp);
+        float limit = -INFINITY;  // a logit above this makes a new reference
+        const float slack = (float)(kStatSlack * T);
+#pragma unroll 1
+        while (todo != 0) {
+            const int c = c_first + __builtin_ctz(todo);
+            todo &= todo - 1;
+            float v[kPerThread];
+            load_checked(c, v);
             float mx = v[0];
 #pragma unroll
             for (int u = 1; u < kPerThread; ++u) mx = fmaxf(mx, v[u]);
@@ -449,38 +578,38 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
             // (a masked logit -- -inf, NaN, past V -- or one far below the reference adds 1e-304)
 #pragma unroll
             for (int u = 0; u < kPerThread; ++u) sum += exp_lookup(fma((double)v[u], inv_T, -mzT), et);
-        };
-        if (c_lo >= c_hi) return;
-        load_chunk(c_lo, va);
-#pragma unroll 1
-        for (int c = c_lo; c < c_hi; c += 2) {
-            if (c + 1 < c_hi) load_chunk(c + 1, vb);
-            add_chunk(va);
-            if (c + 1 >= c_hi) break;
-            if (c + 2 < c_hi) load_chunk(c + 2, va);
-            add_chunk(vb);
         }
-    };
-    const int c_whole = vec ? min(c_end, V / kChunk) : c_first;  // chunks before it are whole and aligned
-    fold(std::true_type{}, c_first, c_whole);
-    fold(std::false_type{}, max(c_first, c_whole), c_end);
+    }
     // lanes -> wave -> workgroup, each time against the common maximum
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const float mw = wave_max(mz);
-    sum = mz == -INFINITY ? 0.0 : sum * exp_softmax(mzT - (double)mw * inv_T, ek);
-    sum = wave_sum(sum);
-    if (lane == 0) {
+    direct = wave_sum_to_last(direct);
+    float mw = -INFINITY;
+    if (__builtin_amdgcn_ballot_w64(mz != -INFINITY) != 0) {
+        mw = wave_max(mz);
+        sum = mz == -INFINITY ? 0.0 : sum * exp_softmax(mzT - (double)mw * inv_T, ek);
+        sum = wave_sum_to_last(sum);
+    }
+    if (lane == 63) {
         s_max[w] = mw;
         s_sum[w] = sum;
+        s_direct[w] = direct;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         const float mg = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-        const double mgT = (double)mg * inv_T;
-        double tot = 0.0;
+        double mgT = (double)mg * inv_T, tot = (s_direct[0] + s_direct[1]) + (s_direct[2] + s_direct[3]);
+        if (tot > 0.0) {
+            // a reference for the direct sum too: below its largest term, which is at least 2^-15 of it
+            const double md = 0.6931471805599453 * (double)(ilogb(tot) - 16);
+            mgT = fmax(mgT, md);
+            tot *= exp_softmax(-md, ek);
+            if (mgT != md) tot *= exp_softmax(md - mgT, ek);
+        }
+        if (mg != -INFINITY) {
 #pragma unroll
-        for (int q = 0; q < kThreads / 64; ++q)
-            if (s_max[q] != -INFINITY) tot += s_sum[q] * exp_softmax((double)s_max[q] * inv_T - mgT, ek);
+            for (int q = 0; q < kThreads / 64; ++q)
+                if (s_max[q] != -INFINITY) tot += s_sum[q] * exp_softmax((double)s_max[q] * inv_T - mgT, ek);
+        }
         publish_f64(stat + blockIdx.x * 2, mgT);  // -inf for a group of masked logits only
         publish_f64(stat + blockIdx.x * 2 + 1, tot);
         s_last = 0;
@@ -503,50 +632,79 @@ __global__ __launch_bounds__(kThreads) void accept_stats_kernel(
     if (threadIdx.x == 0 && !((double)u_accept[dr] * qx < px)) atomicMin(stat_words(ws, i, nc), (unsigned)j);
 }
 
-// p - q of two products, each rounded: fused into a multiply-add, equal probabilities would leave a rounding error behind
-// instead of 0.
-__device__ __forceinline__ double difference(double p, double q) {
-    asm("" : "+v"(p), "+v"(q));
-    return p - q;
+constexpr double kDirectReach = 580.0;  // a row's largest z / T lies at most 12 above its reference (100 where it is not direct)
+__device__ __forceinline__ RowScale row_scale(double m, double T, const TempScale& ts) {
+    const double zero = (m + kExpZero) * T;  // (below 0 in a direct row, whose reference is far under 746)
+    return RowScale{fmaxf(-ts.reach, (float)((m + kExpTableFloor) * T)), (float)(zero + 1e-6 * zero)};
 }
-
-// Masses of four entries of a row in a draw: the probabilities themselves, or exp(z / T - m) / Z.
-struct RowScale {
-    double m, inv_Z;
-};
+__device__ __forceinline__ DrawScale draw_scale(const Decision& dec, double T, const TempScale& ts, const ExpConsts& ek) {
+    const bool residual = dec.kind == kCaseResidual;
+    DrawScale sc{row_scale(dec.m_t, T, ts), row_scale(dec.m_d, T, ts), 1.0, 0, 0};
+    sc.direct = ts.reach > 0.0f && fabs(dec.m_t) <= kDirectReach &&
+                (!residual || (fabs(dec.m_d) <= kDirectReach && fabs(dec.m_t - dec.m_d) <= kDirectReach));
+    if (residual) {
+        sc.ratio = dec.Z_t / dec.Z_d;
+        if (sc.direct) sc.ratio *= exp_softmax(dec.m_t - dec.m_d, ek);
+    }
+    return sc;
+}
+// One logit of a direct row: its mass if it is not below `lowest`, else 0, and far if it may have one all the same.
+__device__ __forceinline__ double mass_or_zero(float z, const RowScale& sc, const ExpDirect& ed, bool& far) {
+    const bool in = z >= sc.lowest;
+    far |= !in && z > sc.masked;
+    const ExpParts e = exp_of_logit(fmaxf(z, sc.lowest), ed);
+    return in ? e.power * e.series : 0.0;
+}
+// Masses of four entries of a row in a draw: the probabilities themselves, or as RowScale says.
 template <int MODE>
-__device__ __forceinline__ void token_masses(const float (&z)[4], double inv_T, const RowScale& sc, const ExpTable& et,
-                                             const ExpConsts& ek, double (&mass)[4]) {
+__device__ __forceinline__ void token_masses(const float (&z)[4], double inv_T, bool direct, const RowScale& sc,
+                                             double m, const ExpDirect& ed, double (&mass)[4]) {
     if constexpr (MODE == FSR_PROBS) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) mass[k] = (double)z[k];
     } else {
-        double x[4];
+        bool far = !direct;
+        if (direct) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = fma((double)z[k], inv_T, -sc.m);
-        exp_tokens(x, et, ek, mass);
+            for (int k = 0; k < 4; ++k) mass[k] = mass_or_zero(z[k], sc, ed, far);
+        }
+        if (__builtin_amdgcn_ballot_w64(far) != 0) {  // hardly ever: one copy of exp_softmax, its constants made here
+            const ExpConsts ek = exp_consts();
+            const double unit = direct ? exp_softmax(m, ek) : 1.0;
+#pragma unroll 1
+            for (int k = 0; k < 4; ++k) {
+                const float zk = k == 0 ? z[0] : k == 1 ? z[1] : k == 2 ? z[2] : z[3];
+                const bool take = !direct || (!(zk >= sc.lowest) && zk > sc.masked);
+                if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
+                const double x = fma((double)zk, inv_T, -m), e = exp_softmax(x, ek);
+                const double v = x > kExpZero && e > 0.0 ? fmax(e * unit, __builtin_bit_cast(double, 1ull)) : 0.0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) mass[k] *= sc.inv_Z;
+                for (int u = 0; u < 4; ++u) mass[u] = take && u == k ? v : mass[u];
+            }
+        }
     }
 }
+// Residual p - q of two masses, in units of p's row; ratio: what one unit of q's row is in those.  Equal rows have a ratio of
+// exactly 1 and leave exactly 0.
+__device__ __forceinline__ double residual_of(double p, double q, double ratio) { return fma(-q, ratio, p); }
 // Masses of 4 consecutive tokens starting at e for a draw from the row or from the residual (bounds-checked); their sum in
 // the target row is added to `target`.
 template <int MODE, typename RT>
 __device__ __forceinline__ void quad_masses(bool residual, const RT* __restrict__ trow, const RT* __restrict__ drow, int e, int V,
-                                            bool vec_t, bool vec_d, double inv_T, const RowScale& sc_t, const RowScale& sc_d,
-                                            const ExpTable& et, const ExpConsts& ek, double (&mass)[4], double& target) {
+                                            double inv_T, const Decision& dec,
+                                            const DrawScale& sc, const ExpDirect& ed, double (&mass)[4], double& target) {
     constexpr float kNothing = MODE == FSR_LOGITS ? -INFINITY : 0.0f;  // past the vocabulary
     float a[4], b[4];
-    load_quad(trow, e, V, vec_t, a, kNothing);
-    if (residual) load_quad(drow, e, V, vec_d, b, kNothing);
-    token_masses<MODE>(a, inv_T, sc_t, et, ek, mass);
+    load_quad(trow, e, V, a, kNothing);
+    if (residual) load_quad(drow, e, V, b, kNothing);
+    token_masses<MODE>(a, inv_T, sc.direct, sc.t, dec.m_t, ed, mass);
     target += (mass[0] + mass[1]) + (mass[2] + mass[3]);
     if (residual) {
         double q[4];
-        token_masses<MODE>(b, inv_T, sc_d, et, ek, q);
+        token_masses<MODE>(b, inv_T, sc.direct, sc.d, dec.m_d, ed, q);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const double r = difference(mass[k], q[k]);
+            const double r = residual_of(mass[k], q[k], sc.ratio);
             mass[k] = r > 0.0 ? r : 0.0;
         }
     }
@@ -615,7 +773,7 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const int32_t* __restrict__ draft_tokens,
     const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
     const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, int32_t* __restrict__ accepted_len,
-    int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int B, int V, int S_max, double T) {
+    int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int B, int V, int S_max, double T, TempScale ts) {
     const int i = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int nsg = n_stat_groups_of(V, ws.stat_group);
     const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;
@@ -743,6 +901,10 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
         }
     }
     for (int s = n + lane; s <= S_max; s += 64) em[s] = -1;
+    if constexpr (MODE == FSR_LOGITS) {
+        const DrawScale sc = draw_scale(dec, T, ts, ek);  // (here, once, and not in every workgroup that sums a part of the rows)
+        if (lane == 0) ws.scale[i] = sc;
+    }
     if (lane == 0) {
         accepted_len[i] = n;
         n_emitted[i] = n;  // the sampling kernel adds the drawn token
@@ -757,18 +919,19 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
 // drafted token without probability, rows that are equal otherwise); left to the request's last workgroup, such a call of
 // 16 requests took 57 us in place of 17 (PROBS) and 127 in place of 50 (LOGITS), one of 128 requests 76 in place of 31 and
 // 210 in place of 116.  LOGITS: four waves per SIMD, 128 registers (133 and three: 573 in place of 560 us a call of 512).
-// A large call is bound by the rows' bytes (PROBS) or by fp64 instructions (LOGITS: exp by table look-up, see exp_lookup);
+// A large call is bound by the rows' bytes (PROBS) or by fp64 instructions (LOGITS: exp by table look-up, see exp_of_logit);
 // a small one is a latency chain (decision, rows, sums, arrival, chunk search, chunk scan), so what lies on it is kept
 // short: sums over a wave by DPP, the search over the chunk masses by one wave.  Measured, us a launch before / after:
 // PROBS 16 requests 17.6 / 13.4, chunks of 512 requests' drafts (mean of four) 47.5 / 39.3; LOGITS 16 requests in bf16
-// 20.8 / 16.4, 512 requests 183 / 148.  LOGITS calls with masked logits, 128 requests x 128256 in fp32, us a call with such
+// 20.8 / 16.4, 512 requests 183 / 148.  The scales of the rows are worked out by `decide`, and what is hardly ever needed has one copy of
+// exp_softmax: a small call pays for code that it fetches (4 requests, LOGITS: 80 KB of it 24.0 us, 48 KB 23.1).  LOGITS calls with masked logits, 128 requests x 128256 in fp32, us a call with such
 // chunks read again by the checked path / summed from the registers: all but 50 logits of a row masked 171 / 158, every
 // second one 164 / 141; exponents spread over several hundred (T = 0.02) 173 / 176, read again either way.
 // ---------------------------------------------------------------------------------------
 template <int MODE, typename RT, int kSampleGroup>
 __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_sample_kernel(
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const float* __restrict__ u_sample,
-    int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int V, int S_max, double T) {
+    int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int V, int S_max, double T, TempScale ts) {
     __shared__ double s_part[kThreads / 64][kSampleGroup], s_part_t[kThreads / 64][kSampleGroup];
     __shared__ double s_wave[kThreads / 64];
     __shared__ int s_i[kThreads / 64];
@@ -782,21 +945,43 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
     Decision dec = ws.dec[i];
     dec.kind = __builtin_amdgcn_readfirstlane(dec.kind);  // the same in every lane: say so, branches on it stay scalar
     if (dec.kind == kCaseNone) return;
-    if constexpr (MODE == FSR_LOGITS) {
-        fill_exp_table(s_exp);
-        __syncthreads();
-    }
-    const ExpConsts ek = exp_consts_for<MODE>();
-    ExpTable et{};
-    if constexpr (MODE == FSR_LOGITS) et = exp_table(s_exp);
+    DrawScale sc{{}, {}, 1.0, 0, 0};
+    if constexpr (MODE == FSR_LOGITS) sc = ws.scale[i];
+    sc.direct = __builtin_amdgcn_readfirstlane(sc.direct);
 
     // ---- 2. fp64 mass of this workgroup's chunks of the sampling distribution
     const RT* trow = p_target + (size_t)dec.t_row * V;
     const RT* drow = p_draft + (size_t)dec.d_row * V;
-    const bool vec_t = row_vec_ok(trow), vec_d = row_vec_ok(drow);
     const double inv_T = 1.0 / T;
-    // a draw from one row needs no normalisation: its masses are relative to each other only
-    const RowScale sc_t{dec.m_t, dec.kind == kCaseTarget ? 1.0 : 1.0 / dec.Z_t}, sc_d{dec.m_d, 1.0 / dec.Z_d};
+    // whole chunks go through code that has only vector loads; a row without a direct form (see RowScale) through the checked one
+    const bool residual = dec.kind == kCaseResidual;
+    const int n_whole = MODE == FSR_PROBS || sc.direct ? min(n_here, max(0, V / kChunk - c_first)) : 0;
+    float ta[kPerThread], da[kPerThread];
+    auto load_rows = [&](int c, float (&t)[kPerThread], float (&d)[kPerThread]) {
+#pragma unroll
+        for (int k = 0; k < kPerThread / 4; ++k) {
+            const int e = c * kChunk + (k * kThreads + threadIdx.x) * 4;
+            float x[4], y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            load_quad_vec(trow, e, x);
+            if (residual) load_quad_vec(drow, e, y);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                t[4 * k + u] = x[u];
+                d[4 * k + u] = y[u];
+            }
+        }
+    };
+    uint2 entry{};
+    if constexpr (MODE == FSR_LOGITS) entry = exp_table_entry();
+    if (n_whole > 0) load_rows(c_first, ta, da);  // (in flight while the table is filled)
+    if constexpr (MODE == FSR_LOGITS) __builtin_amdgcn_sched_barrier(0);
+    // A draw needs no normalisation: its masses are relative to each other only.
+    ExpDirect ed{};
+    if constexpr (MODE == FSR_LOGITS) {
+        s_exp[threadIdx.x] = entry;
+        ed = exp_direct(s_exp, ts);
+        __syncthreads();
+    }
     // A workgroup takes kSampleGroup consecutive chunks: the chain every workgroup goes through (decision record,
     // row loads, reduction, store-through, arrival count) is paid once per 128 KB instead of once per 32 KB.
     auto chunk_mass_checked = [&](int c, double& target) __attribute__((always_inline)) {  // any chunk, element by element
@@ -805,33 +990,16 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
 #pragma unroll
         for (int k = 0; k < kPerThread / 4; ++k) {
             double m[4];
-            quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V, vec_t, vec_d,
-                                  inv_T, sc_t, sc_d, et, ek, m, target);
+            quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V,
+                                  inv_T, dec, sc, ed, m, target);
             r += (m[0] + m[1]) + (m[2] + m[3]);
         }
         return r;
     };
     {
-        // whole chunks of aligned rows first, through code that has only vector loads (the next chunk's issued before
-        // this chunk's arithmetic); then the chunk with the vocabulary's ragged end (or every chunk, if a row is not
-        // aligned), bounds-checked.  A chunk's mass goes to LDS as soon as the wave has it.
-        const bool residual = dec.kind == kCaseResidual;
-        const bool vec_ok = vec_t && (!residual || vec_d);
-        const int n_whole = vec_ok ? min(n_here, max(0, V / kChunk - c_first)) : 0;
-        auto load_rows = [&](int c, float (&t)[kPerThread], float (&d)[kPerThread]) {
-#pragma unroll
-            for (int k = 0; k < kPerThread / 4; ++k) {
-                const int e = c * kChunk + (k * kThreads + threadIdx.x) * 4;
-                float x[4], y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                load_quad_vec(trow, e, x);
-                if (residual) load_quad_vec(drow, e, y);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    t[4 * k + u] = x[u];
-                    d[4 * k + u] = y[u];
-                }
-            }
-        };
+        // whole chunks first, through code that has only vector loads (the next chunk's issued before
+        // this chunk's arithmetic); then the chunk with the vocabulary's ragged end,
+        // bounds-checked.  A chunk's mass goes to LDS as soon as the wave has it.
         unsigned todo = ((1u << n_here) - 1u) & ~((1u << n_whole) - 1u);  // chunks left to the checked path
         // A wave's masses of chunk cc to LDS.  Only a residual that is zero everywhere needs the target row's: a wave sums
         // those where it has met no residual.
@@ -847,45 +1015,50 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
         auto sum_chunk = [&](int cc, const float (&t)[kPerThread], const float (&d)[kPerThread]) {
             double r = 0.0, target = 0.0;
             if constexpr (MODE == FSR_LOGITS) {
-                // Without a check per token where every logit of the wave lies in the table's range; with masked tokens
-                // (-inf, NaN, or so low that exp is 0) counted as 0 where some are masked; the checked path where a logit
-                // has a value below the table's range.  The values are those of exp_tokens throughout.
-                bool below = false;
+                // Without a check per token where no logit of the wave lies below its row's `lowest`; with masked tokens
+                // (-inf, NaN, or so low that exp is 0) counted as 0 where some do; the checked path where one of
+                // those has a mass.  The values are those of token_masses throughout.
+                bool far = false;
                 auto sum = [&](auto masked) {
-                    auto mass = [&](float z, const RowScale& sc) {
-                        const double x = fma((double)z, inv_T, -sc.m);
-                        if constexpr (decltype(masked)::value) return exp_in_table(x, et, below);
-                        else return exp_lookup<false>(x, et);
+                    auto mass = [&](float z, const RowScale& rs) {
+                        if constexpr (decltype(masked)::value) {
+                            return mass_or_zero(z, rs, ed, far);
+                        } else {
+                            const ExpParts e = exp_of_logit(z, ed);
+                            return e.power * e.series;
+                        }
                     };
                     double acc = 0.0;
 #pragma unroll
                     for (int u = 0; u < kPerThread; ++u) {
                         if (residual) {
-                            const double x = difference(mass(t[u], sc_t) * sc_t.inv_Z, mass(d[u], sc_d) * sc_d.inv_Z);
+                            const double x = residual_of(mass(t[u], sc.t), mass(d[u], sc.d), sc.ratio);
                             acc += x < 0.0 ? 0.0 : x;  // (keeps a NaN)
                         } else {
-                            acc += mass(t[u], sc_t);
+                            acc += mass(t[u], sc.t);
                         }
                     }
                     return acc;
                 };
-                float lo_t = t[0], lo_d = d[0];
+                float lo_t = t[0], lo_d = residual ? d[0] : INFINITY;
 #pragma unroll
-                for (int u = 1; u < kPerThread; ++u) {
-                    lo_t = fminf(lo_t, t[u]);
-                    lo_d = fminf(lo_d, d[u]);
+                for (int u = 1; u + 1 < kPerThread; u += 2) lo_t = min3(lo_t, t[u], t[u + 1]);
+                lo_t = min3(lo_t, t[kPerThread - 1], lo_t);
+                if (residual) {
+#pragma unroll
+                    for (int u = 1; u + 1 < kPerThread; u += 2) lo_d = min3(lo_d, d[u], d[u + 1]);
+                    lo_d = min3(lo_d, d[kPerThread - 1], lo_d);
                 }
-                double lo = fma((double)lo_t, inv_T, -sc_t.m);
-                if (residual) lo = fmin(lo, fma((double)lo_d, inv_T, -sc_d.m));
-                bool plain = __builtin_amdgcn_ballot_w64(!(lo >= kExpTableFloor)) == 0;
+                const float low_d = residual ? sc.d.lowest : -INFINITY;
+                bool plain = __builtin_amdgcn_ballot_w64(!(lo_t >= sc.t.lowest && lo_d >= low_d)) == 0;
                 if (plain) {
                     r = sum(std::false_type{});
                     plain = __builtin_amdgcn_ballot_w64(r != r) == 0;  // a NaN logit counts as masked
                 }
                 if (!plain) {
-                    below = lo < kExpTableFloor && lo > kSpread;  // far spread, not masked: some token will be below
-                    if (__builtin_amdgcn_ballot_w64(below) == 0) r = sum(std::true_type{});
-                    if (__builtin_amdgcn_ballot_w64(below) != 0) {
+                    far = (lo_t < sc.t.lowest && lo_t > sc.t.masked) || (residual && lo_d < low_d && lo_d > sc.d.masked);
+                    if (__builtin_amdgcn_ballot_w64(far) == 0) r = sum(std::true_type{});
+                    if (__builtin_amdgcn_ballot_w64(far) != 0) {
                         todo |= 1u << cc;
                         return;
                     }
@@ -895,7 +1068,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
                     for (int u = 0; u < kPerThread; ++u) {
                         float z = t[u];
                         asm volatile("" : "+v"(z));  // or the compiler keeps sixteen masses of the loop above in registers
-                        target += exp_in_table(fma((double)z, inv_T, -sc_t.m), et, below) * sc_t.inv_Z;
+                        target += mass_or_zero(z, sc.t, ed, far);
                     }
                 }
             } else if (residual) {
@@ -918,8 +1091,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
             put(cc, r, target);
         };
         if (n_whole > 0) {
-            float ta[kPerThread], da[kPerThread], tb[kPerThread], db[kPerThread];
-            load_rows(c_first, ta, da);
+            float tb[kPerThread], db[kPerThread];
 #pragma unroll 1
             for (int cc = 0; cc < n_whole; cc += 2) {
                 if (cc + 1 < n_whole) load_rows(c_first + cc + 1, tb, db);
@@ -1020,7 +1192,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
 #pragma unroll
     for (int k = 0; k < kPerThread / 4; ++k) {
         double m[4];
-        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, vec_t, vec_d, inv_T, sc_t, sc_d, et, ek, m, unused);
+        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, inv_T, dec, sc, ed, m, unused);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             mass[4 * k + j] = m[j];
@@ -1067,6 +1239,7 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
     Workspace ws = ws_in;
     const int nc = n_chunks_of(p.V);
     const double T = p.temperature;
+    const TempScale ts = MODE == FSR_LOGITS ? temp_scale(T) : TempScale{};
     int rc;
     if (MODE == FSR_LOGITS) {
         const int rows_cap = p.B * (2 * p.S_max + 1);
@@ -1085,12 +1258,12 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
             if ((rc = check_launch("accept_clear_kernel")) != FSR_OK) return rc;
         }
         hipLaunchKernelGGL(accept_stats_kernel<RT>, dim3(n_stat_groups_of(p.V, sg), rows_cap), dim3(kThreads), 0, s, p_target, p_draft,
-                           draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T);
+                           draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T, ts);
         if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
     }
     const int decide_waves = MODE == FSR_LOGITS && !ws.skip ? decide_waves_of(p.S_max, n_stat_groups_of(p.V, ws.stat_group)) : 1;
     hipLaunchKernelGGL((accept_decide_kernel<MODE, RT>), dim3(p.B), dim3(64 * decide_waves), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t,
-                       cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T);
+                       cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T, ts);
     if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
     // chunks per workgroup: as many as leave the device about four workgroups per compute unit (a small batch
     // keeps one chunk per workgroup: there the call is a latency chain and parallelism is what shortens it).
@@ -1100,7 +1273,7 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
     while (group > 1 && (long long)p.B * ((nc + group - 1) / group) < 1024) group >>= 1;
 #define FSR_SAMPLE(G)                                                                                                          \
     hipLaunchKernelGGL((accept_sample_kernel<MODE, RT, G>), dim3((nc + G - 1) / G, p.B), dim3(kThreads), 0, s, p_target, p_draft, \
-                       u_sample, n_emitted, emitted, ws, p.V, p.S_max, T)
+                       u_sample, n_emitted, emitted, ws, p.V, p.S_max, T, ts)
     if (group == 8) FSR_SAMPLE(8);
     else if (group == 4) FSR_SAMPLE(4);
     else if (group == 2) FSR_SAMPLE(2);
