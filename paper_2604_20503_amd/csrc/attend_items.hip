@@ -1,7 +1,7 @@
 // Verification attention (Sec. 2.1 / 3.1) for the shapes the stream kernel of verify_attention.hip is not built for:
 // fp32 inputs, heads of 64, page sizes other than 16, more than 16 query heads per KV head, very large batches.
-// Nothing is handed from one workgroup to another, so the call needs no workspace, except that bf16 items of a small call
-// are cut into pieces of their keys where the caller brings scratch memory for them.
+// Nothing is handed from one workgroup to another, so the call needs no workspace, except that bf16 items of a small call, and
+// the long ones of a larger call, are cut into pieces of their keys where the caller brings scratch memory for them.
 //
 // What bounds it is reading K and V (bf16) or the fp32 matrix instructions (fp32), so the work is laid out to read a
 // request's keys once per KV head: one workgroup per (request, KV head, group of up to 16 * MT query rows), its waves
@@ -53,6 +53,12 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kMaxSplits = 8;
 constexpr int kSplitKeys = 512;            // an item is not cut into pieces of fewer keys
 constexpr long long kSplitGroups = 256;    // workgroups a call is brought up to by cutting items: one per compute unit
+// Calls of many items cut the longest by their lengths, see BalancedPieces and, for the rule, layout_of.
+constexpr int kBalancedMaxB = 64;          // a request per lane
+constexpr int kBalancedKeys = 1536;        // keys from which an item is worth cutting
+constexpr int kPieceTiles = 8;             // least tiles of a piece that is handed over
+constexpr float kTileBase = 4.0f;          // a tile costs this + the query tiles that ride on it
+enum : int { kWhole = 0, kEven = 1, kBalanced = 2 };  // how items are cut
 
 struct ItemArgs {
     const void* q;
@@ -68,6 +74,7 @@ struct ItemArgs {
     long long page_stride, slot_stride, head_stride;  // of the caches, in bytes
     // bf16: an item is cut into up to `splits` pieces of at least kSplitKeys keys, handed over through the workspace
     int splits;
+    int places;      // balanced pieces: workgroups that run side by side
     float* part_o;   // [items * splits][16 * MTMAX][D] unnormalised sums of the pieces
     float* part_ml;  // [items * splits][16 * MTMAX][4] exponent reference (log2), sum, call tag, unused
     unsigned long long* arrivals;  // [items] (call id << 16 | pieces that have arrived)
@@ -84,12 +91,15 @@ __device__ __forceinline__ void lds_fence() {  // orders a wave's own LDS access
 }
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-template <bool BF16, int D, int MT>
+template <bool BF16, int D, int MT, int CUT>
 struct Map {
     // waves of a workgroup: eight at 256 registers each, or four at 512 where a tile in flight and the accumulators
     // need more than that (measured by the compiler's spill counts)
-    static constexpr int kW = D == 128 || MT == 4 ? 4 : 8;
+    static constexpr bool kLarge = D == 128 || MT == 4;
+    static constexpr int kW = kLarge ? 4 : 8;
+    static constexpr int kParts = CUT == kBalanced ? 2 : 1;  // items that a workgroup may work on side by side
     static constexpr int kThreads = kW * 64;
+    static constexpr int kPerSimd = kLarge ? 1 : 2;          // waves that share a SIMD
     static constexpr int kElem = BF16 ? 2 : 4;
     static constexpr int kTile = BF16 ? 32 : 16;             // keys of a wave tile
     static constexpr int kKt = kTile / 16;
@@ -101,7 +111,7 @@ struct Map {
     static constexpr int kShared = kStage > kRed ? kStage : kRed;
     static constexpr int kMl = kShared;                      // references and sums of all waves
     static constexpr int kQ = kMl + 2 * kW * 16 * MT * 4;
-    static constexpr int kSmem = kQ + MT * kQPieces * 1024;
+    static constexpr int kSmem = kQ + kParts * MT * kQPieces * 1024;
 };
 
 // LDS places of 16-byte chunk ch of key row `row`, such that the accesses of 16 lanes cover all banks: K is written and
@@ -132,17 +142,19 @@ __device__ __forceinline__ void write_out(const ItemArgs& a, size_t at, float x)
     else reinterpret_cast<float*>(a.out)[at] = x;
 }
 
-// The pieces of an item's rows m0 .. m0 + rows - 1, slots slot0 .. slot0 + n - 1, to the rows themselves: four values of a row
-// to a thread at a time.  Ordinary loads: a slot was stored through to memory before its piece was counted, is written and
+// The pieces of an item's rows m0 .. m0 + rows - 1, slots slot0, next, next + step, .., n of them, to the rows themselves: four
+// values of a row to a thread at a time.  Ordinary loads: a slot was stored through to memory before its piece was counted, is written and
 // read once per launch, and caches start a launch without older copies.  A slot that this call did not write makes its rows NaN.
 template <int D, int ROWS>
-__device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0, int m0, int rows, long long slot0, int n) {
-    for (int e = threadIdx.x; e < rows * (D / 4); e += blockDim.x) {
+__device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0, int m0, int rows, long long slot0, long long next, int step,
+                                               int n, int thread, int threads) {
+    for (int e = thread; e < rows * (D / 4); e += threads) {
         const int m = e / (D / 4), d0 = (e % (D / 4)) * 4;
         f32x4 ml[kMaxSplits], o[kMaxSplits];
 #pragma unroll
         for (int k = 0; k < kMaxSplits; ++k) {  // past the last piece: it again, left out below
-            const long long row = (slot0 + min(k, n - 1)) * ROWS + m;
+            const int p = min(k, n - 1);
+            const long long row = (p == 0 ? slot0 : next + (p - 1) * step) * ROWS + m;
             ml[k] = *reinterpret_cast<const f32x4*>(a.part_ml + row * 4);
             o[k] = *reinterpret_cast<const f32x4*>(a.part_o + row * D + d0);
         }
@@ -172,19 +184,28 @@ __device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0,
     }
 }
 
+// Who works on a piece: waves first .. first + waves - 1 of the workgroup, on `pieces` consecutive ones; the item's keys are shared
+// by `of` such parts.
+struct Part {
+    int first, waves, pieces, of;
+};
+
 // Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see (piece sp of n_sp of
 // them), merge the waves, write the rows (or the piece's sums to slot slot0 + sp).  MTMAX: what the LDS is laid out for.
-template <bool BF16, int D, int MTMAX, int MT, bool NT, bool SPLIT>
+template <bool BF16, int D, int MTMAX, int MT, bool NT, int CUT>
 __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0, int sp, int n_sp,
-                                             long long slot0) {
-    typedef Map<BF16, D, MTMAX> L;
+                                             long long slot, const Part& part) {
+    typedef Map<BF16, D, MTMAX, CUT> L;
+    constexpr bool SPLIT = CUT != kWhole;
     constexpr int kTile = L::kTile, kKt = L::kKt, kDB = D / 16, kW = L::kW;
     const int lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6), lg = lane >> 4, li = lane & 15;
     const int kv_cap = (int)min((long long)a.max_pages * a.P, 1LL << 30);
     const int32_t* bt = a.bt + (size_t)i * a.max_pages;
     const char* kc = reinterpret_cast<const char*>(a.k) + (size_t)g * a.head_stride;
     const char* vc = reinterpret_cast<const char*>(a.v) + (size_t)g * a.head_stride;
-    char* qbuf = smem + L::kQ;
+    // the waves of the item: all, or four of them; this one's place among them
+    const int n_waves = CUT == kBalanced ? part.waves : kW, wi = CUT == kBalanced ? w - part.first : w;
+    char* qbuf = smem + L::kQ + (CUT == kBalanced && part.first > 0 ? MT * L::kQPieces * 1024 : 0);
     float* red_m = reinterpret_cast<float*>(smem + L::kMl);  // [kW][16 * MT]
     float* red_l = red_m + kW * 16 * MT;
     char* kbuf = smem + w * 2 * kTile * L::kRow;  // the wave's tiles (bf16)
@@ -193,23 +214,25 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     const int rows = min(16 * MT, M - m0);
     const int first_lim = c + m0 / a.G;                           // last key the group's first row sees
     int kend = min(c + (m0 + rows - 1) / a.G + 1, kv_cap);  // keys any row of the group sees
-    int kb0 = w * kTile;
-    if (SPLIT && n_sp > 1) {  // the piece's even share of their tiles (at most 2^30 keys and eight pieces: the products fit 32 bits)
+    int kb0 = wi * kTile;
+    if (SPLIT && part.of > 1) {  // the piece's even share of their tiles (at most 2^30 keys and eight pieces: the products fit 32 bits)
         const unsigned n_tiles = (unsigned)(kend + kTile - 1) / kTile;
+        const int upto = sp + (CUT == kBalanced ? part.pieces : 1);
         kb0 += (int)(n_tiles * sp / n_sp) * kTile;
-        if (sp + 1 < n_sp) kend = (int)(n_tiles * (sp + 1) / n_sp) * kTile;
+        if (upto < n_sp) kend = (int)(n_tiles * upto / n_sp) * kTile;
     }
-    const int step = kW * kTile;
-    const int nw = kb0 < kend ? (kend - kb0 + step - 1) / step : 0;
+    const int step = n_waves * kTile;
+    const int nw = rows > 0 && kb0 < kend ? (kend - kb0 + step - 1) / step : 0;
     // the wave's first n_plain tiles lie wholly below every row's causal limit
     const int below = min(first_lim + 1, kend) - kTile - kb0;
     const int n_plain = below < 0 ? 0 : below / step + 1;
 
     // ---- query operands to LDS: piece (mt, s) holds for lane (li, lg) 16 bytes of row mt * 16 + li
-    for (int pr = w; pr < MT * L::kQPieces; pr += kW) {
+    for (int pr = wi; pr < MT * L::kQPieces; pr += n_waves) {
         const int m = m0 + (pr / L::kQPieces) * 16 + li;
         const bool ok = m < M;
-        const int j = (ok ? m : m0) / a.G, gq = (ok ? m : m0) % a.G;
+        const int mv = ok ? m : m0 < M ? m0 : 0;  // (the other item of the workgroup may have more rounds than this one)
+        const int j = mv / a.G, gq = mv % a.G;
         const char* src = reinterpret_cast<const char*>(a.q) + ((size_t)(q0 + j) * a.H_q + g * a.G + gq) * L::kRow +
                           64 * (pr % L::kQPieces) + 16 * lg;
         u32x4 x = *reinterpret_cast<const gu32x4*>(src);
@@ -504,57 +527,175 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
         for (int db = 0; db < kDB; ++db)
             *reinterpret_cast<f32x4*>(red + (w * 16 + li) * L::kRedStride + db * 16 + 4 * lg) = acc[mt][db];
         __syncthreads();
-        constexpr int kPer = 16 * D / L::kThreads;  // a thread sums kPer consecutive values of one row
-        const int row = threadIdx.x / (D / kPer), d0 = (threadIdx.x % (D / kPer)) * kPer, m = mt * 16 + row;
-        float top = -INFINITY;
+        // the item's threads sum kPer consecutive values of one row each
+        auto sum_rows = [&](auto waves_, int thread, int first) {
+            constexpr int kWaves = decltype(waves_)::value, kPer = 16 * D / (64 * kWaves);
+            asm volatile("" : "+v"(thread));  // or the offsets below are made at the kernel's start and spilled
+            const int row = thread / (D / kPer), d0 = (thread % (D / kPer)) * kPer, m = mt * 16 + row;
+            float top = -INFINITY;
 #pragma unroll
-        for (int ww = 0; ww < kW; ++ww) top = fmaxf(top, red_m[ww * 16 * MT + m]);
-        const float ref = top == -INFINITY ? 0.0f : top;
-        float sum = 0.0f, o[kPer];
+            for (int ww = 0; ww < kWaves; ++ww) top = fmaxf(top, red_m[(first + ww) * 16 * MT + m]);
+            const float ref = top == -INFINITY ? 0.0f : top;
+            float sum = 0.0f, o[kPer];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) o[u] = 0.0f;
+            for (int u = 0; u < kPer; ++u) o[u] = 0.0f;
 #pragma unroll
-        for (int ww = 0; ww < kW; ++ww) {
-            const float e = exp2_fast(red_m[ww * 16 * MT + m] - ref);  // 0 for a wave that saw no key of the row
-            sum = fmaf(red_l[ww * 16 * MT + m], e, sum);
+            for (int ww = 0; ww < kWaves; ++ww) {
+                const float e = exp2_fast(red_m[(first + ww) * 16 * MT + m] - ref);  // 0 for a wave that saw no key of the row
+                sum = fmaf(red_l[(first + ww) * 16 * MT + m], e, sum);
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const float part = red[(ww * 16 + row) * L::kRedStride + d0 + u];
-                o[u] = fmaf(part, e, o[u]);
+                for (int u = 0; u < kPer; ++u) {
+                    const float part_o = red[((first + ww) * 16 + row) * L::kRedStride + d0 + u];
+                    o[u] = fmaf(part_o, e, o[u]);
+                }
             }
-        }
-        if (SPLIT && n_sp > 1 && m < rows) {
-            const long long row = (slot0 + sp) * (16 * MTMAX) + m;
-            if constexpr (kPer >= 4) {
+            if (SPLIT && part.of > 1 && m < rows) {
+                const long long at = slot * (16 * MTMAX) + m;
+                if constexpr (kPer >= 4) {
 #pragma unroll
-                for (int u = 0; u < kPer; u += 4) store_device(a.part_o, row * D + d0 + u, f32x4{o[u], o[u + 1], o[u + 2], o[u + 3]});
-            } else {  // two neighbours make a vector
-                static_assert(kPer == 2 || kPer >= 4, "a thread's values are whole vectors or half of one");
-                const float o2 = __shfl_down(o[0], 1, 64), o3 = __shfl_down(o[1], 1, 64);
-                if (d0 % 4 == 0) store_device(a.part_o, row * D + d0, f32x4{o[0], o[1], o2, o3});
+                    for (int u = 0; u < kPer; u += 4) store_device(a.part_o, at * D + d0 + u, f32x4{o[u], o[u + 1], o[u + 2], o[u + 3]});
+                } else {  // two neighbours make a vector
+                    static_assert(kPer == 2 || kPer >= 4, "a thread's values are whole vectors or half of one");
+                    const float o2 = __shfl_down(o[0], 1, 64), o3 = __shfl_down(o[1], 1, 64);
+                    if (d0 % 4 == 0) store_device(a.part_o, at * D + d0, f32x4{o[0], o[1], o2, o3});
+                }
+                if (d0 == 0) store_device(a.part_ml, at * 4, f32x4{top, sum, __builtin_bit_cast(float, (uint32_t)a.call_id), 0.0f});
+            } else if (m < rows) {
+                const int j = (m0 + m) / a.G, h = g * a.G + (m0 + m) % a.G;
+                const size_t at = ((size_t)(q0 + j) * a.H_q + h) * D + d0;
+                const float inv = 1.0f / sum;
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) write_out(a, at + u, o[u] * inv);
+                if (a.lse && d0 == 0) a.lse[(size_t)(q0 + j) * a.H_q + h] = top * kLn2 + logf(sum);
             }
-            if (d0 == 0) store_device(a.part_ml, row * 4, f32x4{top, sum, __builtin_bit_cast(float, (uint32_t)a.call_id), 0.0f});
-        } else if (m < rows) {
-            const int j = (m0 + m) / a.G, h = g * a.G + (m0 + m) % a.G;
-            const size_t at = ((size_t)(q0 + j) * a.H_q + h) * D + d0;
-            const float inv = 1.0f / sum;
-#pragma unroll
-            for (int u = 0; u < kPer; ++u) write_out(a, at + u, o[u] * inv);
-            if (a.lse && d0 == 0) a.lse[(size_t)(q0 + j) * a.H_q + h] = top * kLn2 + logf(sum);
+        };
+        if constexpr (CUT == kBalanced) {
+            if (part.waves == 4) sum_rows(std::integral_constant<int, 4>{}, threadIdx.x - 64 * part.first, part.first);
+            else sum_rows(std::integral_constant<int, kW>{}, threadIdx.x, 0);
+        } else {
+            sum_rows(std::integral_constant<int, kW>{}, threadIdx.x, 0);
         }
     }
 }
 
-// SPLIT: one group per item, grid.z counts the pieces its keys are cut into; else grid.z counts the groups.
-template <bool BF16, int D, int MTMAX, bool NT, bool SPLIT>
-__global__ __launch_bounds__((Map<BF16, D, MTMAX>::kThreads)) void attend_items_kernel(ItemArgs a) {
+// Balanced pieces: every item is cut into as many as it takes for none to last longer than a
+// common time, the shortest that leaves no more pieces than there are places for four waves.  A workgroup holds two places.
+// The items of an even number of pieces come first, so that theirs lie side by side: a workgroup whose two places hold pieces of
+// one item works on both with all of its waves.  Every wave works this out for itself, from the lengths in its lanes: some 2 us.
+// D = 64, 32/8 heads, 1-8 drafts, us a call, an item per workgroup / balanced: 20 requests of 256-4096 tokens 37.9 / 29.3, 24 39.0 /
+// 32.6, 32 40.5 / 36.8, 40 49.4 / 40.6, 48 64.8 / 57.3; 32 with log-normal contexts up to 8192 72 / 49; equal lengths, where there
+// is nothing to balance, 32 of 2176 30.6 / 32.8, 48 57.5 / 48.6.  Workgroups of four waves, two to a compute unit, in place of two
+// items side by side in one of eight: 32 of 2176 37.1, and 14 us for 32 of up to 256.
+struct Piece {
+    int i, g, sp, n_sp, place0;  // piece sp of the n_sp of request i's item for KV head g, the first of which has place0
+    int q0, q_len, c;            // the request's rows and context
+};
+template <int MTMAX>
+struct BalancedPieces {
+    int k, from, upto;  // the lane's request: pieces of an item, places of all of its items
+    int q0, ql, c;      // its rows and context
+
+    __device__ __forceinline__ explicit BalancedPieces(const ItemArgs& a) {
+        const int lane = threadIdx.x & 63;
+        float work = 0.0f;
+        int most = 0;
+        q0 = ql = c = 0;
+        if (lane < a.B) {
+            q0 = a.cu_q[lane];
+            ql = min(a.cu_q[lane + 1], a.N_cap) - q0;
+            c = a.ctx[lane];
+            const int M = ql * a.G;
+            if (ql > 0) {
+                const int seen = (int)min((long long)max(c, 0) + ql, min((long long)a.max_pages * a.P, 1LL << 30));
+                const int tiles = max((seen + 31) / 32, 1);
+                work = (float)tiles * (kTileBase + (float)((min(M, 16 * MTMAX) + 15) / 16));
+                // (rows beyond the caller's bound are further rounds: a slot would be written twice, so no pieces then)
+                // two lie side by side and cost nothing; more have to be long enough to be worth handing over
+                most = M <= 16 * MTMAX ? min(kMaxSplits, max(tiles / kPieceTiles, min(tiles, 2))) : 1;
+            }
+        }
+        const float longest = __builtin_bit_cast(float, wave_max_positive(__builtin_bit_cast(int, work)));
+        // times from the longest item's down to an eighth of it, 32 in equal ratios, by bisection; lane n holds longest / time n
+        const float ratios = exp2_fast((float)lane * (3.0f / 31.0f)), share = work * __builtin_amdgcn_rcpf(longest);
+        auto pieces = [&](int n) {
+            const float r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ratios), n));
+            return min(most, max((int)__builtin_ceilf(share * r - 1e-4f), 1));
+        };
+        int lo = 0;
+#pragma unroll
+        for (int bit = 16; bit > 0; bit >>= 1)  // largest n that fits; n = 0, nothing is cut, always does
+            if ((long long)wave_sum_i(pieces(lo + bit)) * a.H_kv <= a.places) lo += bit;
+        k = pieces(lo);
+        const int even = (k & 1) == 0 ? k * a.H_kv : 0, odd = k * a.H_kv - even;
+        const int upto_even = wave_inclusive_scan_dpp(even), upto_odd = wave_inclusive_scan_dpp(odd);
+        upto = even > 0 ? upto_even : odd > 0 ? __builtin_amdgcn_readlane(upto_even, 63) + upto_odd : 0;
+        from = upto - k * a.H_kv;
+    }
+    // What lies at a place; n_sp = 0: nothing.
+    __device__ __forceinline__ Piece at(int place) const {
+        Piece p{0, 0, 0, 0, 0, 0, 0, 0};
+        const unsigned long long mine = __builtin_amdgcn_ballot_w64(place < upto && place >= from);
+        if (mine == 0) return p;
+        p.i = __builtin_ctzll(mine);
+        p.n_sp = __builtin_amdgcn_readlane(k, p.i);
+        const int first = __builtin_amdgcn_readlane(from, p.i);
+        p.g = (int)(((float)(place - first) + 0.5f) * __builtin_amdgcn_rcpf((float)p.n_sp));  // (place - first) / n_sp: small numbers
+        p.g = uniform(p.g);
+        p.place0 = first + p.g * p.n_sp;
+        p.sp = place - p.place0;
+        p.q0 = __builtin_amdgcn_readlane(q0, p.i);
+        p.q_len = __builtin_amdgcn_readlane(ql, p.i);
+        p.c = __builtin_amdgcn_readlane(c, p.i);
+        return p;
+    }
+};
+
+// CUT: one group per item, whose keys are cut into pieces -- evenly, grid.z of them, or by BalancedPieces; else grid.z counts the groups.
+template <bool BF16, int D, int MTMAX, bool NT, int CUT>
+__global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D, MTMAX, CUT>::kPerSimd)) void attend_items_kernel(ItemArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int g = blockIdx.x, i = blockIdx.y;
-    const int q0 = a.cu_q[i], q_len = min(a.cu_q[i + 1], a.N_cap) - q0, c = a.ctx[i];
+    constexpr int kW = Map<BF16, D, MTMAX, CUT>::kW;
+    int g = blockIdx.x, i = blockIdx.y, n_sp = 1, sp = 0, z = blockIdx.z, nz = gridDim.z, mt_group = 0;
+    long long slot = 0;
+    Part part{0, kW, 1, 1};
+    int next_slot = 0, slot_step = 1;
+    bool cut = true;
+    long long slot0 = 0;
+    int q0, q_len, c;
+    if constexpr (CUT == kBalanced) {
+        const BalancedPieces<MTMAX> bp(a);
+        const int half = uniform(threadIdx.x >> 8);
+        const Piece p0 = bp.at(2 * blockIdx.x), p1 = bp.at(2 * blockIdx.x + 1);
+        if (p0.n_sp == 0 && p1.n_sp == 0) return;
+        const bool joint = p0.n_sp > 0 && p1.n_sp > 0 && p0.place0 == p1.place0;
+        const Piece p = joint || half == 0 ? p0 : p1;
+        i = p.i; g = p.g; sp = p.sp; n_sp = p.n_sp;
+        part.first = joint ? 0 : half * 4;
+        part.waves = joint ? 8 : 4;
+        part.pieces = joint ? 2 : 1;
+        const int w0 = p.place0 >> 1;
+        auto parts_of = [](const Piece& x) { return x.n_sp > 0 ? ((x.place0 + x.n_sp - 1) >> 1) - (x.place0 >> 1) + 1 : 1; };
+        part.of = parts_of(p);
+        cut = parts_of(p0) > 1 || parts_of(p1) > 1;
+        slot = joint ? 2 * blockIdx.x : 2 * blockIdx.x + half;
+        slot0 = p.place0;
+        next_slot = 2 * (w0 + 1);
+        slot_step = 2;
+        z = 0;
+        nz = 1;
+        // the same number of query tiles for both, so that their barriers meet (an empty place has no rows)
+        mt_group = max(p0.q_len, p1.q_len) * a.G;
+        q0 = p.q0; q_len = p.q_len; c = p.c;
+    } else {
+        q0 = a.cu_q[i];
+        q_len = min(a.cu_q[i + 1], a.N_cap) - q0;
+        c = a.ctx[i];
+    }
     const int M = q_len * a.G;
-    if (q_len <= 0) return;
-    int n_sp = 1, sp = 0, z = blockIdx.z, nz = gridDim.z;
-    if constexpr (SPLIT) {
+    if (CUT != kBalanced && q_len <= 0) return;
+    const long long word = (long long)i * a.H_kv + g;
+    if constexpr (CUT == kEven) {
+        slot0 = word * gridDim.z;
         // (rows beyond the caller's bound are further rounds: a slot would be written twice, so no pieces then)
         const int seen = (int)min((long long)c + q_len, min((long long)a.max_pages * a.P, 1LL << 30));
         if (M <= 16 * MTMAX) n_sp = max(1, min((int)gridDim.z, seen / kSplitKeys));
@@ -562,47 +703,58 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX>::kThreads)) void attend_items_
         if (sp >= n_sp) return;
         z = 0;
         nz = 1;
+        slot = slot0 + sp;
+        next_slot = (int)slot0 + 1;
+        part.of = n_sp;
     }
-    const long long word = (long long)i * gridDim.x + g, slot0 = word * gridDim.z;
-    for (int m0 = z * 16 * MTMAX; m0 < M; m0 += nz * 16 * MTMAX) {
-        const int mt = (min(M - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
+    if (CUT != kBalanced) mt_group = M;
+    for (int m0 = z * 16 * MTMAX; m0 < mt_group; m0 += nz * 16 * MTMAX) {
+        const int mt = (min(mt_group - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
         if constexpr (MTMAX >= 4)
-            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
+            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
         if constexpr (MTMAX >= 3)
-            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
+            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
         if constexpr (MTMAX >= 2)
-            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
-        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, SPLIT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot0);
+            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
+        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
         __syncthreads();  // before the next group's query operands and tiles
     }
-    if constexpr (SPLIT) {
-        __shared__ int s_last;
-        if (n_sp == 1) return;
+    if constexpr (CUT != kWhole) {
+        __shared__ int s_last[2];
+        if (CUT == kEven ? n_sp == 1 : !cut) return;
+        const int half = part.first > 0 ? 1 : 0, thread = threadIdx.x - 64 * part.first;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the piece is in memory once every wave's stores are acknowledged
         __syncthreads();
-        if (threadIdx.x == 0) s_last = count_arrival(a.arrivals + word, a.call_id) == n_sp;
+        if (thread == 0) s_last[half] = part.of > 1 && count_arrival(a.arrivals + word, a.call_id) == part.of;
         __syncthreads();
-        if (!s_last) return;
-        combine_pieces<D, 16 * MTMAX>(a, g, q0, 0, M, slot0, n_sp);
-        if (threadIdx.x == 0) __atomic_store_n(a.arrivals + word, a.call_id << 16, __ATOMIC_RELAXED);  // for a graph's next replay
+        if (!s_last[half]) return;
+        combine_pieces<D, 16 * MTMAX>(a, g, q0, 0, M, slot0, next_slot, slot_step, part.of, thread, 64 * part.waves);
+        if (thread == 0) __atomic_store_n(a.arrivals + word, a.call_id << 16, __ATOMIC_RELAXED);  // for a graph's next replay
     }
+}
+
+template <bool BF16, int D, int MT, bool NT, int CUT>
+void launch_as(const ItemArgs& a, unsigned z, hipStream_t s) {
+    typedef Map<BF16, D, MT, CUT> L;
+    const dim3 grid = CUT == kBalanced ? dim3((unsigned)(a.places / 2)) : dim3((unsigned)a.H_kv, (unsigned)a.B, z);
+    hipLaunchKernelGGL((attend_items_kernel<BF16, D, MT, NT, CUT>), grid, dim3(L::kThreads), L::kSmem, s, a);
 }
 
 template <bool BF16, int D, int MT>
 int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
-    const dim3 grid((unsigned)a.H_kv, (unsigned)a.B, a.splits > 1 ? (unsigned)a.splits : groups), block(Map<BF16, D, MT>::kThreads);
-    const size_t smem = Map<BF16, D, MT>::kSmem;
     // keys that one workgroup reads once bypass the caches' replacement (non-temporal); further groups of a request
     // find them in the caches.  D = 64, 32/8 heads, 256 to 4096 tokens, us a call over the caches of 24 layers in turn,
     // non-temporal / plain: 16 requests 38.2 / 39.8, 64 70.6 / 78.2, 128 125 / 140, 32/32 heads 64 requests 191 / 216, one
     // request of 8192 tokens 55.2 / 55.7.  (Called again and again on one pair of caches that the last level holds, the
     // plain loads win at the small end: one request of 8192 tokens 54.0 / 47.3.)
     if constexpr (BF16) {
-        if (a.splits > 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true, true>), grid, block, smem, s, a);
-        else if (groups == 1) hipLaunchKernelGGL((attend_items_kernel<true, D, MT, true, false>), grid, block, smem, s, a);
-        else hipLaunchKernelGGL((attend_items_kernel<true, D, MT, false, false>), grid, block, smem, s, a);
+        if (a.places > 0) {
+            if constexpr (!Map<true, D, MT, kBalanced>::kLarge) launch_as<true, D, MT, true, kBalanced>(a, 1, s);
+        } else if (a.splits > 1) launch_as<true, D, MT, true, kEven>(a, (unsigned)a.splits, s);
+        else if (groups == 1) launch_as<true, D, MT, true, kWhole>(a, 1, s);
+        else launch_as<true, D, MT, false, kWhole>(a, groups, s);
     } else {
-        hipLaunchKernelGGL((attend_items_kernel<false, D, MT, false, false>), grid, block, smem, s, a);
+        launch_as<false, D, MT, false, kWhole>(a, groups, s);
     }
     return check_launch("attend_items_kernel");
 }
@@ -612,6 +764,7 @@ struct Layout {
     int mt;           // query tiles of a group
     unsigned groups;  // workgroups an item's rows are dealt to
     int splits;       // pieces an item's keys are cut into at most
+    int places;       // > 0: items are cut by their lengths, into this many pieces in all
     size_t bytes_o, bytes_ml, bytes_cnt;
 };
 Layout layout_of(const fsr_attn_params& p) {
@@ -639,12 +792,19 @@ Layout layout_of(const fsr_attn_params& p) {
         const long long keys = (long long)p.max_pages * p.P;
         const long long units = p.max_workgroups > 0 ? std::min<long long>(p.max_workgroups, kSplitGroups) : kSplitGroups;
         l.splits = (int)std::max(1LL, std::min({(long long)kMaxSplits, keys / kSplitKeys, units / items}));
+        // From more items than half the units to one and a half times as many, heads of 64 (eight waves a workgroup): balanced by
+        // length.  With fewer even pieces do as well (16 requests 26.5 / 26.6), with more the units have several items anyway (56
+        // requests 68.7 / 71.5).  Short contexts are not worth the schedule (32 of up to 256 tokens 10.1 / 11.5).
+        if (p.D == 64 && l.mt < 4 && p.B > 1 && p.B <= kBalancedMaxB && keys >= kBalancedKeys && 2 * items > units && 2 * items <= 3 * units) {
+            l.places = (int)(2 * units);
+            l.splits = 1;
+        }
     }
-    const size_t slots = (size_t)items * l.splits, row = (size_t)16 * l.mt;
-    if (l.splits > 1) {
+    const size_t slots = l.places > 0 ? (size_t)l.places : (size_t)items * l.splits, row = (size_t)16 * l.mt;
+    if (l.splits > 1 || l.places > 0) {
         l.bytes_o = align_up(slots * row * p.D * sizeof(float), 256);
         l.bytes_ml = align_up(slots * row * 4 * sizeof(float), 256);
-        l.bytes_cnt = align_up((size_t)items * sizeof(unsigned long long), 256);
+        l.bytes_cnt = align_up((size_t)items * sizeof(unsigned long long), 256);  // (no more items than places)
     }
     return l;
 }
@@ -664,9 +824,9 @@ int launch_mt(const ItemArgs& a, const Layout& l, hipStream_t s) {
 // For as many slots as any batch uses, so that the size covers smaller batches too (which are cut into more pieces).
 size_t attend_items_workspace_bytes(const fsr_attn_params& p) {
     if (p.dtype != FSR_BF16) return 0;
-    const size_t rows = (size_t)kSplitGroups * 16 * layout_of(p).mt;
+    const size_t slots = (p.D == 64 ? 2 : 1) * (size_t)kSplitGroups, rows = slots * 16 * layout_of(p).mt;
     return align_up(rows * p.D * sizeof(float), 256) + align_up(rows * 4 * sizeof(float), 256) +
-           align_up((size_t)kSplitGroups * sizeof(unsigned long long), 256);
+           align_up(slots * sizeof(unsigned long long), 256);
 }
 
 int attend_items_launch(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_tables,
@@ -688,12 +848,13 @@ int attend_items_launch(const void* q, const void* k_cache, const void* v_cache,
     a.scale_rest = (float)(p->scale - a.scale_log2 / kLog2e);
     Layout l = layout_of(*p);
     // a caller without (enough) scratch memory gets one workgroup per group
-    if (l.splits > 1 && (!workspace || ((uintptr_t)workspace & 255) || ws_bytes < l.bytes_o + l.bytes_ml + l.bytes_cnt)) l.splits = 1;
+    if ((l.splits > 1 || l.places > 0) && (!workspace || ((uintptr_t)workspace & 255) || ws_bytes < l.bytes_o + l.bytes_ml + l.bytes_cnt)) l.splits = 1, l.places = 0;
     a.splits = l.splits;
+    a.places = l.places;
     a.part_o = (float*)workspace;
     a.part_ml = (float*)((char*)workspace + l.bytes_o);
     a.arrivals = (unsigned long long*)((char*)workspace + l.bytes_o + l.bytes_ml);
-    a.call_id = l.splits > 1 ? next_call_id() : 0;
+    a.call_id = l.splits > 1 || l.places > 0 ? next_call_id() : 0;
     if (p->dtype == FSR_BF16) return p->D == 64 ? launch_mt<true, 64>(a, l, s) : launch_mt<true, 128>(a, l, s);
     return p->D == 64 ? launch_mt<false, 64>(a, l, s) : launch_mt<false, 128>(a, l, s);
 }

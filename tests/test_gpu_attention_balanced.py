@@ -1,0 +1,94 @@
+"""GPU parity of bf16 attention over heads of 64 whose items are cut by their lengths (more items than half the compute units, at
+most one and a half times as many): against the oracle, with and without scratch memory, and in graph replays over other lengths."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_utils import announce, check_attention, dev
+from test_gpu_attention_items import make
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fsr():
+    import paper_2604_20503_amd as f
+    f.load_library()
+    return f
+
+
+def lengths(kind, B, rng):
+    if kind == "equal":
+        return np.full(B, 1600), np.full(B, 2)
+    if kind == "one long":
+        ctx = rng.integers(0, 70, B)
+        ctx[B // 2] = 3000
+        return ctx, rng.integers(0, 4, B)
+    return rng.integers(0, 1700, B), rng.integers(0, 4, B)
+
+
+# items per call; one, two and three query tiles; the last two have rows beyond the bound that is given
+@pytest.mark.parametrize("H_q,H_kv,B,hint,token_major,P", [(16, 16, 9, 4, False, 16), (8, 4, 64, 4, True, 16), (64, 8, 17, 4, False, 24),
+                                                           (48, 4, 40, 4, False, 16), (32, 8, 48, 2, True, 16), (24, 6, 30, 1, False, 16)])
+@pytest.mark.parametrize("kind", ["ragged", "one long", "equal"])
+def test_items_balanced_by_length(fsr, oracle, H_q, H_kv, B, hint, token_major, P, kind):
+    announce(f"balanced items {H_q}/{H_kv} B={B} hint={hint} token_major={token_major} P={P} {kind}")
+    rng = np.random.Generator(np.random.PCG64(B + H_q))
+    ctx, spec = lengths(kind, B, rng)
+    if kind != "equal":
+        ctx[0] = 1690  # the block tables are wide enough for pieces
+        ctx[B // 3 + 1] = 100
+    x = make(rng, "bf16", H_q, H_kv, 64, P, ctx, spec)
+    if kind == "ragged":
+        x["cu"][B // 3 + 1] = x["cu"][B // 3]  # a request without rows; the one behind it has its rows as well,
+        x["ctx"][B // 3 + 1] = 90              # on the pages it has
+    scale = 1.0 / 8.0
+    swap = (lambda t: np.ascontiguousarray(np.swapaxes(t, 1, 2))) if token_major else (lambda t: t)
+    q, k, v = dev(x["q"], True), dev(swap(x["k"]), True), dev(swap(x["v"]), True)
+    ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=H_q, H_kv=H_kv, D=64, P=P,
+                                           dtype="bf16", scale=float(np.float32(scale)))
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+    for ws in (None, None, torch.empty(256, dtype=torch.uint8, device="cuda")):  # the second call finds the first one's counts
+        out.fill_(float("nan"))
+        fsr.verify_attention(q, k, v, dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=scale, out=out, lse=lse,
+                             max_q_len=hint, workspace=ws, kv_layout=1 if token_major else 0)
+        torch.cuda.synchronize()
+        check_attention(out, ref, "f32", len(ref))
+        np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
+def test_balanced_items_in_a_graph(fsr):
+    """Replays over contexts that change, with eager calls on the same workspace between them: the bits of an eager call on a
+    workspace of its own."""
+    announce("balanced items in a graph")
+    rng = np.random.Generator(np.random.PCG64(2))
+    B = 20
+    x = make(rng, "bf16", 32, 8, 64, 16, rng.integers(1000, 1700, B), rng.integers(0, 4, B))
+    q, k, v, bt, cu = dev(x["q"], True), dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["cu"])
+    need = fsr.attn_workspace_bytes(B=B, N_cap=q.shape[0], H_q=32, H_kv=8, D=64, P=16, max_pages=bt.shape[1], n_pages=k.shape[0],
+                                    dtype=torch.bfloat16, out_dtype=torch.bfloat16, max_q_len=4)
+    ws, own = (torch.full((need,), 0x55, dtype=torch.uint8, device="cuda") for _ in range(2))
+    c, out, want = dev(x["ctx"]), torch.empty_like(q), torch.empty_like(q)
+
+    def call(ctx, into, workspace):
+        fsr.verify_attention(q, k, v, bt, ctx, None, cu, scale=0.125, out=into, max_q_len=4, workspace=workspace)
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call(c, out, ws)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            call(c, out, ws)
+        for rep in range(4):
+            c.copy_(dev(np.minimum(x["ctx"], rng.integers(0, 1700, B)).astype(np.int32)))
+            out.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            call(c, want, own)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+            call(c, out, ws)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16))
