@@ -89,14 +89,19 @@ __device__ __forceinline__ int wave_sum_i(int v) { return __builtin_amdgcn_readl
 // Count one more arrival on a 64-bit word that holds (call id << 16 | count).  A word left by another
 // call (or never written) counts as zero, so the memory it lives in needs no clearing between calls
 // and HIP-graph replays work.  Returns the count including this arrival.  Device scope.
+// One round trip to memory where others of the call have arrived before (whoever comes last waits for nothing else): the word is
+// added to before it is known whose it is, and one of another call's is replaced by this call's, whichever arrival manages that.
 __device__ __forceinline__ int count_arrival(unsigned long long* word, unsigned long long call_id) {
-    unsigned long long seen = __atomic_load_n(word, __ATOMIC_RELAXED);
     for (;;) {
-        const unsigned long long have = (seen >> 16) == call_id ? (seen & 0xffffu) : 0u;
-        const unsigned long long want = (call_id << 16) | (have + 1);
-        const unsigned long long prev = atomicCAS(word, seen, want);
-        if (prev == seen) return (int)(have + 1);
-        seen = prev;
+        const unsigned long long seen = atomicAdd(word, 1ull);
+        if ((seen >> 16) == call_id) return (int)(seen & 0xffffu) + 1;
+        unsigned long long stale = seen + 1;
+        for (;;) {
+            const unsigned long long prev = atomicCAS(word, stale, (call_id << 16) | 1);
+            if (prev == stale) return 1;
+            if ((prev >> 16) == call_id) break;  // another arrival has: count on its word
+            stale = prev;
+        }
     }
 }
 
