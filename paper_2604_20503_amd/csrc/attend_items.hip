@@ -530,7 +530,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
         // the item's threads sum kPer consecutive values of one row each
         auto sum_rows = [&](auto waves_, int thread, int first) {
             constexpr int kWaves = decltype(waves_)::value, kPer = 16 * D / (64 * kWaves);
-            asm volatile("" : "+v"(thread));  // or the offsets below are made at the kernel's start and spilled
+            if constexpr (BF16) asm volatile("" : "+v"(thread));  // or the offsets below are made at the kernel's start and spilled
             const int row = thread / (D / kPer), d0 = (thread % (D / kPer)) * kPer, m = mt * 16 + row;
             float top = -INFINITY;
 #pragma unroll
