@@ -42,7 +42,7 @@ constexpr int kPerThread = kChunk / kThreads;  // 16 contiguous tokens per threa
 constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (reference, sum) pair
 constexpr int kSkipMinRows = 2048;  // LOGITS mode: rows a call must be able to hold for rows behind a rejection to be left out
 constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
-constexpr int kMaxSampleGroup = 8;  // accept_sample: a workgroup takes 1, 2, 4 or 8 consecutive chunks (see launch_all)
+constexpr int kMaxSampleGroup = 16;  // accept_sample: most consecutive chunks that a workgroup takes (see sample_group_of)
 
 enum : int { kCaseNone = 0, kCaseResidual = 1, kCaseTarget = 2 };
 
@@ -913,8 +913,8 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
 }
 
 // ---------------------------------------------------------------------------------------
-// sample: request i = blockIdx.y; this workgroup owns chunks kSampleGroup * blockIdx.x .. + kSampleGroup - 1 of the
-// vocabulary.  grid = (ceil(n_chunks / kSampleGroup), B)
+// sample: request i = blockIdx.y; this workgroup owns chunks group * blockIdx.x .. + group - 1 of the
+// vocabulary (SINGLE: group is 1).  grid = (ceil(n_chunks / group), B)
 // Where a wave meets no residual in a chunk it sums the target row's masses as well, in case there is none anywhere (a
 // drafted token without probability, rows that are equal otherwise); left to the request's last workgroup, such a call of
 // 16 requests took 57 us in place of 17 (PROBS) and 127 in place of 50 (LOGITS), one of 128 requests 76 in place of 31 and
@@ -928,18 +928,21 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
 // chunks read again by the checked path / summed from the registers: all but 50 logits of a row masked 171 / 158, every
 // second one 164 / 141; exponents spread over several hundred (T = 0.02) 173 / 176, read again either way.
 // ---------------------------------------------------------------------------------------
-template <int MODE, typename RT, int kSampleGroup>
+template <int MODE, typename RT, bool SINGLE>
 __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_sample_kernel(
     const RT* __restrict__ p_target, const RT* __restrict__ p_draft, const float* __restrict__ u_sample,
-    int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int V, int S_max, double T, TempScale ts) {
-    __shared__ double s_part[kThreads / 64][kSampleGroup], s_part_t[kThreads / 64][kSampleGroup];
+    int32_t* __restrict__ n_emitted, int32_t* __restrict__ emitted, Workspace ws, int V, int S_max, double T, TempScale ts,
+    int group) {
+    constexpr int kMost = SINGLE ? 1 : kMaxSampleGroup;
+    __shared__ double s_part[kThreads / 64][kMost], s_part_t[kThreads / 64][kMost];
     __shared__ double s_wave[kThreads / 64];
     __shared__ int s_i[kThreads / 64];
     __shared__ double s_base, s_thr;
     __shared__ int s_chunk, s_fallback, s_last;
     __shared__ uint2 s_exp[MODE == FSR_LOGITS ? 256 : 1];
     const int nc = n_chunks_of(V), i = blockIdx.y;
-    const int c_first = blockIdx.x * kSampleGroup, n_here = min(kSampleGroup, nc - c_first);
+    if (SINGLE) group = 1;
+    const int c_first = blockIdx.x * group, n_here = min(group, nc - c_first);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int32_t* em = emitted + (size_t)i * (S_max + 1);
     Decision dec = ws.dec[i];
@@ -982,7 +985,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
         ed = exp_direct(s_exp, ts);
         __syncthreads();
     }
-    // A workgroup takes kSampleGroup consecutive chunks: the chain every workgroup goes through (decision record,
+    // A workgroup takes `group` consecutive chunks: the chain every workgroup goes through (decision record,
     // row loads, reduction, store-through, arrival count) is paid once per 128 KB instead of once per 32 KB.
     auto chunk_mass_checked = [&](int c, double& target) __attribute__((always_inline)) {  // any chunk, element by element
         double r = 0.0;
@@ -1231,6 +1234,31 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
     }
 }
 
+// Chunks per workgroup of accept_sample.
+// PROBS: a compute unit holds four of its workgroups, and they are alike, so what counts is how many times over the device is
+// filled and what one workgroup takes: its chunks and about two more for the chain it goes through.  Vocabulary 128256, us a
+// call with 1, 2, 4 or 8 chunks, as many as leave 1024 workgroups / like this: 16 requests 16.9 / 16.9, 48 23.4 / 18.4, 96 24.2 /
+// 22.3, 256 48.6 / 48.2; 152064, 128 28.9 / 29.2, 384 81.5 / 81.6 (87.5 with one chunk for the chain).
+// LOGITS: the chain is a smaller part: 96 requests 119.6 / 116.8, 128 165 / 167, 512 503 / 509.
+constexpr int kSamplePlaces = 1024;
+int sample_group_of(int mode, int B, int nc) {
+    if (mode == FSR_LOGITS) {
+        int g = 8;
+        while (g > 1 && (long long)B * ((nc + g - 1) / g) < kSamplePlaces) g >>= 1;
+        return g;
+    }
+    int best = 1;
+    long long least = LLONG_MAX;
+    for (int g = 1; g <= kMaxSampleGroup; ++g) {
+        const long long groups = (long long)B * ((nc + g - 1) / g), cost = (groups + kSamplePlaces - 1) / kSamplePlaces * (std::min(g, nc) + 2);
+        if (cost < least) {
+            least = cost;
+            best = g;
+        }
+    }
+    return best;
+}
+
 template <int MODE, typename RT>
 int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_tokens, const float* u_accept,
                const float* u_sample, const int32_t* cu_t, const int32_t* cu_d, const int32_t* t_rows,
@@ -1265,20 +1293,14 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
     hipLaunchKernelGGL((accept_decide_kernel<MODE, RT>), dim3(p.B), dim3(64 * decide_waves), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t,
                        cu_d, t_rows, d_rows, accepted_len, n_emitted, emitted, ws, p.B, p.V, p.S_max, T, ts);
     if ((rc = check_launch("accept_decide_kernel")) != FSR_OK) return rc;
-    // chunks per workgroup: as many as leave the device about four workgroups per compute unit (a small batch
-    // keeps one chunk per workgroup: there the call is a latency chain and parallelism is what shortens it).
-    // PROBS, vocabulary 128256, us a call with 1024 / 2048 / 4096 workgroups as the line: 64 requests 21.9 / 28.3 / 28.1,
-    // 128 requests 28.5 / 30.6 / 38.6, 512 requests 92.8 / 94.8 / 95.5.
-    int group = kMaxSampleGroup;
-    while (group > 1 && (long long)p.B * ((nc + group - 1) / group) < 1024) group >>= 1;
-#define FSR_SAMPLE(G)                                                                                                          \
-    hipLaunchKernelGGL((accept_sample_kernel<MODE, RT, G>), dim3((nc + G - 1) / G, p.B), dim3(kThreads), 0, s, p_target, p_draft, \
-                       u_sample, n_emitted, emitted, ws, p.V, p.S_max, T, ts)
-    if (group == 8) FSR_SAMPLE(8);
-    else if (group == 4) FSR_SAMPLE(4);
-    else if (group == 2) FSR_SAMPLE(2);
-    else FSR_SAMPLE(1);
-#undef FSR_SAMPLE
+    const int group = sample_group_of(MODE, p.B, nc);
+    const dim3 grid((nc + group - 1) / group, p.B), block(kThreads);
+    if (group == 1)
+        hipLaunchKernelGGL((accept_sample_kernel<MODE, RT, true>), grid, block, 0, s, p_target, p_draft, u_sample, n_emitted, emitted, ws, p.V,
+                           p.S_max, T, ts, group);
+    else
+        hipLaunchKernelGGL((accept_sample_kernel<MODE, RT, false>), grid, block, 0, s, p_target, p_draft, u_sample, n_emitted, emitted, ws, p.V,
+                           p.S_max, T, ts, group);
     return check_launch("accept_sample_kernel");
 }
 
