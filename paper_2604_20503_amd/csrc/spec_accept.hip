@@ -42,7 +42,7 @@ constexpr int kPerThread = kChunk / kThreads;  // 16 contiguous tokens per threa
 constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (reference, sum) pair
 constexpr int kSkipMinRows = 2048;  // LOGITS mode: rows a call must be able to hold for rows behind a rejection to be left out
 constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
-constexpr int kMaxSampleGroup = 16;  // accept_sample: most consecutive chunks that a workgroup takes (see sample_group_of)
+constexpr int kMaxSampleGroup = 8;  // accept_sample: most consecutive chunks that a workgroup takes (see sample_group_of)
 
 enum : int { kCaseNone = 0, kCaseResidual = 1, kCaseTarget = 2 };
 
@@ -1237,8 +1237,10 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
 // Chunks per workgroup of accept_sample.
 // PROBS: a compute unit holds four of its workgroups, and they are alike, so what counts is how many times over the device is
 // filled and what one workgroup takes: its chunks and about two more for the chain it goes through.  Vocabulary 128256, us a
-// call with 1, 2, 4 or 8 chunks, as many as leave 1024 workgroups / like this: 16 requests 16.9 / 16.9, 48 23.4 / 18.4, 96 24.2 /
-// 22.3, 256 48.6 / 48.2; 152064, 128 28.9 / 29.2, 384 81.5 / 81.6 (87.5 with one chunk for the chain).
+// call with 1, 2, 4 or 8 chunks, as many as leave 1024 workgroups / like this: 16 requests 16.9 / 16.9, 48 23.3 / 18.5, 96 24.4 /
+// 22.2, 256 48.6 / 48.2; 152064, 128 28.9 / 29.2, 384 82 / 82.  Beyond two rounds of the largest workgroups the places are taken as
+// they come free (some requests have nothing to sample) and most chunks a workgroup are best: the draw of a chunked step of
+// 512 requests 40.3 us with 8, 45.6 with the 10 that would make it two rounds.
 // LOGITS: the chain is a smaller part: 96 requests 119.6 / 116.8, 128 165 / 167, 512 503 / 509.
 constexpr int kSamplePlaces = 1024;
 int sample_group_of(int mode, int B, int nc) {
@@ -1247,6 +1249,7 @@ int sample_group_of(int mode, int B, int nc) {
         while (g > 1 && (long long)B * ((nc + g - 1) / g) < kSamplePlaces) g >>= 1;
         return g;
     }
+    if ((long long)B * ((nc + kMaxSampleGroup - 1) / kMaxSampleGroup) > 2 * kSamplePlaces) return kMaxSampleGroup;
     int best = 1;
     long long least = LLONG_MAX;
     for (int g = 1; g <= kMaxSampleGroup; ++g) {

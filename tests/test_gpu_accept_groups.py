@@ -1,4 +1,4 @@
-"""PROBS-mode sampling at the numbers of chunks that a workgroup takes (1 to 16, by requests and vocabulary), against the oracle."""
+"""PROBS-mode sampling at the numbers of chunks that a workgroup takes (1 to 8, by requests and vocabulary), against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,7 @@ from gpu_utils import DeviceBatch, announce, check_accept
 pytestmark = pytest.mark.gpu
 
 
-# chunks (whole ones and the ragged end), requests: 1, 2, 3, 5, 10, 14 and 16 chunks a workgroup, and a last one with fewer
+# chunks (whole ones and the ragged end), requests: workgroups that take one chunk, several and all of a row, and a last one with fewer
 @pytest.mark.parametrize("V,B", [(3 * 4096, 300), (4 * 4096 + 1, 400), (9 * 4096 - 3, 320), (10 * 4096, 500), (38 * 4096 - 5, 250),
                                  (26 * 4096 + 7, 480), (47 * 4096, 340), (4097, 2000)])
 def test_chunks_of_a_workgroup(oracle, V, B):
