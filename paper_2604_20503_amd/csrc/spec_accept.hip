@@ -25,13 +25,12 @@
 // All masses are accumulated in fp64 so that the chosen token matches a sequential fp64
 // scan except when u * R lies within rounding of a CDF step.
 #include <algorithm>
-#include <cfloat>
 #include <climits>
-#include <cmath>
 
 #include "common.hpp"
 #include "device_utils.hpp"
 #include "greedy_accept.hpp"
+#include "temp_scale.hpp"
 
 namespace fsr {
 namespace {
@@ -267,28 +266,7 @@ __device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
 // bits, whose product with a logit is exact), four the series and a fifth adds the value to a sum: 12 instructions and a
 // look-up where exp_lookup and its argument take 16.  Errors against exp(z / T), logits N(0, 2^2): 3.0e-16 at most, 8.3e-17
 // root mean square, at every T (by way of z * (1 / T) 1.9e-16 and 6.6e-17 at T = 1, 1.0e-15 and 1.9e-16 at 0.7, 7.9e-15 and 2.2e-15
-// at 0.05, where 1 / T is rounded).  For |z| <= reach only: |z / T| up to 600, where the value and 2^32 times it are normal numbers.
-struct TempScale {
-    double c, c_hi, c_lo;  // 256 / (T ln2); the same in two parts
-    float reach;
-};
-constexpr double kReach = 600.0;
-TempScale temp_scale(double T) {
-    TempScale t{};
-    const long double c = 256.0L / (0.693147180559945309417232121458L * (long double)T);
-    t.c = (double)c;
-    if (!std::isfinite(t.c) || t.c == 0.0) {
-        t.c = 0.0;
-        t.reach = -1.0f;  // no logit is within reach
-        return t;
-    }
-    int e = 0;
-    const double m = std::frexp(t.c, &e);
-    t.c_hi = std::ldexp(std::floor(std::ldexp(m, 29)), e - 29);
-    t.c_lo = (double)(c - (long double)t.c_hi);
-    t.reach = (float)std::min(kReach * T, (double)FLT_MAX);
-    return t;
-}
+// at 0.05, where 1 / T is rounded).  For |z| <= reach only (temp_scale.hpp).
 struct ExpDirect {
     const uint2* tab;  // LDS
     double c, c_hi, c_lo, magic, a4, a3, a2, a1;
