@@ -225,7 +225,8 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     const int nw = rows > 0 && kb0 < kend ? (kend - kb0 + step - 1) / step : 0;
     // the wave's first n_plain tiles lie wholly below every row's causal limit
     const int below = min(first_lim + 1, kend) - kTile - kb0;
-    const int n_plain = below < 0 ? 0 : below / step + 1;
+    // (none where the group has no rows: the other item of the workgroup has more rounds, and this one has loaded nothing)
+    const int n_plain = min(nw, below < 0 ? 0 : below / step + 1);
 
     // ---- query operands to LDS: piece (mt, s) holds for lane (li, lg) 16 bytes of row mt * 16 + li
     for (int pr = wi; pr < MT * L::kQPieces; pr += n_waves) {
@@ -608,8 +609,9 @@ struct BalancedPieces {
             if (ql > 0) {
                 const int seen = (int)min((long long)max(c, 0) + ql, min((long long)a.max_pages * a.P, 1LL << 30));
                 const int tiles = max((seen + 31) / 32, 1);
-                work = (float)tiles * (kTileBase + (float)((min(M, 16 * MTMAX) + 15) / 16));
                 // (rows beyond the caller's bound are further rounds: a slot would be written twice, so no pieces then)
+                const int rounds = (M + 16 * MTMAX - 1) / (16 * MTMAX);
+                work = (float)tiles * (kTileBase * (float)rounds + (float)((M + 15) / 16));
                 // two lie side by side and cost nothing; more have to be long enough to be worth handing over
                 most = M <= 16 * MTMAX ? min(kMaxSplits, max(tiles / kPieceTiles, min(tiles, 2))) : 1;
             }

@@ -27,7 +27,7 @@ def lengths(kind, B, rng):
     return rng.integers(0, 1700, B), rng.integers(0, 4, B)
 
 
-# items per call; one, two and three query tiles; the last two have rows beyond the bound that is given
+# items per call; one, two and three query tiles; in two of the ragged calls a request has rows beyond the bound that is given
 @pytest.mark.parametrize("H_q,H_kv,B,hint,token_major,P", [(16, 16, 9, 4, False, 16), (8, 4, 64, 4, True, 16), (64, 8, 17, 4, False, 24),
                                                            (48, 4, 40, 4, False, 16), (32, 8, 48, 2, True, 16), (24, 6, 30, 1, False, 16)])
 @pytest.mark.parametrize("kind", ["ragged", "one long", "equal"])
@@ -92,3 +92,28 @@ def test_balanced_items_in_a_graph(fsr):
             call(c, out, ws)
             torch.cuda.synchronize()
             assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("H_q,H_kv,B,hint", [(12, 3, 60, 2), (20, 5, 41, 4), (28, 7, 37, 3), (35, 7, 25, 9), (32, 8, 32, 2)])
+def test_rows_beyond_the_bound_beside_others(fsr, oracle, H_q, H_kv, B, hint):
+    """Requests, short and long, with more rows than the bound allows (up to five rounds of 16 to 48 query rows), in workgroups that
+    they share with requests of one round (where the KV heads are an odd number) and with other heads of their own."""
+    announce(f"balanced items, rows beyond the bound {H_q}/{H_kv} B={B} hint={hint}")
+    rng = np.random.Generator(np.random.PCG64(7 * B + hint))
+    ctx, spec = rng.integers(0, 1700, B), rng.integers(0, hint, B)
+    ctx[0] = 1690
+    over = rng.permutation(B)[:B // 3]
+    spec[over] = rng.integers(hint + 2, 5 * hint + 4, len(over))
+    ctx[over[::2]] = rng.integers(0, 100, len(over[::2]))
+    x = make(rng, "bf16", H_q, H_kv, 64, 16, ctx, spec)
+    scale = 1.0 / 8.0
+    ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=H_q, H_kv=H_kv, D=64, P=16,
+                                           dtype="bf16", scale=float(np.float32(scale)))
+    q = dev(x["q"], True)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+    fsr.verify_attention(q, dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=scale, out=out,
+                         lse=lse, max_q_len=hint)
+    torch.cuda.synchronize()
+    check_attention(out, ref, "f32", len(ref))
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
