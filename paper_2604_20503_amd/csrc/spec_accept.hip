@@ -25,6 +25,7 @@
 // All masses are accumulated in fp64 so that the chosen token matches a sequential fp64
 // scan except when u * R lies within rounding of a CDF step.
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 
 #include "common.hpp"
@@ -40,7 +41,7 @@ constexpr int kThreads = 256;       // threads per block in stats / partials / s
 constexpr int kPerThread = kChunk / kThreads;  // 16 contiguous tokens per thread in select
 constexpr int kMaxStatGroup = 8;    // LOGITS mode: most chunks whose softmax statistics one workgroup folds into one (reference, sum) pair
 constexpr int kSkipMinRows = 2048;  // LOGITS mode: rows a call must be able to hold for rows behind a rejection to be left out
-constexpr double kStatSlack = 100.0;  // LOGITS mode: exponents the statistics let grow before they change their reference
+constexpr double kStatSlack = 100.0;  // LOGITS mode, temperatures out of all range: exponents the statistics let grow before they change their reference
 constexpr int kMaxSampleGroup = 8;  // accept_sample: most consecutive chunks that a workgroup takes (see sample_group_of)
 
 enum : int { kCaseNone = 0, kCaseResidual = 1, kCaseTarget = 2 };
@@ -49,15 +50,17 @@ enum : int { kCaseNone = 0, kCaseResidual = 1, kCaseTarget = 2 };
 struct Decision {
     long long t_row;  // storage row of the target distribution to sample from
     long long d_row;  // storage row of the draft distribution (residual case)
-    double m_t, Z_t;  // LOGITS mode: exponent reference (at most kStatSlack below the maximum) and partition sum of the target row
+    double m_t, Z_t;  // LOGITS mode: exponent reference (at most 100 below the maximum) and partition sum of the target row
     double m_d, Z_d;  // ... of the draft row
     int kind;         // kCase*
     int n;            // accepted drafts
 };
-// LOGITS mode, how the rows' masses in a draw are formed, in units that are each row's own: exp(z / T) where the rows' references
-// allow it (direct), else exp(z / T - m).  A direct row takes logits from `lowest` on as they are; one below that is masked
-// if exp(z / T - m) is 0 in fp64, and hardly ever anything else.
+// LOGITS mode, how a row's masses in a draw are formed: exp(z / T) / 2^shift by exp_of_logit (direct; `shift` brings the row's
+// largest near 1), else exp(z / T - m).  A direct row takes logits from `lowest` on as they are; one below that is masked
+// if its mass is 0 in fp64, and hardly ever anything else.
 struct RowScale {
+    double shift;
+    double rest;   // m - shift ln2, 0 if not direct: a mass is exp(z / T - m + rest)
     float lowest;
     float masked;  // below this a logit of a direct row is masked whatever the roundings
 };
@@ -266,7 +269,9 @@ __device__ __forceinline__ double exp_lookup(double x, const ExpTable& k) {
 // bits, whose product with a logit is exact), four the series and a fifth adds the value to a sum: 12 instructions and a
 // look-up where exp_lookup and its argument take 16.  Errors against exp(z / T), logits N(0, 2^2): 3.0e-16 at most, 8.3e-17
 // root mean square, at every T (by way of z * (1 / T) 1.9e-16 and 6.6e-17 at T = 1, 1.0e-15 and 1.9e-16 at 0.7, 7.9e-15 and 2.2e-15
-// at 0.05, where 1 / T is rounded).  For |z| <= reach only (temp_scale.hpp).
+// at 0.05, where 1 / T is rounded).  A shift by a whole power of two costs nothing: it goes into the constant that rounds, so that the
+// low word of the sum is n less 256 shift.  For |z / T - shift ln2| up to 700 or so, where 2^n is a normal number, and
+// |z / T| up to kWidest, where n is exact.
 struct ExpDirect {
     const uint2* tab;  // LDS
     double c, c_hi, c_lo, magic, a4, a3, a2, a1;
@@ -285,12 +290,19 @@ __device__ __forceinline__ ExpDirect exp_direct(const uint2* tab, const TempScal
     asm volatile("" : "+s"(k.c), "+s"(k.c_hi), "+s"(k.c_lo), "+s"(k.a4), "+v"(k.a3), "+s"(k.a2), "+s"(k.a1), "+v"(k.magic));
     return k;
 }
-// exp(z / T) = power * series
+constexpr double kWidest = 5e12;  // 256 / ln2 times it is below 2^51
+constexpr double kRound = 6755399441055744.0;
+__device__ __forceinline__ ExpDirect shifted(ExpDirect k, double shift) {
+    k.magic = kRound - 256.0 * shift;
+    return k;
+}
+constexpr double kLn2Hi = 6.93147180369123816490e-01, kLn2Lo = 1.90821492927058770002e-10;  // ln2 in two parts, see ExpConsts
+__device__ __forceinline__ double less_shift(double m, double shift) { return fma(-shift, kLn2Lo, fma(-shift, kLn2Hi, m)); }
+// exp(z / T) / 2^shift = power * series
 struct ExpParts {
     double power, series;
 };
-__device__ __forceinline__ ExpParts exp_of_logit(float z, const ExpDirect& k) {
-    const double x = (double)z;
+__device__ __forceinline__ ExpParts exp_of_logit(double x, const ExpDirect& k) {
     const double t = fma(x, k.c, k.magic);
     const double n = t - k.magic;
     const uint32_t low = (uint32_t)__builtin_bit_cast(unsigned long long, t);
@@ -314,6 +326,44 @@ __device__ __forceinline__ float min3(float m, float x, float y) {
     asm("v_min3_f32 %0, %1, %2, %0" : "+v"(m) : "v"(x), "v"(y));
     return m;
 }
+__device__ __forceinline__ float max2(float x, float y) {  // (fmaxf quiets its operands first)
+    float m;
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(x), "v"(y));
+    return m;
+}
+// A value that is the same in every lane, said so.
+__device__ __forceinline__ float uniform(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+__device__ __forceinline__ double uniform(double x) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)b), hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// Largest of the wave's values, in every lane.  (The value may come from asm, which the compiler does not keep two instructions
+// away from a DPP read: an instruction of its own first.)
+__device__ __forceinline__ float wave_top(float v) {
+    v = __builtin_canonicalizef(v);
+    auto step = [&](auto ctrl, auto rows) {
+        const int b = __builtin_bit_cast(int, v);
+        v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, decltype(ctrl)::value, decltype(rows)::value, 0xf, false)));
+    };
+    step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+// The least float that is not below x.
+__device__ __forceinline__ float float_up(double x) {
+    const float f = (float)x;
+    if (!((double)f < x)) return f;
+    const uint32_t b = __builtin_bit_cast(uint32_t, f);
+    return f == 0.0f ? __builtin_bit_cast(float, 1u) : __builtin_bit_cast(float, f < 0.0f ? b - 1u : b + 1u);
+}
+constexpr double kLn2 = 0.6931471805599453, kAmple = 1.9151695967140057e-174;  // exp(-400)
 constexpr double kExpZero = -746.0;  // exp of it and of anything less is 0 in fp64
 // The constants for a kernel of the given mode: PROBS mode never evaluates exp and gets an empty set.
 template <int MODE>
@@ -407,21 +457,25 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ stat_a,
 // LOGITS mode: per row and group of ws.stat_group chunks, a reference and the sum of exp(z / T - reference), fp64.
 // grid = (n_stat_groups, (2 * S_max + 1) * B): workgroup row k * B + i takes, of request i, target row k / 2 for even k and
 // draft row k / 2 for odd k, so that the rows of the first drafts are all started before any row of a second draft.
-// Each lane sums exp(z / T) itself over its own elements (16 per chunk) where they are within reach (see exp_of_logit), and else
-// keeps a reference (its first chunk's largest logit, replaced only by one far above it) and a sum relative to
-// it, so the chunks of a group need no exchange between lanes; lanes and waves are
+// Each lane sums exp(z / T) itself over its own elements (16 per chunk) as long as the wave's are within reach (600 temperatures of
+// 0), and exp(z / T) / 2^shift from then on: the shift is the wave's, by the largest logit of the chunk that called for it, and moves
+// only when one lies 600 temperatures further up, so the chunks of a group need no exchange between lanes but then; lanes and waves are
 // combined once, at the end.  Any reference gives the same probabilities; it has to keep the exponents in range.
+// us a launch, 128 requests x 128256 in fp32, a reference taken off every logit / from the logits themselves where those are within
+// reach and else read again / like this: T = 0.005 95 / 181 / 86, all but 50 logits a row masked by -1e9 64 / 117 / 59, T = 1 118 /
+// 105 / 101; 16 requests 26 / 41 / 25, 24.5 / 35 / 25, 26 / 22 / 22.  Registers decide: calls of few rows are workgroups' latencies, and
+// 1 to 3 us slower with five waves per SIMD than with six (the spills of seven cost as much); those that leave rows out are 3 % faster with five.
 // The rows are read once here, with the non-temporal hint (512 requests x 152064 in fp32: call 533 us without, 508 with).  What
 // bounds it is both the rows' bytes and the fp64 instructions: 512 requests 455 us a launch with a reference taken off every logit
 // and ordinary loads, 394 like this (about 2.3 GB; vector ALUs 70 % busy); 16 requests x 128256 in bf16 24.1 / 20.6.
 // ---------------------------------------------------------------------------------------
-template <typename RT>
-__global__ __launch_bounds__(kThreads, 5) void accept_stats_kernel(
+template <typename RT, bool SKIP>  // SKIP: rows behind a rejection are left out (ws.skip)
+__global__ __launch_bounds__(kThreads, SKIP ? 5 : 6) void accept_stats_kernel(
     const RT* __restrict__ z_target, const RT* __restrict__ z_draft, const int32_t* __restrict__ draft_tokens,
     const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
     const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, Workspace ws, int B, int V, int S_max, double T,
     TempScale ts) {
-    __shared__ double s_sum[kThreads / 64], s_direct[kThreads / 64];
+    __shared__ double s_sum[kThreads / 64], s_direct[kThreads / 64], s_shift[kThreads / 64];
     __shared__ float s_max[kThreads / 64];
     __shared__ uint2 s_exp[256];
     __shared__ int s_behind, s_last;
@@ -464,139 +518,176 @@ __global__ __launch_bounds__(kThreads, 5) void accept_stats_kernel(
         }
     };
     const uint2 entry = exp_table_entry();
-    if (!ws.skip && c_first < c_whole) load_chunk(c_first, va);  // (in flight while the table is filled)
+    if (!SKIP && c_first < c_whole) load_chunk(c_first, va);  // (in flight while the table is filled)
     // If a draft before this row's has been rejected, nothing will read the row's statistics.  One lane asks for the whole
     // workgroup: other workgroups may lower the word at any time, and waves that asked for themselves could differ.
     if (threadIdx.x == 0)
-        s_behind = ws.skip && j > 0 &&
+        s_behind = SKIP && j > 0 &&
                    __hip_atomic_load(stat_words(ws, i, nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned)j;
     s_exp[threadIdx.x] = entry;
     __syncthreads();
     if (s_behind) return;
-    unsigned todo = (1u << (c_end - c_first)) - 1u;  // chunks (of the wave's tokens) that the first loop leaves to the second
-    // Chunks whose logits lie within reach, from exp(z / T) itself.  Whole ones: four vector loads per lane and chunk, all in
-    // flight together, the next chunk's issued before this one's arithmetic, and only such loads in the loop: mixed with
-    // bounds-checked ones the compiler orders each vector load behind all loads before it.
-    double direct = 0.0;  // sum of exp(z / T) over this lane's elements
-    {
-        const ExpDirect ed = exp_direct(s_exp, ts);
-        auto add_chunk = [&](const float (&v)[kPerThread], int c) {
+    if (SKIP && c_first < c_whole) load_chunk(c_first, va);
+    float mz = -INFINITY;  // of logits that no shift fits: a reference, one of them,
+    double sum = 0.0;      // and the sum of exp(z / T - mz / T) over those of them in this lane
+    double direct = 0.0, shift = 0.0;  // sum of exp(z / T) / 2^shift over this lane's other elements; the shift is the wave's
+    if (ts.reach > 0.0f) {
+        ExpDirect ed = exp_direct(s_exp, ts);
+        float plain = ts.reach;  // up to which logits are taken without a look at the shift: none once there is one
+        double lowest = -kReach * T;  // the shift less 600
+        float highest = ts.reach, significant = (float)(-500.0 / kReach) * ts.reach;  // and 600 more, 500 less
+        auto add_chunk = [&](const float (&v)[kPerThread]) {
             float top = 0.0f;
 #pragma unroll
             for (int u = 0; u < kPerThread; u += 2) top = max3_abs(top, v[u], v[u + 1]);
-            if (__builtin_amdgcn_ballot_w64(!(top <= ts.reach)) == 0) {
+            if (__builtin_amdgcn_ballot_w64(!(top <= plain)) == 0) {
+                const double before = direct;
 #pragma unroll
                 for (int u = 0; u < kPerThread; ++u) {
-                    const ExpParts e = exp_of_logit(v[u], ed);
+                    const ExpParts e = exp_of_logit((double)v[u], ed);
                     direct = fma(e.power, e.series, direct);
                 }
-            } else {
-                float hi = -INFINITY;
-#pragma unroll
-                for (int u = 0; u < kPerThread; u += 2) hi = max3(hi, v[u], v[u + 1]);
-                if (__builtin_amdgcn_ballot_w64(hi > ts.reach) != 0) return;
-                // Masked logits (-inf, NaN), or some far below the rest: as such they add exp(-600) each, where one of the wave's
-                // is at least exp(-500).  A wave's masked logits alone add nothing; nor do finite ones as low, here.
-                if (__builtin_amdgcn_ballot_w64(hi >= ts.reach * (float)(-500.0 / kReach)) == 0) {
-                    if (__builtin_amdgcn_ballot_w64(hi != -INFINITY) != 0) return;
-                } else {
-#pragma unroll
-                    for (int u = 0; u < kPerThread; ++u) {
-                        const ExpParts e = exp_of_logit(fmaxf(v[u], -ts.reach), ed);
-                        direct = fma(e.power, e.series, direct);
-                    }
-                }
+                if (__builtin_amdgcn_ballot_w64(direct != direct) == 0) return;
+                direct = before;  // a NaN logit counts as masked
             }
-            todo &= ~(1u << (c - c_first));
+            float hi = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < kPerThread; u += 2) hi = max3(hi, v[u], v[u + 1]);
+            const bool low = __builtin_amdgcn_ballot_w64(hi >= significant) == 0;
+            // masked logits only, or nothing beside what the wave has seen
+            if (low && (__builtin_amdgcn_ballot_w64(hi != -INFINITY) == 0 || __builtin_amdgcn_ballot_w64(direct >= kAmple) != 0)) return;
+            if (low || __builtin_amdgcn_ballot_w64(hi > highest) != 0) {  // a shift by the largest
+                double T_ = T, c = ts.c;
+                asm volatile("" : "+s"(T_), "+s"(c));  // or what follows is worked out in front of the loop, and kept in registers
+                const float m = wave_top(hi);
+                if (!(fabs((double)m) <= kWidest * T_)) {
+                    // Floats of such a size lie 6e5 temperatures apart: exp of the next is 0.
+                    if (m > mz) {
+                        mz = m;
+                        sum = 0.0;
+                    }
+                    int n = 0;
+#pragma unroll
+                    for (int u = 0; u < kPerThread; ++u) n += v[u] == mz ? 1 : 0;
+                    sum += (double)n;
+                    return;
+                }
+                // (no further down than the sum allows)
+                const double at = __builtin_amdgcn_ballot_w64(direct > 0.0) != 0 ? fmax((double)m, lowest) : (double)m;
+                const double to = uniform(rint(at * (c / 256.0)));
+                direct = ldexp(direct, (int)fmin(fmax(shift - to, -5000.0), 5000.0));
+                shift = to;
+                plain = -1.0f;
+                ed.magic = kRound - 256.0 * to;
+                lowest = uniform((to * kLn2 - kReach) * T_);
+                highest = uniform(-float_up(-(to * kLn2 + kReach) * T_));
+                significant = uniform(float_up((to * kLn2 - 500.0) * T_));
+            }
+            // What is masked (-inf, NaN), or far below the rest, adds exp(-600) where something has added exp(-500) at least.
+#pragma unroll
+            for (int u = 0; u < kPerThread; ++u) {
+                const ExpParts e = exp_of_logit(fmax((double)v[u], lowest), ed);
+                direct = fma(e.power, e.series, direct);
+            }
         };
-        if (ws.skip && c_first < c_whole) load_chunk(c_first, va);
+        // Whole chunks: four vector loads per lane and chunk, all in flight together, the next chunk's issued before this one's
+        // arithmetic, and only such loads in the loop: mixed with bounds-checked ones the compiler orders each vector load behind
+        // all loads before it.
 #pragma unroll 1
         for (int c = c_first; c < c_whole; c += 2) {
             if (c + 1 < c_whole) load_chunk(c + 1, vb);
-            add_chunk(va, c);
+            add_chunk(va);
             if (c + 1 >= c_whole) break;
             if (c + 2 < c_whole) load_chunk(c + 2, va);
-            add_chunk(vb, c + 1);
+            add_chunk(vb);
         }
         if (c_whole < c_end) {  // the chunk that holds the vocabulary's ragged end
             load_checked(c_whole, va);
-            add_chunk(va, c_whole);
+            add_chunk(va);
         }
-        if (__builtin_amdgcn_ballot_w64(direct != direct) != 0) {  // a NaN logit counts as masked: all chunks again
-            direct = 0.0;
-            todo = (1u << (c_end - c_first)) - 1u;
-        }
-    }
-    // The others, with logits out of reach, against a reference of the lane's own.
-    const double inv_T = 1.0 / T;
-    const ExpConsts ek = exp_consts();
-    float mz = -INFINITY;   // this lane's reference: a logit it has seen, no more than kStatSlack * T below the largest
-    double mzT = 0.0;       // mz / T once mz is finite
-    double sum = 0.0;       // sum of exp(z / T - mz / T) over this lane's elements
-    if (todo != 0) {
+    } else {  // a temperature out of all range: against a reference of the lane's own
         const ExpTable et = exp_table(s_exp);
+        const double inv_T = 1.0 / T;
         float limit = -INFINITY;  // a logit above this makes a new reference
-        const float slack = (float)(kStatSlack * T);
+        double mzT = 0.0;         // mz / T once mz is finite
 #pragma unroll 1
-        while (todo != 0) {
-            const int c = c_first + __builtin_ctz(todo);
-            todo &= todo - 1;
+        for (int c = c_first; c < c_end; ++c) {
             float v[kPerThread];
             load_checked(c, v);
             float mx = v[0];
 #pragma unroll
             for (int u = 1; u < kPerThread; ++u) mx = fmaxf(mx, v[u]);
-            if (mx > limit) {  // rescale what was summed against the old reference
+            if (mx > limit) {
                 const double mxT = (double)mx * inv_T;
-                sum = mz == -INFINITY ? 0.0 : sum * exp_softmax(mzT - mxT, ek);
+                if (mz != -INFINITY) sum *= exp_lookup(mzT - mxT, et);
                 mz = mx;
                 mzT = mxT;
-                limit = mz + slack;
+                limit = mx + (float)(kStatSlack * T);
             }
             // (a masked logit -- -inf, NaN, past V -- or one far below the reference adds 1e-304)
 #pragma unroll
             for (int u = 0; u < kPerThread; ++u) sum += exp_lookup(fma((double)v[u], inv_T, -mzT), et);
         }
     }
+    const ExpConsts ek = exp_consts();
     // lanes -> wave -> workgroup, each time against the common maximum
+    const double inv_T = 1.0 / T;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     direct = wave_sum_to_last(direct);
     float mw = -INFINITY;
     if (__builtin_amdgcn_ballot_w64(mz != -INFINITY) != 0) {
         mw = wave_max(mz);
-        sum = mz == -INFINITY ? 0.0 : sum * exp_softmax(mzT - (double)mw * inv_T, ek);
+        sum = mz == -INFINITY ? 0.0 : sum * exp_softmax(((double)mz - (double)mw) * inv_T, ek);
         sum = wave_sum_to_last(sum);
     }
     if (lane == 63) {
         s_max[w] = mw;
         s_sum[w] = sum;
         s_direct[w] = direct;
+        s_shift[w] = shift;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         const float mg = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-        double mgT = (double)mg * inv_T, tot = (s_direct[0] + s_direct[1]) + (s_direct[2] + s_direct[3]);
-        if (tot > 0.0) {
-            // a reference for the direct sum too: below its largest term, which is at least 2^-15 of it
-            const double md = 0.6931471805599453 * (double)(ilogb(tot) - 16);
-            mgT = fmax(mgT, md);
-            tot *= exp_softmax(-md, ek);
-            if (mgT != md) tot *= exp_softmax(md - mgT, ek);
-        }
-        if (mg != -INFINITY) {
-#pragma unroll
+        double mgT = -INFINITY, tot = (s_direct[0] + s_direct[1]) + (s_direct[2] + s_direct[3]);
+        if (mg == -INFINITY && s_shift[0] == 0.0 && s_shift[1] == 0.0 && s_shift[2] == 0.0 && s_shift[3] == 0.0) {
+            if (tot > 0.0) {  // a reference below the sum's largest term, which is at least 2^-15 of it
+                mgT = kLn2 * (double)(ilogb(tot) - 16);
+                tot *= exp_softmax(-mgT, ek);
+            }
+        } else {
+            double out = 0.0, most = -INFINITY;
+            tot = 0.0;
+#pragma unroll 1
+            for (int q = 0; q < kThreads / 64; ++q) {
+                if (s_max[q] != -INFINITY) out += s_sum[q] * exp_softmax(((double)s_max[q] - (double)mg) * inv_T, ek);
+                if (s_direct[q] > 0.0) most = fmax(most, s_shift[q]);
+            }
+#pragma unroll 1
             for (int q = 0; q < kThreads / 64; ++q)
-                if (s_max[q] != -INFINITY) tot += s_sum[q] * exp_softmax((double)s_max[q] * inv_T - mgT, ek);
+                if (s_direct[q] > 0.0) tot += ldexp(s_direct[q], (int)fmax(s_shift[q] - most, -5000.0));
+            if (mg != -INFINITY) mgT = (double)mg * inv_T;
+            if (tot > 0.0) {
+                const int up = ilogb(tot) - 16;
+                most += (double)up;
+                const double md = most * kLn2, top = fmax(mgT, md);
+                // (md is rounded)
+                tot = ldexp(tot, -up) * exp_softmax((mgT > md ? md - mgT : 0.0) - less_shift(md, most), ek) +
+                      out * exp_softmax(mgT < md ? mgT - md : 0.0, ek);
+                mgT = top;
+            } else {
+                tot = out;
+            }
         }
         publish_f64(stat + blockIdx.x * 2, mgT);  // -inf for a group of masked logits only
         publish_f64(stat + blockIdx.x * 2 + 1, tot);
         s_last = 0;
-        if (ws.skip && j < d_i && j < S_max) {
+        if (SKIP && j < d_i && j < S_max) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the pair is in memory before it is counted
             s_last = atomicAdd(stat_words(ws, i, nc) + 1 + j, 1u) + 1 == 2u * nsg;
         }
     }
-    if (!ws.skip || j >= d_i || j >= S_max) return;
+    if (!SKIP || j >= d_i || j >= S_max) return;
     __syncthreads();
     if (!s_last || threadIdx.x >= 64) return;
     // the draft's rows are done (both lie inside the workspace and the row maps: their workgroups have checked): test it
@@ -610,27 +701,25 @@ __global__ __launch_bounds__(kThreads, 5) void accept_stats_kernel(
     if (threadIdx.x == 0 && !((double)u_accept[dr] * qx < px)) atomicMin(stat_words(ws, i, nc), (unsigned)j);
 }
 
-constexpr double kDirectReach = 580.0;  // a row's largest z / T lies at most 12 above its reference (100 where it is not direct)
-__device__ __forceinline__ RowScale row_scale(double m, double T, const TempScale& ts) {
-    const double zero = (m + kExpZero) * T;  // (below 0 in a direct row, whose reference is far under 746)
-    return RowScale{fmaxf(-ts.reach, (float)((m + kExpTableFloor) * T)), (float)(zero + 1e-6 * zero)};
+constexpr double kBesideFar = 2.65e-261;  // exp(-600): a mass beside which 4096 of exp(-688) are nothing
+// (a row's largest z / T lies at most 100 above its reference)
+__device__ __forceinline__ RowScale row_scale(double m, double T, bool direct) {
+    if (!direct) return RowScale{0.0, 0.0, 0.0f, 0.0f};
+    const double shift = rint(m * 1.4426950408889634), zero = (m + kExpZero) * T;
+    return RowScale{shift, less_shift(m, shift), float_up((shift * kLn2 + kExpTableFloor) * T), (float)(zero - 1e-6 * fabs(zero))};
 }
 __device__ __forceinline__ DrawScale draw_scale(const Decision& dec, double T, const TempScale& ts, const ExpConsts& ek) {
     const bool residual = dec.kind == kCaseResidual;
-    DrawScale sc{row_scale(dec.m_t, T, ts), row_scale(dec.m_d, T, ts), 1.0, 0, 0};
-    sc.direct = ts.reach > 0.0f && fabs(dec.m_t) <= kDirectReach &&
-                (!residual || (fabs(dec.m_d) <= kDirectReach && fabs(dec.m_t - dec.m_d) <= kDirectReach));
-    if (residual) {
-        sc.ratio = dec.Z_t / dec.Z_d;
-        if (sc.direct) sc.ratio *= exp_softmax(dec.m_t - dec.m_d, ek);
-    }
+    const bool direct = ts.reach > 0.0f && fabs(dec.m_t) <= kWidest && (!residual || fabs(dec.m_d) <= kWidest);
+    DrawScale sc{row_scale(dec.m_t, T, direct), row_scale(dec.m_d, T, direct && residual), 1.0, direct, 0};
+    if (residual) sc.ratio = dec.Z_t / dec.Z_d * exp_softmax(sc.t.rest - sc.d.rest, ek);
     return sc;
 }
 // One logit of a direct row: its mass if it is not below `lowest`, else 0, and far if it may have one all the same.
 __device__ __forceinline__ double mass_or_zero(float z, const RowScale& sc, const ExpDirect& ed, bool& far) {
     const bool in = z >= sc.lowest;
     far |= !in && z > sc.masked;
-    const ExpParts e = exp_of_logit(fmaxf(z, sc.lowest), ed);
+    const ExpParts e = exp_of_logit((double)max2(z, sc.lowest), ed);
     return in ? e.power * e.series : 0.0;
 }
 // Masses of four entries of a row in a draw: the probabilities themselves, or as RowScale says.
@@ -648,14 +737,12 @@ __device__ __forceinline__ void token_masses(const float (&z)[4], double inv_T, 
         }
         if (__builtin_amdgcn_ballot_w64(far) != 0) {  // hardly ever: one copy of exp_softmax, its constants made here
             const ExpConsts ek = exp_consts();
-            const double unit = direct ? exp_softmax(m, ek) : 1.0;
 #pragma unroll 1
             for (int k = 0; k < 4; ++k) {
                 const float zk = k == 0 ? z[0] : k == 1 ? z[1] : k == 2 ? z[2] : z[3];
                 const bool take = !direct || (!(zk >= sc.lowest) && zk > sc.masked);
                 if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
-                const double x = fma((double)zk, inv_T, -m), e = exp_softmax(x, ek);
-                const double v = x > kExpZero && e > 0.0 ? fmax(e * unit, __builtin_bit_cast(double, 1ull)) : 0.0;
+                const double x = fma((double)zk, inv_T, -m), v = x > kExpZero ? exp_softmax(x + sc.rest, ek) : 0.0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) mass[u] = take && u == k ? v : mass[u];
             }
@@ -670,12 +757,12 @@ __device__ __forceinline__ double residual_of(double p, double q, double ratio) 
 template <int MODE, typename RT>
 __device__ __forceinline__ void quad_masses(bool residual, const RT* __restrict__ trow, const RT* __restrict__ drow, int e, int V,
                                             double inv_T, const Decision& dec,
-                                            const DrawScale& sc, const ExpDirect& ed, double (&mass)[4], double& target) {
+                                            const DrawScale& sc, const ExpDirect& et, const ExpDirect& ed, double (&mass)[4], double& target) {
     constexpr float kNothing = MODE == FSR_LOGITS ? -INFINITY : 0.0f;  // past the vocabulary
     float a[4], b[4];
     load_quad(trow, e, V, a, kNothing);
     if (residual) load_quad(drow, e, V, b, kNothing);
-    token_masses<MODE>(a, inv_T, sc.direct, sc.t, dec.m_t, ed, mass);
+    token_masses<MODE>(a, inv_T, sc.direct, sc.t, dec.m_t, et, mass);
     target += (mass[0] + mass[1]) + (mass[2] + mass[3]);
     if (residual) {
         double q[4];
@@ -904,7 +991,9 @@ __global__ __launch_bounds__(MODE == FSR_LOGITS ? 64 * kDecideWaves : 64) void a
 // 20.8 / 16.4, 512 requests 183 / 148.  The scales of the rows are worked out by `decide`, and what is hardly ever needed has one copy of
 // exp_softmax: a small call pays for code that it fetches (4 requests, LOGITS: 80 KB of it 24.0 us, 48 KB 23.1).  LOGITS calls with masked logits, 128 requests x 128256 in fp32, us a call with such
 // chunks read again by the checked path / summed from the registers: all but 50 logits of a row masked 171 / 158, every
-// second one 164 / 141; exponents spread over several hundred (T = 0.02) 173 / 176, read again either way.
+// second one 164 / 141.  Exponents spread over several hundred, us a launch with every chunk that holds one below exp(-700) read again / only
+// where a wave has nothing beside them: 128 requests T = 0.02 97 / 59, 16 requests 26.6 / 23.7.  References beyond 580 by the
+// checked path / by the shift: T = 0.005 82 / 69, 29.7 / 24.2.
 // ---------------------------------------------------------------------------------------
 template <int MODE, typename RT, bool SINGLE>
 __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_sample_kernel(
@@ -957,10 +1046,12 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
     if (n_whole > 0) load_rows(c_first, ta, da);  // (in flight while the table is filled)
     if constexpr (MODE == FSR_LOGITS) __builtin_amdgcn_sched_barrier(0);
     // A draw needs no normalisation: its masses are relative to each other only.
-    ExpDirect ed{};
+    ExpDirect et{}, ed{};  // of the target row and of the draft row
     if constexpr (MODE == FSR_LOGITS) {
         s_exp[threadIdx.x] = entry;
         ed = exp_direct(s_exp, ts);
+        et = shifted(ed, sc.t.shift);
+        ed = shifted(ed, sc.d.shift);
         __syncthreads();
     }
     // A workgroup takes `group` consecutive chunks: the chain every workgroup goes through (decision record,
@@ -972,7 +1063,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
         for (int k = 0; k < kPerThread / 4; ++k) {
             double m[4];
             quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, c * kChunk + (k * kThreads + threadIdx.x) * 4, V,
-                                  inv_T, dec, sc, ed, m, target);
+                                  inv_T, dec, sc, et, ed, m, target);
             r += (m[0] + m[1]) + (m[2] + m[3]);
         }
         return r;
@@ -996,16 +1087,17 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
         auto sum_chunk = [&](int cc, const float (&t)[kPerThread], const float (&d)[kPerThread]) {
             double r = 0.0, target = 0.0;
             if constexpr (MODE == FSR_LOGITS) {
-                // Without a check per token where no logit of the wave lies below its row's `lowest`; with masked tokens
-                // (-inf, NaN, or so low that exp is 0) counted as 0 where some do; the checked path where one of
-                // those has a mass.  The values are those of token_masses throughout.
+                // Without a check per token where no logit of the wave lies below its row's `lowest`; where some do, those counted
+                // as 0: they are masked (-inf, NaN, or so low that exp is 0), or have a mass of less than exp(-688), which
+                // is nothing beside a sum of exp(-600); the checked path where the wave has neither.  Otherwise the values are
+                // those of token_masses.
                 bool far = false;
                 auto sum = [&](auto masked) {
-                    auto mass = [&](float z, const RowScale& rs) {
+                    auto mass = [&](float z, const RowScale& rs, const ExpDirect& k) {
                         if constexpr (decltype(masked)::value) {
-                            return mass_or_zero(z, rs, ed, far);
+                            return mass_or_zero(z, rs, k, far);
                         } else {
-                            const ExpParts e = exp_of_logit(z, ed);
+                            const ExpParts e = exp_of_logit((double)z, k);
                             return e.power * e.series;
                         }
                     };
@@ -1013,10 +1105,10 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
 #pragma unroll
                     for (int u = 0; u < kPerThread; ++u) {
                         if (residual) {
-                            const double x = residual_of(mass(t[u], sc.t), mass(d[u], sc.d), sc.ratio);
+                            const double x = residual_of(mass(t[u], sc.t, et), mass(d[u], sc.d, ed), sc.ratio);
                             acc += x < 0.0 ? 0.0 : x;  // (keeps a NaN)
                         } else {
-                            acc += mass(t[u], sc.t);
+                            acc += mass(t[u], sc.t, et);
                         }
                     }
                     return acc;
@@ -1037,9 +1129,8 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
                     plain = __builtin_amdgcn_ballot_w64(r != r) == 0;  // a NaN logit counts as masked
                 }
                 if (!plain) {
-                    far = (lo_t < sc.t.lowest && lo_t > sc.t.masked) || (residual && lo_d < low_d && lo_d > sc.d.masked);
-                    if (__builtin_amdgcn_ballot_w64(far) == 0) r = sum(std::true_type{});
-                    if (__builtin_amdgcn_ballot_w64(far) != 0) {
+                    r = sum(std::true_type{});
+                    if (__builtin_amdgcn_ballot_w64(far) != 0 && __builtin_amdgcn_ballot_w64(r > kBesideFar) == 0) {
                         todo |= 1u << cc;
                         return;
                     }
@@ -1049,7 +1140,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
                     for (int u = 0; u < kPerThread; ++u) {
                         float z = t[u];
                         asm volatile("" : "+v"(z));  // or the compiler keeps sixteen masses of the loop above in registers
-                        target += mass_or_zero(z, sc.t, ed, far);
+                        target += mass_or_zero(z, sc.t, et, far);
                     }
                 }
             } else if (residual) {
@@ -1173,7 +1264,7 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
 #pragma unroll
     for (int k = 0; k < kPerThread / 4; ++k) {
         double m[4];
-        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, inv_T, dec, sc, ed, m, unused);
+        quad_masses<MODE, RT>(dec.kind == kCaseResidual, trow, drow, e0 + 4 * k, V, inv_T, dec, sc, et, ed, m, unused);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             mass[4 * k + j] = m[j];
@@ -1266,8 +1357,8 @@ int launch_all(const RT* p_target, const RT* p_draft, const int32_t* draft_token
             hipLaunchKernelGGL(accept_clear_kernel, dim3((n_words + kThreads - 1) / kThreads), dim3(kThreads), 0, s, ws, n_words, nc);
             if ((rc = check_launch("accept_clear_kernel")) != FSR_OK) return rc;
         }
-        hipLaunchKernelGGL(accept_stats_kernel<RT>, dim3(n_stat_groups_of(p.V, sg), rows_cap), dim3(kThreads), 0, s, p_target, p_draft,
-                           draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T, ts);
+        hipLaunchKernelGGL((ws.skip ? accept_stats_kernel<RT, true> : accept_stats_kernel<RT, false>), dim3(n_stat_groups_of(p.V, sg), rows_cap),
+                           dim3(kThreads), 0, s, p_target, p_draft, draft_tokens, u_accept, cu_t, cu_d, t_rows, d_rows, ws, p.B, p.V, p.S_max, T, ts);
         if ((rc = check_launch("accept_stats_kernel")) != FSR_OK) return rc;
     }
     const int decide_waves = MODE == FSR_LOGITS && !ws.skip ? decide_waves_of(p.S_max, n_stat_groups_of(p.V, ws.stat_group)) : 1;

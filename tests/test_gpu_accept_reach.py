@@ -80,3 +80,54 @@ def test_extreme_temperatures(fsr, oracle, T, dtype):
     gpu = fsr.spec_accept(as_dtype(z_t), as_dtype(z_d), dev(x), dev(u_a), dev(u_s), dev(cu_t), dev(cu_d), S_max=3, mode=1, temperature=T)
     torch.cuda.synchronize()
     check_accept(gpu, ref, u_s)
+
+
+# Requests and drafts that give a workgroup several chunks: of the statistics 8, 4 and 2 (the first and last leave rows behind a
+# rejection out), of the draw 8, 8 and 2.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,S,nc", [(520, 3, 9), (512, 1, 10), (256, 4, 5)])
+@pytest.mark.parametrize("T", [1.0, 0.004])
+@pytest.mark.parametrize("level", [0.0, -590.0, 900.0, 2e6])
+def test_chunks_at_different_levels(fsr, oracle, T, level, B, S, nc, dtype):
+    """Rows whose chunks lie apart: beside each other some whose logits are taken as they are, some that are masked (-inf, NaN, a finite
+    number), some that are far above, far below or between, and a ragged last one."""
+    announce(f"accept levels T={T} level={level} B={B} S={S} nc={nc} {dtype}")
+    rng = np.random.default_rng(nc + B)
+    V, D = nc * 4096 - 1003, 12  # distinct pairs of rows; requests share them
+    # of a chunk, below the row's level, in z / T.  (bf16 has 8 bits, a level of 2e6 in fp32 a grid of 1/8)
+    steps = [0.0, -3.0, -30.0, -480.0, -560.0, -640.0, -693.0, -703.0, -712.0, -2e4, -1e30, -np.inf, np.nan]
+    z_t, z_d = np.empty((D, V), np.float32), np.empty((D, V), np.float32)
+    x = np.empty(D, np.int32)
+    for j in range(D):
+        at = rng.choice(len(steps), nc)
+        at[rng.integers(nc)] = 0
+        if j % 3 == 2:
+            at[:] = np.where(at > 1, len(steps) - 2, at)  # all others masked
+        base = level + np.array(steps)[at] if j % 2 == 0 else np.array(steps)[at]
+        for c in range(nc):
+            e = slice(c * 4096, min(V, (c + 1) * 4096))
+            n = e.stop - e.start
+            z = base[c] + rng.normal(0, 2.0, n)
+            with np.errstate(invalid="ignore"):
+                z_t[j, e] = z * T
+                z_d[j, e] = (z + rng.normal(0, 0.5, n)) * T
+                if j % 4 == 3:
+                    z_d[j, e] += np.float32(300 * T)  # another reference for the draft's row
+        finite = np.where(np.isfinite(z_t[j]), z_t[j], -np.inf)
+        x[j] = rng.choice(np.argsort(finite)[-6:])
+    if dtype == "bf16":
+        z_t, z_d = (torch.from_numpy(z).bfloat16().float().numpy() for z in (z_t, z_d))
+    spec = rng.integers(0, S + 1, B)
+    cu_t, cu_d = (np.concatenate([[0], np.cumsum(n)]).astype(np.int32) for n in (spec + 1, spec))
+    t_rows, d_rows = rng.integers(0, D, cu_t[-1]).astype(np.int32), np.empty(cu_d[-1], np.int32)
+    for i in range(B):
+        d_rows[cu_d[i]:cu_d[i + 1]] = t_rows[cu_t[i]:cu_t[i + 1] - 1]
+    u_a, u_s = (rng.random(n).astype(np.float32) for n in (D, B))
+    u_s[::7] = 0.0
+    masked = [np.where(np.isnan(z), -np.inf, z).astype(np.float32) for z in (z_t, z_d)]
+    ref = oracle.spec_accept(*masked, x, u_a, u_s, cu_t, cu_d, S_max=S, t_rows=t_rows, d_rows=d_rows, mode=1, temperature=T)
+    as_dtype = (lambda z: dev(z).bfloat16()) if dtype == "bf16" else dev  # exact
+    gpu = fsr.spec_accept(as_dtype(z_t), as_dtype(z_d), dev(x), dev(u_a), dev(u_s), dev(cu_t), dev(cu_d), S_max=S,
+                          t_rows=dev(t_rows), d_rows=dev(d_rows), mode=1, temperature=T)
+    torch.cuda.synchronize()
+    check_accept(gpu, ref, u_s)
