@@ -372,6 +372,13 @@ __device__ __forceinline__ ExpConsts exp_consts_for() {
     else return ExpConsts{};
 }
 
+// z / T - m.  Beyond kWidest the two differ by whole units or not at all, and m is the rounded quotient of one of the row's
+// logits: a multiply-add would leave its rounding behind where there is no difference.
+__device__ __forceinline__ double less_reference(float z, double inv_T, double m) {
+    const double d = fma((double)z, inv_T, -m);
+    return fabs(m) > kWidest && __dmul_rn((double)z, inv_T) == m ? 0.0 : d;
+}
+
 // Probability of one entry in fp64: the value itself, or exp(z / T - m) / Z with the two divisions as products
 // by 1 / T and 1 / Z (loop invariants the compiler hoists).  m is a reference that the row's statistics have kept, at most
 // kStatSlack below the largest z / T, and Z the sum relative to the same m.
@@ -380,7 +387,7 @@ __device__ __forceinline__ double prob_of(float x, double T, double m, double Z,
     if constexpr (MODE == FSR_PROBS) {
         return (double)x;
     } else {
-        return exp_softmax((double)x * (1.0 / T) - m, ek) * (1.0 / Z);
+        return exp_softmax(less_reference(x, 1.0 / T, m), ek) * (1.0 / Z);
     }
 }
 
@@ -609,7 +616,6 @@ __global__ __launch_bounds__(kThreads, SKIP ? 5 : 6) void accept_stats_kernel(
         const ExpTable et = exp_table(s_exp);
         const double inv_T = 1.0 / T;
         float limit = -INFINITY;  // a logit above this makes a new reference
-        double mzT = 0.0;         // mz / T once mz is finite
 #pragma unroll 1
         for (int c = c_first; c < c_end; ++c) {
             float v[kPerThread];
@@ -618,15 +624,13 @@ __global__ __launch_bounds__(kThreads, SKIP ? 5 : 6) void accept_stats_kernel(
 #pragma unroll
             for (int u = 1; u < kPerThread; ++u) mx = fmaxf(mx, v[u]);
             if (mx > limit) {
-                const double mxT = (double)mx * inv_T;
-                if (mz != -INFINITY) sum *= exp_lookup(mzT - mxT, et);
+                if (mz != -INFINITY) sum *= exp_lookup(((double)mz - (double)mx) * inv_T, et);
                 mz = mx;
-                mzT = mxT;
                 limit = mx + (float)(kStatSlack * T);
             }
             // (a masked logit -- -inf, NaN, past V -- or one far below the reference adds 1e-304)
 #pragma unroll
-            for (int u = 0; u < kPerThread; ++u) sum += exp_lookup(fma((double)v[u], inv_T, -mzT), et);
+            for (int u = 0; u < kPerThread; ++u) sum += exp_lookup(((double)v[u] - (double)mz) * inv_T, et);
         }
     }
     const ExpConsts ek = exp_consts();
@@ -742,7 +746,7 @@ __device__ __forceinline__ void token_masses(const float (&z)[4], double inv_T, 
                 const float zk = k == 0 ? z[0] : k == 1 ? z[1] : k == 2 ? z[2] : z[3];
                 const bool take = !direct || (!(zk >= sc.lowest) && zk > sc.masked);
                 if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
-                const double x = fma((double)zk, inv_T, -m), v = x > kExpZero ? exp_softmax(x + sc.rest, ek) : 0.0;
+                const double x = less_reference(zk, inv_T, m), v = x > kExpZero ? exp_softmax(x + sc.rest, ek) : 0.0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) mass[u] = take && u == k ? v : mass[u];
             }

@@ -48,25 +48,26 @@ def test_logits_within_reach_and_beyond(fsr, oracle, T, shift, third):
 
 # Temperatures at which 600 of them are no normal float.  Small ones: a certain token (log-probabilities, the largest logit is
 # 0) drafted by a row whose largest logit is 1; large ones: every token alike, half of them masked in the draft's row, and a
-# uniform that is decided by how many.  Powers of two, whose quotients by T differ by rounding only where 1 / T does: z / T is an
-# fp64 number, and of 1e17 and more its rounding is whole units of the exponent, here as in the oracle.
+# uniform that is decided by how many.  Powers of two, whose products with 1 / T are exact, or whole numbers: of 1e17 and more a
+# quotient's rounding is whole units of the exponent.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("powers", [True, False])
 @pytest.mark.parametrize("T", [1e-300, 1e-60, 1e-50, 1e-44, 1.9e-41, 2.1e-41, 1e-30, 1e30, 5e35, 6e35, 1e38, 3e38, 1e45, 1e300])
-def test_extreme_temperatures(fsr, oracle, T, dtype):
-    announce(f"accept extreme temperature T={T} {dtype}")
+def test_extreme_temperatures(fsr, oracle, T, powers, dtype):
+    announce(f"accept extreme temperature T={T} powers={powers} {dtype}")
     rng = np.random.default_rng(3)
     spec, V = np.array([1, 2, 0, 3]), 8197
     cu_t, cu_d = (np.concatenate([[0], np.cumsum(n)]).astype(np.int32) for n in (spec + 1, spec))
     x = rng.integers(0, V, cu_d[-1]).astype(np.int32)
-    z_t = -(2.0 ** rng.integers(0, 5, (cu_t[-1], V))).astype(np.float32)
-    z_d = -(2.0 ** rng.integers(0, 5, (cu_d[-1], V))).astype(np.float32)
+    low = (lambda n: -(2.0 ** rng.integers(0, 5, (n, V)))) if powers else (lambda n: -rng.integers(1, 10, (n, V)))
+    z_t, z_d = low(cu_t[-1]).astype(np.float32), low(cu_d[-1]).astype(np.float32)
     if T < 1:
-        z_t[np.arange(len(z_t)), rng.integers(0, V, len(z_t))] = 0.0
+        z_t[np.arange(len(z_t)), rng.integers(0, V, len(z_t))] = 0.0 if powers else -0.75
         for i in range(len(spec)):
             for j in range(spec[i]):
                 z_t[cu_t[i] + j] = np.minimum(z_t[cu_t[i] + j], -1.0)
-                z_t[cu_t[i] + j, x[cu_d[i] + j]] = 0.0
-                z_d[cu_d[i] + j, x[cu_d[i] + j]] = 1.0
+                z_t[cu_t[i] + j, x[cu_d[i] + j]] = 0.0 if powers else -0.75  # (three quarters: its quotient is rounded too)
+                z_d[cu_d[i] + j, x[cu_d[i] + j]] = 1.0 if powers else 3.0
         u_a = np.full(cu_d[-1], 0.5, np.float32)
     else:
         drop = rng.random(z_d.shape) < 0.5
