@@ -53,11 +53,14 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kMaxSplits = 8;
 constexpr int kSplitKeys = 512;            // an item is not cut into pieces of fewer keys
 constexpr long long kSplitGroups = 256;    // workgroups a call is brought up to by cutting items: one per compute unit
-// Calls of many items cut the longest by their lengths, see BalancedPieces and, for the rule, layout_of.
+// Calls of many items cut the longest by their lengths, see BalancedPieces and, for the rule, layout_of.  us a call: a base of 2 /
+// 4 / 8 for a tile 48 requests of 256-4096 tokens 56.6 / 56.6 / 63.3, 20 28.4 / 28.5 / 30.0, 40 log-normal 54.9 / 59.2 / 59.7, 16/16 heads, 16 of
+// 256-4096 35.1 / 32.8 / 32.8; pieces of 4 / 8 / 16 tiles 32 of up to 2048 25.2 / 25.2 / 26.2, others alike.
 constexpr int kBalancedMaxB = 64;          // a request per lane
 constexpr int kBalancedKeys = 1536;        // keys from which an item is worth cutting
 constexpr int kPieceTiles = 8;             // least tiles of a piece that is handed over
 constexpr float kTileBase = 4.0f;          // a tile costs this + the query tiles that ride on it
+constexpr float kWorthCutting = 100.0f;    // what cutting has to take off at least, in those costs of four waves
 enum : int { kWhole = 0, kEven = 1, kBalanced = 2 };  // how items are cut
 
 struct ItemArgs {
@@ -74,9 +77,9 @@ struct ItemArgs {
     long long page_stride, slot_stride, head_stride;  // of the caches, in bytes
     // bf16: an item is cut into up to `splits` pieces of at least kSplitKeys keys, handed over through the workspace
     int splits;
-    int places;      // balanced pieces: workgroups that run side by side
-    float* part_o;   // [items * splits][16 * MTMAX][D] unnormalised sums of the pieces
-    float* part_ml;  // [items * splits][16 * MTMAX][4] exponent reference (log2), sum, call tag, unused
+    int places;      // balanced pieces: how many a call has at most, two to a workgroup
+    float* part_o;   // [items * splits, or places][16 * MTMAX][D] unnormalised sums of the pieces
+    float* part_ml;  // [items * splits, or places][16 * MTMAX][4] exponent reference (log2), sum, call tag, unused
     unsigned long long* arrivals;  // [items] (call id << 16 | pieces that have arrived)
     unsigned long long call_id;
     float scale_log2, scale_rest;  // softmax scale times log2(e), and (times ln 2) what rounding took off it
@@ -146,15 +149,15 @@ __device__ __forceinline__ void write_out(const ItemArgs& a, size_t at, float x)
 // values of a row to a thread at a time.  Ordinary loads: a slot was stored through to memory before its piece was counted, is written and
 // read once per launch, and caches start a launch without older copies.  A slot that this call did not write makes its rows NaN.
 template <int D, int ROWS>
-__device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0, int m0, int rows, long long slot0, long long next, int step,
-                                               int n, int thread, int threads) {
+__device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0, int m0, int rows, int slot0, int next, int step, int n,
+                                               int thread, int threads) {
     for (int e = thread; e < rows * (D / 4); e += threads) {
         const int m = e / (D / 4), d0 = (e % (D / 4)) * 4;
         f32x4 ml[kMaxSplits], o[kMaxSplits];
 #pragma unroll
         for (int k = 0; k < kMaxSplits; ++k) {  // past the last piece: it again, left out below
             const int p = min(k, n - 1);
-            const long long row = (p == 0 ? slot0 : next + (p - 1) * step) * ROWS + m;
+            const long long row = (long long)(p == 0 ? slot0 : next + (p - 1) * step) * ROWS + m;
             ml[k] = *reinterpret_cast<const f32x4*>(a.part_ml + row * 4);
             o[k] = *reinterpret_cast<const f32x4*>(a.part_o + row * D + d0);
         }
@@ -184,17 +187,17 @@ __device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0,
     }
 }
 
-// Who works on a piece: waves first .. first + waves - 1 of the workgroup, on `pieces` consecutive ones; the item's keys are shared
-// by `of` such parts.
+// Who works on a piece: the waves of the workgroup, all on one or (balanced) on two consecutive ones, or each four on one; the item's
+// keys are shared by `of` such parts.
 struct Part {
-    int first, waves, pieces, of;
+    int waves, of;
 };
 
 // Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see (piece sp of n_sp of
-// them), merge the waves, write the rows (or the piece's sums to slot slot0 + sp).  MTMAX: what the LDS is laid out for.
+// them), merge the waves, write the rows (or the piece's sums to the workspace).  MTMAX: what the LDS is laid out for.
 template <bool BF16, int D, int MTMAX, int MT, bool NT, int CUT>
 __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0, int sp, int n_sp,
-                                             long long slot, const Part& part) {
+                                             const Part& part) {
     typedef Map<BF16, D, MTMAX, CUT> L;
     constexpr bool SPLIT = CUT != kWhole;
     constexpr int kTile = L::kTile, kKt = L::kKt, kDB = D / 16, kW = L::kW;
@@ -204,8 +207,8 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     const char* kc = reinterpret_cast<const char*>(a.k) + (size_t)g * a.head_stride;
     const char* vc = reinterpret_cast<const char*>(a.v) + (size_t)g * a.head_stride;
     // the waves of the item: all, or four of them; this one's place among them
-    const int n_waves = CUT == kBalanced ? part.waves : kW, wi = CUT == kBalanced ? w - part.first : w;
-    char* qbuf = smem + L::kQ + (CUT == kBalanced && part.first > 0 ? MT * L::kQPieces * 1024 : 0);
+    const int n_waves = CUT == kBalanced ? part.waves : kW, wi = CUT == kBalanced ? w & (n_waves - 1) : w;
+    char* qbuf = smem + L::kQ + (CUT == kBalanced && wi != w ? MT * L::kQPieces * 1024 : 0);
     float* red_m = reinterpret_cast<float*>(smem + L::kMl);  // [kW][16 * MT]
     float* red_l = red_m + kW * 16 * MT;
     char* kbuf = smem + w * 2 * kTile * L::kRow;  // the wave's tiles (bf16)
@@ -217,7 +220,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
     int kb0 = wi * kTile;
     if (SPLIT && part.of > 1) {  // the piece's even share of their tiles (at most 2^30 keys and eight pieces: the products fit 32 bits)
         const unsigned n_tiles = (unsigned)(kend + kTile - 1) / kTile;
-        const int upto = sp + (CUT == kBalanced ? part.pieces : 1);
+        const int upto = sp + (CUT == kBalanced ? part.waves >> 2 : 1);
         kb0 += (int)(n_tiles * sp / n_sp) * kTile;
         if (upto < n_sp) kend = (int)(n_tiles * upto / n_sp) * kTile;
     }
@@ -551,7 +554,8 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
                 }
             }
             if (SPLIT && part.of > 1 && m < rows) {
-                const long long at = slot * (16 * MTMAX) + m;
+                const int slot = CUT == kBalanced ? 2 * blockIdx.x + (first > 0 ? 1 : 0) : (i * a.H_kv + g) * gridDim.z + sp;
+                const long long at = (long long)slot * (16 * MTMAX) + m;
                 if constexpr (kPer >= 4) {
 #pragma unroll
                     for (int u = 0; u < kPer; u += 4) store_device(a.part_o, at * D + d0 + u, f32x4{o[u], o[u + 1], o[u + 2], o[u + 3]});
@@ -571,7 +575,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
             }
         };
         if constexpr (CUT == kBalanced) {
-            if (part.waves == 4) sum_rows(std::integral_constant<int, 4>{}, threadIdx.x - 64 * part.first, part.first);
+            if (part.waves == 4) sum_rows(std::integral_constant<int, 4>{}, threadIdx.x & 255, w & 4);
             else sum_rows(std::integral_constant<int, kW>{}, threadIdx.x, 0);
         } else {
             sum_rows(std::integral_constant<int, kW>{}, threadIdx.x, 0);
@@ -582,11 +586,19 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
 // Balanced pieces: every item is cut into as many as it takes for none to last longer than a
 // common time, the shortest that leaves no more pieces than there are places for four waves.  A workgroup holds two places.
 // The items of an even number of pieces come first, so that theirs lie side by side: a workgroup whose two places hold pieces of
-// one item works on both with all of its waves.  Every wave works this out for itself, from the lengths in its lanes: some 2 us.
-// D = 64, 32/8 heads, 1-8 drafts, us a call, an item per workgroup / balanced: 20 requests of 256-4096 tokens 37.9 / 29.3, 24 39.0 /
-// 32.6, 32 40.5 / 36.8, 40 49.4 / 40.6, 48 64.8 / 57.3; 32 with log-normal contexts up to 8192 72 / 49; equal lengths, where there
-// is nothing to balance, 32 of 2176 30.6 / 32.8, 48 57.5 / 48.6.  Workgroups of four waves, two to a compute unit, in place of two
+// one item works on both with all of its waves.  Every wave works this out for itself, from the lengths in its lanes.  Where
+// there is little to gain every item has a workgroup to itself, and the search is left out: code that a workgroup runs once costs its
+// fetch, 2 us here with the search, the arguments in the order of their use and a stack frame, 0.5 us without.
+// D = 64, 32/8 heads, 1-8 drafts, us a call over the caches of 12 layers in turn, an item per workgroup / balanced, always searched /
+// like this (gain): 20 requests of 256-4096 tokens 37.6 / 28.8 / 28.5 (236), 24 38.2 / 31.8 / 31.6 (215), 32 40.1 / 36.8 / 36.6 (193),
+// 40 49.0 / 40.2 / 40.0, 48 64.0 / 56.7 / 56.4; 32 with log-normal contexts up to 8192 73 / 49.3 / 48.6 (495); 16/16 heads, 16 of 256-4096
+// 34.3 / 32.6 / 32.6 (126); 32 of up to 2048 25.0 / 25.6 / 25.3 (103), of up to 1536 21.0 / 23.7 / 21.6 (67), up to 256 8.6 / 10.5 /
+// 9.2 (12); equal lengths, 20 of 1600 21.3 / 25.3 / 22.1 (66), 24 of 2176 31.1 / 33.0 / 32.1 (97), 32 of 2176 34.4 / 37.0 / 35.3
+// (45), 40 49.0 / 46.8 / 46.7, 48 58.4 / 49.5 / 49.2.  Workgroups of four waves, two to a compute unit, in place of two
 // items side by side in one of eight: 32 of 2176 37.1, and 14 us for 32 of up to 256.
+__device__ __forceinline__ int small_quotient(int x, int d) {  // x / d, both the same in every lane
+    return uniform((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
+}
 struct Piece {
     int i, g, sp, n_sp, place0;  // piece sp of the n_sp of request i's item for KV head g, the first of which has place0
     int q0, q_len, c;            // the request's rows and context
@@ -595,38 +607,43 @@ template <int MTMAX>
 struct BalancedPieces {
     int k, from, upto;  // the lane's request: pieces of an item, places of all of its items
     int q0, ql, c;      // its rows and context
+    bool whole;         // every item is two pieces, which one workgroup takes
 
     __device__ __forceinline__ explicit BalancedPieces(const ItemArgs& a) {
         const int lane = threadIdx.x & 63;
-        float work = 0.0f;
-        int most = 0;
         q0 = ql = c = 0;
         if (lane < a.B) {
             q0 = a.cu_q[lane];
             ql = min(a.cu_q[lane + 1], a.N_cap) - q0;
             c = a.ctx[lane];
-            const int M = ql * a.G;
-            if (ql > 0) {
-                const int seen = (int)min((long long)max(c, 0) + ql, min((long long)a.max_pages * a.P, 1LL << 30));
-                const int tiles = max((seen + 31) / 32, 1);
-                // (rows beyond the caller's bound are further rounds: a slot would be written twice, so no pieces then)
-                const int rounds = (M + 16 * MTMAX - 1) / (16 * MTMAX);
-                work = (float)tiles * (kTileBase * (float)rounds + (float)((M + 15) / 16));
-                // two lie side by side and cost nothing; more have to be long enough to be worth handing over
-                most = M <= 16 * MTMAX ? min(kMaxSplits, max(tiles / kPieceTiles, min(tiles, 2))) : 1;
-            }
         }
+        // (the other arguments are sent for while these come: later each would be another round trip)
+        asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.bt), "s"(a.H_q), "s"(a.G), "s"(a.n_pages), "s"(a.page_stride), "s"(a.slot_stride), "s"(a.head_stride), "s"(a.p_shift));
+        // rows beyond the caller's bound are further rounds (a slot would be written twice: no pieces then)
+        const int M = max(ql, 0) * a.G, mt = (M + 15) >> 4, rounds = (mt + MTMAX - 1) / MTMAX;
+        const int tiles = (min(max(c, 0), (int)min((long long)a.max_pages * a.P, 1LL << 30)) + ql + 31) >> 5;
+        const float work = (float)tiles * (kTileBase * (float)rounds + (float)mt);
         const float longest = __builtin_bit_cast(float, wave_max_positive(__builtin_bit_cast(int, work)));
+        const float share = work * __builtin_amdgcn_rcpf(longest);
+        // With an item to a workgroup the call lasts as long as its longest; cut, no less than its share of the sum.
+        const float sum = (float)wave_sum_i((int)(share * 65536.0f)) * (1.0f / 65536.0f);
+        const float gain = longest * (0.5f - sum * (float)a.H_kv * __builtin_amdgcn_rcpf((float)a.places));
+        whole = 2 * a.B * a.H_kv <= a.places && __builtin_amdgcn_ballot_w64(gain > kWorthCutting) == 0;
+        k = from = upto = 0;
+        if (whole) return;
+        // two lie side by side and cost nothing; more have to be long enough to be worth handing over
+        const int most = ql <= 0 ? 0 : rounds > 1 ? 1 : min(kMaxSplits, max(tiles / kPieceTiles, min(tiles, 2)));
         // times from the longest item's down to an eighth of it, 32 in equal ratios, by bisection; lane n holds longest / time n
-        const float ratios = exp2_fast((float)lane * (3.0f / 31.0f)), share = work * __builtin_amdgcn_rcpf(longest);
-        auto pieces = [&](int n) {
+        // (to a quarter / eighth / sixteenth, us a call: 20 requests 31.3 / 28.5 / 30.0, 32 of up to 2048 24.8 / 25.2 / 24.9, others alike)
+        const float ratios = exp2_fast((float)lane * (3.0f / 31.0f));
+        auto pieces = [=](int n) {
             const float r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ratios), n));
             return min(most, max((int)__builtin_ceilf(share * r - 1e-4f), 1));
         };
         int lo = 0;
 #pragma unroll
         for (int bit = 16; bit > 0; bit >>= 1)  // largest n that fits; n = 0, nothing is cut, always does
-            if ((long long)wave_sum_i(pieces(lo + bit)) * a.H_kv <= a.places) lo += bit;
+            if (wave_sum_i(pieces(lo + bit)) * a.H_kv <= a.places) lo += bit;
         k = pieces(lo);
         const int even = (k & 1) == 0 ? k * a.H_kv : 0, odd = k * a.H_kv - even;
         const int upto_even = wave_inclusive_scan_dpp(even), upto_odd = wave_inclusive_scan_dpp(odd);
@@ -641,8 +658,7 @@ struct BalancedPieces {
         p.i = __builtin_ctzll(mine);
         p.n_sp = __builtin_amdgcn_readlane(k, p.i);
         const int first = __builtin_amdgcn_readlane(from, p.i);
-        p.g = (int)(((float)(place - first) + 0.5f) * __builtin_amdgcn_rcpf((float)p.n_sp));  // (place - first) / n_sp: small numbers
-        p.g = uniform(p.g);
+        p.g = small_quotient(place - first, p.n_sp);
         p.place0 = first + p.g * p.n_sp;
         p.sp = place - p.place0;
         p.q0 = __builtin_amdgcn_readlane(q0, p.i);
@@ -658,36 +674,44 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int kW = Map<BF16, D, MTMAX, CUT>::kW;
     int g = blockIdx.x, i = blockIdx.y, n_sp = 1, sp = 0, z = blockIdx.z, nz = gridDim.z, mt_group = 0;
-    long long slot = 0;
-    Part part{0, kW, 1, 1};
-    int next_slot = 0, slot_step = 1;
+    Part part{kW, 1};
     bool cut = true;
-    long long slot0 = 0;
     int q0, q_len, c;
+    // what is needed again behind the keys' loops, of each half (scalar registers are short in them)
+    __shared__ int s_place0[2], s_word[2];
     if constexpr (CUT == kBalanced) {
         const BalancedPieces<MTMAX> bp(a);
-        const int half = uniform(threadIdx.x >> 8);
-        const Piece p0 = bp.at(2 * blockIdx.x), p1 = bp.at(2 * blockIdx.x + 1);
-        if (p0.n_sp == 0 && p1.n_sp == 0) return;
-        const bool joint = p0.n_sp > 0 && p1.n_sp > 0 && p0.place0 == p1.place0;
-        const Piece p = joint || half == 0 ? p0 : p1;
-        i = p.i; g = p.g; sp = p.sp; n_sp = p.n_sp;
-        part.first = joint ? 0 : half * 4;
-        part.waves = joint ? 8 : 4;
-        part.pieces = joint ? 2 : 1;
-        const int w0 = p.place0 >> 1;
-        auto parts_of = [](const Piece& x) { return x.n_sp > 0 ? ((x.place0 + x.n_sp - 1) >> 1) - (x.place0 >> 1) + 1 : 1; };
-        part.of = parts_of(p);
-        cut = parts_of(p0) > 1 || parts_of(p1) > 1;
-        slot = joint ? 2 * blockIdx.x : 2 * blockIdx.x + half;
-        slot0 = p.place0;
-        next_slot = 2 * (w0 + 1);
-        slot_step = 2;
         z = 0;
         nz = 1;
-        // the same number of query tiles for both, so that their barriers meet (an empty place has no rows)
-        mt_group = max(p0.q_len, p1.q_len) * a.G;
-        q0 = p.q0; q_len = p.q_len; c = p.c;
+        if (bp.whole) {
+            i = small_quotient(blockIdx.x, a.H_kv);
+            g = blockIdx.x - i * a.H_kv;
+            if (i >= a.B) return;
+            q0 = __builtin_amdgcn_readlane(bp.q0, i);
+            q_len = __builtin_amdgcn_readlane(bp.ql, i);
+            c = __builtin_amdgcn_readlane(bp.c, i);
+            if (q_len <= 0) return;
+            cut = false;
+            mt_group = q_len * a.G;
+        } else {
+            const int half = uniform(threadIdx.x >> 8);
+            const Piece p0 = bp.at(2 * blockIdx.x), p1 = bp.at(2 * blockIdx.x + 1);
+            if (p0.n_sp == 0 && p1.n_sp == 0) return;
+            const bool joint = p0.n_sp > 0 && p1.n_sp > 0 && p0.place0 == p1.place0;
+            const Piece p = joint || half == 0 ? p0 : p1;
+            i = p.i; g = p.g; sp = p.sp; n_sp = p.n_sp;
+            part.waves = joint ? 8 : 4;
+            auto parts_of = [](const Piece& x) { return x.n_sp > 0 ? ((x.place0 + x.n_sp - 1) >> 1) - (x.place0 >> 1) + 1 : 1; };
+            part.of = parts_of(p);
+            cut = parts_of(p0) > 1 || parts_of(p1) > 1;
+            if ((threadIdx.x & 255) == 0) {
+                s_place0[half] = p.place0;
+                s_word[half] = p.i * a.H_kv + p.g;
+            }
+            // the same number of query tiles for both, so that their barriers meet (an empty place has no rows)
+            mt_group = max(p0.q_len, p1.q_len) * a.G;
+            q0 = p.q0; q_len = p.q_len; c = p.c;
+        }
     } else {
         q0 = a.cu_q[i];
         q_len = min(a.cu_q[i + 1], a.N_cap) - q0;
@@ -695,9 +719,7 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
     }
     const int M = q_len * a.G;
     if (CUT != kBalanced && q_len <= 0) return;
-    const long long word = (long long)i * a.H_kv + g;
     if constexpr (CUT == kEven) {
-        slot0 = word * gridDim.z;
         // (rows beyond the caller's bound are further rounds: a slot would be written twice, so no pieces then)
         const int seen = (int)min((long long)c + q_len, min((long long)a.max_pages * a.P, 1LL << 30));
         if (M <= 16 * MTMAX) n_sp = max(1, min((int)gridDim.z, seen / kSplitKeys));
@@ -705,32 +727,34 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
         if (sp >= n_sp) return;
         z = 0;
         nz = 1;
-        slot = slot0 + sp;
-        next_slot = (int)slot0 + 1;
         part.of = n_sp;
     }
     if (CUT != kBalanced) mt_group = M;
     for (int m0 = z * 16 * MTMAX; m0 < mt_group; m0 += nz * 16 * MTMAX) {
         const int mt = (min(mt_group - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
         if constexpr (MTMAX >= 4)
-            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
+            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
         if constexpr (MTMAX >= 3)
-            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
+            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
         if constexpr (MTMAX >= 2)
-            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
-        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, slot, part);
+            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
+        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
         __syncthreads();  // before the next group's query operands and tiles
     }
     if constexpr (CUT != kWhole) {
         __shared__ int s_last[2];
         if (CUT == kEven ? n_sp == 1 : !cut) return;
-        const int half = part.first > 0 ? 1 : 0, thread = threadIdx.x - 64 * part.first;
+        const int half = CUT == kBalanced ? uniform(threadIdx.x >> 8) & (part.waves == 4 ? 1 : 0) : 0;
+        const int thread = CUT == kBalanced && part.waves == 4 ? threadIdx.x & 255 : threadIdx.x;
+        const int word = CUT == kBalanced ? uniform(s_word[half]) : i * a.H_kv + g;
+        const int slot0 = CUT == kBalanced ? uniform(s_place0[half]) : word * (int)gridDim.z;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the piece is in memory once every wave's stores are acknowledged
         __syncthreads();
         if (thread == 0) s_last[half] = part.of > 1 && count_arrival(a.arrivals + word, a.call_id) == part.of;
         __syncthreads();
         if (!s_last[half]) return;
-        combine_pieces<D, 16 * MTMAX>(a, g, q0, 0, M, slot0, next_slot, slot_step, part.of, thread, 64 * part.waves);
+        combine_pieces<D, 16 * MTMAX>(a, g, q0, 0, M, slot0, CUT == kBalanced ? 2 * ((slot0 >> 1) + 1) : slot0 + 1, CUT == kBalanced ? 2 : 1,
+                                      part.of, thread, CUT == kBalanced ? 64 * part.waves : 64 * kW);
         if (thread == 0) __atomic_store_n(a.arrivals + word, a.call_id << 16, __ATOMIC_RELAXED);  // for a graph's next replay
     }
 }
@@ -796,7 +820,7 @@ Layout layout_of(const fsr_attn_params& p) {
         l.splits = (int)std::max(1LL, std::min({(long long)kMaxSplits, keys / kSplitKeys, units / items}));
         // From more items than half the units to one and a half times as many, heads of 64 (eight waves a workgroup): balanced by
         // length.  With fewer even pieces do as well (16 requests 26.5 / 26.6), with more the units have several items anyway (56
-        // requests 68.7 / 71.5).  Short contexts are not worth the schedule (32 of up to 256 tokens 10.1 / 11.5).
+        // requests 68.7 / 71.5).  Tables of so few pages hold nothing that is worth it (32 of up to 1536 tokens 21.0 / 21.6).
         if (p.D == 64 && l.mt < 4 && p.B > 1 && p.B <= kBalancedMaxB && keys >= kBalancedKeys && 2 * items > units && 2 * items <= 3 * units) {
             l.places = (int)(2 * units);
             l.splits = 1;

@@ -117,3 +117,29 @@ def test_rows_beyond_the_bound_beside_others(fsr, oracle, H_q, H_kv, B, hint):
     torch.cuda.synchronize()
     check_attention(out, ref, "f32", len(ref))
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("H_q,H_kv,B,hint,ctx_hi", [(32, 8, 32, 4, 300), (28, 7, 36, 4, 90), (12, 3, 61, 3, 700), (64, 8, 17, 4, 1), (32, 8, 32, 2, 256)])
+def test_short_contexts_in_wide_tables(fsr, oracle, H_q, H_kv, B, hint, ctx_hi):
+    """Little to gain by cutting: an item to a workgroup, requests without rows and (the last call) rows beyond the bound among them."""
+    announce(f"short contexts in wide tables {H_q}/{H_kv} B={B} hint={hint} ctx_hi={ctx_hi}")
+    rng = np.random.Generator(np.random.PCG64(B + ctx_hi))
+    spec = rng.integers(0, hint, B)
+    if hint == 2:
+        spec[rng.permutation(B)[:9]] = rng.integers(3, 12, 9)
+    x = make(rng, "bf16", H_q, H_kv, 64, 16, rng.integers(0, ctx_hi + 1, B), spec)
+    x["bt"] = np.ascontiguousarray(np.pad(x["bt"], ((0, 0), (0, 200 - x["bt"].shape[1])), constant_values=-1))
+    x["cu"][5] = x["cu"][4]  # no rows; the request behind it has them as well, on the pages it has
+    x["ctx"][5] = 0
+    scale = 1.0 / 8.0
+    x["bt"][5, :3] = x["bt"][5, 0]
+    ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=H_q, H_kv=H_kv, D=64, P=16,
+                                           dtype="bf16", scale=float(np.float32(scale)))
+    q = dev(x["q"], True)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+    fsr.verify_attention(q, dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=scale, out=out,
+                         lse=lse, max_q_len=hint)
+    torch.cuda.synchronize()
+    check_attention(out, ref, "f32", len(ref))
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
