@@ -143,3 +143,75 @@ def test_short_contexts_in_wide_tables(fsr, oracle, H_q, H_kv, B, hint, ctx_hi):
     torch.cuda.synchronize()
     check_attention(out, ref, "f32", len(ref))
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("units,B", [(33, 5), (64, 9), (65, 5), (128, 15)])
+def test_balanced_within_the_callers_workgroups(fsr, oracle, units, B):
+    """Items between half the units that the caller owns, odd numbers of them too, and one and a half times as many."""
+    announce(f"balanced items max_workgroups={units}")
+    rng = np.random.Generator(np.random.PCG64(units))
+    ctx, spec = rng.integers(0, 1700, B), rng.integers(0, 4, B)
+    ctx[0], ctx[1:3] = 1690, 60
+    x = make(rng, "bf16", 32, 8, 64, 16, ctx, spec)
+    ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=32, H_kv=8, D=64, P=16, dtype="bf16", scale=0.125)
+    q = dev(x["q"], True)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda")
+    fsr.verify_attention(q, dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=0.125, out=out,
+                         lse=lse, max_q_len=4, max_workgroups=units)
+    torch.cuda.synchronize()
+    check_attention(out, ref, "f32", len(ref))
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
+def test_balanced_through_the_built_in_scratch(fsr):
+    """fsr_verify_attention_static against fsr_verify_attention, bit for bit."""
+    announce("balanced items static")
+    rng = np.random.Generator(np.random.PCG64(4))
+    ctx, spec = rng.integers(0, 1700, 20), rng.integers(0, 4, 20)
+    ctx[0] = 1690
+    x = make(rng, "bf16", 32, 8, 64, 16, ctx, spec)
+    q, k, v, bt, c, cu = dev(x["q"], True), dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["ctx"]), dev(x["cu"])
+    outs = [torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    lses = [torch.zeros(q.shape[:2], dtype=torch.float32, device="cuda") for _ in range(2)]
+    fsr.verify_attention(q, k, v, bt, c, None, cu, scale=0.125, out=outs[0], lse=lses[0], max_q_len=4)
+    fsr.verify_attention_static(q, k, v, bt, c, cu, scale=0.125, out=outs[1], lse=lses[1], max_q_len=4)
+    torch.cuda.synchronize()
+    assert not torch.isnan(outs[0].float()).any()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)) and torch.equal(lses[0], lses[1])
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_values_that_are_not_finite_in_balanced_pieces(fsr, oracle, bad):
+    """Such values of V reach exactly the rows that see their key: across the cuts of an item, and beside another item of the workgroup."""
+    announce(f"balanced items bad={bad}")
+    rng = np.random.Generator(np.random.PCG64(12))
+    H_kv, B = 7, 29  # an odd number of pieces side by side
+    ctx, spec = rng.integers(100, 1700, B), rng.integers(0, 4, B)
+    ctx[0] = 1690
+    x = make(rng, "bf16", 14, H_kv, 64, 16, ctx, spec)
+    store = np.uint16(0x7FC0 if np.isnan(bad) else 0x7F80 if bad > 0 else 0xFF80)
+    hit = {}
+    for i in range(0, B, 3):  # a key of one KV head; some only the later rows see
+        key = int(ctx[i]) + int(spec[i]) if i % 2 else int(rng.integers(0, ctx[i]))
+        g, d = int(rng.integers(H_kv)), int(rng.integers(64))
+        x["v"].view(np.uint16)[x["bt"][i, key // 16], g, key % 16, d] = store
+        hit[i] = (g, key, d)
+    q = dev(x["q"], True)
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    fsr.verify_attention(q, dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["ctx"]), None, dev(x["cu"]), scale=0.125, out=out, max_q_len=4)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    want_bad = np.zeros(got.shape, bool)
+    for i, (g, key, d) in hit.items():
+        for j in range(spec[i] + 1):
+            if key <= ctx[i] + j:
+                want_bad[x["cu"][i] + j, 2 * g:2 * g + 2, d] = True
+    assert np.array_equal(~np.isfinite(got), want_bad)
+    assert np.array_equal(np.isnan(got[want_bad]), np.full(want_bad.sum(), np.isnan(bad)))
+    clean = x["v"].copy()
+    for i, (g, key, d) in hit.items():
+        clean.view(np.uint16)[x["bt"][i, key // 16], g, key % 16, d] = 0
+    ref, _ = oracle.verify_attention(x["q"], x["k"], clean, x["bt"], x["ctx"], x["cu"], H_q=14, H_kv=H_kv, D=64, P=16, dtype="bf16", scale=0.125)
+    got[want_bad] = ref[want_bad]
+    check_attention(torch.from_numpy(got), ref, "f32", len(ref))
