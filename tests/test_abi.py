@@ -136,3 +136,17 @@ def test_missing_argument_helper_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "_MARSHAL_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(FileNotFoundError, match="nope.so is missing: build it"):
         binding.load_library()
+
+
+@pytest.mark.parametrize("D,max_q_len,slots,tiles", [(64, 4, 512, 1), (64, 8, 512, 2), (64, 12, 512, 3), (64, 16, 256, 4), (64, 0, 256, 4), (128, 20, 256, 3)])
+def test_scratch_of_the_items_kernel(lib, D, max_q_len, slots, tiles):
+    """Two pieces of an item for each compute unit where a batch of heads of 64 can be cut by its lengths (up to three query tiles),
+    else one: sums, references, arrival counts."""
+    from paper_2604_20503_amd import binding as b
+    for B in (1, 20, 64, 300):
+        p = b.AttnParams(B=B, N_cap=4096, H_q=32, H_kv=8, D=D, P=24, max_pages=200, n_pages=1000, dtype=1, out_dtype=1, scale=0.1,
+                         max_q_len=max_q_len, max_workgroups=0, kv_layout=0)
+        out = ctypes.c_size_t(0)
+        assert lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(out)) == 0
+        rows = slots * 16 * tiles
+        assert out.value == rows * D * 4 + rows * 16 + slots * 8
