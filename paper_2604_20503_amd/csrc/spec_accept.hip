@@ -1313,7 +1313,8 @@ __global__ __launch_bounds__(kThreads, MODE == FSR_LOGITS ? 4 : 1) void accept_s
 // call with 1, 2, 4 or 8 chunks, as many as leave 1024 workgroups / like this: 16 requests 16.9 / 16.9, 48 23.3 / 18.5, 96 24.4 /
 // 22.2, 256 48.6 / 48.2; 152064, 128 28.9 / 29.2, 384 82 / 82.  Beyond two rounds of the largest workgroups the places are taken as
 // they come free (some requests have nothing to sample) and most chunks a workgroup are best: the draw of a chunked step of
-// 512 requests 40.3 us with 8, 45.6 with the 10 that would make it two rounds.
+// 512 requests 40.3 us with 8, 45.6 with the 10 that would make it two rounds.  One chunk / two / three for the chain: 384 x 152064 75.6 /
+// 72.1 / 72.0, 30 sizes of 16 to 512 requests and 32000 to 152064 tokens otherwise alike.
 // LOGITS: the chain is a smaller part: 96 requests 119.6 / 116.8, 128 165 / 167, 512 503 / 509.
 constexpr int kSamplePlaces = 1024;
 int sample_group_of(int mode, int B, int nc) {
