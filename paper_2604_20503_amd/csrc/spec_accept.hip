@@ -471,13 +471,14 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ stat_a,
 // us a launch, 128 requests x 128256 in fp32, a reference taken off every logit / from the logits themselves where those are within
 // reach and else read again / like this: T = 0.005 95 / 181 / 86, all but 50 logits a row masked by -1e9 64 / 117 / 59, T = 1 118 /
 // 105 / 101; 16 requests 26 / 41 / 25, 24.5 / 35 / 25, 26 / 22 / 22.  Registers decide: calls of few rows are workgroups' latencies, and
-// 1 to 3 us slower with five waves per SIMD than with six (the spills of seven cost as much); those that leave rows out are 3 % faster with five.
+// 1 to 3 us slower with five waves per SIMD than with six (in fp32 the spills of seven cost as much; in bf16, us a call with six / seven, 64
+// requests x 128256 96.6 / 95.8, 16 with all but 50 logits masked 41.5 / 40.6); those that leave rows out are 3 % faster with five.
 // The rows are read once here, with the non-temporal hint (512 requests x 152064 in fp32: call 533 us without, 508 with).  What
 // bounds it is both the rows' bytes and the fp64 instructions: 512 requests 455 us a launch with a reference taken off every logit
 // and ordinary loads, 394 like this (about 2.3 GB; vector ALUs 70 % busy); 16 requests x 128256 in bf16 24.1 / 20.6.
 // ---------------------------------------------------------------------------------------
 template <typename RT, bool SKIP>  // SKIP: rows behind a rejection are left out (ws.skip)
-__global__ __launch_bounds__(kThreads, SKIP ? 5 : 6) void accept_stats_kernel(
+__global__ __launch_bounds__(kThreads, SKIP ? 5 : sizeof(RT) == 2 ? 7 : 6) void accept_stats_kernel(
     const RT* __restrict__ z_target, const RT* __restrict__ z_draft, const int32_t* __restrict__ draft_tokens,
     const float* __restrict__ u_accept, const int32_t* __restrict__ cu_t, const int32_t* __restrict__ cu_d,
     const int32_t* __restrict__ t_rows, const int32_t* __restrict__ d_rows, Workspace ws, int B, int V, int S_max, double T,
