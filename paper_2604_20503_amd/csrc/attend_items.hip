@@ -847,11 +847,11 @@ int launch_mt(const ItemArgs& a, const Layout& l, hipStream_t s) {
 
 }  // namespace
 
-// For as many slots as any batch uses, so that the size covers smaller batches too (which are cut into more pieces).
+// For as many slots as any batch uses, so that the size covers smaller batches and fewer rows a request too (which are cut into more
+// pieces): heads of 64 two slots a workgroup of up to three query tiles, which is more than one of four.
 size_t attend_items_workspace_bytes(const fsr_attn_params& p) {
     if (p.dtype != FSR_BF16) return 0;
-    const int mt = layout_of(p).mt;
-    const size_t slots = (p.D == 64 && mt < 4 ? 2 : 1) * (size_t)kSplitGroups, rows = slots * 16 * mt;  // (balanced: two a workgroup)
+    const size_t slots = (p.D == 64 ? 2 : 1) * (size_t)kSplitGroups, rows = slots * 16 * std::min(layout_of(p).mt, 3);
     return align_up(rows * p.D * sizeof(float), 256) + align_up(rows * 4 * sizeof(float), 256) +
            align_up(slots * sizeof(unsigned long long), 256);
 }

@@ -138,15 +138,28 @@ def test_missing_argument_helper_fails_loudly(monkeypatch, tmp_path):
         binding.load_library()
 
 
-@pytest.mark.parametrize("D,max_q_len,slots,tiles", [(64, 4, 512, 1), (64, 8, 512, 2), (64, 12, 512, 3), (64, 16, 256, 4), (64, 0, 256, 4), (128, 20, 256, 3)])
-def test_scratch_of_the_items_kernel(lib, D, max_q_len, slots, tiles):
-    """Two pieces of an item for each compute unit where a batch of heads of 64 can be cut by its lengths (up to three query tiles),
-    else one: sums, references, arrival counts."""
+def _attn_bytes(lib, **shape):
     from paper_2604_20503_amd import binding as b
+    p = b.AttnParams(**{**dict(B=20, N_cap=4096, H_q=32, H_kv=8, D=64, P=24, max_pages=200, n_pages=1000, dtype=1, out_dtype=1, scale=0.1,
+                               max_q_len=0, max_workgroups=0, kv_layout=0), **shape})
+    out = ctypes.c_size_t(0)
+    assert lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(out)) == 0
+    return out.value
+
+
+@pytest.mark.parametrize("D,max_q_len,slots,tiles", [(64, 4, 512, 1), (64, 8, 512, 2), (64, 12, 512, 3), (64, 16, 512, 3), (64, 0, 512, 3), (128, 20, 256, 3)])
+def test_scratch_of_the_items_kernel(lib, D, max_q_len, slots, tiles):
+    """Two pieces of an item for each compute unit where a batch of heads of 64 can be cut by its lengths (up to three query tiles; one
+    piece of four takes less), else one: sums, references, arrival counts."""
     for B in (1, 20, 64, 300):
-        p = b.AttnParams(B=B, N_cap=4096, H_q=32, H_kv=8, D=D, P=24, max_pages=200, n_pages=1000, dtype=1, out_dtype=1, scale=0.1,
-                         max_q_len=max_q_len, max_workgroups=0, kv_layout=0)
-        out = ctypes.c_size_t(0)
-        assert lib.fsr_attn_workspace_bytes(ctypes.byref(p), ctypes.byref(out)) == 0
         rows = slots * 16 * tiles
-        assert out.value == rows * D * 4 + rows * 16 + slots * 8
+        assert _attn_bytes(lib, B=B, D=D, max_q_len=max_q_len) == rows * D * 4 + rows * 16 + slots * 8
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H_q,H_kv", [(32, 8), (16, 16), (71, 71)])
+def test_scratch_covers_smaller_calls(lib, D, H_q, H_kv):
+    """The size for some shapes covers every smaller number of rows, bound on a request's rows, and batch."""
+    for field in ("N_cap", "max_q_len", "B"):
+        sizes = [_attn_bytes(lib, P=24, D=D, H_q=H_q, H_kv=H_kv, **{"B": 2, field: n}) for n in range(2, 80)]
+        assert sizes == sorted(sizes), field
