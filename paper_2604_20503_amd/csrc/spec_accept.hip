@@ -137,16 +137,18 @@ __device__ __forceinline__ float to_float(uint16_t x) { return __builtin_bit_cas
 typedef __attribute__((__vector_size__(16), __aligned__(4))) float row_f32x4;
 typedef __attribute__((__vector_size__(8), __aligned__(2))) uint16_t row_u16x4;
 template <bool NT = false>  // with the non-temporal hint
-__device__ __forceinline__ void load_quad_vec(const float* __restrict__ row, int e, float (&x)[4]) {
+__device__ __forceinline__ row_f32x4 raw_quad(const float* __restrict__ row, int e) {
     const row_f32x4* p = reinterpret_cast<const row_f32x4*>(row + e);
-    const row_f32x4 t = NT ? __builtin_nontemporal_load(p) : *p;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = t[k];
+    return NT ? __builtin_nontemporal_load(p) : *p;
 }
 template <bool NT = false>
-__device__ __forceinline__ void load_quad_vec(const uint16_t* __restrict__ row, int e, float (&x)[4]) {
+__device__ __forceinline__ row_u16x4 raw_quad(const uint16_t* __restrict__ row, int e) {
     const row_u16x4* p = reinterpret_cast<const row_u16x4*>(row + e);
-    const row_u16x4 t = NT ? __builtin_nontemporal_load(p) : *p;
+    return NT ? __builtin_nontemporal_load(p) : *p;
+}
+template <typename RT>
+__device__ __forceinline__ void load_quad_vec(const RT* __restrict__ row, int e, float (&x)[4]) {
+    const auto t = raw_quad(row, e);
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = to_float(t[k]);
 }
@@ -475,7 +477,7 @@ __device__ __forceinline__ void combine_stats(const double* __restrict__ stat_a,
 // requests x 128256 96.6 / 95.8, 16 with all but 50 logits masked 41.5 / 40.6); those that leave rows out are 3 % faster with five.
 // The rows are read once here, with the non-temporal hint (512 requests x 152064 in fp32: call 533 us without, 508 with).  What
 // bounds it is both the rows' bytes and the fp64 instructions: 512 requests 455 us a launch with a reference taken off every logit
-// and ordinary loads, 394 like this (about 2.3 GB; vector ALUs 70 % busy); 16 requests x 128256 in bf16 24.1 / 20.6.
+// and ordinary loads, 394 like this (about 2.3 GB; vector ALUs 70 % busy); 16 requests x 128256 in bf16 23.8 / 18.4.
 // ---------------------------------------------------------------------------------------
 template <typename RT, bool SKIP>  // SKIP: rows behind a rejection are left out (ws.skip)
 __global__ __launch_bounds__(kThreads, SKIP ? 5 : sizeof(RT) == 2 ? 7 : 6) void accept_stats_kernel(
@@ -506,15 +508,13 @@ __global__ __launch_bounds__(kThreads, SKIP ? 5 : sizeof(RT) == 2 ? 7 : 6) void 
     }
     const int c_first = blockIdx.x * ws.stat_group, c_end = min(nc, c_first + ws.stat_group);
     const int c_whole = min(c_end, V / kChunk);  // chunks before it are whole
-    float va[kPerThread], vb[kPerThread];
-    auto load_chunk = [&](int c, float (&v)[kPerThread]) {
+    // (as they come from memory: made floats where they are loaded, 16-bit ones take twice the registers, and are waited for there:
+    // us a launch, 16 requests x 128256 20.0 / 18.4)
+    typedef decltype(raw_quad<true>(rows, 0)) Raw;
+    Raw va[kPerThread / 4], vb[kPerThread / 4];
+    auto load_chunk = [&](int c, Raw (&v)[kPerThread / 4]) {
 #pragma unroll
-        for (int q = 0; q < kPerThread / 4; ++q) {
-            float x[4];
-            load_quad_vec<true>(rows, c * kChunk + (q * kThreads + threadIdx.x) * 4, x);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[q * 4 + u] = x[u];
-        }
+        for (int q = 0; q < kPerThread / 4; ++q) v[q] = raw_quad<true>(rows, c * kChunk + (q * kThreads + threadIdx.x) * 4);
     };
     auto load_checked = [&](int c, float (&v)[kPerThread]) {
 #pragma unroll
@@ -598,20 +598,27 @@ __global__ __launch_bounds__(kThreads, SKIP ? 5 : sizeof(RT) == 2 ? 7 : 6) void 
                 direct = fma(e.power, e.series, direct);
             }
         };
+        auto add_raw = [&](const Raw (&r)[kPerThread / 4]) {
+            float v[kPerThread];
+#pragma unroll
+            for (int u = 0; u < kPerThread; ++u) v[u] = to_float(r[u / 4][u % 4]);
+            add_chunk(v);
+        };
         // Whole chunks: four vector loads per lane and chunk, all in flight together, the next chunk's issued before this one's
         // arithmetic, and only such loads in the loop: mixed with bounds-checked ones the compiler orders each vector load behind
         // all loads before it.
 #pragma unroll 1
         for (int c = c_first; c < c_whole; c += 2) {
             if (c + 1 < c_whole) load_chunk(c + 1, vb);
-            add_chunk(va);
+            add_raw(va);
             if (c + 1 >= c_whole) break;
             if (c + 2 < c_whole) load_chunk(c + 2, va);
-            add_chunk(vb);
+            add_raw(vb);
         }
         if (c_whole < c_end) {  // the chunk that holds the vocabulary's ragged end
-            load_checked(c_whole, va);
-            add_chunk(va);
+            float v[kPerThread];
+            load_checked(c_whole, v);
+            add_chunk(v);
         }
     } else {  // a temperature out of all range: against a reference of the lane's own
         const ExpTable et = exp_table(s_exp);
