@@ -315,7 +315,8 @@ __device__ __forceinline__ ExpParts exp_of_logit(double x, const ExpDirect& k) {
     p.series = fma(fma(fma(fma(k.a4, r, k.a3), r, k.a2), r, k.a1), r, 1.0);
     return p;
 }
-// Largest magnitude, largest and smallest of three (one instruction each; a NaN is passed over).
+// Largest magnitude, largest and smallest of three (one instruction each; a quiet NaN is passed over, a signalling one too in waves
+// that have called pass_over_nans, and else hides the value beside it).
 __device__ __forceinline__ float max3_abs(float m, float x, float y) {
     asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x), "v"(y));
     return m;
@@ -333,6 +334,9 @@ __device__ __forceinline__ float max2(float x, float y) {  // (fmaxf quiets its 
     asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(x), "v"(y));
     return m;
 }
+// The IEEE bit of the wave's mode off (bit 9 of hardware register 1): minima and maxima return the operand that is no NaN whatever
+// kind of NaN the other is.
+__device__ __forceinline__ void pass_over_nans() { __builtin_amdgcn_s_setreg(1 | 9 << 6, 0); }
 // A value that is the same in every lane, said so.
 __device__ __forceinline__ float uniform(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
@@ -489,6 +493,7 @@ __global__ __launch_bounds__(kThreads, SKIP ? 5 : sizeof(RT) == 2 ? 7 : 6) void 
     __shared__ float s_max[kThreads / 64];
     __shared__ uint2 s_exp[256];
     __shared__ int s_behind, s_last;
+    pass_over_nans();
     const int nc = n_chunks_of(V), nsg = n_stat_groups_of(V, ws.stat_group);
     const int k = blockIdx.y / B, i = blockIdx.y - k * B, j = k >> 1;
     const int t0 = cu_t[i], t_i = cu_t[i + 1] - t0, d0 = cu_d[i], d_i = cu_d[i + 1] - d0;

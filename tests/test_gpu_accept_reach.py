@@ -132,3 +132,34 @@ def test_chunks_at_different_levels(fsr, oracle, T, level, B, S, nc, dtype):
                           t_rows=dev(t_rows), d_rows=dev(d_rows), mode=1, temperature=T)
     torch.cuda.synchronize()
     check_accept(gpu, ref, u_s)
+
+
+# A NaN that is quiet, or signalling as bits read from anywhere can be, in front of and behind the row's largest logit.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bits", [0x7FC0, 0x7F81, 0xFFA0])
+@pytest.mark.parametrize("level", [0.0, 900.0, -900.0])
+@pytest.mark.parametrize("at", [2 * 256 * 4 + 2, 8192 + 507])  # of a whole chunk, of the ragged one
+def test_a_nan_beside_the_largest_logit(fsr, oracle, at, level, bits, dtype):
+    announce(f"accept nan {bits:x} beside {at} level={level} {dtype}")
+    rng = np.random.default_rng(at)
+    spec, V = np.array([1, 3, 0, 2]), 9001
+    cu_t, cu_d = (np.concatenate([[0], np.cumsum(n)]).astype(np.int32) for n in (spec + 1, spec))
+    z_t, z_d = (np.round(level + rng.normal(0, 2, (n, V)) * 4).astype(np.float32) / 4 for n in (cu_t[-1], cu_d[-1]))
+    x = rng.integers(0, V, cu_d[-1]).astype(np.int32)
+    x[::2] = at
+    for z in (z_t, z_d):
+        z[:] = torch.from_numpy(z).bfloat16().float().numpy()
+        z[:, at] = level + 650.0 if level == 0.0 else level + 40.0
+        z[:, at] = torch.from_numpy(z[:, at]).bfloat16().float().numpy()
+        z[:, at ^ 1] = -np.inf  # what a NaN logit counts as
+    x[x == at ^ 1] = at
+    u_a, u_s = (rng.random(n).astype(np.float32) for n in (cu_d[-1], len(spec)))
+    ref = oracle.spec_accept(z_t, z_d, x, u_a, u_s, cu_t, cu_d, S_max=3, mode=1)
+    tensors = []
+    for z in (z_t, z_d):
+        b = z.view(np.uint32).copy()
+        b[:, at ^ 1] = np.uint32(bits << 16)
+        tensors.append(dev((b >> 16).astype(np.uint16), True) if dtype == "bf16" else dev(b.view(np.int32)).view(torch.float32))
+    gpu = fsr.spec_accept(*tensors, dev(x), dev(u_a), dev(u_s), dev(cu_t), dev(cu_d), S_max=3, mode=1)
+    torch.cuda.synchronize()
+    check_accept(gpu, ref, u_s)
