@@ -379,10 +379,11 @@ __device__ __forceinline__ ExpConsts exp_consts_for() {
 }
 
 // z / T - m.  Beyond kWidest the two differ by whole units or not at all, and m is the rounded quotient of one of the row's
-// logits: a multiply-add would leave its rounding behind where there is no difference.
+// logits: a multiply-add would leave its rounding behind where there is no difference.  (An infinite m is that of a row without
+// any mass: NaN or infinite, which counts as none.)
 __device__ __forceinline__ double less_reference(float z, double inv_T, double m) {
     const double d = fma((double)z, inv_T, -m);
-    return fabs(m) > kWidest && __dmul_rn((double)z, inv_T) == m ? 0.0 : d;
+    return fabs(m) > kWidest && fabs(m) < INFINITY && __dmul_rn((double)z, inv_T) == m ? 0.0 : d;
 }
 
 // Probability of one entry in fp64: the value itself, or exp(z / T - m) / Z with the two divisions as products

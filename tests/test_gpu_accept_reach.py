@@ -163,3 +163,34 @@ def test_a_nan_beside_the_largest_logit(fsr, oracle, at, level, bits, dtype):
     gpu = fsr.spec_accept(*tensors, dev(x), dev(u_a), dev(u_s), dev(cu_t), dev(cu_d), S_max=3, mode=1)
     torch.cuda.synchronize()
     check_accept(gpu, ref, u_s)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [1.0, 1e-30, 1e-300])
+@pytest.mark.parametrize("nothing", [-np.inf, np.nan, np.inf])
+def test_rows_without_any_mass(fsr, oracle, nothing, T, dtype):
+    """Target and draft rows that are masked throughout: they accept nothing, and a draw from one has no token to give but the first."""
+    announce(f"accept rows of {nothing} T={T} {dtype}")
+    rng = np.random.default_rng(1)
+    spec, V = np.array([2, 2, 1, 2, 1, 0]), 9001
+    cu_t, cu_d = (np.concatenate([[0], np.cumsum(n)]).astype(np.int32) for n in (spec + 1, spec))
+    z_t, z_d = (rng.integers(-8, 8, (n, V)).astype(np.float32) * np.float32(2.0 ** round(np.log2(max(T, 1e-30)))) for n in (cu_t[-1], cu_d[-1]))
+    x = rng.integers(0, V, cu_d[-1]).astype(np.int32)
+    for i in range(len(spec)):
+        for j in range(spec[i]):
+            z_t[cu_t[i] + j, x[cu_d[i] + j]] = 16 * np.abs(z_t).max()
+    for row in (cu_t[0], cu_t[2] + 1, cu_t[3] + 1, cu_t[5]):
+        z_t[row] = nothing
+    z_d[cu_d[3] + 1] = nothing
+    u_a, u_s = np.full(cu_d[-1], 0.01, np.float32), np.linspace(0, 0.99, len(spec)).astype(np.float32)
+    masked = [np.where(np.isnan(z), -np.inf, z).astype(np.float32) for z in (z_t, z_d)]
+    with np.errstate(all="ignore"):
+        ref = oracle.spec_accept(*masked, x, u_a, u_s, cu_t, cu_d, S_max=2, mode=1, temperature=T)
+    as_dtype = (lambda z: dev(z).bfloat16()) if dtype == "bf16" else dev  # exact
+    acc, nem, em = (t.cpu().numpy() for t in fsr.spec_accept(as_dtype(z_t), as_dtype(z_d), dev(x), dev(u_a), dev(u_s), dev(cu_t), dev(cu_d),
+                                                             S_max=2, mode=1, temperature=T))
+    assert np.array_equal(acc, ref["accepted_len"]) and np.array_equal(acc, [0, 2, 1, 1, 1, 0])
+    assert np.array_equal(nem, acc + 1)
+    for i in range(len(spec)):
+        want = list(ref["emitted"][i][:acc[i] + (i in (1, 4))]) + ([0] if i not in (1, 4) else [])  # (the oracle gives no token at all)
+        assert list(em[i]) == want + [-1] * (3 - len(want)), i
