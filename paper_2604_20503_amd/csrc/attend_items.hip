@@ -60,7 +60,7 @@ constexpr int kBalancedMaxB = 64;          // a request per lane
 constexpr int kBalancedKeys = 1536;        // keys from which an item is worth cutting
 constexpr int kPieceTiles = 8;             // least tiles of a piece that is handed over
 constexpr float kTileBase = 4.0f;          // a tile costs this + the query tiles that ride on it
-constexpr float kWorthCutting = 100.0f;    // what cutting has to take off at least, in those costs of four waves
+constexpr float kWorthCutting = 110.0f;    // what cutting has to take off at least, in those costs of four waves
 enum : int { kWhole = 0, kEven = 1, kBalanced = 2 };  // how items are cut
 
 struct ItemArgs {
@@ -587,15 +587,17 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
 // common time, the shortest that leaves no more pieces than there are places for four waves.  A workgroup holds two places.
 // The items of an even number of pieces come first, so that theirs lie side by side: a workgroup whose two places hold pieces of
 // one item works on both with all of its waves.  Every wave works this out for itself, from the lengths in its lanes.  Where
-// there is little to gain every item has a workgroup to itself, and the search is left out: code that a workgroup runs once costs its
-// fetch, 2 us here with the search, the arguments in the order of their use and a stack frame, 0.5 us without.
-// D = 64, 32/8 heads, 1-8 drafts, us a call over the caches of 12 layers in turn, an item per workgroup / balanced, always searched /
-// like this (gain): 20 requests of 256-4096 tokens 37.6 / 28.8 / 28.5 (236), 24 38.2 / 31.8 / 31.6 (215), 32 40.1 / 36.8 / 36.6 (193),
-// 40 49.0 / 40.2 / 40.0, 48 64.0 / 56.7 / 56.4; 32 with log-normal contexts up to 8192 73 / 49.3 / 48.6 (495); 16/16 heads, 16 of 256-4096
-// 34.3 / 32.6 / 32.6 (126); 32 of up to 2048 25.0 / 25.6 / 25.3 (103), of up to 1536 21.0 / 23.7 / 21.6 (67), up to 256 8.6 / 10.5 /
-// 9.2 (12); equal lengths, 20 of 1600 21.3 / 25.3 / 22.1 (66), 24 of 2176 31.1 / 33.0 / 32.1 (97), 32 of 2176 34.4 / 37.0 / 35.3
-// (45), 40 49.0 / 46.8 / 46.7, 48 58.4 / 49.5 / 49.2.  Workgroups of four waves, two to a compute unit, in place of two
-// items side by side in one of eight: 32 of 2176 37.1, and 14 us for 32 of up to 256.
+// there is little to gain every item has a workgroup to itself, the search is left out and what runs is the code of whole items: code
+// that a workgroup runs once costs its fetch, 2 us with the search, the arguments in the order of their use and a stack frame, 0.5 to 1 us
+// without but with four or eight waves to an item and its place looked up.
+// D = 64, 32/8 heads, 1-7 drafts, us a call over the caches of 12 layers in turn, an item per workgroup / balanced, always searched /
+// like this (gain): 20 requests of 256-4096 tokens 38.8 / 29.7 / 29.7 (242), 24 38.6 / 32.2 / 32.4, 32 40.4 / 35.0 / 34.9 (207), 48 64.1 /
+// 53.6 / 53.7; 32 with log-normal contexts 34.6 / 24.8 / 24.7 (245); 16/16 heads, 10 of up to 3500 25.1 / 19.0 / 18.8 (173), 16 of
+// 256-4096 35.1 / 33.2 / 33.3 (132); 20 of up to 2048 24.2 / 23.2 / 23.2 (124), 26 of up to 2600 28.0 / 27.7 / 27.7 (131), 32 of up
+// to 3000 32.2 / 32.3 / 32.1 (132), of up to 2600 29.6 / 30.2 / 30.2 (115); 26 of up to 2048 25.1 / 26.0 / 24.9 (107), 32 of up to 2048
+// 25.1 / 26.6 / 25.1 (101), up to 1024 16.2 / 20.5 / 16.3 (42), up to 256 9.7 / 11.7 / 9.7 (15); equal lengths, 20 of 1600 22.3 /
+// 26.0 / 22.3 (62), 24 of 2176 27.4 / 29.8 / 27.7 (60), 32 of 2176 32.1 / 33.6 / 32.2 (12), 48 55.0 / 49.6 / 49.5.  Workgroups
+// of four waves, two to a compute unit, in place of two items side by side in one of eight: 32 of 2176 37.1, and 14 us for 32 of up to 256.
 __device__ __forceinline__ int small_quotient(int x, int d) {  // x / d, both the same in every lane
     return uniform((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
 }
@@ -603,11 +605,11 @@ struct Piece {
     int i, g, sp, n_sp, place0;  // piece sp of the n_sp of request i's item for KV head g, the first of which has place0
     int q0, q_len, c;            // the request's rows and context
 };
-template <int MTMAX>
+template <int MTMAX, bool WHOLE>  // WHOLE: there are no more items than workgroups
 struct BalancedPieces {
     int k, from, upto;  // the lane's request: pieces of an item, places of all of its items
     int q0, ql, c;      // its rows and context
-    bool whole;         // every item is two pieces, which one workgroup takes
+    bool whole;         // every item has a workgroup to itself
 
     __device__ __forceinline__ explicit BalancedPieces(const ItemArgs& a) {
         const int lane = threadIdx.x & 63;
@@ -628,7 +630,7 @@ struct BalancedPieces {
         // With an item to a workgroup the call lasts as long as its longest; cut, no less than its share of the sum.
         const float sum = (float)wave_sum_i((int)(share * 65536.0f)) * (1.0f / 65536.0f);
         const float gain = longest * (0.5f - sum * (float)a.H_kv * __builtin_amdgcn_rcpf((float)a.places));
-        whole = 2 * a.B * a.H_kv <= a.places && __builtin_amdgcn_ballot_w64(gain > kWorthCutting) == 0;
+        whole = WHOLE && __builtin_amdgcn_ballot_w64(gain > kWorthCutting) == 0;
         k = from = upto = 0;
         if (whole) return;
         // two lie side by side and cost nothing; more have to be long enough to be worth handing over
@@ -668,8 +670,24 @@ struct BalancedPieces {
     }
 };
 
-// CUT: one group per item, whose keys are cut into pieces -- evenly, grid.z of them, or by BalancedPieces; else grid.z counts the groups.
+// attend_group for as many query tiles as the group really has: mt_group rows of whoever shares the workgroup, from m0 on.
 template <bool BF16, int D, int MTMAX, bool NT, int CUT>
+__device__ __forceinline__ void attend_rows(const ItemArgs& a, char* smem, int i, int g, int q0, int M, int c, int m0, int mt_group, int sp, int n_sp,
+                                            const Part& part) {
+    const int mt = (min(mt_group - m0, 16 * MTMAX) + 15) >> 4;
+    if constexpr (MTMAX >= 4)
+        if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
+    if constexpr (MTMAX >= 3)
+        if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
+    if constexpr (MTMAX >= 2)
+        if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
+    if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
+    __syncthreads();  // before the next group's query operands and tiles
+}
+
+// CUT: one group per item, whose keys are cut into pieces -- evenly, grid.z of them, or by BalancedPieces; else grid.z counts the groups.
+// WHOLE: see BalancedPieces.
+template <bool BF16, int D, int MTMAX, bool NT, int CUT, bool WHOLE = false>
 __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D, MTMAX, CUT>::kPerSimd)) void attend_items_kernel(ItemArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int kW = Map<BF16, D, MTMAX, CUT>::kW;
@@ -680,38 +698,39 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
     // what is needed again behind the keys' loops, of each half (scalar registers are short in them)
     __shared__ int s_place0[2], s_word[2];
     if constexpr (CUT == kBalanced) {
-        const BalancedPieces<MTMAX> bp(a);
+        const BalancedPieces<MTMAX, WHOLE> bp(a);
         z = 0;
         nz = 1;
-        if (bp.whole) {
-            i = small_quotient(blockIdx.x, a.H_kv);
-            g = blockIdx.x - i * a.H_kv;
-            if (i >= a.B) return;
-            q0 = __builtin_amdgcn_readlane(bp.q0, i);
-            q_len = __builtin_amdgcn_readlane(bp.ql, i);
-            c = __builtin_amdgcn_readlane(bp.c, i);
-            if (q_len <= 0) return;
-            cut = false;
-            mt_group = q_len * a.G;
-        } else {
-            const int half = uniform(threadIdx.x >> 8);
-            const Piece p0 = bp.at(2 * blockIdx.x), p1 = bp.at(2 * blockIdx.x + 1);
-            if (p0.n_sp == 0 && p1.n_sp == 0) return;
-            const bool joint = p0.n_sp > 0 && p1.n_sp > 0 && p0.place0 == p1.place0;
-            const Piece p = joint || half == 0 ? p0 : p1;
-            i = p.i; g = p.g; sp = p.sp; n_sp = p.n_sp;
-            part.waves = joint ? 8 : 4;
-            auto parts_of = [](const Piece& x) { return x.n_sp > 0 ? ((x.place0 + x.n_sp - 1) >> 1) - (x.place0 >> 1) + 1 : 1; };
-            part.of = parts_of(p);
-            cut = parts_of(p0) > 1 || parts_of(p1) > 1;
-            if ((threadIdx.x & 255) == 0) {
-                s_place0[half] = p.place0;
-                s_word[half] = p.i * a.H_kv + p.g;
+        if constexpr (WHOLE) {
+            if (bp.whole) {
+                i = small_quotient(blockIdx.x, a.H_kv);
+                g = blockIdx.x - i * a.H_kv;
+                if (i >= a.B) return;
+                q0 = __builtin_amdgcn_readlane(bp.q0, i);
+                q_len = __builtin_amdgcn_readlane(bp.ql, i);
+                c = __builtin_amdgcn_readlane(bp.c, i);
+                const int M = q_len * a.G;
+                for (int m0 = 0; m0 < M; m0 += 16 * MTMAX) attend_rows<BF16, D, MTMAX, NT, kWhole>(a, smem, i, g, q0, M, c, m0, M, 0, 1, part);
+                return;
             }
-            // the same number of query tiles for both, so that their barriers meet (an empty place has no rows)
-            mt_group = max(p0.q_len, p1.q_len) * a.G;
-            q0 = p.q0; q_len = p.q_len; c = p.c;
         }
+        const int half = uniform(threadIdx.x >> 8);
+        const Piece p0 = bp.at(2 * blockIdx.x), p1 = bp.at(2 * blockIdx.x + 1);
+        if (p0.n_sp == 0 && p1.n_sp == 0) return;
+        const bool joint = p0.n_sp > 0 && p1.n_sp > 0 && p0.place0 == p1.place0;
+        const Piece p = joint || half == 0 ? p0 : p1;
+        i = p.i; g = p.g; sp = p.sp; n_sp = p.n_sp;
+        part.waves = joint ? 8 : 4;
+        auto parts_of = [](const Piece& x) { return x.n_sp > 0 ? ((x.place0 + x.n_sp - 1) >> 1) - (x.place0 >> 1) + 1 : 1; };
+        part.of = parts_of(p);
+        cut = parts_of(p0) > 1 || parts_of(p1) > 1;
+        if ((threadIdx.x & 255) == 0) {
+            s_place0[half] = p.place0;
+            s_word[half] = p.i * a.H_kv + p.g;
+        }
+        // the same number of query tiles for both, so that their barriers meet (an empty place has no rows)
+        mt_group = max(p0.q_len, p1.q_len) * a.G;
+        q0 = p.q0; q_len = p.q_len; c = p.c;
     } else {
         q0 = a.cu_q[i];
         q_len = min(a.cu_q[i + 1], a.N_cap) - q0;
@@ -730,17 +749,8 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
         part.of = n_sp;
     }
     if (CUT != kBalanced) mt_group = M;
-    for (int m0 = z * 16 * MTMAX; m0 < mt_group; m0 += nz * 16 * MTMAX) {
-        const int mt = (min(mt_group - m0, 16 * MTMAX) + 15) >> 4;  // query tiles the group really has
-        if constexpr (MTMAX >= 4)
-            if (mt == 4) attend_group<BF16, D, MTMAX, 4, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
-        if constexpr (MTMAX >= 3)
-            if (mt == 3) attend_group<BF16, D, MTMAX, 3, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
-        if constexpr (MTMAX >= 2)
-            if (mt == 2) attend_group<BF16, D, MTMAX, 2, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
-        if (mt == 1) attend_group<BF16, D, MTMAX, 1, NT, CUT>(a, smem, i, g, q0, M, c, m0, sp, n_sp, part);
-        __syncthreads();  // before the next group's query operands and tiles
-    }
+    for (int m0 = z * 16 * MTMAX; m0 < mt_group; m0 += nz * 16 * MTMAX)
+        attend_rows<BF16, D, MTMAX, NT, CUT>(a, smem, i, g, q0, M, c, m0, mt_group, sp, n_sp, part);
     if constexpr (CUT != kWhole) {
         __shared__ int s_last[2];
         if (CUT == kEven ? n_sp == 1 : !cut) return;
@@ -759,11 +769,11 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
     }
 }
 
-template <bool BF16, int D, int MT, bool NT, int CUT>
+template <bool BF16, int D, int MT, bool NT, int CUT, bool WHOLE = false>
 void launch_as(const ItemArgs& a, unsigned z, hipStream_t s) {
     typedef Map<BF16, D, MT, CUT> L;
     const dim3 grid = CUT == kBalanced ? dim3((unsigned)(a.places / 2)) : dim3((unsigned)a.H_kv, (unsigned)a.B, z);
-    hipLaunchKernelGGL((attend_items_kernel<BF16, D, MT, NT, CUT>), grid, dim3(L::kThreads), L::kSmem, s, a);
+    hipLaunchKernelGGL((attend_items_kernel<BF16, D, MT, NT, CUT, WHOLE>), grid, dim3(L::kThreads), L::kSmem, s, a);
 }
 
 template <bool BF16, int D, int MT>
@@ -775,7 +785,10 @@ int launch(const ItemArgs& a, unsigned groups, hipStream_t s) {
     // plain loads win at the small end: one request of 8192 tokens 54.0 / 47.3.)
     if constexpr (BF16) {
         if (a.places > 0) {
-            if constexpr (!Map<true, D, MT, kBalanced>::kLarge) launch_as<true, D, MT, true, kBalanced>(a, 1, s);
+            if constexpr (!Map<true, D, MT, kBalanced>::kLarge) {
+                if (2 * a.B * a.H_kv <= a.places) launch_as<true, D, MT, true, kBalanced, true>(a, 1, s);
+                else launch_as<true, D, MT, true, kBalanced>(a, 1, s);
+            }
         } else if (a.splits > 1) launch_as<true, D, MT, true, kEven>(a, (unsigned)a.splits, s);
         else if (groups == 1) launch_as<true, D, MT, true, kWhole>(a, 1, s);
         else launch_as<true, D, MT, false, kWhole>(a, groups, s);
@@ -820,7 +833,7 @@ Layout layout_of(const fsr_attn_params& p) {
         l.splits = (int)std::max(1LL, std::min({(long long)kMaxSplits, keys / kSplitKeys, units / items}));
         // From more items than half the units to one and a half times as many, heads of 64 (eight waves a workgroup): balanced by
         // length.  With fewer even pieces do as well (16 requests 26.5 / 26.6), with more the units have several items anyway (56
-        // requests 68.7 / 71.5).  Tables of so few pages hold nothing that is worth it (32 of up to 1536 tokens 21.0 / 21.6).
+        // requests 68.7 / 71.5).  Tables of so few pages hold nothing that is worth it (see kWorthCutting).
         if (p.D == 64 && l.mt < 4 && p.B > 1 && p.B <= kBalancedMaxB && keys >= kBalancedKeys && 2 * items > units && 2 * items <= 3 * units) {
             l.places = (int)(2 * units);
             l.splits = 1;

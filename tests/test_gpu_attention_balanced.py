@@ -145,13 +145,14 @@ def test_short_contexts_in_wide_tables(fsr, oracle, H_q, H_kv, B, hint, ctx_hi):
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("longest", [1690, 4100])  # cut only where the items do not fit otherwise, cut
 @pytest.mark.parametrize("units,B", [(33, 5), (64, 9), (65, 5), (128, 15)])
-def test_balanced_within_the_callers_workgroups(fsr, oracle, units, B):
+def test_balanced_within_the_callers_workgroups(fsr, oracle, units, B, longest):
     """Items between half the units that the caller owns, odd numbers of them too, and one and a half times as many."""
-    announce(f"balanced items max_workgroups={units}")
+    announce(f"balanced items max_workgroups={units} longest={longest}")
     rng = np.random.Generator(np.random.PCG64(units))
     ctx, spec = rng.integers(0, 1700, B), rng.integers(0, 4, B)
-    ctx[0], ctx[1:3] = 1690, 60
+    ctx[0], ctx[1:3] = longest, 60
     x = make(rng, "bf16", 32, 8, 64, 16, ctx, spec)
     ref, lse_ref = oracle.verify_attention(x["q"], x["k"], x["v"], x["bt"], x["ctx"], x["cu"], H_q=32, H_kv=8, D=64, P=16, dtype="bf16", scale=0.125)
     q = dev(x["q"], True)
@@ -164,12 +165,13 @@ def test_balanced_within_the_callers_workgroups(fsr, oracle, units, B):
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
 
 
-def test_balanced_through_the_built_in_scratch(fsr):
+@pytest.mark.parametrize("longest", [1690, 4100])  # whole items, cut ones
+def test_balanced_through_the_built_in_scratch(fsr, longest):
     """fsr_verify_attention_static against fsr_verify_attention, bit for bit."""
-    announce("balanced items static")
+    announce(f"balanced items static longest={longest}")
     rng = np.random.Generator(np.random.PCG64(4))
     ctx, spec = rng.integers(0, 1700, 20), rng.integers(0, 4, 20)
-    ctx[0] = 1690
+    ctx[0] = longest
     x = make(rng, "bf16", 32, 8, 64, 16, ctx, spec)
     q, k, v, bt, c, cu = dev(x["q"], True), dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["ctx"]), dev(x["cu"])
     outs = [torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
@@ -188,7 +190,7 @@ def test_values_that_are_not_finite_in_balanced_pieces(fsr, oracle, bad):
     rng = np.random.Generator(np.random.PCG64(12))
     H_kv, B = 7, 29  # an odd number of pieces side by side
     ctx, spec = rng.integers(100, 1700, B), rng.integers(0, 4, B)
-    ctx[0] = 1690
+    ctx[:6:2] = 4100, 3300, 2900  # long enough to be cut
     x = make(rng, "bf16", 14, H_kv, 64, 16, ctx, spec)
     store = np.uint16(0x7FC0 if np.isnan(bad) else 0x7F80 if bad > 0 else 0xFF80)
     hit = {}
@@ -215,3 +217,44 @@ def test_values_that_are_not_finite_in_balanced_pieces(fsr, oracle, bad):
     ref, _ = oracle.verify_attention(x["q"], x["k"], clean, x["bt"], x["ctx"], x["cu"], H_q=14, H_kv=H_kv, D=64, P=16, dtype="bf16", scale=0.125)
     got[want_bad] = ref[want_bad]
     check_attention(torch.from_numpy(got), ref, "f32", len(ref))
+
+
+def test_cut_and_whole_items_in_a_graph(fsr):
+    """Replays over contexts that are worth cutting and others that are not, with eager calls on the same workspace between them: the
+    bits of an eager call on a workspace of its own."""
+    announce("cut and whole items in a graph")
+    rng = np.random.Generator(np.random.PCG64(3))
+    B = 20
+    x = make(rng, "bf16", 32, 8, 64, 16, np.full(B, 4100), rng.integers(0, 4, B))
+    q, k, v, bt, cu = dev(x["q"], True), dev(x["k"], True), dev(x["v"], True), dev(x["bt"]), dev(x["cu"])
+    need = fsr.attn_workspace_bytes(B=B, N_cap=q.shape[0], H_q=32, H_kv=8, D=64, P=16, max_pages=bt.shape[1], n_pages=k.shape[0],
+                                    dtype=torch.bfloat16, out_dtype=torch.bfloat16, max_q_len=4)
+    ws, own = (torch.full((need,), 0x55, dtype=torch.uint8, device="cuda") for _ in range(2))
+    c, out, want = dev(x["ctx"]), torch.empty_like(q), torch.empty_like(q)
+
+    def call(into, workspace):
+        fsr.verify_attention(q, k, v, bt, c, None, cu, scale=0.125, out=into, max_q_len=4, workspace=workspace)
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        call(out, ws)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            call(out, ws)
+        for rep in range(6):
+            ctx = rng.integers(0, 200 if rep == 2 else 1700, B)
+            if rep in (0, 1, 4):
+                ctx[rng.permutation(B)[:3]] = 3900, 4100, 2500
+            c.copy_(dev(ctx.astype(np.int32)))
+            out.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            before = own.clone()
+            call(want, own)
+            torch.cuda.synchronize()
+            assert (not torch.equal(before, own)) == (rep in (0, 1, 4))  # whole items leave no pieces
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+            call(out, ws)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16))
