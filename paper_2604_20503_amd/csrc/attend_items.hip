@@ -191,6 +191,7 @@ __device__ __forceinline__ void combine_pieces(const ItemArgs& a, int g, int q0,
 // keys are shared by `of` such parts.
 struct Part {
     int waves, of;
+    int slot;  // (evenly cut) of the piece in the workspace
 };
 
 // Query rows m0 .. of item (request i, KV head g), at most 16 * MT of them: stream the keys they see (piece sp of n_sp of
@@ -554,7 +555,7 @@ __device__ __forceinline__ void attend_group(const ItemArgs& a, char* smem, int 
                 }
             }
             if (SPLIT && part.of > 1 && m < rows) {
-                const int slot = CUT == kBalanced ? 2 * blockIdx.x + (first > 0 ? 1 : 0) : (i * a.H_kv + g) * gridDim.z + sp;
+                const int slot = CUT == kBalanced ? 2 * blockIdx.x + (first > 0 ? 1 : 0) : part.slot;
                 const long long at = (long long)slot * (16 * MTMAX) + m;
                 if constexpr (kPer >= 4) {
 #pragma unroll
@@ -692,7 +693,7 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int kW = Map<BF16, D, MTMAX, CUT>::kW;
     int g = blockIdx.x, i = blockIdx.y, n_sp = 1, sp = 0, z = blockIdx.z, nz = gridDim.z, mt_group = 0;
-    Part part{kW, 1};
+    Part part{kW, 1, 0};
     bool cut = true;
     int q0, q_len, c;
     // what is needed again behind the keys' loops, of each half (scalar registers are short in them)
@@ -744,9 +745,10 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
         if (M <= 16 * MTMAX) n_sp = max(1, min((int)gridDim.z, seen / kSplitKeys));
         sp = blockIdx.z;
         if (sp >= n_sp) return;
+        part.of = n_sp;
+        part.slot = uniform((i * a.H_kv + g) * nz + sp);  // (here: the grid's size is a load, and a round trip behind the keys' loops)
         z = 0;
         nz = 1;
-        part.of = n_sp;
     }
     if (CUT != kBalanced) mt_group = M;
     for (int m0 = z * 16 * MTMAX; m0 < mt_group; m0 += nz * 16 * MTMAX)
@@ -757,7 +759,7 @@ __global__ __launch_bounds__((Map<BF16, D, MTMAX, CUT>::kThreads), (Map<BF16, D,
         const int half = CUT == kBalanced ? uniform(threadIdx.x >> 8) & (part.waves == 4 ? 1 : 0) : 0;
         const int thread = CUT == kBalanced && part.waves == 4 ? threadIdx.x & 255 : threadIdx.x;
         const int word = CUT == kBalanced ? uniform(s_word[half]) : i * a.H_kv + g;
-        const int slot0 = CUT == kBalanced ? uniform(s_place0[half]) : word * (int)gridDim.z;
+        const int slot0 = CUT == kBalanced ? uniform(s_place0[half]) : part.slot - sp;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the piece is in memory once every wave's stores are acknowledged
         __syncthreads();
         if (thread == 0) s_last[half] = part.of > 1 && count_arrival(a.arrivals + word, a.call_id) == part.of;
